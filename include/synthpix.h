@@ -162,7 +162,8 @@ typedef struct {
 typedef struct {
     int32_t tile_w, tile_h;
     int32_t chunk;              /* particles per binning block (256 .. 16384, multiple of 256) */
-    int32_t cap;                /* particles staged in LDS per render pass (32 .. 256)        */
+    int32_t cap;                /* 32 .. 256; accepted and reported, no longer a tuning choice: a
+                                   render pass stages up to 256 particles whatever it holds   */
     int32_t persistent;         /* 1: one persistent render launch whose workgroups (as many as
                                    the device holds) pop (frame, tile) items from per-XCD work
                                    queues; 0: one workgroup per item.  Same images either way. */
@@ -181,9 +182,9 @@ synthpix_status synthpix_default_tiling(const synthpix_pair* pairs_host, int32_t
                                         const synthpix_render_params* rp, synthpix_tiling* out);
 
 /* The tilings a plan's autotuner may choose for these parameters (the default
- * first): every compiled tile shape x LDS particle capacity whose LDS fits,
- * with 2048-particle binning blocks, then the binning block sizes it tries for
- * the fastest of those, then the persistent form of the fastest.  Writes at most max_out entries, the total count to
+ * first): every tile shape it considers with 2048-particle binning blocks, then
+ * the binning block sizes it tries for the fastest of those, then the
+ * persistent form of the fastest.  Writes at most max_out entries, the total count to
  * *n_out. */
 synthpix_status synthpix_tiling_candidates(const synthpix_render_params* rp, synthpix_tiling* out,
                                            int32_t max_out, int32_t* n_out);
@@ -479,8 +480,8 @@ typedef struct synthpix_plan synthpix_plan;
 /* Build a plan for a fixed batch signature (pair table and parameters):
  * copies the pair table to plan-owned device memory, sizes and allocates the
  * render workspace and the device-side io descriptor, and, if `autotune` != 0,
- * times the compiled tiling candidates (synthpix_tiling_candidates: tile shape
- * x LDS particle capacity, then the binning block size of the fastest) on this
+ * times the tiling candidates (synthpix_tiling_candidates: tile shape, then
+ * the binning block size of the fastest) on this
  * batch and keeps the fastest (all candidates give bit-identical images).  The
  * whole path -- seed, advect, bin, render, epilogue -- is then captured once
  * into a hipGraph whose kernels take their buffers, draw key and pair-id

@@ -150,7 +150,6 @@ sp::RenderConfig make_config(const synthpix_render_params& rp, const synthpix_ti
     c.tile_w = t.tile_w;
     c.tile_h = t.tile_h;
     c.chunk = t.chunk;
-    c.cap = t.cap;
     c.persistent = t.persistent;
     c.apron = rp.blur_radius;
     c.d_max = rp.d_max;
@@ -159,9 +158,6 @@ sp::RenderConfig make_config(const synthpix_render_params& rp, const synthpix_ti
     c.log_th = 0;
     while ((1 << c.log_th) < c.tile_h) ++c.log_th;
     const int span = (int)std::floor(3.0 * (double)rp.d_max) + 4;   // patch side bound incl. rounding
-    const int RW = c.tile_w + 2 * c.apron, RH = c.tile_h + 2 * c.apron;
-    c.wmax = span < (RW > RH ? RW : RH) ? span : (RW > RH ? RW : RH);
-    c.wm4 = (c.wmax + 3) & ~3;
     c.kx = (span + 2 * c.apron) / c.tile_w + 2;
     c.ky = (span + 2 * c.apron) / c.tile_h + 2;
     return c;
@@ -387,7 +383,6 @@ sp::RenderConfig order_config(const synthpix_pair* ph, int32_t n_pairs)
     c.tile_w = c.tile_h = 1 << lb;
     c.log_tw = c.log_th = lb;
     c.chunk = chunk;
-    c.cap = 32;
     c.apron = 0;
     c.kx = c.ky = 1;     // one entry per particle
     c.d_max = 1.0f;
@@ -738,10 +733,6 @@ synthpix_status synthpix_render_pair(const synthpix_pair* pairs_host, const synt
     if (ws_bytes < wl.total)
         return fail(SP_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, wl.total);
     if ((st = check_extras(extras))) return st;
-    const bool aniso = aniso_in_use(*rp, extras);
-    if (sp::render_lds_bytes(cfg, aniso) > 160 * 1024)
-        return fail(SP_ERR_UNSUPPORTED, "tiling needs %zu bytes of LDS per workgroup (max 163840)",
-                    sp::render_lds_bytes(cfg, aniso));
     const hipError_t e = enqueue_render(pairs_dev, n_pairs, cfg, T, wl, x1, y1, x2, y2, z, d, I0, *rp, images,
                                         workspace, as_stream(stream), nullptr, extras);
     if (e != hipSuccess) return hip_fail(e, "render launch");
@@ -1004,10 +995,6 @@ extern "C" synthpix_status synthpix_render_pair_noalloc(const synthpix_pair* pai
                     "synthpix_render_pair with a caller workspace)",
                     wl.total, (size_t)SYNTHPIX_STATIC_SCRATCH_BYTES);
     if ((st = check_extras(extras))) return st;
-    const bool aniso = aniso_in_use(*rp, extras);
-    if (sp::render_lds_bytes(cfg, aniso) > 160 * 1024)
-        return fail(SP_ERR_UNSUPPORTED, "tiling needs %zu bytes of LDS per workgroup (max 163840)",
-                    sp::render_lds_bytes(cfg, aniso));
     void* ws = nullptr;
     if ((st = scratch_of_current_device(&ws))) return st;
     // every part of the workspace the kernels read is written earlier in the same
@@ -1095,20 +1082,13 @@ hipError_t enqueue_batch(synthpix_plan* P, const synthpix_tiling& t, hipStream_t
 
 const int CHUNK_CANDIDATES[] = {1024, 4096, 8192};
 
-// Tile shape x LDS capacity candidates (2048-particle binning blocks), default first.
-std::vector<synthpix_tiling> shape_candidates(const synthpix_render_params& rp)
+// Tile shape candidates (2048-particle binning blocks), default first.
+std::vector<synthpix_tiling> shape_candidates()
 {
     std::vector<synthpix_tiling> out;
     out.push_back(default_tiling());
-    const int shapes[][2] = {{32, 32}, {64, 32}, {64, 64}, {128, 32}, {32, 16}, {64, 16}};
-    const int caps[] = {32, 64, 128};
-    for (const auto& sh : shapes)
-        for (int cap : caps) {
-            synthpix_tiling t{sh[0], sh[1], 2048, cap, 0};
-            if (t.tile_w == out[0].tile_w && t.tile_h == out[0].tile_h && t.cap == out[0].cap) continue;
-            if (sp::render_lds_bytes(make_config(rp, t)) > 160 * 1024) continue;
-            out.push_back(t);
-        }
+    const int shapes[][2] = {{32, 32}, {64, 64}, {128, 32}, {32, 16}, {64, 16}};
+    for (const auto& sh : shapes) out.push_back(synthpix_tiling{sh[0], sh[1], 2048, out[0].cap, 0});
     return out;
 }
 
@@ -1134,7 +1114,7 @@ synthpix_status synthpix_tiling_candidates(const synthpix_render_params* rp, syn
     if (!n_out || (max_out > 0 && !out)) return fail(SP_ERR_INVALID_ARG, "out and n_out must be non-NULL");
     synthpix_status st = check_render_params(rp);
     if (st) return st;
-    std::vector<synthpix_tiling> c = shape_candidates(*rp);
+    std::vector<synthpix_tiling> c = shape_candidates();
     for (int ch : CHUNK_CANDIDATES) c.push_back(synthpix_tiling{c[0].tile_w, c[0].tile_h, ch, c[0].cap, 0});
     c.push_back(synthpix_tiling{c[0].tile_w, c[0].tile_h, c[0].chunk, c[0].cap, 1});
     for (int32_t i = 0; i < max_out && i < (int32_t)c.size(); ++i) out[i] = c[i];
@@ -1186,7 +1166,7 @@ synthpix_status synthpix_plan_create(const synthpix_pair* pairs_host, int32_t n_
         return hip_fail(e, "plan set-up");
     }
     // workspace for the largest candidate (every shape with every binning block size)
-    std::vector<synthpix_tiling> shapes = autotune ? shape_candidates(*rp) : std::vector<synthpix_tiling>{t0};
+    std::vector<synthpix_tiling> shapes = autotune ? shape_candidates() : std::vector<synthpix_tiling>{t0};
     size_t ws = order_bytes(pairs_host, n_pairs);   // the advection order shares the render workspace
     std::vector<synthpix_tiling> ok;
     for (const auto& t : shapes) {

@@ -13,7 +13,7 @@
 //   bin_scan    : per tile, chunk bases inside its list and its total; per
 //                 (pair, frame), the exclusive scan of the totals -> list offsets
 //   bin_scatter : per chunk, LDS cursors -> particle indices into tile lists
-//   render_tile : per (pair, frame, tile) stage the list in LDS, splat footprints
+//   render_tile : per (pair, frame, tile) stage the list in LDS, splat the patches
 //                 into an LDS fixed-point accumulator (tile + blur apron), then
 //                 blur, noise, quantise and store.
 // No global atomics: counts, cursors and pixel sums all live in LDS.  Pixel sums
@@ -429,74 +429,59 @@ scan_tiles(const PairLayout* __restrict__ L, const uint32_t* __restrict__ tile_c
 
 // ------------------------------------------------------------------ render
 
-// LDS carve-up of one render workgroup (all offsets 16-byte aligned).
-struct RenderLds {
-    int acc_words;           // RH * RW + 8 of slack, rounded up to a multiple of 4
-    int tables;              // CAP * WM4 floats per table
-    size_t bytes;
-};
+constexpr int STAGE = 256;      // particles staged per pass, one per thread
+constexpr int SLACK = 24;       // accumulator words past the region (a row's zero columns may overrun it)
+constexpr int SIZES = 64;       // patch sizes told apart when a pass is sorted
 
-__host__ __device__ inline RenderLds render_lds_shape(int tw, int th, int apron, int cap, int wm4, bool aniso)
-{
-    RenderLds L;
-    const int RW = tw + 2 * apron, RH = th + 2 * apron;
-    L.acc_words = (RH * RW + 8 + 3) & ~3;
-    L.tables = cap * wm4;
-    size_t work = (size_t)cap * 16                                  // staged (x, y, kappa_x, Af)
-                + (size_t)cap * 4                                   // staged patch box
-                + (aniso ? (size_t)cap * 8 : 0)                     // staged (kappa_y, kappa_xy)
-                + (size_t)L.tables * sizeof(float)                  // column factors gx
-                + (size_t)L.tables * sizeof(uint16_t)               // work items
-                + 64;                                                // scan scratch
-    size_t blur = (size_t)RH * tw * sizeof(float);
-    L.bytes = (size_t)L.acc_words * 4 + (work > blur ? work : blur);
-    return L;
-}
-
-__host__ __device__ inline RenderLds render_lds(const RenderConfig& c, bool aniso)
-{
-    return render_lds_shape(c.tile_w, c.tile_h, c.apron, c.cap, c.wm4, aniso);
-}
-
-// Exclusive scan of one counter over a workgroup of 256 threads (4 waves of
-// 64) in which only the first n threads can hold a nonzero value: waves past
-// them skip their in-wave scan.  In-wave inclusive scan with DPP: row shifts
-// by 1, 2, 4, 8 within each row of 16 lanes, then the row broadcasts of lanes
-// 15 and 31 into the rows above.
+// In-wave inclusive scan with DPP: row shifts by 1, 2, 4, 8 within each row of
+// 16 lanes, then the row broadcasts of lanes 15 and 31 into the rows above.
 template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_add(int v)
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
 {
-    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 
-__device__ __forceinline__ int stage_scan(int v, int n, int* s_wave, int& total)
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
 {
-    const int wid = threadIdx.x >> 6;
-    int inc = v;
-    if (wid * 64 < n) {
-        inc = dpp_add<0x111, 0xF>(inc);
-        inc = dpp_add<0x112, 0xF>(inc);
-        inc = dpp_add<0x114, 0xF>(inc);
-        inc = dpp_add<0x118, 0xF>(inc);
-        inc = dpp_add<0x142, 0xA>(inc);
-        inc = dpp_add<0x143, 0xC>(inc);
-    }
-    if ((threadIdx.x & 63) == 63) s_wave[wid] = inc;
-    __syncthreads();
-    int before = 0;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const int sw = s_wave[w];
-        if (w < wid) before += sw;
-        total += sw;
-    }
-    return before + inc - v;
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    v = dpp_add<0x143, 0xC>(v);
+    return v;
 }
 
 __device__ __forceinline__ uint32_t pack_box(int c0, int w, int r0, int h)
 {
     return (uint32_t)c0 | ((uint32_t)w << 8) | ((uint32_t)r0 << 16) | ((uint32_t)h << 24);
+}
+
+// K columns of one particle's patch, from column fx on, over its rows j, j + step,
+// ..: the column factors stay in registers (zero past the patch's pw columns),
+// each row's factor is formed as the row is added.  fx, fy: the first column's
+// and row j's pixel centres (exact in binary32, so adding small integers to
+// them gives every other centre exactly).
+template <int K, int RW>
+__device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, float kx, int pw, float fy, float y,
+                                              float ky, float Af, int j, int h, int step)
+{
+    float gx[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const float dx = (fx + (float)k) - x;
+        const float g = expneg_lt80(kx * (dx * dx));
+        gx[k] = k < pw ? g : 0.0f;
+    }
+#pragma unroll 1
+    for (; j < h; j += step) {
+        const float dy = fy - y;
+        const float rv = Af * expneg_lt80(ky * (dy * dy));
+#pragma unroll
+        for (int k = 0; k < K; ++k) atomicAdd(dst + k, (uint32_t)(rv * gx[k]));
+        fy += (float)step;
+        dst += step * RW;
+    }
 }
 
 // Tile renderer, templated on the tile shape and the blur radius (tile-local
@@ -506,12 +491,29 @@ __device__ __forceinline__ uint32_t pack_box(int c0, int w, int r0, int h)
 // rho = 0 keeps the separable factors (with kappa_y for the rows), rho != 0
 // evaluates exp(-q) per pixel, q = dx (kappa_x dx + kappa_xy dy) + kappa_y dy^2,
 // kappa_xy = -16 rho / (om d d_y); the patch is |dx| <= 1.5 d, |dy| <= 1.5 d_y.
+//
+// The tile's particles are staged in LDS up to 256 at a time, one per thread,
+// sorted by patch size (a counting sort on LDS counters), and splatted one
+// particle per lane: a lane keeps its patch's column factors in registers and
+// walks down the rows, so an exponential is computed once per patch column and
+// row and no factor passes through LDS.  The sort makes a wave's 64 patches
+// nearly equal, so few lanes idle.  Lists that leave most of a wave empty give
+// each particle 2 or 4 lanes, which take its rows in turn.
+// Bound by VALU issue (exponentials, products, the epilogue's draws), with the
+// LDS adds close behind (7.4 clocks per wave at 64 unrelated addresses, 6.5 at
+// eight rows of eight patches: the order of the lanes hardly matters).  Measured
+// against one patch row per lane with the column factors in an LDS table:
+// 64 pairs of 1024^2 at 0.05 ppp, 3x3 blur, noise: 505 -> 385 us; 32 pairs of
+// 2048^2 at 0.1 ppp, d to 6, 5x5 blur: 2.97 -> 2.31 ms; uneven pairs, ppp to
+// 0.1: 940 -> 664 us.  Of the first, the epilogue takes about 150 us, the
+// staging 80 and the splat 130.  Sorting by width alone or by an estimate of
+// the work was slower (397 and 408 us).
 template <int TW, int TH, int B, bool ANISO, bool PERSIST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PERSIST ? 6 : 8)))
 render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__ L, int n_pairs,
             const float4* __restrict__ rec0, const float4* __restrict__ rec1, const uint2* __restrict__ box0,
             const uint2* __restrict__ box1, const float2* __restrict__ shp0,
-            const float2* __restrict__ shp1, EpilogueArgs a, int cap, int wm4,
+            const float2* __restrict__ shp1, EpilogueArgs a, int spread,
             const uint32_t* __restrict__ tile_count, const int64_t* __restrict__ tile_offset,
             const int32_t* __restrict__ entries, int64_t tiles_total, uint32_t* __restrict__ status,
             uint32_t* __restrict__ queue)
@@ -520,28 +522,29 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     static_assert(TW + 6 < 256 && TH + 6 < 256, "patch boxes are packed in bytes");
     static_assert(B >= 0 && B <= 3, "blur radius 0..3");
     constexpr int Q4 = TW / 4;
+    constexpr int RW = TW + 2 * B;
+    constexpr int RH = TH + 2 * B;
+    constexpr int ACC = (RH * RW + SLACK + 3) & ~3;
+    constexpr int STAGE_BYTES = STAGE * (16 + 4 + (ANISO ? 8 : 0));
+    constexpr int BLUR_BYTES = B > 0 ? RH * TW * 4 : 0;
     float wb[2 * B + 1];
 #pragma unroll
     for (int q = 0; q <= 2 * B; ++q) wb[q] = a.blur_w[q];
-    extern __shared__ __align__(16) unsigned char smem[];
-    const RenderLds lay = render_lds_shape(TW, TH, B, cap, wm4, ANISO);
-    constexpr int b = B;
-    constexpr int RW = TW + 2 * B;
-    constexpr int RH = TH + 2 * B;
-    const int WM = wm4;
-    uint32_t* acc = reinterpret_cast<uint32_t*>(smem);
-    float4* stg = reinterpret_cast<float4*>(acc + lay.acc_words);       // (x, y, kappa, Af)
-    uint32_t* box = reinterpret_cast<uint32_t*>(stg + cap);              // c0 | w | r0 | h bytes
-    float2* stg2 = reinterpret_cast<float2*>(box + cap);                // (kappa_y, kappa_xy), ANISO only
-    float* gx = reinterpret_cast<float*>(ANISO ? reinterpret_cast<uint32_t*>(stg2 + cap) : box + cap);
-    uint16_t* items = reinterpret_cast<uint16_t*>(gx + lay.tables);     // tables entries
-    int* s_wave = reinterpret_cast<int*>(items + lay.tables);
-    float* tmp = reinterpret_cast<float*>(stg);   // blur scratch, reuses the particle tables
+    __shared__ __align__(16) uint32_t acc[ACC];
+    __shared__ __align__(16) unsigned char work[STAGE_BYTES > BLUR_BYTES ? STAGE_BYTES : BLUR_BYTES];
+    float4* stg = reinterpret_cast<float4*>(work);                  // (x, y, kappa_x, Af)
+    float2* stg2 = reinterpret_cast<float2*>(stg + STAGE);          // (kappa_y, kappa_xy), ANISO only
+    uint32_t* box = reinterpret_cast<uint32_t*>(work + STAGE * (ANISO ? 24 : 16));   // c0 | w | r0 | h bytes
+    float* tmp = reinterpret_cast<float*>(work);                    // blur scratch, reuses the staging
+    __shared__ uint32_t s_hist[2][SIZES];       // particles of each patch size, by pass parity
     // fixed-point range bound: a difference array over the region's rows of the
     // staged particles' integer peaks (each particle's peak added over the rows
     // its patch covers).  Every term a particle adds to a pixel is at most its
-    // peak, so a row's prefix sum bounds every pixel sum of that row.
+    // peak, so a row's prefix sum bounds every pixel sum of that row.  The tile's
+    // whole sum (in units of 256, rounded up) bounds every row: the rows are only
+    // summed where it reaches the range.
     __shared__ unsigned long long s_rows[RH + 1];
+    __shared__ unsigned long long s_sum;
 
     // PERSIST: a persistent work list.  Each workgroup pops (frame, tile) items
     // from the queue of its XCD until the queue is empty; the items of one XCD
@@ -562,10 +565,11 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     const unsigned q8 = n_items >> 3, r8 = n_items & 7u;
     const unsigned lo = split ? (xq < r8 ? xq * (q8 + 1) : r8 * (q8 + 1) + (xq - r8) * q8) : 0u;
     const unsigned len = split ? (xq < r8 ? q8 + 1 : q8) : n_items;
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
     for (;;) {
     int64_t item;
     if (PERSIST) {
-        if (threadIdx.x == 0) s_pop = atomicAdd(&queue[xq], 1u);
+        if (t == 0) s_pop = atomicAdd(&queue[xq], 1u);
         __syncthreads();
         const unsigned kq = (unsigned)__builtin_amdgcn_readfirstlane((int)s_pop);   // uniform: one scalar value
         if (kq >= len) break;             // the same value in every thread of the workgroup
@@ -584,145 +588,123 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     const int tl = (int)(tile - tile_base);
     const int ty = tl / ntx;
     const int tx = tl - ty * ntx;
-    const int rx0 = tx * TW - b;          // region origin in image pixels
-    const int ry0 = ty * TH - b;
+    const int rx0 = tx * TW - B;          // region origin in image pixels
+    const int ry0 = ty * TH - B;
     const int cnt = (int)tile_count[item];
-    const int64_t off = tile_offset[item];
-    const float4* __restrict__ rec = f ? rec1 : rec0;
-    const uint2* __restrict__ bxs = f ? box1 : box0;
-    const float2* __restrict__ shp = f ? shp1 : shp0;
+    const int32_t* __restrict__ list = entries + tile_offset[item];
+    const float4* __restrict__ rec = (f ? rec1 : rec0) + p_off;
+    const uint2* __restrict__ bxs = (f ? box1 : box0) + p_off;
+    const float2* __restrict__ shp = (f ? shp1 : shp0) + p_off;
 
-    for (int k = threadIdx.x; k < (lay.acc_words >> 2); k += 256)
-        reinterpret_cast<uint4*>(acc)[k] = make_uint4(0u, 0u, 0u, 0u);
-    for (int k = threadIdx.x; k <= RH; k += 256) s_rows[k] = 0ull;
+    for (int k = t; k < ACC / 4; k += 256) reinterpret_cast<uint4*>(acc)[k] = make_uint4(0u, 0u, 0u, 0u);
+    for (int k = t; k <= RH; k += 256) s_rows[k] = 0ull;
+    if (t < 2 * SIZES) (&s_hist[0][0])[t] = 0u;
+    if (t == 0) s_sum = 0ull;
+    __syncthreads();
 
-    // the record of a thread's particle in the next pass is loaded one pass ahead,
-    // so its two dependent loads overlap the current pass's factor and splat work
-    float4 next = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    uint2 next_bx = make_uint2(EMPTY_BOX, EMPTY_BOX);
-    float2 next_sh = make_float2(0.0f, 0.0f);
-    if ((int)threadIdx.x < min(cap, cnt)) {
-        const int e = entries[off + threadIdx.x];
-        next = rec[p_off + e];
-        next_bx = bxs[p_off + e];
-        if (ANISO) next_sh = shp[p_off + e];
-    }
-    for (int base = 0; base < cnt; base += cap) {
-        const int n = min(cap, cnt - base);
-        const float4 r = next;
-        const uint2 pb = next_bx;
-        const float2 rs = next_sh;
-        if ((int)threadIdx.x < cap && base + cap + (int)threadIdx.x < cnt) {
-            const int e = entries[off + base + cap + threadIdx.x];
-            next = rec[p_off + e];
-            next_bx = bxs[p_off + e];
-            if (ANISO) next_sh = shp[p_off + e];
-        }
-        __syncthreads();
-        // stage: one particle per thread; its patch box (image pixels) clipped to the region
+    for (int base = 0, par = 0; base < cnt; base += STAGE, par ^= 1) {
+        // one particle per thread; its patch box (image pixels) clipped to the region
+        float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float2 rs = make_float2(0.0f, 0.0f);
         int w = 0, h = 0, c0 = 0, r0 = 0;
-        if ((int)threadIdx.x < n) {
+        if (base + t < cnt) {
+            const int e = list[base + t];
+            r = rec[e];
+            const uint2 pb = bxs[e];
+            if (ANISO) rs = shp[e];
             if (!box_empty(pb)) {
-                int a0 = (int)(pb.x & 0xffffu), a1 = (int)(pb.x >> 16);
-                int b0 = (int)(pb.y & 0xffffu), b1 = (int)(pb.y >> 16);
-                a0 = max(a0, rx0);
-                a1 = min(a1, rx0 + RW - 1);
-                b0 = max(b0, ry0);
-                b1 = min(b1, ry0 + RH - 1);
+                const int a0 = max((int)(pb.x & 0xffffu), rx0), a1 = min((int)(pb.x >> 16), rx0 + RW - 1);
+                const int b0 = max((int)(pb.y & 0xffffu), ry0), b1 = min((int)(pb.y >> 16), ry0 + RH - 1);
                 if (a0 <= a1 && b0 <= b1) {
                     w = a1 - a0 + 1;
                     h = b1 - b0 + 1;
-                    if (w > WM || h > WM) {            // cannot happen for d <= d_max
-                        atomicOr(status, SP_STATUS_D_ABOVE_MAX);
-                        w = 0;
-                        h = 0;
-                    }
                     c0 = a0 - rx0;
                     r0 = b0 - ry0;
                 }
             }
-            stg[threadIdx.x] = r;                                   // (x, y, kappa_x, Af)
-            if (ANISO) stg2[threadIdx.x] = rs;                      // (kappa_y, kappa_xy)
-            box[threadIdx.x] = pack_box(c0, w, r0, h);
-            if (w > 0) {
-                const unsigned long long pk = (unsigned long long)r.w;
-                atomicAdd(&s_rows[r0], pk);
-                atomicAdd(&s_rows[r0 + h], 0ull - pk);
-            }
-            // zero column factors up to the next multiple of four: the splat adds
-            // whole quads, the columns past the patch adding zero (the factor pass
-            // then overwrites the quad's columns inside the patch)
-            if (w & 3)
-                *reinterpret_cast<float4*>(gx + threadIdx.x * WM + (w & ~3)) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
-        // work items: one per patch line j < max(w, h); item j carries the j-th
-        // column factor (if j < w) and the j-th row factor (if j < h)
-        const int m = w > h ? w : h;
-        int tm_;
-        const int em = stage_scan(m, n, s_wave, tm_);
-        const uint16_t tag = (uint16_t)(threadIdx.x << 8);
-        for (int j = 0; j < m; ++j) items[em + j] = tag | (uint16_t)j;
+        const int size = min(max(w, h), SIZES - 1);
+        uint32_t rank = 0, peak = 0;
+        if (w > 0) {
+            rank = atomicAdd(&s_hist[par][size], 1u);
+            const unsigned long long pk = (unsigned long long)r.w;
+            atomicAdd(&s_rows[r0], pk);
+            atomicAdd(&s_rows[r0 + h], 0ull - pk);
+            peak = (uint32_t)(r.w * 0x1p-8f) + 1u;
+        }
+        peak = wave_scan(peak);
+        if (lane == 63 && peak) atomicAdd(&s_sum, (unsigned long long)peak);
         __syncthreads();
-        // separable factors: gx per patch column here; the row factor Af * gy of
-        // a patch row is formed by the splat item that adds that row (every
-        // argument lies in [0, 18.1]: no range check needed)
-        for (int i = threadIdx.x; i < tm_; i += 256) {
-            const int it = items[i];
-            const int k = it >> 8, j = it & 255;
-            const uint32_t bx = box[k];
-            if (j < (int)((bx >> 8) & 255u) && (!ANISO || stg2[k].y == 0.0f)) {
-                const float4 sf = stg[k];
-                const float dx = ((float)(rx0 + (int)(bx & 255u) + j) + 0.5f) - sf.x;
-                gx[k * WM + j] = expneg_lt80(sf.z * (dx * dx));
-            }
+        // largest patches first: lane l of every wave scans size SIZES - 1 - l
+        const uint32_t inc = wave_scan(s_hist[par][SIZES - 1 - lane]);
+        const int n = __builtin_amdgcn_readlane((int)inc, SIZES - 2);       // patches of size >= 1
+        const uint32_t above = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (SIZES - 2 - size), (int)inc);
+        if (w > 0) {
+            const int slot = (int)((size < SIZES - 1 ? above : 0u) + rank);
+            stg[slot] = r;
+            if (ANISO) stg2[slot] = rs;
+            box[slot] = pack_box(c0, w, r0, h);
         }
         __syncthreads();
-        // splat: one patch row per work item, eight columns per step; columns past
-        // the patch edge carry zero factors (the accumulator has slack for the overrun)
-        for (int i = threadIdx.x; i < tm_; i += 256) {
-            const int it = items[i];
-            const int k = it >> 8, j = it & 255;
-            const uint32_t bx = box[k];
-            if (j >= (int)(bx >> 24)) continue;
-            const int pc0 = (int)(bx & 255u), pw = (int)((bx >> 8) & 255u), pr0 = (int)((bx >> 16) & 255u);
-            const float4 sf = stg[k];
-            const float dy = ((float)(ry0 + pr0 + j) + 0.5f) - sf.y;
+        if (t < SIZES) s_hist[par][t] = 0u;      // next used two passes on, past a barrier
+        // lanes per particle: 1, or 2 or 4 where the particles then still fit in `spread`
+        // lanes; 4 for the full model, whose patches (two diameters, an exponential per
+        // pixel) the sort leaves uneven (16 pairs of 1024^2: 1 / 4 / 8 lanes 187 / 146 /
+        // 155 us, one patch row per lane 177)
+        const int lp = ANISO || 4 * n <= spread ? 2 : 2 * n <= spread ? 1 : 0;
+        for (int s0 = wave * (64 >> lp); s0 < n; s0 += 4 * (64 >> lp)) {
+            const int slot = s0 + (lane >> lp);
+            const int step = 1 << lp, j = lane & (step - 1);
+            const bool on = slot < n;
+            const uint32_t bx = on ? box[slot] : 0u;
+            const float4 sf = stg[on ? slot : s0];
+            const int pc0 = (int)(bx & 255u), pw = (int)((bx >> 8) & 255u);
+            const int pr0 = (int)((bx >> 16) & 255u), ph = (int)(bx >> 24);
             uint32_t* dst = acc + (pr0 + j) * RW + pc0;
+            const float fx = (float)(rx0 + pc0) + 0.5f, fy = (float)(ry0 + pr0 + j) + 0.5f;
+            float ky = sf.z;
+            int hs = ph;
             if (ANISO) {
-                const float2 s2 = stg2[k];
+                const float2 s2 = stg2[on ? slot : s0];
+                ky = s2.x;
                 if (s2.y != 0.0f) {
                     // rho != 0: one exponential per pixel of the row
-                    const float ra = s2.y * dy, rb = s2.x * (dy * dy);
-                    for (int c = 0; c < pw; ++c) {
-                        const float dx = ((float)(rx0 + pc0 + c) + 0.5f) - sf.x;
-                        const float q = __builtin_fmaxf(__builtin_fmaf(dx, __builtin_fmaf(sf.z, dx, ra), rb), 0.0f);
-                        atomicAdd(dst + c, (uint32_t)(sf.w * expneg(q)));
+                    float fr = fy;
+                    for (int jr = j; jr < ph; jr += step) {
+                        const float dy = fr - sf.y;
+                        const float ra = s2.y * dy, rb = s2.x * (dy * dy);
+                        uint32_t* dr = dst + (jr - j) * RW;
+                        float fc = fx;
+                        for (int c = 0; c < pw; ++c) {
+                            const float dx = fc - sf.x;
+                            const float q = __builtin_fmaxf(__builtin_fmaf(dx, __builtin_fmaf(sf.z, dx, ra), rb), 0.0f);
+                            atomicAdd(dr + c, (uint32_t)(sf.w * expneg(q)));
+                            fc += 1.0f;
+                        }
+                        fr += (float)step;
                     }
-                    continue;
+                    hs = 0;                       // nothing left for the separable form
                 }
+                if (__builtin_amdgcn_ballot_w64(hs > 0) == 0) continue;
             }
-            const float rv = sf.w * expneg_lt80((ANISO ? stg2[k].x : sf.z) * (dy * dy));
-            const float* gk = gx + k * WM;
-            for (int cs0 = 0; cs0 < pw; cs0 += 8) {
-                const float4 g0 = *reinterpret_cast<const float4*>(gk + cs0);
-                atomicAdd(dst + cs0 + 0, (uint32_t)(rv * g0.x));
-                atomicAdd(dst + cs0 + 1, (uint32_t)(rv * g0.y));
-                atomicAdd(dst + cs0 + 2, (uint32_t)(rv * g0.z));
-                atomicAdd(dst + cs0 + 3, (uint32_t)(rv * g0.w));
-                if (pw - cs0 > 4) {
-                    const float4 g1 = *reinterpret_cast<const float4*>(gk + cs0 + 4);
-                    atomicAdd(dst + cs0 + 4, (uint32_t)(rv * g1.x));
-                    atomicAdd(dst + cs0 + 5, (uint32_t)(rv * g1.y));
-                    atomicAdd(dst + cs0 + 6, (uint32_t)(rv * g1.z));
-                    atomicAdd(dst + cs0 + 7, (uint32_t)(rv * g1.w));
-                }
-            }
+#define SP_SPLAT(K_) splat_columns<K_, RW>(dst, fx, sf.x, sf.z, pw, fy, sf.y, ky, sf.w, j, hs, step)
+            if (!__builtin_amdgcn_ballot_w64(pw > 4)) SP_SPLAT(4);
+            else if (!__builtin_amdgcn_ballot_w64(pw > 6)) SP_SPLAT(6);
+            else if (!__builtin_amdgcn_ballot_w64(pw > 8)) SP_SPLAT(8);
+            else if (!__builtin_amdgcn_ballot_w64(pw > 10)) SP_SPLAT(10);
+            else if (!__builtin_amdgcn_ballot_w64(pw > 12)) SP_SPLAT(12);
+            else if (!__builtin_amdgcn_ballot_w64(pw > 16)) SP_SPLAT(16);
+            else if (!__builtin_amdgcn_ballot_w64(pw > 20)) SP_SPLAT(20);
+            else
+                for (int cb = 0; __builtin_amdgcn_ballot_w64(pw > cb) != 0; cb += 16)
+                    splat_columns<16, RW>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
+                                          pw > cb ? hs : 0, step);
+#undef SP_SPLAT
         }
     }
-    // prefix sums of the row bounds (wave 0): flag a row whose bound reaches 2^32
     __syncthreads();
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
+    // prefix sums of the row bounds (wave 0): flag a row whose bound reaches 2^32
+    if (s_sum >= (1ull << 24) && t < 64) {
         unsigned long long carry = 0ull, top = 0ull;
         for (int c = 0; c <= RH; c += 64) {
             unsigned long long v = c + lane <= RH ? s_rows[c + lane] : 0ull;
@@ -747,7 +729,10 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     constexpr float FIX = 0x1p-24f;
     if constexpr (B > 0) {
         // horizontal pass over all region rows: four tile columns per work item
-        for (int k = threadIdx.x; k < RH * Q4; k += 256) {
+#pragma unroll
+        for (int k0 = 0; k0 < RH * Q4; k0 += 256) {
+            const int k = k0 + t;
+            if (k0 + 256 > RH * Q4 && k >= RH * Q4) break;
             const int r = k / Q4;
             const int c = (k % Q4) * 4;
             // the fixed-point scale rides on the weights: w (v 2^-24) and (w 2^-24) v
@@ -778,11 +763,10 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     // the current one (the Philox rounds are one long dependent chain)
     const bool noisy = a.noise_sigma > 0.0f;
     u32x4 w_next = {0u, 0u, 0u, 0u};
-    if (noisy && (int)threadIdx.x < TH * Q4)
-        w_next = draw((uint32_t)((ty * TH + (int)threadIdx.x / Q4) * Wq + ((tx * TW) >> 2) + (int)threadIdx.x % Q4),
-                      STREAM_NOISE0 + f, pid, a.seed);
+    if (noisy && t < TH * Q4)
+        w_next = draw((uint32_t)((ty * TH + t / Q4) * Wq + ((tx * TW) >> 2) + t % Q4), STREAM_NOISE0 + f, pid, a.seed);
 #pragma unroll 1
-    for (int gi = threadIdx.x; gi < TH * Q4; gi += 256) {
+    for (int gi = t; gi < TH * Q4; gi += 256) {
         const int r = gi / Q4;
         const int c4 = (gi % Q4) * 4;
         const int R = ty * TH + r;
@@ -855,8 +839,6 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     }
 }
 
-size_t render_lds_bytes(const RenderConfig& cfg, bool aniso) { return render_lds(cfg, aniso).bytes; }
-
 // Tile shapes with a compiled renderer (width x height).
 bool render_shape_supported(int tw, int th)
 {
@@ -882,22 +864,21 @@ static void launch_scans(const PairLayout* L, int n_pairs, uint32_t* hist, uint3
 
 // Launches one renderer instantiation: one workgroup per item, or (persistent
 // kernels) as many workgroups as the device holds at once, from the kernel's
-// occupancy at this LDS size (cached per kernel and size).  The persistent
-// form is compiled for the isotropic renderer; anisotropic batches run one
-// workgroup per item.
+// occupancy (cached per kernel).  The persistent form is compiled for the
+// isotropic renderer; anisotropic batches run one workgroup per item.
 template <typename K, typename... Args>
-static void launch_tile_kernel(K kernel, dim3 grid, size_t lds, hipStream_t s, bool persistent, Args... args)
+static void launch_tile_kernel(K kernel, dim3 grid, hipStream_t s, bool persistent, Args... args)
 {
     if (persistent) {
         static std::mutex mu;
-        static std::map<std::pair<const void*, size_t>, int> cache;
+        static std::map<const void*, int> cache;
         int per_cu = 0;
         {
             std::lock_guard<std::mutex> lk(mu);
-            const auto key = std::make_pair(reinterpret_cast<const void*>(kernel), lds);
+            const void* key = reinterpret_cast<const void*>(kernel);
             auto it = cache.find(key);
             if (it == cache.end()) {
-                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, lds) != hipSuccess)
+                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess)
                     per_cu = 0;
                 cache[key] = per_cu;
             } else {
@@ -909,11 +890,11 @@ static void launch_tile_kernel(K kernel, dim3 grid, size_t lds, hipStream_t s, b
             if (grid.x > cap) grid.x = cap;
         }
     }
-    hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, args...);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, args...);
 }
 
 template <int TW, int TH>
-static void launch_render_shape(dim3 grid, size_t lds, hipStream_t s, const RenderArgs& a, const RenderConfig& cfg,
+static void launch_render_shape(dim3 grid, hipStream_t s, const RenderArgs& a, const RenderConfig& cfg,
                                 const PairLayout* L, const float4* r0, const float4* r1, const uint2* b0,
                                 const uint2* b1, const float2* h0, const float2* h1, const uint32_t* tile_count,
                                 const int64_t* tile_offset, const int32_t* entries, int64_t tiles, uint32_t* status)
@@ -925,21 +906,25 @@ static void launch_render_shape(dim3 grid, size_t lds, hipStream_t s, const Rend
     ea.seed = a.seed;
     ea.iod = a.iod;
     for (int q = 0; q < 7; ++q) ea.blur_w[q] = a.blur_w[q];
+    // a grid of under four workgroups per CU leaves most of the chip idle and
+    // spreads a tile's particles over all four waves (a shorter walk), a larger
+    // one over as few waves as hold them (less work in all)
+    const int spread = grid.x < 4u * (unsigned)device_cu_count() ? 256 : 64;
 #define SP_B(B_)                                                                                                 \
     case B_:                                                                                                     \
         if (a.aniso)                                                                                             \
-            launch_tile_kernel(render_tile<TW, TH, B_, true, false>, grid, lds, s, false, a.pairs, L, a.n_pairs, \
-                               r0, r1, b0, b1, h0, h1, ea, cfg.cap, cfg.wm4, tile_count, tile_offset, entries,   \
+            launch_tile_kernel(render_tile<TW, TH, B_, true, false>, grid, s, false, a.pairs, L, a.n_pairs, \
+                               r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries,   \
                                tiles,                                                                            \
                                status, status + 8);                                                              \
         else if (cfg.persistent)                                                                                 \
-            launch_tile_kernel(render_tile<TW, TH, B_, false, true>, grid, lds, s, true, a.pairs, L, a.n_pairs,  \
-                               r0, r1, b0, b1, h0, h1, ea, cfg.cap, cfg.wm4, tile_count, tile_offset, entries,   \
+            launch_tile_kernel(render_tile<TW, TH, B_, false, true>, grid, s, true, a.pairs, L, a.n_pairs,  \
+                               r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries,   \
                                tiles,                                                                            \
                                status, status + 8);                                                              \
         else                                                                                                     \
-            launch_tile_kernel(render_tile<TW, TH, B_, false, false>, grid, lds, s, false, a.pairs, L,           \
-                               a.n_pairs, r0, r1, b0, b1, h0, h1, ea, cfg.cap, cfg.wm4, tile_count,              \
+            launch_tile_kernel(render_tile<TW, TH, B_, false, false>, grid, s, false, a.pairs, L,           \
+                               a.n_pairs, r0, r1, b0, b1, h0, h1, ea, spread, tile_count,              \
                                tile_offset, entries, tiles, status, status + 8);                                 \
         break;
     switch (cfg.apron) { SP_B(0) SP_B(1) SP_B(2) SP_B(3) default: break; }
@@ -1015,11 +1000,10 @@ hipError_t launch_render(const RenderArgs& a, const RenderConfig& cfg, const Bat
     if (e != hipSuccess) return e;
     if (tot.tiles > 0) {
         TimedScope ts("render_tile", s);
-        const size_t lds = render_lds_bytes(cfg, a.aniso);
         const dim3 grid((unsigned)(2 * tot.tiles));
 #define SP_SHAPE(W_, H_)                                                                                        \
     if (cfg.tile_w == W_ && cfg.tile_h == H_)                                                                   \
-        launch_render_shape<W_, H_>(grid, lds, s, a, cfg, L, rec0, rec1, box0, box1, shp0, shp1, tile_count,   \
+        launch_render_shape<W_, H_>(grid, s, a, cfg, L, rec0, rec1, box0, box1, shp0, shp1, tile_count,   \
                                     tile_offset, entries, tot.tiles, status);                                   \
     else
         SP_SHAPE(8, 8) SP_SHAPE(16, 16) SP_SHAPE(32, 16) SP_SHAPE(32, 32) SP_SHAPE(64, 16) SP_SHAPE(64, 32)

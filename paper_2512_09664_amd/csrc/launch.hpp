@@ -53,11 +53,9 @@ __device__ __forceinline__ int find_pair_by_tile(const PairLayout* L, int n_pair
 }
 
 struct RenderConfig {
-    int tile_w, tile_h, chunk, cap;
+    int tile_w, tile_h, chunk;
     int log_tw, log_th;     // tile sizes are powers of two
     int apron;              // blur radius b
-    int wmax;               // largest per-particle patch side the LDS tables hold
-    int wm4;                // wmax rounded up to a multiple of 4 (row stride of the tables)
     int kx, ky;             // bound on tiles touched per particle per axis
     float d_max;
     int persistent;         // renderer grid capped at the device's resident workgroups
@@ -216,7 +214,6 @@ struct EpilogueArgs {
 hipError_t launch_bins(const RenderArgs& a, const RenderConfig& cfg, const BatchTotals& tot, char* ws,
                        const WorkspaceLayout& wl, hipStream_t s);
 
-size_t render_lds_bytes(const RenderConfig& cfg, bool aniso = false);
 bool render_shape_supported(int tile_w, int tile_h);
 
 hipError_t launch_render(const RenderArgs& a, const RenderConfig& cfg, const BatchTotals& tot,

@@ -1,0 +1,49 @@
+"""The renderer's staging and splat at the sizes where they change form, against
+the binary32 mirror bit for bit (pixel sums are exact integers)."""
+
+import numpy as np
+import pytest
+
+pytest.importorskip("torch")
+import torch  # noqa: E402
+
+import gpu_util as gu  # noqa: E402
+import paper_2512_09664_amd as sp  # noqa: E402
+from oracle import ra32 as ra  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(H, W, n, d_range, tile, seed, box=None):
+    rng = np.random.default_rng([seed, n, H, W])
+    x0, x1, y0, y1 = box or (-3.0, W + 3.0, -3.0, H + 3.0)
+    q = {"x": rng.uniform(x0, x1, n), "y": rng.uniform(y0, y1, n), "z": rng.uniform(-1, 1, n),
+         "d": rng.uniform(*d_range, n), "I0": rng.uniform(0.05, 0.2, n)}
+    q = {k: v.astype(np.float32) for k, v in q.items()}
+    x2, y2 = (q[k] + rng.uniform(-2, 2, n).astype(np.float32) for k in ("x", "y"))
+    b = gu.batch_for([(H, W)], [(4, 4)], [n])
+    t = {k: gu.to_dev(v) for k, v in q.items()}
+    rp = sp.render_params(0.5, 16.0 if d_range[1] > 8 else 8.0, 0, 0.7, 0.0, 0)
+    img = sp.render_pair(b, t["x"], t["y"], gu.to_dev(x2), gu.to_dev(y2), t["z"], t["d"], t["I0"], rp,
+                         sp.tiling(*tile))
+    torch.cuda.synchronize()
+    got = gu.to_np(img).reshape(2, H, W)
+    for f, (xx, yy) in enumerate(((q["x"], q["y"]), (x2, y2))):
+        assert np.array_equal(got[f], ra.render(xx, yy, q["z"], q["d"], q["I0"], H, W, 0.5)), f
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 600])
+@pytest.mark.parametrize("tile", [(64, 32, 2048, 64), (64, 32, 2048, 64, 1)])
+def test_list_lengths(n, tile):
+    """One tile's list: 1, 2 and 4 lanes per particle, one pass and several."""
+    _check(32, 64, n, (1.0, 5.0), tile, 1, box=(8.0, 56.0, 8.0, 24.0))
+
+
+@pytest.mark.parametrize("d", [(0.2, 1.2), (1.0, 2.0), (1.8, 2.7), (2.5, 3.4), (3.2, 4.0), (3.9, 5.4), (5.2, 6.7),
+                               (6.5, 16.0)])
+@pytest.mark.parametrize("tile", [(8, 8, 256, 32), (64, 64, 2048, 128)])
+def test_patch_widths(d, tile):
+    """Every width class of the column factors, whole patches and patches cut by
+    tiles far smaller than them; 8 x 8 tiles make a grid that fills the chip
+    (fewest lanes per particle), 64 x 64 tiles one that does not."""
+    _check(190, 186, 700, d, tile, 2)
