@@ -26,34 +26,34 @@ __device__ __forceinline__ int pair_active(const synthpix_pair& P, uint64_t pid,
     return na < (double)P.n_max ? (int)na : P.n_max;
 }
 
+// Workgroups below `blocks` seed the particles, the ones after them write the
+// pairs' counts and densities.
 __global__ void __launch_bounds__(256)
-pair_scalars_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, synthpix_seed_params prm,
-                    uint64_t seed, int32_t* __restrict__ n_active_out, double* __restrict__ ppp_out,
-                    const synthpix_batch_io* __restrict__ iod, int32_t* __restrict__ live_out)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_pairs) return;
-    uint64_t base = 0;
-    if (iod) {
-        seed = iod->seed;
-        base = iod->pair_id_base;
-        n_active_out = iod->n_active;
-        ppp_out = iod->ppp;
-    }
-    double ppp;
-    const int na = pair_active(pairs[p], pairs[p].pair_id + base, prm, seed, &ppp);
-    if (n_active_out) n_active_out[p] = na;
-    if (ppp_out) ppp_out[p] = ppp;
-    if (live_out) live_out[p] = na;
-}
-
-__global__ void __launch_bounds__(256)
-seed_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span,
+seed_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span, unsigned blocks,
             synthpix_seed_params prm, uint64_t seed,
             float* __restrict__ x, float* __restrict__ y, float* __restrict__ z,
-            float* __restrict__ d, float* __restrict__ I0, const synthpix_batch_io* __restrict__ iod,
-            bool masked_still)
+            float* __restrict__ d, float* __restrict__ I0, int32_t* __restrict__ n_active_out,
+            double* __restrict__ ppp_out, const synthpix_batch_io* __restrict__ iod,
+            int32_t* __restrict__ live_out)
 {
+    if (blockIdx.x >= blocks) {
+        const int p = (int)(blockIdx.x - blocks) * 256 + (int)threadIdx.x;
+        if (p >= n_pairs) return;
+        uint64_t base = 0;
+        if (iod) {
+            seed = iod->seed;
+            base = iod->pair_id_base;
+            n_active_out = iod->n_active;
+            ppp_out = iod->ppp;
+        }
+        double ppp;
+        const int na = pair_active(pairs[p], pairs[p].pair_id + base, prm, seed, &ppp);
+        if (n_active_out) n_active_out[p] = na;
+        if (ppp_out) ppp_out[p] = ppp;
+        if (live_out) live_out[p] = na;
+        return;
+    }
+    const bool masked_still = iod && live_out;
     const int64_t g0 = (int64_t)blockIdx.x * blockDim.x;
     const int64_t g = g0 + threadIdx.x;
     if (g >= n_span) return;
@@ -489,14 +489,11 @@ hipError_t launch_seed(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_sp
                        const synthpix_batch_io* iod, int32_t* live)
 {
     TimedScope ts("seed", s);
-    if (n_active || ppp || iod || live)
-        hipLaunchKernelGGL(pair_scalars_kernel, dim3((unsigned)((n_pairs + 255) / 256)), dim3(256), 0, s, pairs_dev,
-                           n_pairs, prm, seed, n_active, ppp, iod, live);
-    if (n_span > 0) {
-        const int64_t blocks = (n_span + 255) / 256;
-        hipLaunchKernelGGL(seed_kernel, dim3((unsigned)blocks), dim3(256), 0, s, pairs_dev, n_pairs, n_span,
-                           prm, seed, x, y, z, d, I0, iod, iod != nullptr && live != nullptr);
-    }
+    const unsigned blocks = (unsigned)((n_span + 255) / 256);
+    const unsigned more = n_active || ppp || iod || live ? (unsigned)((n_pairs + 255) / 256) : 0u;
+    if (blocks + more > 0)
+        hipLaunchKernelGGL(seed_kernel, dim3(blocks + more), dim3(256), 0, s, pairs_dev, n_pairs, n_span, blocks, prm,
+                           seed, x, y, z, d, I0, n_active, ppp, iod, live);
     return hipGetLastError();
 }
 
