@@ -183,6 +183,7 @@ synthpix_status batch_totals(const synthpix_pair* ph, int32_t n_pairs, const sp:
         T.hist += 2 * n_chunks * nt;
         T.entries += 2 * cap;
         T.max_tiles = std::max<int64_t>(T.max_tiles, nt);
+        T.max_n = std::max<int64_t>(T.max_n, P.n_max);
     }
     if (T.chunks >= 65536 * 32768LL || T.tiles * 2 >= ((int64_t)1 << 31))
         return fail(SP_ERR_UNSUPPORTED, "batch too large for one launch");
@@ -435,6 +436,17 @@ BwdPlan bwd_plan(const synthpix_pair* ph, int32_t n_pairs, int64_t span, const s
                       eblur_span(ph, n_pairs, rp.blur_radius, b.tile, mse), b.tile, n_loss);
     b.total = b.wl.total + b.ob * (b.tile ? 2 : 1);
     return b;
+}
+
+// Whether the home-block order pays for an advection.  Per particle and bilinear
+// sample, index order costs about 7.9 ps and the order 2.4 ps plus, once, 24 ps
+// per particle and about 14 us of sorting (64 pairs of 1024^2, 3.4 M particles,
+// 16 samples: 423 against 142 us, 4 samples 113 / 116; one pair of 2048^2, 210 k
+// particles, 16 samples 34 / 53; of 512^2, 13 k particles, 9 / 25).
+bool order_pays(int64_t n_span, const synthpix_advect_params& ap)
+{
+    const double samples = (double)ap.substeps * (ap.integrator == SP_RK4 ? 4 : 1);
+    return (double)n_span * (5.5 * samples - 24.0) > 14e6;
 }
 
 // Builds the home-block order of (x, y) in `ws` at byte offset `base` and
@@ -697,6 +709,8 @@ synthpix_status synthpix_advect(const synthpix_pair* pairs_host, const synthpix_
         const size_t need = order_bytes(pairs_host, n_pairs);
         if (!need) return fail(SP_ERR_UNSUPPORTED, "batch too large for the advection order");
         if (ws_bytes < need) return fail(SP_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
+    }
+    if (workspace && order_pays(span, *ap)) {
         const hipError_t e = enqueue_order(pairs_host, pairs_dev, n_pairs, x1, y1, static_cast<char*>(workspace), 0,
                                            as_stream(stream), &order);
         if (e != hipSuccess) return hip_fail(e, "advect order launch");
@@ -1062,10 +1076,13 @@ hipError_t enqueue_batch(synthpix_plan* P, const synthpix_tiling& t, hipStream_t
     hipError_t e = sp::launch_seed(P->pairs_dev, P->n_pairs, P->span, P->sp, io.seed, io.x1, io.y1, io.z, io.d,
                                    io.I0, io.n_active, io.ppp, s, iod, P->live);
     if (e != hipSuccess) return e;
-    sp::AdvectOrder order{nullptr, nullptr};
-    e = enqueue_order(P->pairs_host.data(), P->pairs_dev, P->n_pairs, io.x1, io.y1, static_cast<char*>(P->workspace),
-                      0, s, &order, iod, P->live);
-    if (e != hipSuccess) return e;
+    sp::AdvectOrder order{};
+    order.live = P->live;
+    if (order_pays(P->span, P->ap)) {
+        e = enqueue_order(P->pairs_host.data(), P->pairs_dev, P->n_pairs, io.x1, io.y1,
+                          static_cast<char*>(P->workspace), 0, s, &order, iod, P->live);
+        if (e != hipSuccess) return e;
+    }
     e = sp::launch_advect(P->pairs_dev, P->n_pairs, P->span, io.flow, P->ap, io.x1, io.y1, io.x2, io.y2, s, order,
                           iod);
     if (e != hipSuccess) return e;

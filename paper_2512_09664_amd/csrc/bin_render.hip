@@ -6,13 +6,14 @@
 // square patches |dx|, |dy| <= 1.5 d (Section 2, "Efficient rasterization").
 //
 // Pipeline of one call (all pairs of a batch at once):
-//   bin_layout  : per-pair prefix tables (one block)
-//   prep        : per particle and frame, a 16-byte record (x, y, d, fixed-point
-//                 peak); d < 0 marks a particle that adds nothing
-//   bin_count   : per (pair, frame, particle chunk) LDS histogram of tile hits
-//   bin_scan    : per tile, chunk bases inside its list and its total; per
+//   bin_count   : per (pair, particle chunk), both frames' particle records (x, y,
+//                 kappa, fixed-point peak) and patch boxes, and an LDS histogram of
+//                 the tiles the boxes touch
+//   scans       : per tile, chunk bases inside its list and its total; per
 //                 (pair, frame), the exclusive scan of the totals -> list offsets
-//   bin_scatter : per chunk, LDS cursors -> particle indices into tile lists
+//   bin_scatter : per (pair, frame, chunk), LDS cursors -> particle indices into
+//                 tile lists
+//   (bins_small : the three of them in one launch, for small pairs)
 //   render_tile : per (pair, frame, tile) stage the list in LDS, splat the patches
 //                 into an LDS fixed-point accumulator (tile + blur apron), then
 //                 blur, noise, quantise and store.
@@ -37,7 +38,91 @@ __device__ __forceinline__ int find_pair_by_chunk(const PairLayout* L, int n_pai
     return lo;
 }
 
+// In-wave inclusive scan with DPP: row shifts by 1, 2, 4, 8 within each row of
+// 16 lanes, then the row broadcasts of lanes 15 and 31 into the rows above.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
+{
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    v = dpp_add<0x143, 0xC>(v);
+    return v;
+}
+
+// Exclusive prefix over the lanes of a wave.
+__device__ __forceinline__ int64_t wave_before(int64_t v)
+{
+    int64_t inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t u = __shfl_up(inc, o, 64);
+        if ((int)(threadIdx.x & 63) >= o) inc += u;
+    }
+    return inc - v;
+}
+
 // ------------------------------------------------------------------ layout
+
+// Batches of at most a wave of pairs need no layout launch: each wave of the
+// first binning kernel sums the pairs' sizes itself, one pair per lane, and takes
+// its workgroup's pair from them (one launch, about 5 us, less per call).
+constexpr int INLINE_PAIRS = 64;
+
+// Lane l's layout entry of pair l (l < n_pairs <= 64).
+__device__ __forceinline__ PairLayout lane_layout(const synthpix_pair* __restrict__ pairs, int n_pairs,
+                                                  const RenderConfig& cfg)
+{
+    const int l = (int)(threadIdx.x & 63);
+    PairLayout o{};
+    int64_t nt = 0, cap = 0;
+    if (l < n_pairs) {
+        const int n = pairs[l].n_max;
+        o.n_chunks = (n + cfg.chunk - 1) / cfg.chunk;
+        o.ntx = (pairs[l].W + cfg.tile_w - 1) >> cfg.log_tw;
+        o.nty = (pairs[l].H + cfg.tile_h - 1) >> cfg.log_th;
+        nt = (int64_t)o.ntx * o.nty;
+        cap = (int64_t)n * cfg.kx * cfg.ky;
+    }
+    o.entry_cap = cap;
+    o.chunk_base = (int32_t)wave_scan((uint32_t)o.n_chunks) - o.n_chunks;
+    o.tile_base = (int32_t)(wave_scan((uint32_t)nt) - (uint32_t)nt);
+    o.hist_base = wave_before(2 * (int64_t)o.n_chunks * nt);
+    o.entry_base = wave_before(2 * cap);
+    return o;
+}
+
+// The pair of chunk cb and its layout from the lanes' entries, as wave-uniform
+// values; workgroup 0 stores all entries and clears the status words.
+__device__ __forceinline__ int chunk_pair(const synthpix_pair* __restrict__ pairs, int n_pairs,
+                                          const RenderConfig& cfg, int cb, PairLayout* __restrict__ L,
+                                          uint32_t* __restrict__ status, PairLayout& o)
+{
+    const PairLayout mine = lane_layout(pairs, n_pairs, cfg);
+    const int l = (int)(threadIdx.x & 63);
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        if (l < n_pairs) L[l] = mine;
+        if (l < 16 && status) status[l] = 0u;
+    }
+    const int p = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(l < n_pairs && mine.chunk_base <= cb));
+    o.chunk_base = __builtin_amdgcn_readlane(mine.chunk_base, p);
+    o.n_chunks = __builtin_amdgcn_readlane(mine.n_chunks, p);
+    o.tile_base = __builtin_amdgcn_readlane(mine.tile_base, p);
+    o.ntx = __builtin_amdgcn_readlane(mine.ntx, p);
+    o.nty = __builtin_amdgcn_readlane(mine.nty, p);
+    o.flags = 0u;
+    o.hist_base = __shfl(mine.hist_base, p, 64);
+    o.entry_base = __shfl(mine.entry_base, p, 64);
+    o.entry_cap = __shfl(mine.entry_cap, p, 64);
+    return p;
+}
 
 __global__ void __launch_bounds__(256)
 bin_layout(const synthpix_pair* __restrict__ pairs, int n_pairs, RenderConfig cfg,
@@ -83,7 +168,7 @@ bin_layout(const synthpix_pair* __restrict__ pairs, int n_pairs, RenderConfig cf
             o.tile_base = (int32_t)(s_carry[1] + s_part[1][t] - v[1]);
             o.ntx = ntx;
             o.nty = nty;
-            o.pad_ = 0;
+            o.flags = 0u;
             o.hist_base = s_carry[2] + s_part[2][t] - v[2];
             o.entry_base = s_carry[3] + s_part[3][t] - v[3];
             o.entry_cap = cap;
@@ -97,57 +182,40 @@ bin_layout(const synthpix_pair* __restrict__ pairs, int n_pairs, RenderConfig cf
 
 // ------------------------------------------------------------------ particle records
 
-// Per particle and frame: the record (x, y, kappa, Af) with kappa = 8 / (d d)
-// and Af = min(2^24 I0 exp(-z^2 / (2 s^2)), 2^32 - 256), and the patch box
-// |dx|, |dy| <= 1.5 d clipped to the image (computed once here for every tile
-// list and tile that uses the particle).  Particles that add nothing (I0 <= 0,
-// d <= 0 or not a number, non-finite position) or whose d exceeds d_max
-// (flagged) get an empty box.  With live counts (captured plans), the masked
-// slots past a pair's count are skipped: the binning passes skip them too.
-__global__ void __launch_bounds__(256)
-prep_records(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span, RenderArgs a,
-             float d_max, float4* __restrict__ rec0, float4* __restrict__ rec1, uint2* __restrict__ box0,
-             uint2* __restrict__ box1, uint32_t* __restrict__ status)
+// One particle's record in one frame: (x, y, kappa_x, Af), its patch box clipped
+// to the image, in the anisotropic layout (kappa_y, kappa_xy), and the status
+// bits it raises.
+struct Record {
+    float4 rec;
+    uint2 box;
+    float2 shp;
+    uint32_t flags;
+};
+
+// The isotropic record: kappa = 8 / (d d), Af = min(2^24 I0 exp(-z^2 / (2 s^2)),
+// 2^32 - 256), the patch |dx|, |dy| <= 1.5 d.  Particles that add nothing (I0 <=
+// 0, d <= 0 or not a number, non-finite position) or whose d exceeds d_max
+// (flagged) get an empty box.
+__device__ __forceinline__ void record_iso(float x, float y, float z, float d, float I0, int W, int H,
+                                           float sheet_sigma, float d_max, Record& o)
 {
-    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x;
-    const int64_t g = g0 + threadIdx.x;
-    if (g >= n_span) return;
-    const int p = find_pair_from(pairs, n_pairs, g0, g);
-    const int64_t i = g - pairs[p].particle_offset;
-    if (i < 0 || i >= (a.live ? (int64_t)min(a.live[p], pairs[p].n_max) : (int64_t)pairs[p].n_max)) return;
-    if (a.iod) {
-        a.x[0] = a.iod->x1;
-        a.y[0] = a.iod->y1;
-        a.x[1] = a.iod->x2;
-        a.y[1] = a.iod->y2;
-        a.z = a.iod->z;
-        a.d = a.iod->d;
-        a.I0 = a.iod->I0;
-    }
-    const int W = pairs[p].W, H = pairs[p].H;
-    const float cs = 0.5f / (a.sheet_sigma * a.sheet_sigma);
-    const float z = a.z[g], d = a.d[g], I0 = a.I0[g];
-    const float x1 = a.x[0][g], y1 = a.y[0][g], x2 = a.x[1][g], y2 = a.y[1][g];
+    const float cs = 0.5f / (sheet_sigma * sheet_sigma);
     const float Af = fixed_peak(I0 * expneg((z * z) * cs));
     bool live = (I0 > 0.0f) && (d > 0.0f);
+    o.flags = 0u;
     if (live && !(d <= d_max)) {
-        atomicOr(status, SP_STATUS_D_ABOVE_MAX);
+        o.flags = SP_STATUS_D_ABOVE_MAX;
         live = false;
     }
     const float R = 1.5f * d;
-    const uint2 empty = make_uint2(EMPTY_BOX, EMPTY_BOX);
-    const float kap = live ? 8.0f / (d * d) : 0.0f;
-    rec0[g] = make_float4(x1, y1, kap, Af);
-    rec1[g] = make_float4(x2, y2, kap, Af);
-    box0[g] = live ? patch_box(x1, y1, R, R, W, H) : empty;
-    box1[g] = live ? patch_box(x2, y2, R, R, W, H) : empty;
+    o.rec = make_float4(x, y, live ? 8.0f / (d * d) : 0.0f, Af);
+    o.box = live ? patch_box(x, y, R, R, W, H) : make_uint2(EMPTY_BOX, EMPTY_BOX);
 }
 
 // The full particle model's records (Eq. 1 with sigma_y and rho; frame-2
 // parameter variation, the sentence after Eq. 1; per-frame hiding, Section 2
 // "Considerations on the aggregation"; the Remark 1 sheet law; frame-2 z from
-// the out-of-plane motion).  Per particle and frame: the record (x, y, d or -1,
-// 2^24 A) and, in the anisotropic layout, (d_y, rho).  Frame-2 parameters are
+// the out-of-plane motion).  Frame-2 parameters are
 // frame 1's plus zero-mean Gaussians (Philox stream 2: Box-Muller of words 0, 1
 // and 2, 3, cosine then sine, for d, d_y, rho, I0), clipped to [0, d_max],
 // [-0.99, 0.99] and [0, inf) (masked particles stay dark); a particle is hidden
@@ -166,83 +234,158 @@ __device__ __forceinline__ float model_peak(float I0, float z, const RenderArgs&
     return I0 * expneg((float)0.39894228040143267794 * pw);
 }
 
-__global__ void __launch_bounds__(256)
-prep_records_model(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span, RenderArgs a, float d_max,
-                   float4* __restrict__ rec0, float4* __restrict__ rec1, uint2* __restrict__ box0,
-                   uint2* __restrict__ box1, float2* __restrict__ shp0, float2* __restrict__ shp1,
-                   uint32_t* __restrict__ status)
+// The model's record of particle i (slot g) in frame f; hide: the particle's
+// words of stream 7 (read where hide_p > 0).
+__device__ __forceinline__ void record_model(const RenderArgs& a, int f, int64_t g, uint32_t i, uint64_t pid,
+                                             const u32x4& hide, int W, int H, float d_max, Record& o)
 {
-    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x;
-    const int64_t g = g0 + threadIdx.x;
-    if (g >= n_span) return;
-    const int p = find_pair_from(pairs, n_pairs, g0, g);
-    const int64_t i = g - pairs[p].particle_offset;
-    if (i < 0 || i >= pairs[p].n_max) return;
-    const uint64_t pid = pairs[p].pair_id;
-    const float x1 = a.x[0][g], y1 = a.y[0][g], x2 = a.x[1][g], y2 = a.y[1][g];
-    const float z1 = a.z[g];
-    const float z2 = a.z2 ? a.z2[g] : z1;
-    const float d = a.d[g];
-    const float dy = a.dy ? a.dy[g] : d;
-    const float r = a.rho ? a.rho[g] : 0.0f;
-    const float I = a.I0[g];
-    float d2 = d, dy2 = dy, r2 = r, I2 = I;
-    if (a.jit_d > 0.0f || a.jit_rho > 0.0f || a.jit_I0 > 0.0f) {
-        const u32x4 w = draw((uint32_t)i, STREAM_JITTER, pid, a.seed);
+    const float x = f ? a.x[1][g] : a.x[0][g], y = f ? a.y[1][g] : a.y[0][g];
+    const float z = f && a.z2 ? a.z2[g] : a.z[g];
+    float d = a.d[g];
+    float dy = a.dy ? a.dy[g] : d;
+    float r = a.rho ? a.rho[g] : 0.0f;
+    float I = a.I0[g];
+    if (f && (a.jit_d > 0.0f || a.jit_rho > 0.0f || a.jit_I0 > 0.0f)) {
+        const u32x4 w = draw(i, STREAM_JITTER, pid, a.seed);
         const float R0 = __builtin_sqrtf(-2.0f * log_ra(u24_open0(w.a)));
         const float R1 = __builtin_sqrtf(-2.0f * log_ra(u24_open0(w.c)));
         const float2 t0 = cossin2pi_ra(u24(w.b));
         const float2 t1 = cossin2pi_ra(u24(w.d));
         if (a.jit_d > 0.0f) {
-            d2 = __builtin_fminf(__builtin_fmaxf(__builtin_fmaf(a.jit_d, R0 * t0.x, d), 0.0f), d_max);
-            dy2 = __builtin_fminf(__builtin_fmaxf(__builtin_fmaf(a.jit_d, R0 * t0.y, dy), 0.0f), d_max);
+            d = __builtin_fminf(__builtin_fmaxf(__builtin_fmaf(a.jit_d, R0 * t0.x, d), 0.0f), d_max);
+            dy = __builtin_fminf(__builtin_fmaxf(__builtin_fmaf(a.jit_d, R0 * t0.y, dy), 0.0f), d_max);
         }
-        if (a.jit_rho > 0.0f) r2 = __builtin_fminf(__builtin_fmaxf(__builtin_fmaf(a.jit_rho, R1 * t1.x, r), -0.99f), 0.99f);
-        if (a.jit_I0 > 0.0f) I2 = I > 0.0f ? __builtin_fmaxf(__builtin_fmaf(a.jit_I0, R1 * t1.y, I), 0.0f) : 0.0f;
+        if (a.jit_rho > 0.0f) r = __builtin_fminf(__builtin_fmaxf(__builtin_fmaf(a.jit_rho, R1 * t1.x, r), -0.99f), 0.99f);
+        if (a.jit_I0 > 0.0f) I = I > 0.0f ? __builtin_fmaxf(__builtin_fmaf(a.jit_I0, R1 * t1.y, I), 0.0f) : 0.0f;
     }
-    float I1 = I;
-    if (a.hide_p > 0.0f) {
-        const u32x4 w = draw((uint32_t)i, STREAM_HIDE, pid, a.seed);
-        if (u24(w.a) < a.hide_p) I1 = 0.0f;
-        if (u24(w.b) < a.hide_p) I2 = 0.0f;
+    if (a.hide_p > 0.0f && u24(f ? hide.b : hide.a) < a.hide_p) I = 0.0f;
+    bool live = (I > 0.0f) && (d > 0.0f) && (dy > 0.0f);
+    o.flags = 0u;
+    if (live && !(d <= d_max && dy <= d_max)) {
+        o.flags = SP_STATUS_D_ABOVE_MAX;
+        live = false;
     }
-    const float dd[2] = {d, d2}, ddy[2] = {dy, dy2}, rr[2] = {r, r2}, II[2] = {I1, I2};
-    const float xx[2] = {x1, x2}, yy[2] = {y1, y2}, zz[2] = {z1, z2};
-    const int W = pairs[p].W, H = pairs[p].H;
-#pragma unroll
-    for (int f = 0; f < 2; ++f) {
-        bool live = (II[f] > 0.0f) && (dd[f] > 0.0f) && (ddy[f] > 0.0f);
-        if (live && !(dd[f] <= d_max && ddy[f] <= d_max)) {
-            atomicOr(status, SP_STATUS_D_ABOVE_MAX);
-            live = false;
-        }
-        if (live && !(__builtin_fabsf(rr[f]) <= 0.99f)) {
-            atomicOr(status, SP_STATUS_BAD_SHAPE);
-            live = false;
-        }
-        // om = 1 - rho^2; kappa_x = 8 / (om d^2), kappa_y = 8 / (om d_y^2),
-        // kappa_xy = -16 rho / (om d d_y) (0 for rho = 0: the separable form)
-        const float om = __builtin_fmaf(-rr[f], rr[f], 1.0f);
-        const float kx = live ? 8.0f / (om * (dd[f] * dd[f])) : 0.0f;
-        const float ky = live ? 8.0f / (om * (ddy[f] * ddy[f])) : 0.0f;
-        const float kxy = (live && rr[f] != 0.0f) ? (-16.0f * rr[f]) / (om * (dd[f] * ddy[f])) : 0.0f;
-        (f ? rec1 : rec0)[g] = make_float4(xx[f], yy[f], kx, fixed_peak(model_peak(II[f], zz[f], a)));
-        (f ? box1 : box0)[g] = live ? patch_box(xx[f], yy[f], 1.5f * dd[f], 1.5f * ddy[f], W, H)
-                                    : make_uint2(EMPTY_BOX, EMPTY_BOX);
-        if (a.aniso) (f ? shp1 : shp0)[g] = make_float2(ky, kxy);
+    if (live && !(__builtin_fabsf(r) <= 0.99f)) {
+        o.flags = SP_STATUS_BAD_SHAPE;
+        live = false;
     }
+    // om = 1 - rho^2; kappa_x = 8 / (om d^2), kappa_y = 8 / (om d_y^2),
+    // kappa_xy = -16 rho / (om d d_y) (0 for rho = 0: the separable form)
+    const float om = __builtin_fmaf(-r, r, 1.0f);
+    const float kx = live ? 8.0f / (om * (d * d)) : 0.0f;
+    const float ky = live ? 8.0f / (om * (dy * dy)) : 0.0f;
+    const float kxy = (live && r != 0.0f) ? (-16.0f * r) / (om * (d * dy)) : 0.0f;
+    o.rec = make_float4(x, y, kx, fixed_peak(model_peak(I, z, a)));
+    o.box = live ? patch_box(x, y, 1.5f * d, 1.5f * dy, W, H) : make_uint2(EMPTY_BOX, EMPTY_BOX);
+    o.shp = make_float2(ky, kxy);
 }
-
-// ------------------------------------------------------------------ membership
 
 // ------------------------------------------------------------------ count / scatter
 
-template <bool SCATTER>
+// Both frames' records of a chunk's particles (computed once for every tile list
+// and tile that uses them) and its tile histograms: frame f's count of a tile in
+// half f of one LDS word (a chunk has at most 2^14 particles).  A particle whose
+// diameter or rho is out of range gets an empty box that carries the status bits
+// (the status words are cleared by this launch, so the scatter raises them).
+// With live counts (captured plans), the masked slots past a pair's count are
+// skipped, here and in the scatter.  INLINE: at most 64 pairs, no layout launch.
+// Bound by the records' arithmetic and their traffic (28 B read, 48 B written per
+// particle).  The records pass the caches by, so that the boxes and histograms
+// the next launches read stay there; so do the inputs where they would fill the
+// last-level cache by themselves (STREAM).  Layout, records, count, scans and
+// scatter as six launches / as three: 64 pairs of 1024^2 139 / 107 us, 16 of
+// 512^2 45 / 31, one of 512^2 37 / 26, uneven pairs (8.2 M particles) 295 / 280;
+// 13.4 M particles in dense 2048^2 pairs the same.  1024 threads against 256: 16
+// pairs of 512^2 31 / 37 us.
+constexpr int COUNT_THREADS = 1024;
+
+template <bool STREAM>
+__device__ __forceinline__ float load_once(const float* p)
+{
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+__device__ __forceinline__ void store_once(float4* p, const float4& v)
+{
+    typedef float vec4 __attribute__((ext_vector_type(4)));
+    const vec4 u = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(u, reinterpret_cast<vec4*>(p));
+}
+
+template <bool MODEL, bool INLINE, bool STREAM>
+__global__ void __launch_bounds__(COUNT_THREADS)
+bin_count(const synthpix_pair* __restrict__ pairs, PairLayout* __restrict__ L, int n_pairs, RenderArgs a,
+          RenderConfig cfg, float4* __restrict__ rec0, float4* __restrict__ rec1, uint2* __restrict__ box0,
+          uint2* __restrict__ box1, float2* __restrict__ shp0, float2* __restrict__ shp1,
+          uint32_t* __restrict__ hist, unsigned n_chunks_total, const int32_t* __restrict__ live,
+          uint32_t* __restrict__ status)
+{
+    extern __shared__ uint32_t lh[];
+    const unsigned cb = xcd_contiguous(blockIdx.x, n_chunks_total);
+    int p;
+    PairLayout PL;
+    if (INLINE) {
+        p = chunk_pair(pairs, n_pairs, cfg, (int)cb, L, status, PL);
+    } else {
+        p = find_pair_by_chunk(L, n_pairs, cb);
+        PL = L[p];
+    }
+    const synthpix_pair P = pairs[p];
+    const int chunk = (int)cb - PL.chunk_base;
+    const int nt = PL.ntx * PL.nty;
+    const int i_end = min(live ? min(live[p], P.n_max) : P.n_max, (chunk + 1) * cfg.chunk);
+    // a chunk past the live slots holds nothing (and is not scanned): the whole
+    // workgroup returns before its barrier
+    if (live && chunk * cfg.chunk >= i_end) return;
+    if (!MODEL && a.iod) a.use(*a.iod);
+    for (int k = threadIdx.x; k < nt; k += COUNT_THREADS) lh[k] = 0u;
+    __syncthreads();
+    for (int i = chunk * cfg.chunk + (int)threadIdx.x; i < i_end; i += COUNT_THREADS) {
+        const int64_t g = P.particle_offset + i;
+        u32x4 hide = {0u, 0u, 0u, 0u};
+        float z = 0.0f, d = 0.0f, I0 = 0.0f;
+        if (MODEL) {
+            if (a.hide_p > 0.0f) hide = draw((uint32_t)i, STREAM_HIDE, P.pair_id, a.seed);
+        } else {
+            z = load_once<STREAM>(a.z + g);
+            d = load_once<STREAM>(a.d + g);
+            I0 = load_once<STREAM>(a.I0 + g);
+        }
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            Record o;
+            if (MODEL)
+                record_model(a, f, g, (uint32_t)i, P.pair_id, hide, P.W, P.H, cfg.d_max, o);
+            else
+                record_iso(load_once<STREAM>(a.x[f] + g), load_once<STREAM>(a.y[f] + g), z, d, I0, P.W, P.H,
+                           a.sheet_sigma, cfg.d_max, o);
+            if (o.flags) o.box.y = EMPTY_BOX | (o.flags << EMPTY_FLAGS);
+            store_once((f ? rec1 : rec0) + g, o.rec);
+            (f ? box1 : box0)[g] = o.box;
+            if (MODEL && a.aniso) (f ? shp1 : shp0)[g] = o.shp;
+            int tx0, tx1, ty0, ty1;
+            if (!tile_rect(o.box, cfg, PL.ntx, PL.nty, tx0, tx1, ty0, ty1)) continue;
+            for (int ty = ty0; ty <= ty1; ++ty)
+                for (int tx = tx0; tx <= tx1; ++tx) atomicAdd(&lh[ty * PL.ntx + tx], 1u << (16 * f));
+        }
+    }
+    __syncthreads();
+    uint32_t* gh = hist + PL.hist_base + (int64_t)chunk * nt;
+    uint32_t* gh1 = gh + (int64_t)PL.n_chunks * nt;
+    for (int k = threadIdx.x; k < nt; k += COUNT_THREADS) {
+        const uint32_t v = lh[k];
+        gh[k] = v & 0xffffu;
+        gh1[k] = v >> 16;
+    }
+}
+
 __global__ void __launch_bounds__(256)
-bin_pass(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__ L, int n_pairs,
-         const uint2* __restrict__ box0, const uint2* __restrict__ box1, RenderConfig cfg, uint32_t* __restrict__ hist,
-         const int64_t* __restrict__ tile_offset, int64_t tiles_total, int32_t* __restrict__ entries,
-         unsigned n_chunks_total, const int32_t* __restrict__ live)
+bin_scatter(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__ L, int n_pairs,
+            const uint2* __restrict__ box0, const uint2* __restrict__ box1, RenderConfig cfg,
+            const uint32_t* __restrict__ hist, const int64_t* __restrict__ tile_offset, int64_t tiles_total,
+            int32_t* __restrict__ entries, unsigned n_chunks_total, const int32_t* __restrict__ live,
+            uint32_t* __restrict__ status)
 {
     extern __shared__ uint32_t lh[];
     const int f = blockIdx.y;
@@ -252,16 +395,15 @@ bin_pass(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__
     const PairLayout PL = L[p];
     const int chunk = (int)cb - PL.chunk_base;
     const int nt = PL.ntx * PL.nty;
-    uint32_t* gh = hist + PL.hist_base + ((int64_t)f * PL.n_chunks + chunk) * nt;
+    const uint32_t* gh = hist + PL.hist_base + ((int64_t)f * PL.n_chunks + chunk) * nt;
     int32_t* seg = entries + PL.entry_base + (int64_t)f * PL.entry_cap;
-    // scatter cursors start at the chunk's first slot in each tile list
+    // cursors start at the chunk's first slot in each tile list
     const int64_t* toff = tile_offset + f * tiles_total + PL.tile_base;
     const int64_t seg0 = PL.entry_base + (int64_t)f * PL.entry_cap;
     const int i_end = min(live ? min(live[p], P.n_max) : P.n_max, (chunk + 1) * cfg.chunk);
-    // a chunk past the live slots holds nothing (and is not scanned): the whole
-    // workgroup returns before its barrier
+    // a chunk past the live slots holds nothing: the whole workgroup returns before its barrier
     if (live && chunk * cfg.chunk >= i_end) return;
-    for (int t = threadIdx.x; t < nt; t += blockDim.x) lh[t] = SCATTER ? gh[t] + (uint32_t)(toff[t] - seg0) : 0u;
+    for (int t = threadIdx.x; t < nt; t += blockDim.x) lh[t] = gh[t] + (uint32_t)(toff[t] - seg0);
     __syncthreads();
     const uint2* __restrict__ bxs = f ? box1 : box0;
     // BIN_ILP particles per thread and step: their box loads and LDS atomic
@@ -278,17 +420,13 @@ bin_pass(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__
         for (int q = 0; q < BIN_ILP; ++q) {
             const int i = i0 + q * blockDim.x;
             int tx0, tx1, ty0, ty1;
-            if (!tile_rect(r[q], cfg, PL.ntx, PL.nty, tx0, tx1, ty0, ty1)) continue;
+            if (!tile_rect(r[q], cfg, PL.ntx, PL.nty, tx0, tx1, ty0, ty1)) {
+                if (r[q].y >> EMPTY_FLAGS) atomicOr(status, r[q].y >> EMPTY_FLAGS);
+                continue;
+            }
             for (int ty = ty0; ty <= ty1; ++ty)
-                for (int tx = tx0; tx <= tx1; ++tx) {
-                    const uint32_t slot = atomicAdd(&lh[ty * PL.ntx + tx], 1u);
-                    if (SCATTER) seg[slot] = i;
-                }
+                for (int tx = tx0; tx <= tx1; ++tx) seg[atomicAdd(&lh[ty * PL.ntx + tx], 1u)] = i;
         }
-    }
-    if (!SCATTER) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < nt; t += blockDim.x) gh[t] = lh[t];
     }
 }
 
@@ -315,9 +453,9 @@ __device__ __forceinline__ int home_block(float x, float y, int W, int H, const 
     return s0 * PL.ntx + col * rows + (by - s0);
 }
 
-template <bool SCATTER>
+template <bool SCATTER, bool INLINE>
 __global__ void __launch_bounds__(256)
-order_pass(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__ L, int n_pairs,
+order_pass(const synthpix_pair* __restrict__ pairs, PairLayout* __restrict__ L, int n_pairs,
            const float* __restrict__ x, const float* __restrict__ y, RenderConfig cfg, uint32_t* __restrict__ hist,
            const int64_t* __restrict__ tile_offset, int32_t* __restrict__ entries, unsigned n_chunks_total,
            const synthpix_batch_io* __restrict__ iod, const int32_t* __restrict__ live)
@@ -328,9 +466,15 @@ order_pass(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict
         y = iod->y1;
     }
     const unsigned cb = xcd_contiguous(blockIdx.x, n_chunks_total);
-    const int p = find_pair_by_chunk(L, n_pairs, cb);
+    int p;
+    PairLayout PL;
+    if (INLINE) {
+        p = chunk_pair(pairs, n_pairs, cfg, (int)cb, L, nullptr, PL);
+    } else {
+        p = find_pair_by_chunk(L, n_pairs, cb);
+        PL = L[p];
+    }
     const synthpix_pair P = pairs[p];
-    const PairLayout PL = L[p];
     const int chunk = (int)cb - PL.chunk_base;
     const int nt = PL.ntx * PL.nty;
     uint32_t* gh = hist + PL.hist_base + (int64_t)chunk * nt;
@@ -354,6 +498,219 @@ order_pass(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict
     }
 }
 
+// ------------------------------------------------------------------ small pairs
+
+// One workgroup does a whole pair's (and frame's) binning where the pairs are
+// small: layout, records, tile counts, their scan and the scatter in one launch
+// instead of six, the counts never leaving LDS.  It walks the particles twice
+// with 1024 threads.
+constexpr int SMALL_THREADS = 1024;
+
+// Pair p's layout: the tiles and entry slots of the pairs before it, summed over
+// the workgroup (the chunk tables of the chunked passes stay empty).
+__device__ __forceinline__ PairLayout small_layout(const synthpix_pair* __restrict__ pairs, int p,
+                                                   const RenderConfig& cfg, int64_t (*s_part)[SMALL_THREADS / 64])
+{
+    int64_t tiles = 0, slots = 0;
+    for (int q = (int)threadIdx.x; q < p; q += SMALL_THREADS) {
+        const int tx = (pairs[q].W + cfg.tile_w - 1) >> cfg.log_tw, ty = (pairs[q].H + cfg.tile_h - 1) >> cfg.log_th;
+        tiles += (int64_t)tx * ty;
+        slots += 2 * (int64_t)pairs[q].n_max * cfg.kx * cfg.ky;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        tiles += __shfl_xor(tiles, o, 64);
+        slots += __shfl_xor(slots, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s_part[0][threadIdx.x >> 6] = tiles;
+        s_part[1][threadIdx.x >> 6] = slots;
+    }
+    __syncthreads();
+    tiles = slots = 0;
+#pragma unroll
+    for (int w = 0; w < SMALL_THREADS / 64; ++w) {
+        tiles += s_part[0][w];
+        slots += s_part[1][w];
+    }
+    PairLayout o;
+    o.chunk_base = 0;
+    o.n_chunks = 0;
+    o.tile_base = (int32_t)tiles;
+    o.ntx = (pairs[p].W + cfg.tile_w - 1) >> cfg.log_tw;
+    o.nty = (pairs[p].H + cfg.tile_h - 1) >> cfg.log_th;
+    o.flags = 0u;
+    o.hist_base = 0;
+    o.entry_base = slots;
+    o.entry_cap = (int64_t)pairs[p].n_max * cfg.kx * cfg.ky;
+    return o;
+}
+
+// Exclusive scan of the nt tile counts in lh, in place; counts and list offsets
+// (seg0 plus the prefix) go to count and offset.
+__device__ __forceinline__ void small_scan(uint32_t* lh, int nt, int64_t seg0, uint32_t* __restrict__ count,
+                                           int64_t* __restrict__ offset, uint32_t* s_wave)
+{
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (int b = 0; b < nt; b += SMALL_THREADS) {
+        const int t = b + (int)threadIdx.x;
+        const uint32_t v = t < nt ? lh[t] : 0u;
+        const uint32_t inc = wave_scan(v);
+        if (lane == 63) s_wave[wid] = inc;
+        __syncthreads();
+        uint32_t before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < SMALL_THREADS / 64; ++w) {
+            const uint32_t sw = s_wave[w];
+            if (w < wid) before += sw;
+            total += sw;
+        }
+        if (t < nt) {
+            const uint32_t at = carry + before + inc - v;
+            lh[t] = at;
+            count[t] = v;
+            offset[t] = seg0 + at;
+        }
+        carry += total;
+        __syncthreads();
+    }
+}
+
+// Grid (pair, frame).  A status bit of pair p and frame f is left in the pair's
+// layout: the renderer raises it (the status words are cleared here, by one of
+// the workgroups).
+template <bool MODEL>
+__global__ void __launch_bounds__(SMALL_THREADS)
+bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig cfg, PairLayout* __restrict__ L,
+           float4* __restrict__ rec0, float4* __restrict__ rec1, uint2* __restrict__ box0, uint2* __restrict__ box1,
+           float2* __restrict__ shp0, float2* __restrict__ shp1, uint32_t* __restrict__ tile_count,
+           int64_t* __restrict__ tile_offset, int64_t tiles_total, int32_t* __restrict__ entries,
+           const int32_t* __restrict__ live, uint32_t* __restrict__ status)
+{
+    extern __shared__ uint32_t lh[];
+    __shared__ int64_t s_part[2][SMALL_THREADS / 64];
+    __shared__ uint32_t s_wave[SMALL_THREADS / 64];
+    __shared__ uint32_t s_flags;
+    const int p = blockIdx.x, f = blockIdx.y, t = (int)threadIdx.x;
+    if (!MODEL && a.iod) a.use(*a.iod);
+    const synthpix_pair P = pairs[p];
+    if (t == 0) s_flags = 0u;
+    if (p == 0 && f == 0 && t < 16) status[t] = 0u;
+    const PairLayout o = small_layout(pairs, p, cfg, s_part);
+    const int nt = o.ntx * o.nty;
+    for (int k = t; k < nt; k += SMALL_THREADS) lh[k] = 0u;
+    __syncthreads();
+    float4* __restrict__ rec = (f ? rec1 : rec0) + P.particle_offset;
+    uint2* __restrict__ box = (f ? box1 : box0) + P.particle_offset;
+    float2* __restrict__ shp = (f ? shp1 : shp0) + P.particle_offset;
+    const int n = live ? min(live[p], P.n_max) : P.n_max;
+    uint32_t flags = 0u;
+    // two particles per thread and step, so that their loads overlap
+    for (int i0 = t; i0 < n; i0 += 2 * SMALL_THREADS) {
+        Record r[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int i = i0 + q * SMALL_THREADS;
+            const int64_t g = P.particle_offset + min(i, n - 1);
+            if (MODEL) {
+                u32x4 hide = {0u, 0u, 0u, 0u};
+                if (a.hide_p > 0.0f) hide = draw((uint32_t)i, STREAM_HIDE, P.pair_id, a.seed);
+                record_model(a, f, g, (uint32_t)i, P.pair_id, hide, P.W, P.H, cfg.d_max, r[q]);
+            } else {
+                record_iso((f ? a.x[1] : a.x[0])[g], (f ? a.y[1] : a.y[0])[g], a.z[g], a.d[g], a.I0[g], P.W, P.H, a.sheet_sigma, cfg.d_max, r[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int i = i0 + q * SMALL_THREADS;
+            if (i >= n) break;
+            rec[i] = r[q].rec;
+            box[i] = r[q].box;
+            if (MODEL && a.aniso) shp[i] = r[q].shp;
+            flags |= r[q].flags;
+            int tx0, tx1, ty0, ty1;
+            if (!tile_rect(r[q].box, cfg, o.ntx, o.nty, tx0, tx1, ty0, ty1)) continue;
+            for (int ty = ty0; ty <= ty1; ++ty)
+                for (int tx = tx0; tx <= tx1; ++tx) atomicAdd(&lh[ty * o.ntx + tx], 1u);
+        }
+    }
+    if (flags) atomicOr(&s_flags, flags);
+    __syncthreads();
+    const int64_t seg0 = o.entry_base + (int64_t)f * o.entry_cap;
+    small_scan(lh, nt, seg0, tile_count + f * tiles_total + o.tile_base, tile_offset + f * tiles_total + o.tile_base,
+               s_wave);
+    if (t == 0) {
+        if (f == 0) {
+            L[p].tile_base = o.tile_base;
+            L[p].ntx = o.ntx;
+            L[p].nty = o.nty;
+            L[p].entry_base = o.entry_base;
+            L[p].entry_cap = o.entry_cap;
+        }
+        reinterpret_cast<uint8_t*>(&L[p].flags)[f] = (uint8_t)s_flags;
+    }
+    int32_t* seg = entries + seg0;
+    for (int i = t; i < n; i += SMALL_THREADS) {
+        int tx0, tx1, ty0, ty1;
+        if (!tile_rect(box[i], cfg, o.ntx, o.nty, tx0, tx1, ty0, ty1)) continue;
+        for (int ty = ty0; ty <= ty1; ++ty)
+            for (int tx = tx0; tx <= tx1; ++tx) seg[atomicAdd(&lh[ty * o.ntx + tx], 1u)] = i;
+    }
+}
+
+// The home-block order of small pairs in one launch: one workgroup per pair.
+__global__ void __launch_bounds__(SMALL_THREADS)
+order_small(const synthpix_pair* __restrict__ pairs, const float* __restrict__ x, const float* __restrict__ y,
+            RenderConfig cfg, PairLayout* __restrict__ L, uint32_t* __restrict__ tile_count,
+            int64_t* __restrict__ tile_offset, int32_t* __restrict__ entries,
+            const synthpix_batch_io* __restrict__ iod, const int32_t* __restrict__ live)
+{
+    extern __shared__ uint32_t lh[];
+    __shared__ int64_t s_part[2][SMALL_THREADS / 64];
+    __shared__ uint32_t s_wave[SMALL_THREADS / 64];
+    const int p = blockIdx.x, t = (int)threadIdx.x;
+    if (iod) {
+        x = iod->x1;
+        y = iod->y1;
+    }
+    const synthpix_pair P = pairs[p];
+    const PairLayout o = small_layout(pairs, p, cfg, s_part);
+    const int nt = o.ntx * o.nty;
+    for (int k = t; k < nt; k += SMALL_THREADS) lh[k] = 0u;
+    __syncthreads();
+    x += P.particle_offset;
+    y += P.particle_offset;
+    const int n = live ? min(live[p], P.n_max) : P.n_max;
+    for (int i = t; i < n; i += SMALL_THREADS) atomicAdd(&lh[home_block(x[i], y[i], P.W, P.H, o, cfg)], 1u);
+    __syncthreads();
+    small_scan(lh, nt, o.entry_base, tile_count + o.tile_base, tile_offset + o.tile_base, s_wave);
+    if (t == 0) L[p] = o;
+    int32_t* seg = entries + o.entry_base;
+    for (int i = t; i < n; i += SMALL_THREADS)
+        seg[atomicAdd(&lh[home_block(x[i], y[i], P.W, P.H, o, cfg)], 1u)] = i;
+}
+
+// ------------------------------------------------------------------ scans
+
+// Exclusive prefix, in place, of one tile's nc chunk counts (nt apart); their sum.
+__device__ __forceinline__ uint32_t scan_column(uint32_t* __restrict__ h, int nt, int nc)
+{
+    constexpr int U = 8;                 // chunk rows loaded together
+    uint32_t run = 0;
+    for (int c0 = 0; c0 < nc; c0 += U) {
+        uint32_t v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) v[k] = c0 + k < nc ? h[(int64_t)(c0 + k) * nt] : 0u;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (c0 + k < nc) h[(int64_t)(c0 + k) * nt] = run;
+            run += v[k];
+        }
+    }
+    return run;
+}
+
 // Per (pair, frame, tile), one thread each: exclusive prefix of the chunk
 // histograms over the chunks, in place (each chunk's first slot inside the
 // tile's list), and the tile's total.  Consecutive threads take consecutive
@@ -372,58 +729,80 @@ scan_chunks(const PairLayout* __restrict__ L, int n_pairs, uint32_t* __restrict_
     const int nt = PL.ntx * PL.nty;
     const int t = (int)(gt - PL.tile_base);
     const int nc = live ? min(PL.n_chunks, (max(live[p], 0) + chunk - 1) / chunk) : PL.n_chunks;
-    uint32_t* h = hist + PL.hist_base + (int64_t)f * PL.n_chunks * nt + t;
-    constexpr int U = 8;                 // chunk rows loaded together
-    uint32_t run = 0;
-    for (int c0 = 0; c0 < nc; c0 += U) {
-        uint32_t v[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = c0 + k < nc ? h[(int64_t)(c0 + k) * nt] : 0u;
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            if (c0 + k < nc) h[(int64_t)(c0 + k) * nt] = run;
-            run += v[k];
-        }
-    }
+    const uint32_t run = scan_column(hist + PL.hist_base + (int64_t)f * PL.n_chunks * nt + t, nt, nc);
     tile_count[f * tiles_total + gt] = run;
+}
+
+// Exclusive scan over a workgroup of SCAN_THREADS.
+constexpr int SCAN_THREADS = 1024;
+
+__device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t* s_wave, uint32_t& total)
+{
+    const int wid = threadIdx.x >> 6;
+    const uint32_t inc = wave_scan(v);
+    if ((threadIdx.x & 63) == 63) s_wave[wid] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+        const uint32_t sw = s_wave[w];
+        if (w < wid) before += sw;
+        total += sw;
+    }
+    __syncthreads();
+    return before + inc - v;
 }
 
 // Per (pair, frame): exclusive scan of the tile totals -> absolute offsets of
 // the tile lists (the pair-frame segment's base plus the prefix).
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(SCAN_THREADS)
 scan_tiles(const PairLayout* __restrict__ L, const uint32_t* __restrict__ tile_count,
            int64_t* __restrict__ tile_offset, int64_t tiles_total)
 {
-    __shared__ uint32_t s_wave[4];
+    __shared__ uint32_t s_wave[SCAN_THREADS / 64];
     const int p = blockIdx.x;
     const int f = blockIdx.y;
     const PairLayout PL = L[p];
     const int nt = PL.ntx * PL.nty;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const uint32_t* cnt = tile_count + f * tiles_total + PL.tile_base;
     int64_t* out = tile_offset + f * tiles_total + PL.tile_base;
     int64_t carry = PL.entry_base + (int64_t)f * PL.entry_cap;
-    for (int b = 0; b < nt; b += 256) {
+    for (int b = 0; b < nt; b += SCAN_THREADS) {
         const int t = b + threadIdx.x;
-        const uint32_t v = t < nt ? cnt[t] : 0u;
-        uint32_t inc = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t x = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += x;
-        }
-        if (lane == 63) s_wave[wid] = inc;
-        __syncthreads();
-        uint32_t before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const uint32_t sw = s_wave[w];
-            if (w < wid) before += sw;
-            total += sw;
-        }
-        if (t < nt) out[t] = carry + (int64_t)(before + inc - v);
+        uint32_t total;
+        const uint32_t before = block_before(t < nt ? cnt[t] : 0u, s_wave, total);
+        if (t < nt) out[t] = carry + (int64_t)before;
         carry += total;
-        __syncthreads();
+    }
+}
+
+// Both scans in one launch, one workgroup per (pair, frame): where a pair has few
+// chunks the walk over them is short, and the launch it saves is worth more
+// (SCAN_FUSED steps of chunks x 1024 tiles, about 0.2 us each).
+constexpr int SCAN_FUSED = 64;
+
+__global__ void __launch_bounds__(SCAN_THREADS)
+scan_pair(const PairLayout* __restrict__ L, uint32_t* __restrict__ hist, uint32_t* __restrict__ tile_count,
+          int64_t* __restrict__ tile_offset, int64_t tiles_total, const int32_t* __restrict__ live, int chunk)
+{
+    __shared__ uint32_t s_wave[SCAN_THREADS / 64];
+    const int p = blockIdx.x;
+    const int f = blockIdx.y;
+    const PairLayout PL = L[p];
+    const int nt = PL.ntx * PL.nty;
+    const int nc = live ? min(PL.n_chunks, (max(live[p], 0) + chunk - 1) / chunk) : PL.n_chunks;
+    int64_t carry = PL.entry_base + (int64_t)f * PL.entry_cap;
+    for (int b = 0; b < nt; b += SCAN_THREADS) {
+        const int t = b + threadIdx.x;
+        const uint32_t run = t < nt ? scan_column(hist + PL.hist_base + (int64_t)f * PL.n_chunks * nt + t, nt, nc) : 0u;
+        uint32_t total;
+        const uint32_t before = block_before(run, s_wave, total);
+        if (t < nt) {
+            tile_count[f * tiles_total + PL.tile_base + t] = run;
+            tile_offset[f * tiles_total + PL.tile_base + t] = carry + (int64_t)before;
+        }
+        carry += total;
     }
 }
 
@@ -432,25 +811,6 @@ scan_tiles(const PairLayout* __restrict__ L, const uint32_t* __restrict__ tile_c
 constexpr int STAGE = 256;      // particles staged per pass, one per thread
 constexpr int SLACK = 24;       // accumulator words past the region (a row's zero columns may overrun it)
 constexpr int SIZES = 64;       // patch sizes told apart when a pass is sorted
-
-// In-wave inclusive scan with DPP: row shifts by 1, 2, 4, 8 within each row of
-// 16 lanes, then the row broadcasts of lanes 15 and 31 into the rows above.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
-{
-    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
-}
-
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
-{
-    v = dpp_add<0x111, 0xF>(v);
-    v = dpp_add<0x112, 0xF>(v);
-    v = dpp_add<0x114, 0xF>(v);
-    v = dpp_add<0x118, 0xF>(v);
-    v = dpp_add<0x142, 0xA>(v);
-    v = dpp_add<0x143, 0xC>(v);
-    return v;
-}
 
 __device__ __forceinline__ uint32_t pack_box(int c0, int w, int r0, int h)
 {
@@ -590,6 +950,10 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     const int tx = tl - ty * ntx;
     const int rx0 = tx * TW - B;          // region origin in image pixels
     const int ry0 = ty * TH - B;
+    if (tl == 0 && t == 0) {
+        const uint32_t fl = (L[p].flags >> (8 * f)) & 255u;      // raised by the small pairs' binning
+        if (fl) atomicOr(status, fl);
+    }
     const int cnt = (int)tile_count[item];
     const int32_t* __restrict__ list = entries + tile_offset[item];
     const float4* __restrict__ rec = (f ? rec1 : rec0) + p_off;
@@ -852,14 +1216,21 @@ bool render_shape_supported(int tw, int th)
 
 // ------------------------------------------------------------------ launcher
 
-static void launch_scans(const PairLayout* L, int n_pairs, uint32_t* hist, uint32_t* tile_count,
-                         int64_t* tile_offset, int64_t tiles, int frames, hipStream_t s, const int32_t* live,
+static void launch_scans(const PairLayout* L, int n_pairs, uint32_t* hist, const BatchTotals& tot,
+                         uint32_t* tile_count, int64_t* tile_offset, int frames, hipStream_t s, const int32_t* live,
                          int chunk)
 {
+    const int64_t tiles = tot.tiles;
+    const int64_t steps = ((tot.max_n + chunk - 1) / chunk) * ((tot.max_tiles + SCAN_THREADS - 1) / SCAN_THREADS);
+    if (steps <= SCAN_FUSED) {
+        hipLaunchKernelGGL(scan_pair, dim3((unsigned)n_pairs, frames), dim3(SCAN_THREADS), 0, s, L, hist, tile_count,
+                           tile_offset, tiles, live, chunk);
+        return;
+    }
     hipLaunchKernelGGL(scan_chunks, dim3((unsigned)((tiles + 255) / 256), frames), dim3(256), 0, s, L, n_pairs, hist,
                        tile_count, tiles, live, chunk);
-    hipLaunchKernelGGL(scan_tiles, dim3((unsigned)n_pairs, frames), dim3(256), 0, s, L, tile_count, tile_offset,
-                       tiles);
+    hipLaunchKernelGGL(scan_tiles, dim3((unsigned)n_pairs, frames), dim3(SCAN_THREADS), 0, s, L, tile_count,
+                       tile_offset, tiles);
 }
 
 // Launches one renderer instantiation: one workgroup per item, or (persistent
@@ -931,6 +1302,17 @@ static void launch_render_shape(dim3 grid, hipStream_t s, const RenderArgs& a, c
 #undef SP_B
 }
 
+// Whether one workgroup per pair (and frame) bins a batch: the pairs' particles
+// take one CU about 2.3 us per 1024 (order 0.7 us), the chunked launches 25 (16)
+// us however few there are (one pair of 3277 particles 14 / 25 us, of 13107 37 /
+// 26; order 9 / 16 and 18 / 15).
+constexpr int SMALL_BINS = 8192, SMALL_ORDER = 8192;
+
+static bool small_pairs(const BatchTotals& tot, int most)
+{
+    return tot.max_n <= most && tot.max_tiles <= 8192;
+}
+
 hipError_t launch_bins(const RenderArgs& a, const RenderConfig& cfg, const BatchTotals& tot, char* ws,
                        const WorkspaceLayout& wl, hipStream_t s)
 {
@@ -947,37 +1329,49 @@ hipError_t launch_bins(const RenderArgs& a, const RenderConfig& cfg, const Batch
     float2* shp0 = reinterpret_cast<float2*>(ws + wl.shapes);
     float2* shp1 = shp0 + tot.n_span;
 
-    {
+    const size_t hist_lds = (size_t)tot.max_tiles * sizeof(uint32_t);
+    // the full model's prep writes every slot; live counts only with the isotropic prep
+    const int32_t* live = a.model ? nullptr : a.live;
+    if (small_pairs(tot, SMALL_BINS)) {
+        TimedScope ts("bins", s);
+        const dim3 grid((unsigned)a.n_pairs, 2), block(SMALL_THREADS);
+        if (a.model)
+            hipLaunchKernelGGL(bins_small<true>, grid, block, hist_lds, s, a.pairs, a, cfg, L, rec0, rec1, box0, box1,
+                               shp0, shp1, tile_count, tile_offset, tot.tiles, entries, live, status);
+        else
+            hipLaunchKernelGGL(bins_small<false>, grid, block, hist_lds, s, a.pairs, a, cfg, L, rec0, rec1, box0,
+                               box1, shp0, shp1, tile_count, tile_offset, tot.tiles, entries, live, status);
+        return hipGetLastError();
+    }
+    const bool inl = a.n_pairs <= INLINE_PAIRS && tot.chunks > 0;
+    if (!inl) {
         TimedScope ts("bin_layout", s);
         hipLaunchKernelGGL(bin_layout, dim3(1), dim3(256), 0, s, a.pairs, a.n_pairs, cfg, L, status);
     }
-    if (tot.n_span > 0) {
-        TimedScope ts("prep", s);
-        if (a.model)
-            hipLaunchKernelGGL(prep_records_model, dim3((unsigned)((tot.n_span + 255) / 256)), dim3(256), 0, s,
-                               a.pairs, a.n_pairs, tot.n_span, a, cfg.d_max, rec0, rec1, box0, box1, shp0, shp1,
-                               status);
-        else
-            hipLaunchKernelGGL(prep_records, dim3((unsigned)((tot.n_span + 255) / 256)), dim3(256), 0, s, a.pairs,
-                               a.n_pairs, tot.n_span, a, cfg.d_max, rec0, rec1, box0, box1, status);
-    }
-    const size_t hist_lds = (size_t)tot.max_tiles * sizeof(uint32_t);
-    const dim3 bgrid((unsigned)tot.chunks, 2);
-    // the full model's prep writes every slot; live counts only with the isotropic prep
-    const int32_t* live = a.model ? nullptr : a.live;
     if (tot.chunks > 0) {
         TimedScope ts("bin_count", s);
-        hipLaunchKernelGGL(bin_pass<false>, bgrid, dim3(256), hist_lds, s, a.pairs, L, a.n_pairs, box0, box1, cfg,
-                           hist, tile_offset, tot.tiles, entries, (unsigned)tot.chunks, live);
+        const dim3 grid((unsigned)tot.chunks), block(COUNT_THREADS);
+        // seven floats per particle above half of the 256 MB last-level cache
+        const bool stream = 28 * tot.n_span > (int64_t)128 << 20;
+#define SP_COUNT(MODEL_, INLINE_, STREAM_)                                                                        \
+    hipLaunchKernelGGL((bin_count<MODEL_, INLINE_, STREAM_>), grid, block, hist_lds, s, a.pairs, L, a.n_pairs, a,   \
+                       cfg, rec0, rec1, box0, box1, shp0, shp1, hist, (unsigned)tot.chunks, live, status)
+        if (a.model && inl) SP_COUNT(true, true, false);
+        else if (a.model) SP_COUNT(true, false, false);
+        else if (inl && stream) SP_COUNT(false, true, true);
+        else if (inl) SP_COUNT(false, true, false);
+        else if (stream) SP_COUNT(false, false, true);
+        else SP_COUNT(false, false, false);
+#undef SP_COUNT
     }
     if (tot.tiles > 0) {
         TimedScope ts("bin_scan", s);
-        launch_scans(L, a.n_pairs, hist, tile_count, tile_offset, tot.tiles, 2, s, live, cfg.chunk);
+        launch_scans(L, a.n_pairs, hist, tot, tile_count, tile_offset, 2, s, live, cfg.chunk);
     }
     if (tot.chunks > 0) {
         TimedScope ts("bin_scatter", s);
-        hipLaunchKernelGGL(bin_pass<true>, bgrid, dim3(256), hist_lds, s, a.pairs, L, a.n_pairs, box0, box1, cfg,
-                           hist, tile_offset, tot.tiles, entries, (unsigned)tot.chunks, live);
+        hipLaunchKernelGGL(bin_scatter, dim3((unsigned)tot.chunks, 2), dim3(256), hist_lds, s, a.pairs, L, a.n_pairs,
+                           box0, box1, cfg, hist, tile_offset, tot.tiles, entries, (unsigned)tot.chunks, live, status);
     }
     return hipGetLastError();
 }
@@ -1025,14 +1419,23 @@ hipError_t launch_order(const synthpix_pair* pairs_dev, int n_pairs, const float
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + ol.hist);
     int32_t* entries = reinterpret_cast<int32_t*>(ws + ol.entries);
     TimedScope ts("order", s);
-    hipLaunchKernelGGL(bin_layout, dim3(1), dim3(256), 0, s, pairs_dev, n_pairs, cfg, L, status);
-    if (tot.chunks == 0) return hipGetLastError();
     const size_t hist_lds = (size_t)tot.max_tiles * sizeof(uint32_t);
-    hipLaunchKernelGGL(order_pass<false>, dim3((unsigned)tot.chunks), dim3(256), hist_lds, s, pairs_dev, L, n_pairs, x,
-                       y, cfg, hist, tile_offset, entries, (unsigned)tot.chunks, iod, live);
-    launch_scans(L, n_pairs, hist, tile_count, tile_offset, tot.tiles, 1, s, live, cfg.chunk);
-    hipLaunchKernelGGL(order_pass<true>, dim3((unsigned)tot.chunks), dim3(256), hist_lds, s, pairs_dev, L, n_pairs, x,
-                       y, cfg, hist, tile_offset, entries, (unsigned)tot.chunks, iod, live);
+    if (small_pairs(tot, SMALL_ORDER)) {
+        hipLaunchKernelGGL(order_small, dim3((unsigned)n_pairs), dim3(SMALL_THREADS), hist_lds, s, pairs_dev, x, y,
+                           cfg, L, tile_count, tile_offset, entries, iod, live);
+        return hipGetLastError();
+    }
+    const bool inl = n_pairs <= INLINE_PAIRS && tot.chunks > 0;
+    if (!inl) hipLaunchKernelGGL(bin_layout, dim3(1), dim3(256), 0, s, pairs_dev, n_pairs, cfg, L, status);
+    if (tot.chunks == 0) return hipGetLastError();
+#define SP_ORDER(SCATTER_, INLINE_)                                                                               \
+    hipLaunchKernelGGL((order_pass<SCATTER_, INLINE_>), dim3((unsigned)tot.chunks), dim3(256), hist_lds, s,        \
+                       pairs_dev, L, n_pairs, x, y, cfg, hist, tile_offset, entries, (unsigned)tot.chunks, iod, live)
+    if (inl) SP_ORDER(false, true);
+    else SP_ORDER(false, false);
+    launch_scans(L, n_pairs, hist, tot, tile_count, tile_offset, 1, s, live, cfg.chunk);
+    SP_ORDER(true, false);
+#undef SP_ORDER
     return hipGetLastError();
 }
 

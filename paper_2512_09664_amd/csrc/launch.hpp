@@ -35,7 +35,7 @@ struct PairLayout {
     int32_t n_chunks;       // ceil(n_max / chunk)
     int32_t tile_base;      // first tile of the pair (prefix over pairs)
     int32_t ntx, nty;       // tiles per row / column
-    int32_t pad_;
+    uint32_t flags;         // status bits of the pair's records, frame f in byte f (small pairs)
     int64_t hist_base;      // first per-(frame, chunk, tile) count of the pair
     int64_t entry_base;     // first entry slot of the pair (frame 2 at + entry_cap)
     int64_t entry_cap;      // entry slots per frame
@@ -68,6 +68,7 @@ struct RenderConfig {
 // the low and high halves of .x, rows r0 .. r1 in those of .y.  A particle that
 // adds nothing has c1 < c0 (EMPTY_BOX).
 constexpr uint32_t EMPTY_BOX = 1u;
+constexpr int EMPTY_FLAGS = 16;     // an empty box's .y may carry status bits from this bit on
 
 __device__ __forceinline__ uint2 patch_box(float x, float y, float Rx, float Ry, int W, int H)
 {
@@ -103,6 +104,7 @@ struct BatchTotals {
     int64_t hist;           // 2 * sum n_chunks * tiles
     int64_t entries;        // 2 * sum entry_cap
     int64_t max_tiles;      // max ntx * nty over pairs (LDS histogram size)
+    int64_t max_n;          // max n_max over pairs
 };
 
 // Workspace layout (byte offsets, 256-aligned).
@@ -197,6 +199,18 @@ struct RenderArgs {
     float sheet_dz0, sheet_shape;   // Remark 1: thickness and shape factor
     bool model;                     // any of the above in use (the model's prep kernel runs)
     bool aniso;                     // shape records in use (d_y != d or rho != 0 possible)
+
+    // a captured plan's particle buffers
+    __device__ __forceinline__ void use(const synthpix_batch_io& io)
+    {
+        x[0] = io.x1;
+        y[0] = io.y1;
+        x[1] = io.x2;
+        y[1] = io.y2;
+        z = io.z;
+        d = io.d;
+        I0 = io.I0;
+    }
 };
 
 // What the tile renderer's epilogue needs (kept small: kernel arguments live in SGPRs).

@@ -1,0 +1,100 @@
+"""The binning and order forms (one launch for small pairs, three for larger
+ones, with and without a layout launch, fused and separate scans) against the
+oracle's tile lists and against the advection in index order."""
+
+import numpy as np
+import pytest
+
+pytest.importorskip("torch")
+import torch  # noqa: E402
+
+import gpu_util as gu  # noqa: E402
+import paper_2512_09664_amd as sp  # noqa: E402
+from oracle import bins as obins  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _particles(sizes, counts, seed):
+    rng = np.random.default_rng(seed)
+    out = {k: [] for k in ("x", "y", "x2", "y2", "z", "d", "I0")}
+    for (H, W), n in zip(sizes, counts):
+        x, y = rng.uniform(-4, W + 4, n), rng.uniform(-4, H + 4, n)
+        out["x"].append(x)
+        out["y"].append(y)
+        out["x2"].append(x + rng.uniform(-3, 3, n))
+        out["y2"].append(y + rng.uniform(-3, 3, n))
+        out["z"].append(rng.uniform(-1, 1, n))
+        out["d"].append(rng.uniform(1.0, 5.0, n))
+        out["I0"].append(np.where(rng.random(n) < 0.1, 0.0, 0.01))
+    return {k: np.concatenate(v).astype(np.float32) for k, v in out.items()}
+
+
+# pairs of one launch (at most 8192 particles), of three, a wave of pairs and one more
+BATCHES = [([(96, 128)], [8192]), ([(96, 128)], [8193]), ([(40, 24)] * 63 + [(96, 128)], [3] * 63 + [9000]),
+           ([(40, 24)] * 64 + [(96, 128)], [3, 0] * 32 + [9000]), ([(40, 24)] * 65, [7, 0, 30, 1, 0] * 13)]
+
+
+@pytest.mark.parametrize("batch", range(len(BATCHES)))
+@pytest.mark.parametrize("tile", [(64, 32, 2048, 64), (8, 8, 256, 64)])
+def test_lists_match_oracle(batch, tile):
+    sizes, counts = BATCHES[batch]
+    q = _particles(sizes, counts, batch)
+    b = gu.batch_for(sizes, [(4, 4)] * len(sizes), counts)
+    rp = sp.render_params(0.5, 5.0, 1, 0.7, 0.0, 12)
+    t = {k: gu.to_dev(v) for k, v in q.items()}
+    tl = sp.tiling(*tile)
+    ws = sp.alloc_workspace(b, rp, tl)
+    sp.render_pair(b, t["x"], t["y"], t["x2"], t["y2"], t["z"], t["d"], t["I0"], rp, tl, workspace=ws)
+    torch.cuda.synchronize()
+    assert sp.read_status(ws) == 0
+    count, offset, entries = (gu.to_np(v) for v in sp.bin_views(b, rp, tl, ws))
+    base = o = 0
+    for (H, W), n in zip(sizes, counts):
+        sl = slice(o, o + n)
+        o += n
+        nt = int(np.prod(obins.tile_grid(H, W, tile[1], tile[0])))
+        for f, (xk, yk) in enumerate((("x", "y"), ("x2", "y2"))):
+            if not (q["I0"][sl] > 0).any():          # the oracle takes at least one particle
+                assert not count[f, base:base + nt].any()
+                continue
+            c, off, ent = obins.bin_frame(q[xk][sl], q[yk][sl], q["d"][sl], q["I0"][sl], H, W, tile[1], tile[0], 1)
+            assert np.array_equal(count[f, base:base + nt], c)
+            go = offset[f, base:base + nt]
+            assert np.array_equal(go - go[0], off[:-1])
+            for k in range(nt):
+                assert np.array_equal(np.sort(entries[go[k]:go[k] + c[k]]), ent[off[k]:off[k + 1]])
+        base += nt
+
+
+@pytest.mark.parametrize("batch", range(len(BATCHES)))
+def test_flags_are_raised_and_cleared(batch):
+    """A diameter above d_max in either frame's lists raises its bit in every
+    form; the next call on the same workspace clears it."""
+    sizes, counts = BATCHES[batch]
+    q = _particles(sizes, counts, batch)
+    b = gu.batch_for(sizes, [(4, 4)] * len(sizes), counts)
+    rp = sp.render_params(0.5, 5.0, 0, 0.7, 0.0, 0)
+    t = {k: gu.to_dev(v) for k, v in q.items()}
+    ws = sp.alloc_workspace(b, rp)
+    for d, want in ((6.0, sp._lib.SP_STATUS_D_ABOVE_MAX), (2.0, 0)):
+        t["d"][-1], t["I0"][-1] = d, 0.01
+        sp.render_pair(b, t["x"], t["y"], t["x2"], t["y2"], t["z"], t["d"], t["I0"], rp, workspace=ws)
+        torch.cuda.synchronize()
+        assert sp.read_status(ws) == want
+
+
+@pytest.mark.parametrize("batch", range(len(BATCHES)))
+def test_order_does_not_change_positions(batch):
+    """Enough substeps that the home-block order is built: the same bits as in
+    index order."""
+    sizes, counts = BATCHES[batch]
+    q = _particles(sizes, counts, batch)
+    b = gu.batch_for(sizes, [(12, 10)] * len(sizes), counts)
+    flow = gu.to_dev(np.random.default_rng(batch).normal(0, 1, b.n_flow).astype(np.float32))
+    ap = sp.advect_params(1.0, 1024, "rk4")
+    x, y = gu.to_dev(q["x"]), gu.to_dev(q["y"])
+    ordered = sp.advect(b, flow, ap, x, y)
+    plain = sp.advect(b, flow, ap, x, y, ordered=False)
+    for u, v in zip(ordered, plain):
+        assert torch.equal(u, v)
