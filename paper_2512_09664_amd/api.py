@@ -7,6 +7,7 @@ entry points: ``seed``, ``advect``, ``render_pair``, ``render_pair_backward``.
 
 from __future__ import annotations
 
+import copy
 import ctypes
 from dataclasses import dataclass
 from typing import Optional, Sequence, Tuple
@@ -17,12 +18,16 @@ import torch
 from . import _lib as L
 
 
+# Addresses and streams cross as plain integers (the declared void * arguments
+# take them as they are), without an object made for each: one 256^2 pair's
+# seed, advect and render calls are host time, not kernels.
+
 def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _need_cuda(*ts):
@@ -32,6 +37,19 @@ def _need_cuda(*ts):
 
 
 U16 = getattr(torch, "uint16", torch.int16)
+
+_PAIR = np.dtype(L.Pair)
+
+
+def _pair_ids(ids):
+    return np.array([int(v) & 0xFFFFFFFFFFFFFFFF for v in ids], dtype=np.uint64)
+
+
+def _upload(tab: np.ndarray, device, non_blocking: bool):
+    """The pair table as a ctypes array and on the device."""
+    t = torch.from_numpy(tab.view(np.uint8))
+    dev = t.pin_memory().to(device, non_blocking=True) if non_blocking else t.to(device)
+    return (L.Pair * len(tab)).from_buffer_copy(tab), dev
 
 
 def particle_count(H: int, W: int, ppp: float) -> int:
@@ -54,6 +72,8 @@ class PairBatch:
     grids: Tuple[Tuple[int, int], ...]
     n_max: Tuple[int, ...]
 
+    _gapless = False     # every element of the packed arrays lies in a pair's range (set by build)
+
     @staticmethod
     def build(sizes: Sequence[Tuple[int, int]], grids: Sequence[Tuple[int, int]], n_max: Sequence[int],
               pair_ids: Optional[Sequence[int]] = None, device="cuda",
@@ -67,32 +87,37 @@ class PairBatch:
         if gaps[2] % 2:
             raise ValueError("flow gaps must be even (one (u, v) node is two floats)")
         n = len(sizes)
-        arr = (L.Pair * n)()
-        po = io = fo = 0
-        for p in range(n):
-            H, W = sizes[p]
-            Gh, Gw = grids[p]
-            po, io, fo = po + gaps[0], io + gaps[1], fo + gaps[2]
-            arr[p].H, arr[p].W, arr[p].Gh, arr[p].Gw = int(H), int(W), int(Gh), int(Gw)
-            arr[p].n_max = int(n_max[p])
-            arr[p].reserved = 0
-            arr[p].particle_offset = po
-            arr[p].image_offset = io
-            arr[p].flow_offset = fo
-            arr[p].pair_id = int(pair_ids[p]) if pair_ids is not None else p
-            po += int(n_max[p])
-            io += 2 * int(H) * int(W)
-            fo += 2 * int(Gh) * int(Gw)
+        tab = np.zeros(n, dtype=_PAIR)
+        hw = np.array([(int(H), int(W)) for H, W in sizes], dtype=np.int64).reshape(n, 2)
+        g = np.array([(int(Gh), int(Gw)) for Gh, Gw in grids[:n]], dtype=np.int64).reshape(n, 2)
+        nm = np.array([int(v) for v in n_max[:n]], dtype=np.int64)
+        tab["H"], tab["W"], tab["Gh"], tab["Gw"], tab["n_max"] = hw[:, 0], hw[:, 1], g[:, 0], g[:, 1], nm
+        nodes = 2 * g[:, 0] * g[:, 1]
+
+        def packed(sizes_, gap):
+            end = np.cumsum(sizes_ + gap)
+            return end - sizes_, int(end[-1]) if n else 0
+
+        tab["particle_offset"], po = packed(nm, gaps[0])
+        tab["image_offset"], io = packed(2 * hw[:, 0] * hw[:, 1], gaps[1])
+        tab["flow_offset"], fo = packed(nodes, gaps[2])
+        tab["pair_id"] = np.arange(n, dtype=np.uint64) if pair_ids is None else _pair_ids(pair_ids[:n])
         if flow_index is not None:
-            fo = 0
-            for p in range(n):
-                arr[p].flow_offset = 2 * int(grids[p][0]) * int(grids[p][1]) * int(flow_index[p])
-                fo = max(fo, int(arr[p].flow_offset) + 2 * int(grids[p][0]) * int(grids[p][1]))
-        raw = np.frombuffer(bytes(arr), dtype=np.uint8).copy()
-        t = torch.from_numpy(raw)
-        dev = t.pin_memory().to(device, non_blocking=True) if non_blocking else t.to(device)
-        return PairBatch(arr, dev, n, po, io, fo, tuple(map(tuple, sizes)), tuple(map(tuple, grids)),
-                         tuple(int(v) for v in n_max))
+            tab["flow_offset"] = nodes * np.array([int(v) for v in flow_index[:n]], dtype=np.int64)
+            fo = int((tab["flow_offset"] + nodes).max()) if n else 0
+        host, dev = _upload(tab, device, non_blocking)
+        b = PairBatch(host, dev, n, po, io, fo, tuple(map(tuple, sizes)), tuple(map(tuple, grids)),
+                      tuple(int(v) for v in n_max))
+        b._gapless = not any(gaps)
+        return b
+
+    def with_pair_ids(self, pair_ids: Sequence[int], non_blocking: bool = False) -> "PairBatch":
+        """The same batch under other pair ids (its own table on host and device)."""
+        tab = np.frombuffer(self.host, dtype=_PAIR).copy()
+        tab["pair_id"] = _pair_ids(pair_ids)
+        b = copy.copy(self)
+        b.host, b.dev = _upload(tab, self.dev.device, non_blocking)
+        return b
 
     @property
     def host_ptr(self):
@@ -168,7 +193,7 @@ def tiling_candidates(rp):
 
 def default_tiling(batch: PairBatch, rp):
     t = L.Tiling()
-    L.check(L.load().synthpix_default_tiling(batch.host_ptr, batch.n_pairs, ctypes.byref(rp), ctypes.byref(t)))
+    L.check(L.load().synthpix_default_tiling(batch.host, batch.n_pairs, ctypes.byref(rp), ctypes.byref(t)))
     return t
 
 
@@ -181,7 +206,7 @@ def seed(batch: PairBatch, sp, seed_value: int, out=None):
     if "n_active" not in o:
         o["n_active"] = torch.empty(batch.n_pairs, dtype=torch.int32, device=dev)
         o["ppp"] = torch.empty(batch.n_pairs, dtype=torch.float64, device=dev)
-    L.check(L.load().synthpix_seed(batch.host_ptr, batch.dev_ptr, batch.n_pairs, ctypes.byref(sp),
+    L.check(L.load().synthpix_seed(batch.host, batch.dev.data_ptr(), batch.n_pairs, ctypes.byref(sp),
                                    int(seed_value), _ptr(o["x"]), _ptr(o["y"]), _ptr(o["z"]), _ptr(o["d"]),
                                    _ptr(o["I0"]), _ptr(o["n_active"]), _ptr(o["ppp"]), _stream()))
     return o
@@ -189,7 +214,7 @@ def seed(batch: PairBatch, sp, seed_value: int, out=None):
 
 def advect_workspace_size(batch: PairBatch) -> int:
     n = ctypes.c_size_t(0)
-    L.check(L.load().synthpix_advect_workspace_size(batch.host_ptr, batch.n_pairs, ctypes.byref(n)))
+    L.check(L.load().synthpix_advect_workspace_size(batch.host, batch.n_pairs, ctypes.byref(n)))
     return n.value
 
 
@@ -204,7 +229,7 @@ def advect(batch: PairBatch, flow: torch.Tensor, ap, x1: torch.Tensor, y1: torch
         x2 = torch.empty_like(x1) if x2 is None else x2
         y2 = torch.empty_like(y1) if y2 is None else y2
         z2 = torch.empty_like(z1) if z2 is None else z2
-        L.check(L.load().synthpix_advect(batch.host_ptr, batch.dev_ptr, batch.n_pairs, _ptr(flow), ctypes.byref(ap),
+        L.check(L.load().synthpix_advect(batch.host, batch.dev.data_ptr(), batch.n_pairs, _ptr(flow), ctypes.byref(ap),
                                          _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), _ptr(wflow), _ptr(z1), _ptr(z2),
                                          None, 0, _stream()))
         return x2, y2, z2
@@ -213,7 +238,7 @@ def advect(batch: PairBatch, flow: torch.Tensor, ap, x1: torch.Tensor, y1: torch
     if ordered and workspace is None:
         workspace = torch.empty(max(advect_workspace_size(batch), 256), dtype=torch.uint8, device=x1.device)
     ws, nb = (_ptr(workspace), workspace.numel()) if ordered else (None, 0)
-    L.check(L.load().synthpix_advect(batch.host_ptr, batch.dev_ptr, batch.n_pairs, _ptr(flow), ctypes.byref(ap),
+    L.check(L.load().synthpix_advect(batch.host, batch.dev.data_ptr(), batch.n_pairs, _ptr(flow), ctypes.byref(ap),
                                      _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), None, None, None, ws, nb, _stream()))
     return x2, y2
 
@@ -224,7 +249,7 @@ def seed_shape(batch: PairBatch, sp, rho, seed_value: int, out=None):
     n = max(batch.n_particles, 1)
     dy, r = out if out is not None else (torch.empty(n, dtype=torch.float32, device=dev),
                                          torch.empty(n, dtype=torch.float32, device=dev))
-    L.check(L.load().synthpix_seed_shape(batch.host_ptr, batch.dev_ptr, batch.n_pairs, ctypes.byref(sp),
+    L.check(L.load().synthpix_seed_shape(batch.host, batch.dev.data_ptr(), batch.n_pairs, ctypes.byref(sp),
                                          float(rho[0]), float(rho[1]), int(seed_value), _ptr(dy), _ptr(r), _stream()))
     return dy, r
 
@@ -235,7 +260,7 @@ def flow_field(batch: PairBatch, flow: torch.Tensor, out: Optional[torch.Tensor]
     _need_cuda(flow, out)
     if out is None:
         out = torch.empty(batch.n_pixels, dtype=torch.float32, device=flow.device)
-    L.check(L.load().synthpix_flow_field(batch.host_ptr, batch.dev_ptr, batch.n_pairs, _ptr(flow), _ptr(out),
+    L.check(L.load().synthpix_flow_field(batch.host, batch.dev.data_ptr(), batch.n_pairs, _ptr(flow), _ptr(out),
                                          _stream()))
     return out
 
@@ -249,7 +274,7 @@ def histogram_match(batch: PairBatch, images: torch.Tensor, target: torch.Tensor
     L.check(L.load().synthpix_histogram_workspace_size(batch.n_pairs, int(bits), ctypes.byref(n)))
     if workspace is None:
         workspace = torch.empty(max(n.value, 256), dtype=torch.uint8, device=images.device)
-    L.check(L.load().synthpix_histogram_match(batch.host_ptr, batch.dev_ptr, batch.n_pairs, int(bits), _ptr(target),
+    L.check(L.load().synthpix_histogram_match(batch.host, batch.dev.data_ptr(), batch.n_pairs, int(bits), _ptr(target),
                                               _ptr(images), _ptr(workspace), workspace.numel(), _stream()))
     return workspace
 
@@ -295,7 +320,7 @@ def workspace_size(batch: PairBatch, rp, tile=None, backward=False) -> int:
     (True) or ``render_pair_backward_mse`` (``"mse"``)."""
     n = ctypes.c_size_t(0)
     kind = 2 if backward == "mse" else 1 if backward else 0
-    L.check(L.load().synthpix_workspace_size(batch.host_ptr, batch.n_pairs, ctypes.byref(rp),
+    L.check(L.load().synthpix_workspace_size(batch.host, batch.n_pairs, ctypes.byref(rp),
                                              ctypes.byref(tile) if tile is not None else None,
                                              kind, ctypes.byref(n)))
     return n.value
@@ -310,7 +335,7 @@ def bin_views(batch: PairBatch, rp, tile=None, workspace: torch.Tensor = None):
     """Tile counts, offsets and member lists written into ``workspace`` by the
     last ``render_pair`` call with the same batch, parameters and tiling."""
     v = L.BinViews()
-    L.check(L.load().synthpix_bin_views_of(batch.host_ptr, batch.n_pairs, ctypes.byref(rp),
+    L.check(L.load().synthpix_bin_views_of(batch.host, batch.n_pairs, ctypes.byref(rp),
                                            ctypes.byref(tile) if tile is not None else None, ctypes.byref(v)))
     T = int(v.tiles)
     ws = workspace
@@ -360,11 +385,11 @@ def render_pair(batch: PairBatch, x1, y1, x2, y2, z, d, I0, rp, tile=None, image
     _need_cuda(x1, y1, x2, y2, z, d, I0)
     dev = x1.device
     if images is None:
-        # zero-filled: the library writes only the pairs' image ranges
-        images = torch.zeros(batch.n_pixels, dtype=U16 if rp.bits > 0 else torch.float32, device=dev)
+        # zero-filled where there are gaps: the library writes only the pairs' image ranges
+        images = (torch.empty if batch._gapless else torch.zeros)(batch.n_pixels, dtype=U16 if rp.bits > 0 else torch.float32, device=dev)
     if workspace is None:
         workspace = alloc_workspace(batch, rp, tile)
-    L.check(L.load().synthpix_render_pair(batch.host_ptr, batch.dev_ptr, batch.n_pairs,
+    L.check(L.load().synthpix_render_pair(batch.host, batch.dev.data_ptr(), batch.n_pairs,
                                           ctypes.byref(tile) if tile is not None else None,
                                           _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), _ptr(z), _ptr(d), _ptr(I0),
                                           _extras(dy, rho, z2), ctypes.byref(rp), _ptr(images), _ptr(workspace),
@@ -379,7 +404,7 @@ def render_pair_noalloc(batch: PairBatch, x1, y1, x2, y2, z, d, I0, rp, images, 
     ``status``: optional int32/uint32 device tensor of one element that receives
     the device status word."""
     _need_cuda(x1, y1, x2, y2, z, d, I0, images, status)
-    L.check(L.load().synthpix_render_pair_noalloc(batch.host_ptr, batch.dev_ptr, batch.n_pairs,
+    L.check(L.load().synthpix_render_pair_noalloc(batch.host, batch.dev.data_ptr(), batch.n_pairs,
                                                   ctypes.byref(tile) if tile is not None else None,
                                                   _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), _ptr(z), _ptr(d),
                                                   _ptr(I0), _extras(dy, rho, z2), ctypes.byref(rp), _ptr(images),
@@ -400,7 +425,7 @@ def render_pair_backward(batch: PairBatch, flow, x1, y1, z, d, I0, rp, grad_imag
     if workspace is None:
         workspace = alloc_workspace(batch, rp, tile, backward=True)
     L.check(L.load().synthpix_render_pair_backward(
-        batch.host_ptr, batch.dev_ptr, batch.n_pairs, ctypes.byref(tile) if tile is not None else None,
+        batch.host, batch.dev.data_ptr(), batch.n_pairs, ctypes.byref(tile) if tile is not None else None,
         _ptr(flow), _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), _ptr(z), _ptr(d), _ptr(I0), ctypes.byref(rp),
         _ptr(grad_images), _ptr(g["x1"]), _ptr(g["y1"]), _ptr(g["z"]), _ptr(g["d"]), _ptr(g["I0"]),
         _ptr(g["sheet"]), _ptr(g["sheet_total"]), _ptr(g["flow"]), _ptr(workspace), workspace.numel(), _stream()))
@@ -428,7 +453,7 @@ def render_pair_backward_mse(batch: PairBatch, flow, x1, y1, z, d, I0, rp, image
     if workspace is None:
         workspace = alloc_workspace(batch, rp, tile, backward="mse")
     L.check(L.load().synthpix_render_pair_backward_mse(
-        batch.host_ptr, batch.dev_ptr, batch.n_pairs, ctypes.byref(tile) if tile is not None else None,
+        batch.host, batch.dev.data_ptr(), batch.n_pairs, ctypes.byref(tile) if tile is not None else None,
         _ptr(flow), _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), _ptr(z), _ptr(d), _ptr(I0), ctypes.byref(rp),
         _ptr(images), _ptr(target), float(scale), _ptr(lv), _ptr(g["x1"]), _ptr(g["y1"]), _ptr(g["z"]),
         _ptr(g["d"]), _ptr(g["I0"]), _ptr(g["sheet"]), _ptr(g["sheet_total"]), _ptr(g["flow"]), _ptr(workspace),
@@ -478,7 +503,7 @@ class Plan:
         self.rp = rp
         self._b = _batch_io(io, seed_value, 0)
         h = ctypes.c_void_p(None)
-        L.check(L.load().synthpix_plan_create(batch.host_ptr, batch.n_pairs, ctypes.byref(sp), ctypes.byref(ap),
+        L.check(L.load().synthpix_plan_create(batch.host, batch.n_pairs, ctypes.byref(sp), ctypes.byref(ap),
                                               ctypes.byref(rp), ctypes.byref(self._b), 1 if autotune else 0,
                                               1 if advance_pair_ids else 0, _stream(), ctypes.byref(h)))
         self._h = h

@@ -218,8 +218,11 @@ class Sampler:
                          for k in ("x1", "y1", "x2", "y2", "z", "d", "I0", "dy", "rho", "z2")}
             self._buf["n_active"] = torch.empty(self.B, dtype=torch.int32, device=self.dev)
             self._buf["ppp"] = torch.empty(self.B, dtype=torch.float64, device=self.dev)
-            base = self._pairs(0)
-            self._ws = api.alloc_workspace(base, self.rprm)
+            per = self.B // self.F
+            self._base = api.PairBatch.build([(H, W)] * self.B, [(self.Gh, self.Gw)] * self.B, [self.n_max] * self.B,
+                                             device=self.dev, flow_index=[i // per for i in range(self.B)],
+                                             non_blocking=True)
+            self._ws = api.alloc_workspace(self._base, self.rprm)
             self._hws = None
         self._graph = c.use_graph and c.isotropic and c.particle_reuse is None
 
@@ -227,11 +230,12 @@ class Sampler:
 
     def _pairs(self, k: int):
         """The batch's pair table: pair i uses flow field i // (B / F); pair ids
-        continue across batches so every batch draws new particles and noise."""
-        per = self.B // self.F
-        return api.PairBatch.build([(self.H, self.W)] * self.B, [(self.Gh, self.Gw)] * self.B, [self.n_max] * self.B,
-                                   [k * self.B + i for i in range(self.B)], device=self.dev,
-                                   flow_index=[i // per for i in range(self.B)], non_blocking=True)
+        continue across batches so every batch draws new particles and noise.  A
+        captured plan adds the batch's first pair id itself, so its batches share
+        one table."""
+        if self._graph or k == 0:
+            return self._base
+        return self._base.with_pair_ids(range(k * self.B, (k + 1) * self.B), non_blocking=True)
 
     def _load_flows(self, k: int):
         epoch = k // self.cfg.batches_per_flow
