@@ -285,12 +285,12 @@ synthpix_status synthpix_seed(const synthpix_pair* pairs_host, const synthpix_pa
  * motion of Remark 1's particles, z2 = z1 + the integral of the out-of-plane
  * velocity w along the in-plane trajectory (same integrator stages); wflow
  * holds each pair's [Gh][Gw] w grid (sheet units per frame, registered like
- * the (u, v) grid) at float offset pair.flow_offset / 2.  The 3-D form runs in
- * particle index order (the workspace is not used).
+ * the (u, v) grid) at float offset pair.flow_offset / 2.
  * workspace: optional device scratch, 256-byte aligned, of at least
  * synthpix_advect_workspace_size bytes (any workspace sized by
- * synthpix_workspace_size also fits).  With it, particles are first ordered by
- * home block so that neighbouring threads sample neighbouring grid cells; the
+ * synthpix_workspace_size also fits; the 3-D form ignores one that does not).
+ * With it, particles are first ordered by home block, where the number of samples
+ * repays it, so that neighbouring threads sample neighbouring grid cells; the
  * results are identical with or without it (NULL: particle index order). */
 synthpix_status synthpix_advect(const synthpix_pair* pairs_host, const synthpix_pair* pairs_dev,
                                 int32_t n_pairs, const float* flow, const synthpix_advect_params* ap,

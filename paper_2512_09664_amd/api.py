@@ -225,22 +225,17 @@ def advect(batch: PairBatch, flow: torch.Tensor, ap, x1: torch.Tensor, y1: torch
     render workspace), else a temporary.  With ``wflow`` (each pair's w grid)
     and ``z1``, z is moved too and (x2, y2, z2) is returned."""
     _need_cuda(flow, x1, y1, wflow, z1, z2)
-    if wflow is not None:
-        x2 = torch.empty_like(x1) if x2 is None else x2
-        y2 = torch.empty_like(y1) if y2 is None else y2
-        z2 = torch.empty_like(z1) if z2 is None else z2
-        L.check(L.load().synthpix_advect(batch.host, batch.dev.data_ptr(), batch.n_pairs, _ptr(flow), ctypes.byref(ap),
-                                         _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), _ptr(wflow), _ptr(z1), _ptr(z2),
-                                         None, 0, _stream()))
-        return x2, y2, z2
     x2 = torch.empty_like(x1) if x2 is None else x2
     y2 = torch.empty_like(y1) if y2 is None else y2
+    if wflow is not None and z2 is None:
+        z2 = torch.empty_like(z1)
     if ordered and workspace is None:
         workspace = torch.empty(max(advect_workspace_size(batch), 256), dtype=torch.uint8, device=x1.device)
     ws, nb = (_ptr(workspace), workspace.numel()) if ordered else (None, 0)
+    w, zi, zo = (_ptr(wflow), _ptr(z1), _ptr(z2)) if wflow is not None else (None, None, None)
     L.check(L.load().synthpix_advect(batch.host, batch.dev.data_ptr(), batch.n_pairs, _ptr(flow), ctypes.byref(ap),
-                                     _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), None, None, None, ws, nb, _stream()))
-    return x2, y2
+                                     _ptr(x1), _ptr(y1), _ptr(x2), _ptr(y2), w, zi, zo, ws, nb, _stream()))
+    return (x2, y2) if wflow is None else (x2, y2, z2)
 
 
 def seed_shape(batch: PairBatch, sp, rho, seed_value: int, out=None):

@@ -698,25 +698,27 @@ synthpix_status synthpix_advect(const synthpix_pair* pairs_host, const synthpix_
         if (!dev_ptr_ok(wflow) || !dev_ptr_ok(z1) || !dev_ptr_ok(z2))
             return fail(SP_ERR_INVALID_ARG, "wflow, z1, z2 must be 4-byte aligned device pointers");
         if (z1 == z2) return fail(SP_ERR_INVALID_ARG, "z2 must not alias z1");
-        const hipError_t e = sp::launch_advect3(pairs_dev, n_pairs, span, flow, wflow, *ap, x1, y1, z1, x2, y2, z2,
-                                                as_stream(stream));
-        if (e != hipSuccess) return hip_fail(e, "advect launch");
-        return SP_OK;
     }
-    sp::AdvectOrder order{nullptr, nullptr};
+    sp::AdvectOrder order{};
+    bool usable = workspace != nullptr;
     if (workspace) {
-        if (!aligned(workspace, 256)) return fail(SP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
         const size_t need = order_bytes(pairs_host, n_pairs);
-        if (!need) return fail(SP_ERR_UNSUPPORTED, "batch too large for the advection order");
-        if (ws_bytes < need) return fail(SP_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
+        if (wflow) {
+            // motion out of the plane takes any workspace and uses one that fits
+            usable = aligned(workspace, 256) && need && ws_bytes >= need;
+        } else {
+            if (!aligned(workspace, 256)) return fail(SP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
+            if (!need) return fail(SP_ERR_UNSUPPORTED, "batch too large for the advection order");
+            if (ws_bytes < need) return fail(SP_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
+        }
     }
-    if (workspace && order_pays(span, *ap)) {
+    if (usable && order_pays(span, *ap)) {
         const hipError_t e = enqueue_order(pairs_host, pairs_dev, n_pairs, x1, y1, static_cast<char*>(workspace), 0,
                                            as_stream(stream), &order);
         if (e != hipSuccess) return hip_fail(e, "advect order launch");
     }
     const hipError_t e = sp::launch_advect(pairs_dev, n_pairs, span, flow, *ap, x1, y1, x2, y2, as_stream(stream),
-                                           order);
+                                           order, nullptr, wflow, z1, z2);
     if (e != hipSuccess) return hip_fail(e, "advect launch");
     return SP_OK;
 }

@@ -10,12 +10,13 @@
 namespace sp {
 
 // Two consecutive (u, v) nodes as one 16-byte load (8-byte aligned address; the
-// hardware handles the unaligned vector access).
+// hardware handles the unaligned vector access), from global memory also where
+// the pointer came out of a descriptor.
 __device__ __forceinline__ float4 load_pair(const float2* p)
 {
-    float4 v;
-    __builtin_memcpy(&v, p, sizeof(v));
-    return v;
+    typedef float vec4 __attribute__((ext_vector_type(4), aligned(8)));
+    const vec4 v = *(const __attribute__((address_space(1))) vec4*)p;
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 
 struct FlowView {
@@ -27,59 +28,80 @@ struct FlowView {
 // A rectangle of a pair's grid nodes copied to LDS (rows wi0 .., columns wj0 ..,
 // wh x ww nodes, row-major, wh and ww >= 1); NO_WIN (a single node, which holds
 // no whole cell) means none.  The nodes themselves are passed separately, as
-// the workgroup's LDS array of (u, v) floats.
+// the workgroup's LDS arrays of (u, v) pairs and, for motion out of the plane, w.
 struct FlowWin {
     int wi0, wj0, wh, ww;
 };
 
 constexpr FlowWin NO_WIN = {0, 0, 1, 1};
 
-typedef __attribute__((address_space(3))) const float lds_float;   // LDS (group segment) word
+typedef float vec2f __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const vec2f lds_vec2;     // LDS (group segment) (u, v) node
+typedef __attribute__((address_space(3))) const float lds_float;    // LDS word
 
-__device__ __forceinline__ float2 sample_flow(const FlowView& fv, float px, float py,
-                                              const FlowWin& win = NO_WIN,
-                                              lds_float* lds = nullptr)
+// The grid cell of image position (px, py), clamped to the node hull (not a
+// number: cell 0), and the position inside it.  A median clamps in one
+// instruction; truncation is the floor of the clamped, non-negative coordinate.
+struct FlowCell {
+    int i0, j0;
+    float fx, fy;
+};
+
+__device__ __forceinline__ FlowCell flow_cell(const FlowView& fv, float px, float py)
 {
-    float gx = px * fv.sx - 0.5f;
-    float gy = py * fv.sy - 0.5f;
-    gx = __builtin_fminf(__builtin_fmaxf(gx, 0.0f), (float)(fv.Gw - 1));
-    gy = __builtin_fminf(__builtin_fmaxf(gy, 0.0f), (float)(fv.Gh - 1));
-    int j0 = (int)__builtin_floorf(gx);
-    int i0 = (int)__builtin_floorf(gy);
-    j0 = j0 > fv.Gw - 2 ? fv.Gw - 2 : j0;
-    i0 = i0 > fv.Gh - 2 ? fv.Gh - 2 : i0;
-    const float fx = gx - (float)j0;
-    const float fy = gy - (float)i0;
-    // the cell's two nodes of one grid row are adjacent: one 16-byte load per row,
-    // from the LDS window when the cell lies inside it
+    const float gx = __builtin_amdgcn_fmed3f(px * fv.sx - 0.5f, 0.0f, (float)(fv.Gw - 1));
+    const float gy = __builtin_amdgcn_fmed3f(py * fv.sy - 0.5f, 0.0f, (float)(fv.Gh - 1));
+    FlowCell c;
+    c.j0 = min((int)gx, fv.Gw - 2);
+    c.i0 = min((int)gy, fv.Gh - 2);
+    c.fx = gx - (float)c.j0;
+    c.fy = gy - (float)c.i0;
+    return c;
+}
+
+__device__ __forceinline__ float bilinear(float a, float b, float c, float e, float fx, float fy)
+{
+    const float top = __builtin_fmaf(fx, b - a, a);
+    const float bot = __builtin_fmaf(fx, e - c, c);
+    return __builtin_fmaf(fy, bot - top, top);
+}
+
+// Whether the cell lies in the window: 0 <= li < wh - 1 and 0 <= lj < ww - 1, each
+// as one unsigned comparison.
+__device__ __forceinline__ bool in_window(const FlowCell& c, const FlowWin& win)
+{
+    return ((unsigned)(c.i0 - win.wi0) < (unsigned)(win.wh - 1)) & ((unsigned)(c.j0 - win.wj0) < (unsigned)(win.ww - 1));
+}
+
+__device__ __forceinline__ unsigned window_node(const FlowCell& c, const FlowWin& win)
+{
+    return __umul24((unsigned)(c.i0 - win.wi0), (unsigned)win.ww) + (unsigned)(c.j0 - win.wj0);
+}
+
+// (u, v) of a cell: its two nodes of one grid row are adjacent, one 16-byte load
+// per row, from the LDS window when the cell lies inside it.
+__device__ __forceinline__ float2 sample_cell(const FlowView& fv, const FlowCell& c, bool inside, const FlowWin& win,
+                                              lds_vec2* lds)
+{
     float4 r0, r1;
-    const int li = i0 - win.wi0, lj = j0 - win.wj0;
-    // 0 <= li < wh - 1 and 0 <= lj < ww - 1, each as one unsigned comparison
-    if ((unsigned)li < (unsigned)(win.wh - 1) && (unsigned)lj < (unsigned)(win.ww - 1)) {
-        // (u, v) nodes as float pairs: row li from node lj on, then row li + 1
-        lds_float* w0 = lds + 2 * (li * win.ww + lj);
-        lds_float* w1 = w0 + 2 * win.ww;
-        r0 = make_float4(w0[0], w0[1], w0[2], w0[3]);
-        r1 = make_float4(w1[0], w1[1], w1[2], w1[3]);
+    if (inside) {
+        lds_vec2* w0 = lds + window_node(c, win);
+        lds_vec2* w1 = w0 + win.ww;
+        const vec2f a = w0[0], b = w0[1], d = w1[0], e = w1[1];
+        r0 = make_float4(a.x, a.y, b.x, b.y);
+        r1 = make_float4(d.x, d.y, e.x, e.y);
     } else {
-        const float2* row0 = fv.F + (size_t)i0 * fv.Gw + j0;
-        r0 = load_pair(row0);
-        r1 = load_pair(row0 + fv.Gw);
+        // nodes of one pair's grid (at most 2^26): 32-bit offsets
+        const uint32_t k = (uint32_t)c.i0 * (uint32_t)fv.Gw + (uint32_t)c.j0;
+        r0 = load_pair(fv.F + k);
+        r1 = load_pair(fv.F + k + fv.Gw);
     }
-    const float2 a = make_float2(r0.x, r0.y), b = make_float2(r0.z, r0.w);
-    const float2 c = make_float2(r1.x, r1.y), e = make_float2(r1.z, r1.w);
-    float2 out;
-    {
-        const float top = __builtin_fmaf(fx, b.x - a.x, a.x);
-        const float bot = __builtin_fmaf(fx, e.x - c.x, c.x);
-        out.x = __builtin_fmaf(fy, bot - top, top);
-    }
-    {
-        const float top = __builtin_fmaf(fx, b.y - a.y, a.y);
-        const float bot = __builtin_fmaf(fx, e.y - c.y, c.y);
-        out.y = __builtin_fmaf(fy, bot - top, top);
-    }
-    return out;
+    return make_float2(bilinear(r0.x, r0.z, r1.x, r1.z, c.fx, c.fy), bilinear(r0.y, r0.w, r1.y, r1.w, c.fx, c.fy));
+}
+
+__device__ __forceinline__ float2 sample_flow(const FlowView& fv, float px, float py)
+{
+    return sample_cell(fv, flow_cell(fv, px, py), false, NO_WIN, nullptr);
 }
 
 __device__ __forceinline__ FlowView flow_view(const synthpix_pair& P, const float* flow)
@@ -91,6 +113,13 @@ __device__ __forceinline__ FlowView flow_view(const synthpix_pair& P, const floa
     fv.sx = (float)P.Gw / (float)P.W;
     fv.sy = (float)P.Gh / (float)P.H;
     return fv;
+}
+
+// (((k1 + 2 k2) + 2 k3) + k4) / 6, each sum rounded (2 k is exact, so the doubled
+// terms fuse).
+__device__ __forceinline__ float rk4_mean(float k1, float k2, float k3, float k4)
+{
+    return (__builtin_fmaf(2.0f, k3, __builtin_fmaf(2.0f, k2, k1)) + k4) / 6.0f;
 }
 
 // One substep of the frozen-field integrator, the same operations in the same
@@ -108,10 +137,8 @@ __device__ __forceinline__ void substep(const FlowView& fv, float& px, float& py
     const float2 k2 = sample_flow(fv, __builtin_fmaf(hh, k1.x, px), __builtin_fmaf(hh, k1.y, py));
     const float2 k3 = sample_flow(fv, __builtin_fmaf(hh, k2.x, px), __builtin_fmaf(hh, k2.y, py));
     const float2 k4 = sample_flow(fv, __builtin_fmaf(h, k3.x, px), __builtin_fmaf(h, k3.y, py));
-    const float su = ((k1.x + 2.0f * k2.x) + 2.0f * k3.x) + k4.x;
-    const float sv = ((k1.y + 2.0f * k2.y) + 2.0f * k3.y) + k4.y;
-    px = __builtin_fmaf(h, su / 6.0f, px);
-    py = __builtin_fmaf(h, sv / 6.0f, py);
+    px = __builtin_fmaf(h, rk4_mean(k1.x, k2.x, k3.x, k4.x), px);
+    py = __builtin_fmaf(h, rk4_mean(k1.y, k2.y, k3.y, k4.y), py);
 }
 
 }  // namespace sp

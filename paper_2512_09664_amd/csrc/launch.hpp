@@ -157,20 +157,17 @@ hipError_t launch_advance(synthpix_batch_io* iod, uint64_t step, hipStream_t s);
 // a kernel argument, so the call is stream-ordered and io may be reused at once).
 hipError_t launch_store_io(synthpix_batch_io* iod, const synthpix_batch_io& io, hipStream_t s);
 
+// wflow, z1, z2: motion out of the plane too (all null: none).
 hipError_t launch_advect(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_span, const float* flow,
                          const synthpix_advect_params& ap, const float* x1, const float* y1, float* x2,
-                         float* y2, hipStream_t s, AdvectOrder order = AdvectOrder{nullptr, nullptr},
-                         const synthpix_batch_io* iod = nullptr);
+                         float* y2, hipStream_t s, AdvectOrder order = AdvectOrder{},
+                         const synthpix_batch_io* iod = nullptr, const float* wflow = nullptr,
+                         const float* z1 = nullptr, float* z2 = nullptr);
 
 // Second diameter and correlation per candidate particle (Philox stream 6).
 hipError_t launch_seed_shape(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_span,
                              const synthpix_seed_params& prm, float rho_lo, float rho_hi, uint64_t seed, float* dy,
                              float* rho, hipStream_t s);
-
-// Three-dimensional motion: (x2, y2, z2) under the (u, v) grid and the w grid.
-hipError_t launch_advect3(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_span, const float* flow,
-                          const float* wflow, const synthpix_advect_params& ap, const float* x1, const float* y1,
-                          const float* z1, float* x2, float* y2, float* z2, hipStream_t s);
 
 struct RenderArgs {
     const synthpix_pair* pairs;

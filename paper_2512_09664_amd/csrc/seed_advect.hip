@@ -102,93 +102,73 @@ seed_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span
     I0[g] = ((int)i < n_active) ? __builtin_fmaf(prm.I0_hi - prm.I0_lo, u24(hw.a), prm.I0_lo) : 0.0f;
 }
 
-// Bilinear sample of the pair's (u, v) grid at image position (px, py).
-// One frozen-field substep sequence; the update order is fixed (see the
-// reference arithmetic): Euler p = fma(h, u, p); RK4 stages at fma(h/2, k, p)
-// and fma(h, k3, p), update p = fma(h, (((k1 + 2 k2) + 2 k3) + k4) / 6, p).
-__device__ __forceinline__ float2 integrate(const FlowView& fv, float px, float py, float dt,
-                                            int substeps, int integrator)
-{
-    const float h = dt / (float)substeps;
-    const float hh = h * 0.5f;
-    for (int s = 0; s < substeps; ++s) {
-        if (integrator == SP_EULER) {
-            const float2 u = sample_flow(fv, px, py);
-            px = __builtin_fmaf(h, u.x, px);
-            py = __builtin_fmaf(h, u.y, py);
-        } else {
-            const float2 k1 = sample_flow(fv, px, py);
-            const float2 k2 = sample_flow(fv, __builtin_fmaf(hh, k1.x, px), __builtin_fmaf(hh, k1.y, py));
-            const float2 k3 = sample_flow(fv, __builtin_fmaf(hh, k2.x, px), __builtin_fmaf(hh, k2.y, py));
-            const float2 k4 = sample_flow(fv, __builtin_fmaf(h, k3.x, px), __builtin_fmaf(h, k3.y, py));
-            const float su = ((k1.x + 2.0f * k2.x) + 2.0f * k3.x) + k4.x;
-            const float sv = ((k1.y + 2.0f * k2.y) + 2.0f * k3.y) + k4.y;
-            px = __builtin_fmaf(h, su / 6.0f, px);
-            py = __builtin_fmaf(h, sv / 6.0f, py);
-        }
-    }
-    return make_float2(px, py);
-}
-
-// N particles per thread, integrated in lockstep: each substep's bilinear
-// samples are chains of dependent L2 reads, so independent particles in one
-// thread overlap those latencies.
-template <int N>
-__device__ __forceinline__ void integrate_n(const FlowView* fv, float* px, float* py, float dt, int substeps,
-                                            int integrator, const FlowWin* win, lds_float* lds)
-{
-    const float h = dt / (float)substeps;
-    const float hh = h * 0.5f;
-    for (int s = 0; s < substeps; ++s) {
-        if (integrator == SP_EULER) {
-            float2 u[N];
-#pragma unroll
-            for (int q = 0; q < N; ++q) u[q] = sample_flow(fv[q], px[q], py[q], win[q], lds);
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                px[q] = __builtin_fmaf(h, u[q].x, px[q]);
-                py[q] = __builtin_fmaf(h, u[q].y, py[q]);
-            }
-        } else {
-            float2 k1[N], k2[N], k3[N], k4[N];
-#pragma unroll
-            for (int q = 0; q < N; ++q) k1[q] = sample_flow(fv[q], px[q], py[q], win[q], lds);
-#pragma unroll
-            for (int q = 0; q < N; ++q)
-                k2[q] = sample_flow(fv[q], __builtin_fmaf(hh, k1[q].x, px[q]), __builtin_fmaf(hh, k1[q].y, py[q]),
-                                    win[q], lds);
-#pragma unroll
-            for (int q = 0; q < N; ++q)
-                k3[q] = sample_flow(fv[q], __builtin_fmaf(hh, k2[q].x, px[q]), __builtin_fmaf(hh, k2[q].y, py[q]),
-                                    win[q], lds);
-#pragma unroll
-            for (int q = 0; q < N; ++q)
-                k4[q] = sample_flow(fv[q], __builtin_fmaf(h, k3[q].x, px[q]), __builtin_fmaf(h, k3[q].y, py[q]),
-                                    win[q], lds);
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                const float su = ((k1[q].x + 2.0f * k2[q].x) + 2.0f * k3[q].x) + k4[q].x;
-                const float sv = ((k1[q].y + 2.0f * k2[q].y) + 2.0f * k3[q].y) + k4[q].y;
-                px[q] = __builtin_fmaf(h, su / 6.0f, px[q]);
-                py[q] = __builtin_fmaf(h, sv / 6.0f, py[q]);
-            }
-        }
-    }
-}
-
-constexpr int ADVECT_ILP = 1;
-constexpr int ADVECT_WIN_NODES = 2048;   // LDS window of grid nodes (16 KB)
+constexpr int ADVECT_WIN_NODES = 2048;   // LDS window of grid nodes (16 KB, 24 KB with w)
 constexpr int ADVECT_WIN_MARGIN = 4;     // cells added around the starting cells
 
+struct Velocity {
+    float u, v, w;
+};
+
+// (u, v) and, with W3, the out-of-plane velocity w (one float per node, registered
+// like the (u, v) grid) at (px, py).
+template <bool W3>
+__device__ __forceinline__ Velocity velocity(const FlowView& fv, const float* __restrict__ G, float px, float py,
+                                             const FlowWin& win, lds_vec2* lds, lds_float* ldsw)
+{
+    const FlowCell c = flow_cell(fv, px, py);
+    const bool inside = in_window(c, win);
+    const float2 u = sample_cell(fv, c, inside, win, lds);
+    Velocity o = {u.x, u.y, 0.0f};
+    if constexpr (W3) {
+        float a, b, d, e;
+        if (inside) {
+            lds_float* w0 = ldsw + window_node(c, win);
+            lds_float* w1 = w0 + win.ww;
+            a = w0[0];
+            b = w0[1];
+            d = w1[0];
+            e = w1[1];
+        } else {
+            const float* w0 = G + (size_t)c.i0 * fv.Gw + c.j0;
+            const float* w1 = w0 + fv.Gw;
+            a = w0[0];
+            b = w0[1];
+            d = w1[0];
+            e = w1[1];
+        }
+        o.w = bilinear(a, b, d, e, c.fx, c.fy);
+    }
+    return o;
+}
+
+// One particle per thread through the frozen field; the update order is fixed
+// (see the reference arithmetic): Euler p = fma(h, u, p); RK4 stages at
+// fma(h/2, k, p) and fma(h, k3, p), update p = fma(h, (((k1 + 2 k2) + 2 k3) + k4) /
+// 6, p).  W3 (Remark 1's particles in 3-D space under a 3-D flow): z integrates
+// w(x, y) with the same stages, w_k at the k-th stage position.
+//
 // SORTED: thread slots follow the home-block order (neighbouring lanes sample
 // neighbouring grid cells, so the bilinear gathers share cache lines); each
-// slot reads its particle index from the order's entry list.
-template <bool SORTED>
+// slot reads its particle index from the order's entry list, and the grid nodes
+// around the workgroup's starting cells are copied to LDS.  (Sorting the
+// positions themselves and taking the results back to index order in a launch of
+// its own moves the random accesses out of this kernel: 64 pairs of 1024^2, order
+// and advection 154 -> 177 us, 32 dense pairs of 2048^2 960 -> 952.)
+//
+// A wave whose slots belong to several pairs takes them one after another, so a
+// pair's grid, scales and window are wave-uniform (scalar) values.
+// Bound together by VALU issue (0.87 of the nominal rate), the LDS window's reads
+// (active 0.74 of the time, half of it bank conflicts) and, for large pairs, the
+// random reads and writes of the positions: 64 pairs of 1024^2, RK4 x 4, 110 us, 80
+// with no substep at all; 32 dense pairs of 2048^2, RK4 x 8, 750 us, 685 without.
+// Motion out of the plane (16 pairs of 1024^2) took 222 us in index order without
+// the window, 48 us and 24 for the order with it.
+template <bool SORTED, bool W3>
 __global__ void __launch_bounds__(256)
 advect_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span,
-              const float* __restrict__ flow, synthpix_advect_params ap,
-              const float* __restrict__ x1, const float* __restrict__ y1,
-              float* __restrict__ x2, float* __restrict__ y2, AdvectOrder order,
+              const float* __restrict__ flow, const float* __restrict__ wflow, synthpix_advect_params ap,
+              const float* __restrict__ x1, const float* __restrict__ y1, const float* __restrict__ z1,
+              float* __restrict__ x2, float* __restrict__ y2, float* __restrict__ z2, AdvectOrder order,
               const synthpix_batch_io* __restrict__ iod)
 {
     if (iod) {
@@ -199,55 +179,40 @@ advect_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_sp
         y2 = iod->y2;
     }
     // consecutive particle blocks (same pair, same flow grid) stay on one XCD
-    const int64_t g0 = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * (256 * ADVECT_ILP);
-    const int64_t base = g0 + threadIdx.x;
-    FlowView fv[ADVECT_ILP];
-    float px[ADVECT_ILP], py[ADVECT_ILP];
-    int64_t gi[ADVECT_ILP];
-#pragma unroll
-    for (int q = 0; q < ADVECT_ILP; ++q) {
-        const int64_t g = base + 256 * q;
-        gi[q] = -1;
-        px[q] = py[q] = 0.0f;
-        fv[q] = FlowView{reinterpret_cast<const float2*>(flow), 2, 2, 1.0f, 1.0f};
-        if (g < n_span) {
-            const int p = find_pair_from(pairs, n_pairs, g0, g);
-            const synthpix_pair P = pairs[p];
-            const int64_t i = g - P.particle_offset;
-            if (i >= 0 && i < (order.live ? (int64_t)order.live[p] : (int64_t)P.n_max)) {
-                gi[q] = SORTED ? P.particle_offset + order.entries[order.L[p].entry_base + i] : g;
-                fv[q] = flow_view(P, flow);
-                px[q] = x1[gi[q]];
-                py[q] = y1[gi[q]];
-            }
+    const int64_t g0 = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * 256;
+    const int64_t slot = g0 + threadIdx.x;
+    float px = 0.0f, py = 0.0f, pz = 0.0f;
+    int64_t g = 0;
+    int p = -1;                              // the slot's pair (-1: no particle to move)
+    if (slot < n_span) {
+        const int q = find_pair_from(pairs, n_pairs, g0, slot);
+        const int64_t i = slot - pairs[q].particle_offset;
+        if (i >= 0 && i < (order.live ? (int64_t)order.live[q] : (int64_t)pairs[q].n_max)) {
+            p = q;
+            g = SORTED ? pairs[q].particle_offset + order.entries[order.L[q].entry_base + i] : slot;
+            px = x1[g];
+            py = y1[g];
+            if (W3) pz = z1[g];
         }
     }
     // SORTED: the workgroup's particles start in a compact patch of the image;
     // the grid nodes around their starting cells (those of the first slot's
     // pair, grown by a margin) are copied to LDS when they fit
-    __shared__ float2 s_win[ADVECT_WIN_NODES];
+    __shared__ vec2f s_win[SORTED ? ADVECT_WIN_NODES : 1];
+    __shared__ float s_winw[SORTED && W3 ? ADVECT_WIN_NODES : 1];
     __shared__ int s_box[4][4];
     __shared__ int s_pair;
-    FlowWin win[ADVECT_ILP];
-#pragma unroll
-    for (int q = 0; q < ADVECT_ILP; ++q) win[q] = NO_WIN;
+    FlowWin win0 = NO_WIN;                   // the window and its pair
+    int pw = -1;
     if (SORTED) {
-        if (threadIdx.x == 0) s_pair = gi[0] >= 0 ? find_pair_from(pairs, n_pairs, g0, g0) : -1;
+        if (threadIdx.x == 0) s_pair = p;
         __syncthreads();
-        const int sp_ = s_pair;
+        pw = __builtin_amdgcn_readfirstlane(s_pair);
         int bi0 = 1 << 30, bj0 = 1 << 30, bi1 = -1, bj1 = -1;
-        bool mine[ADVECT_ILP];
-#pragma unroll
-        for (int q = 0; q < ADVECT_ILP; ++q) {
-            mine[q] = gi[q] >= 0 && sp_ >= 0 && fv[q].F == flow_view(pairs[sp_], flow).F;
-            if (mine[q]) {
-                const float gx = __builtin_fminf(__builtin_fmaxf(px[q] * fv[q].sx - 0.5f, 0.0f), (float)(fv[q].Gw - 1));
-                const float gy = __builtin_fminf(__builtin_fmaxf(py[q] * fv[q].sy - 0.5f, 0.0f), (float)(fv[q].Gh - 1));
-                bj0 = min(bj0, (int)gx);
-                bj1 = max(bj1, (int)gx);
-                bi0 = min(bi0, (int)gy);
-                bi1 = max(bi1, (int)gy);
-            }
+        if (pw >= 0 && p == pw) {
+            const FlowCell c = flow_cell(flow_view(pairs[pw], flow), px, py);
+            bj0 = bj1 = c.j0;
+            bi0 = bi1 = c.i0;
         }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
@@ -263,45 +228,72 @@ advect_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_sp
             s_box[threadIdx.x >> 6][3] = bj1;
         }
         __syncthreads();
-        if (sp_ >= 0) {
-            const synthpix_pair Q = pairs[sp_];
+        if (pw >= 0) {
+            const synthpix_pair Q = pairs[pw];
             bi0 = max(min(min(s_box[0][0], s_box[1][0]), min(s_box[2][0], s_box[3][0])) - ADVECT_WIN_MARGIN, 0);
             bj0 = max(min(min(s_box[0][1], s_box[1][1]), min(s_box[2][1], s_box[3][1])) - ADVECT_WIN_MARGIN, 0);
             bi1 = min(max(max(s_box[0][2], s_box[1][2]), max(s_box[2][2], s_box[3][2])) + ADVECT_WIN_MARGIN + 1,
                       Q.Gh - 1);
             bj1 = min(max(max(s_box[0][3], s_box[1][3]), max(s_box[2][3], s_box[3][3])) + ADVECT_WIN_MARGIN + 1,
                       Q.Gw - 1);
-            const int wh = bi1 - bi0 + 1, ww = bj1 - bj0 + 1;
-            if (bi1 >= bi0 && bj1 >= bj0 && wh * ww <= ADVECT_WIN_NODES) {
-                const float2* F = reinterpret_cast<const float2*>(flow + Q.flow_offset);
+            const int wi0 = __builtin_amdgcn_readfirstlane(bi0), wj0 = __builtin_amdgcn_readfirstlane(bj0);
+            const int wh = __builtin_amdgcn_readfirstlane(bi1) - wi0 + 1;
+            const int ww = __builtin_amdgcn_readfirstlane(bj1) - wj0 + 1;
+            if (wh >= 1 && ww >= 1 && wh * ww <= ADVECT_WIN_NODES) {
+                const vec2f* F = reinterpret_cast<const vec2f*>(flow + Q.flow_offset);
                 // window row of node k without an integer division: (k + 1/2) / ww lies at
                 // least 1/(2 ww) from an integer and, for k < 2048, the float product errs
                 // by under 2048 * 2^-21 / ww, so truncation gives floor(k / ww)
                 const float inv_ww = 1.0f / (float)ww;
                 for (int k = threadIdx.x; k < wh * ww; k += 256) {
                     const int r = (int)(((float)k + 0.5f) * inv_ww);
-                    s_win[k] = F[(int64_t)(bi0 + r) * Q.Gw + bj0 + (k - r * ww)];
+                    const int64_t node = (int64_t)(wi0 + r) * Q.Gw + wj0 + (k - r * ww);
+                    s_win[k] = F[node];
+                    if (W3) s_winw[k] = wflow[Q.flow_offset / 2 + node];
                 }
-#pragma unroll
-                for (int q = 0; q < ADVECT_ILP; ++q)
-                    if (mine[q]) win[q] = FlowWin{bi0, bj0, wh, ww};
+                win0 = FlowWin{wi0, wj0, wh, ww};
             }
         }
         __syncthreads();
     }
-    // a wave none of whose slots holds a particle to move (slots past every
-    // pair's range or, with live counts, masked candidates) skips the steps
-    bool any = false;
-#pragma unroll
-    for (int q = 0; q < ADVECT_ILP; ++q) any = any || gi[q] >= 0;
-    if (__builtin_amdgcn_ballot_w64(any) != 0)
-        integrate_n<ADVECT_ILP>(fv, px, py, ap.dt, ap.substeps, ap.integrator, win, (lds_float*)s_win);
-#pragma unroll
-    for (int q = 0; q < ADVECT_ILP; ++q) {
-        if (gi[q] >= 0) {
-            x2[gi[q]] = px[q];
-            y2[gi[q]] = py[q];
+    const float h = ap.dt / (float)ap.substeps;
+    const float hh = h * 0.5f;
+    lds_vec2* lds = (lds_vec2*)s_win;
+    lds_float* ldsw = (lds_float*)s_winw;
+    // the wave's pairs, in turn (lanes without a particle belong to none)
+    for (unsigned long long left = __builtin_amdgcn_ballot_w64(p >= 0); left != 0;) {
+        const int q = __builtin_amdgcn_readlane(p, __builtin_ctzll(left));
+        left &= ~__builtin_amdgcn_ballot_w64(p == q);
+        if (p != q) continue;
+        const FlowView fv = flow_view(pairs[q], flow);
+        const float* G = W3 ? wflow + pairs[q].flow_offset / 2 : nullptr;
+        const FlowWin win = SORTED && q == pw ? win0 : NO_WIN;
+        if (ap.integrator == SP_EULER) {
+            for (int s = 0; s < ap.substeps; ++s) {
+                const Velocity k = velocity<W3>(fv, G, px, py, win, lds, ldsw);
+                px = __builtin_fmaf(h, k.u, px);
+                py = __builtin_fmaf(h, k.v, py);
+                if (W3) pz = __builtin_fmaf(h, k.w, pz);
+            }
+        } else {
+            for (int s = 0; s < ap.substeps; ++s) {
+                const Velocity k1 = velocity<W3>(fv, G, px, py, win, lds, ldsw);
+                const Velocity k2 = velocity<W3>(fv, G, __builtin_fmaf(hh, k1.u, px), __builtin_fmaf(hh, k1.v, py),
+                                                 win, lds, ldsw);
+                const Velocity k3 = velocity<W3>(fv, G, __builtin_fmaf(hh, k2.u, px), __builtin_fmaf(hh, k2.v, py),
+                                                 win, lds, ldsw);
+                const Velocity k4 = velocity<W3>(fv, G, __builtin_fmaf(h, k3.u, px), __builtin_fmaf(h, k3.v, py),
+                                                 win, lds, ldsw);
+                px = __builtin_fmaf(h, rk4_mean(k1.u, k2.u, k3.u, k4.u), px);
+                py = __builtin_fmaf(h, rk4_mean(k1.v, k2.v, k3.v, k4.v), py);
+                if (W3) pz = __builtin_fmaf(h, rk4_mean(k1.w, k2.w, k3.w, k4.w), pz);
+            }
         }
+    }
+    if (p >= 0) {
+        x2[g] = px;
+        y2[g] = py;
+        if (W3) z2[g] = pz;
     }
 }
 
@@ -332,82 +324,6 @@ seed_shape_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t 
     }
     dy[g] = v;
     rho[g] = __builtin_fmaf(rho_hi - rho_lo, u24(w.d), rho_lo);
-}
-
-// Bilinear, clamped sample of a pair's scalar grid (the out-of-plane velocity w,
-// one float per node, registered like the (u, v) grid).
-__device__ __forceinline__ float sample_scalar(const float* __restrict__ G, const FlowView& fv, float px, float py)
-{
-    float gx = px * fv.sx - 0.5f;
-    float gy = py * fv.sy - 0.5f;
-    gx = __builtin_fminf(__builtin_fmaxf(gx, 0.0f), (float)(fv.Gw - 1));
-    gy = __builtin_fminf(__builtin_fmaxf(gy, 0.0f), (float)(fv.Gh - 1));
-    int j0 = (int)__builtin_floorf(gx);
-    int i0 = (int)__builtin_floorf(gy);
-    j0 = j0 > fv.Gw - 2 ? fv.Gw - 2 : j0;
-    i0 = i0 > fv.Gh - 2 ? fv.Gh - 2 : i0;
-    const float fx = gx - (float)j0;
-    const float fy = gy - (float)i0;
-    const float* a = G + (size_t)i0 * fv.Gw + j0;
-    const float* c = a + fv.Gw;
-    const float top = __builtin_fmaf(fx, a[1] - a[0], a[0]);
-    const float bot = __builtin_fmaf(fx, c[1] - c[0], c[0]);
-    return __builtin_fmaf(fy, bot - top, top);
-}
-
-// Three-dimensional motion (Remark 1's particles in 3-D space under a 3-D
-// flow): the in-plane trajectory of advect_kernel, and z integrating the
-// out-of-plane velocity w(x, y) with the same stages (Euler z = fma(h, w, z);
-// RK4 z = fma(h, (((w1 + 2 w2) + 2 w3) + w4) / 6, z), w_k at the k-th stage
-// position).  One particle per thread in index order.
-__global__ void __launch_bounds__(256)
-advect3_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_span, const float* __restrict__ flow,
-               const float* __restrict__ wflow, synthpix_advect_params ap, const float* __restrict__ x1,
-               const float* __restrict__ y1, const float* __restrict__ z1, float* __restrict__ x2,
-               float* __restrict__ y2, float* __restrict__ z2)
-{
-    const int64_t g0 = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * 256;
-    const int64_t g = g0 + threadIdx.x;
-    if (g >= n_span) return;
-    const int p = find_pair_from(pairs, n_pairs, g0, g);
-    const synthpix_pair P = pairs[p];
-    const int64_t i = g - P.particle_offset;
-    if (i < 0 || i >= P.n_max) return;
-    const FlowView fv = flow_view(P, flow);
-    const float* W = wflow + P.flow_offset / 2;
-    float px = x1[g], py = y1[g], pz = z1[g];
-    const float h = ap.dt / (float)ap.substeps;
-    const float hh = h * 0.5f;
-    for (int s = 0; s < ap.substeps; ++s) {
-        if (ap.integrator == SP_EULER) {
-            const float2 u = sample_flow(fv, px, py);
-            const float w = sample_scalar(W, fv, px, py);
-            px = __builtin_fmaf(h, u.x, px);
-            py = __builtin_fmaf(h, u.y, py);
-            pz = __builtin_fmaf(h, w, pz);
-        } else {
-            const float2 k1 = sample_flow(fv, px, py);
-            const float w1 = sample_scalar(W, fv, px, py);
-            const float ax = __builtin_fmaf(hh, k1.x, px), ay = __builtin_fmaf(hh, k1.y, py);
-            const float2 k2 = sample_flow(fv, ax, ay);
-            const float w2 = sample_scalar(W, fv, ax, ay);
-            const float bx = __builtin_fmaf(hh, k2.x, px), by = __builtin_fmaf(hh, k2.y, py);
-            const float2 k3 = sample_flow(fv, bx, by);
-            const float w3 = sample_scalar(W, fv, bx, by);
-            const float cx = __builtin_fmaf(h, k3.x, px), cy = __builtin_fmaf(h, k3.y, py);
-            const float2 k4 = sample_flow(fv, cx, cy);
-            const float w4 = sample_scalar(W, fv, cx, cy);
-            const float su = ((k1.x + 2.0f * k2.x) + 2.0f * k3.x) + k4.x;
-            const float sv = ((k1.y + 2.0f * k2.y) + 2.0f * k3.y) + k4.y;
-            const float sw = ((w1 + 2.0f * w2) + 2.0f * w3) + w4;
-            px = __builtin_fmaf(h, su / 6.0f, px);
-            py = __builtin_fmaf(h, sv / 6.0f, py);
-            pz = __builtin_fmaf(h, sw / 6.0f, pz);
-        }
-    }
-    x2[g] = px;
-    y2[g] = py;
-    z2[g] = pz;
 }
 
 // Ground-truth flow of each pair (the sampler's flow_fields): the pair's (u, v)
@@ -444,17 +360,6 @@ hipError_t launch_seed_shape(const synthpix_pair* pairs_dev, int n_pairs, int64_
     TimedScope ts("seed_shape", s);
     hipLaunchKernelGGL(seed_shape_kernel, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, pairs_dev, n_pairs,
                        n_span, prm, rho_lo, rho_hi, seed, dy, rho);
-    return hipGetLastError();
-}
-
-hipError_t launch_advect3(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_span, const float* flow,
-                          const float* wflow, const synthpix_advect_params& ap, const float* x1, const float* y1,
-                          const float* z1, float* x2, float* y2, float* z2, hipStream_t s)
-{
-    if (n_span <= 0) return hipSuccess;
-    TimedScope ts("advect", s);
-    hipLaunchKernelGGL(advect3_kernel, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, pairs_dev, n_pairs,
-                       n_span, flow, wflow, ap, x1, y1, z1, x2, y2, z2);
     return hipGetLastError();
 }
 
@@ -499,17 +404,20 @@ hipError_t launch_seed(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_sp
 
 hipError_t launch_advect(const synthpix_pair* pairs_dev, int n_pairs, int64_t n_span, const float* flow,
                          const synthpix_advect_params& ap, const float* x1, const float* y1, float* x2,
-                         float* y2, hipStream_t s, AdvectOrder order, const synthpix_batch_io* iod)
+                         float* y2, hipStream_t s, AdvectOrder order, const synthpix_batch_io* iod,
+                         const float* wflow, const float* z1, float* z2)
 {
     if (n_span <= 0) return hipSuccess;
-    const int64_t blocks = (n_span + 256 * ADVECT_ILP - 1) / (256 * ADVECT_ILP);
     TimedScope ts("advect", s);
-    if (order.entries)
-        hipLaunchKernelGGL(advect_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, pairs_dev, n_pairs, n_span,
-                           flow, ap, x1, y1, x2, y2, order, iod);
-    else
-        hipLaunchKernelGGL(advect_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, pairs_dev, n_pairs, n_span,
-                           flow, ap, x1, y1, x2, y2, order, iod);
+    const dim3 grid((unsigned)((n_span + 255) / 256)), block(256);
+#define SP_ADVECT(SORTED_, W3_)                                                                                    \
+    hipLaunchKernelGGL((advect_kernel<SORTED_, W3_>), grid, block, 0, s, pairs_dev, n_pairs, n_span, flow, wflow,   \
+                       ap, x1, y1, z1, x2, y2, z2, order, iod)
+    if (order.entries && wflow) SP_ADVECT(true, true);
+    else if (order.entries) SP_ADVECT(true, false);
+    else if (wflow) SP_ADVECT(false, true);
+    else SP_ADVECT(false, false);
+#undef SP_ADVECT
     return hipGetLastError();
 }
 

@@ -283,13 +283,13 @@ class Sampler:
                     # particle reuse: last batch's second positions moved on by dt'
                     ap2 = api.advect_params(float(reuse["dt"]), c.substeps, c.integrator)
                     if self._w_dev is not None:
-                        api.advect(pairs, self._flow_dev, ap2, b["x2"], b["y2"], b["x1"], b["y1"],
+                        api.advect(pairs, self._flow_dev, ap2, b["x2"], b["y2"], b["x1"], b["y1"], self._ws,
                                    wflow=self._w_dev, z1=b["z2"], z2=b["z"])
                     else:
                         api.advect(pairs, self._flow_dev, ap2, b["x2"], b["y2"], b["x1"], b["y1"], self._ws)
                 z2 = None
                 if self._w_dev is not None:
-                    api.advect(pairs, self._flow_dev, self.aprm, b["x1"], b["y1"], b["x2"], b["y2"],
+                    api.advect(pairs, self._flow_dev, self.aprm, b["x1"], b["y1"], b["x2"], b["y2"], self._ws,
                                wflow=self._w_dev, z1=b["z"], z2=b["z2"])
                     z2 = b["z2"]
                 else:

@@ -98,3 +98,26 @@ def test_order_does_not_change_positions(batch):
     plain = sp.advect(b, flow, ap, x, y, ordered=False)
     for u, v in zip(ordered, plain):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("integrator", ["euler", "rk4"])
+@pytest.mark.parametrize("batch", range(len(BATCHES)))
+def test_order_does_not_change_positions_out_of_plane(batch, integrator):
+    """Motion out of the plane: planar results and z as in index order, with
+    waves and windows that straddle pairs, and particles that leave the window;
+    a workspace too small for the order is passed over."""
+    sizes, counts = BATCHES[batch]
+    q = _particles(sizes, counts, batch)
+    b = gu.batch_for(sizes, [(12, 10)] * len(sizes), counts)
+    rng = np.random.default_rng(batch)
+    flow = gu.to_dev(rng.normal(0, 6, b.n_flow).astype(np.float32))
+    w = gu.to_dev(rng.normal(0, 1, b.n_flow // 2).astype(np.float32))
+    ap = sp.advect_params(1.0, 1024, integrator)
+    x, y, z = (gu.to_dev(q[k]) for k in ("x", "y", "z"))
+    ordered = sp.advect(b, flow, ap, x, y, wflow=w, z1=z)
+    plain = sp.advect(b, flow, ap, x, y, wflow=w, z1=z, ordered=False)
+    small = sp.advect(b, flow, ap, x, y, wflow=w, z1=z, workspace=torch.empty(256, dtype=torch.uint8, device=gu.DEV))
+    planar = sp.advect(b, flow, ap, x, y)
+    for u, v, s in zip(ordered, plain, small):
+        assert torch.equal(u, v) and torch.equal(u, s)
+    assert torch.equal(planar[0], ordered[0]) and torch.equal(planar[1], ordered[1])
