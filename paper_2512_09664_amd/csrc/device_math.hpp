@@ -219,6 +219,25 @@ __device__ __forceinline__ unsigned xcd_contiguous(unsigned b, unsigned n)
     return xcd < rem ? xcd * (q + 1) + slot : rem * (q + 1) + (xcd - rem) * q + slot;
 }
 
+// In-wave inclusive scan with DPP: row shifts by 1, 2, 4, 8 within each row of
+// 16 lanes, then the row broadcasts of lanes 15 and 31 into the rows above.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
+{
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    v = dpp_add<0x143, 0xC>(v);
+    return v;
+}
+
 // Pair lookup: the pair whose particle range [offset, offset + n_max) holds g.
 // Pairs are sorted by particle_offset (validated on the host).
 __device__ __forceinline__ int find_pair_by_particle(const synthpix_pair* pairs, int n_pairs, int64_t g)

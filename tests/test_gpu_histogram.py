@@ -79,3 +79,27 @@ def test_histogram_match_full_size():
     assert sp.read_status(ws) == 0
     for (p, f, got), src in zip(_frames(batch, img), before):
         assert np.array_equal(got, oh.match(src, target, 12))
+
+
+@pytest.mark.parametrize("size", [(1, 1), (1, 7), (1, 8), (1, 9), (3, 5), (1, 23), (255, 257), (256, 128), (181, 181),
+                                  (256, 256), (257, 256)])
+@pytest.mark.parametrize("gap", range(8))
+def test_unaligned_and_ragged_images(size, gap):
+    """Images at every 2-byte alignment, shorter than one vector and a pixel
+    around the workgroups' chunks; codes above the range count as the largest."""
+    H, W = size
+    bits, n = 6, 2 * H * W
+    b = sp.PairBatch.build([size] * 2, [(2, 2)] * 2, [0] * 2, device=DEV, gaps=(0, gap, 0))
+    rng = np.random.default_rng([H, W, gap])
+    im = np.where(rng.random(b.n_pixels) < 0.5, 0, rng.integers(0, (1 << bits) + 3, b.n_pixels)).astype(np.uint16)
+    target = rng.integers(0, 9, 1 << bits).astype(np.uint32)
+    target[0] += 1
+    dev = to_dev(im.view(np.int16)).view(sp.api.U16)
+    sp.histogram_match(b, dev, to_dev(target), bits)
+    got, want = to_np(dev), im.copy()
+    for p in range(2):
+        for f in range(2):
+            o = (p + 1) * gap + p * n + f * H * W
+            src = np.minimum(im[o:o + H * W], (1 << bits) - 1).reshape(H, W)
+            want[o:o + H * W] = oh.match(src, target, bits).reshape(-1)
+    assert np.array_equal(got, want)
