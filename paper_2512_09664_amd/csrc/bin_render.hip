@@ -789,7 +789,10 @@ scan_pair(const PairLayout* __restrict__ L, uint32_t* __restrict__ hist, uint32_
 
 // ------------------------------------------------------------------ render
 
-constexpr int STAGE = 256;      // particles staged per pass, one per thread
+// Threads of a renderer workgroup, and particles staged per pass (one per thread):
+// 512 for tiles of 4096 pixels, so that the four of them a CU's LDS holds still
+// fill its 32 wave slots.
+constexpr int render_threads(int tw, int th) { return tw * th >= 4096 ? 512 : 256; }
 constexpr int SLACK = 24;       // accumulator words past the region (a row's zero columns may overrun it)
 constexpr int SIZES = 64;       // patch sizes told apart when a pass is sorted
 
@@ -833,7 +836,7 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
 // evaluates exp(-q) per pixel, q = dx (kappa_x dx + kappa_xy dy) + kappa_y dy^2,
 // kappa_xy = -16 rho / (om d d_y); the patch is |dx| <= 1.5 d, |dy| <= 1.5 d_y.
 //
-// The tile's particles are staged in LDS up to 256 at a time, one per thread,
+// The tile's particles are staged in LDS up to 256 (512) at a time, one per thread,
 // sorted by patch size (a counting sort on LDS counters), and splatted one
 // particle per lane: a lane keeps its patch's column factors in registers and
 // walks down the rows, so an exponential is computed once per patch column and
@@ -843,14 +846,14 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
 // Bound by VALU issue (exponentials, products, the epilogue's draws), with the
 // LDS adds close behind (7.4 clocks per wave at 64 unrelated addresses, 6.5 at
 // eight rows of eight patches: the order of the lanes hardly matters).  Measured
-// against one patch row per lane with the column factors in an LDS table:
-// 64 pairs of 1024^2 at 0.05 ppp, 3x3 blur, noise: 505 -> 385 us; 32 pairs of
-// 2048^2 at 0.1 ppp, d to 6, 5x5 blur: 2.97 -> 2.31 ms; uneven pairs, ppp to
-// 0.1: 940 -> 664 us.  Of the first, the epilogue takes about 150 us, the
-// staging 80 and the splat 130.  Sorting by width alone or by an estimate of
-// the work was slower (397 and 408 us).
+// with 64 x 32 tiles against one patch row per lane with the column factors in an
+// LDS table: 64 pairs of 1024^2 at 0.05 ppp, 3x3 blur, noise: 505 -> 385 us; 32
+// pairs of 2048^2 at 0.1 ppp, d to 6, 5x5 blur: 2.97 -> 2.31 ms; uneven pairs, ppp
+// to 0.1: 940 -> 664 us; with 64 x 64 tiles 340 us, 2.06 ms and 620 us.  Of the
+// first, the epilogue takes about 150 us.  Sorting by width alone or by an
+// estimate of the work was slower (397 and 408 us with 64 x 32 tiles).
 template <int TW, int TH, int B, bool ANISO, bool PERSIST>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PERSIST ? 6 : 8)))
+__global__ void __launch_bounds__(render_threads(TW, TH)) __attribute__((amdgpu_waves_per_eu(PERSIST ? 6 : 8)))
 render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__ L, int n_pairs,
             const float4* __restrict__ rec0, const float4* __restrict__ rec1, const uint2* __restrict__ box0,
             const uint2* __restrict__ box1, const float2* __restrict__ shp0,
@@ -862,6 +865,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     static_assert(TW % 4 == 0 && (TW & (TW - 1)) == 0 && (TH & (TH - 1)) == 0, "power-of-two tiles");
     static_assert(TW + 6 < 256 && TH + 6 < 256, "patch boxes are packed in bytes");
     static_assert(B >= 0 && B <= 3, "blur radius 0..3");
+    constexpr int NT = render_threads(TW, TH), STAGE = NT;
     constexpr int Q4 = TW / 4;
     constexpr int RW = TW + 2 * B;
     constexpr int RH = TH + 2 * B;
@@ -941,8 +945,8 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     const uint2* __restrict__ bxs = (f ? box1 : box0) + p_off;
     const float2* __restrict__ shp = (f ? shp1 : shp0) + p_off;
 
-    for (int k = t; k < ACC / 4; k += 256) reinterpret_cast<uint4*>(acc)[k] = make_uint4(0u, 0u, 0u, 0u);
-    for (int k = t; k <= RH; k += 256) s_rows[k] = 0ull;
+    for (int k = t; k < ACC / 4; k += NT) reinterpret_cast<uint4*>(acc)[k] = make_uint4(0u, 0u, 0u, 0u);
+    for (int k = t; k <= RH; k += NT) s_rows[k] = 0ull;
     if (t < 2 * SIZES) (&s_hist[0][0])[t] = 0u;
     if (t == 0) s_sum = 0ull;
     __syncthreads();
@@ -997,7 +1001,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
         // pixel) the sort leaves uneven (16 pairs of 1024^2: 1 / 4 / 8 lanes 187 / 146 /
         // 155 us, one patch row per lane 177)
         const int lp = ANISO || 4 * n <= spread ? 2 : 2 * n <= spread ? 1 : 0;
-        for (int s0 = wave * (64 >> lp); s0 < n; s0 += 4 * (64 >> lp)) {
+        for (int s0 = wave * (64 >> lp); s0 < n; s0 += (NT / 64) * (64 >> lp)) {
             const int slot = s0 + (lane >> lp);
             const int step = 1 << lp, j = lane & (step - 1);
             const bool on = slot < n;
@@ -1075,9 +1079,9 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     if constexpr (B > 0) {
         // horizontal pass over all region rows: four tile columns per work item
 #pragma unroll
-        for (int k0 = 0; k0 < RH * Q4; k0 += 256) {
+        for (int k0 = 0; k0 < RH * Q4; k0 += NT) {
             const int k = k0 + t;
-            if (k0 + 256 > RH * Q4 && k >= RH * Q4) break;
+            if (k0 + NT > RH * Q4 && k >= RH * Q4) break;
             const int r = k / Q4;
             const int c = (k % Q4) * 4;
             // the fixed-point scale rides on the weights: w (v 2^-24) and (w 2^-24) v
@@ -1111,13 +1115,13 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     if (noisy && t < TH * Q4)
         w_next = draw((uint32_t)((ty * TH + t / Q4) * Wq + ((tx * TW) >> 2) + t % Q4), STREAM_NOISE0 + f, pid, a.seed);
 #pragma unroll 1
-    for (int gi = t; gi < TH * Q4; gi += 256) {
+    for (int gi = t; gi < TH * Q4; gi += NT) {
         const int r = gi / Q4;
         const int c4 = (gi % Q4) * 4;
         const int R = ty * TH + r;
         const int C = tx * TW + c4;
         const u32x4 w = w_next;
-        const int gn = gi + 256;
+        const int gn = gi + NT;
         if (noisy && gn < TH * Q4)
             w_next = draw((uint32_t)((ty * TH + gn / Q4) * Wq + ((tx * TW) >> 2) + gn % Q4), STREAM_NOISE0 + f, pid,
                           a.seed);
@@ -1219,7 +1223,7 @@ static void launch_scans(const PairLayout* L, int n_pairs, uint32_t* hist, const
 // occupancy (cached per kernel).  The persistent form is compiled for the
 // isotropic renderer; anisotropic batches run one workgroup per item.
 template <typename K, typename... Args>
-static void launch_tile_kernel(K kernel, dim3 grid, hipStream_t s, bool persistent, Args... args)
+static void launch_tile_kernel(K kernel, dim3 grid, int threads, hipStream_t s, bool persistent, Args... args)
 {
     if (persistent) {
         static std::mutex mu;
@@ -1230,7 +1234,7 @@ static void launch_tile_kernel(K kernel, dim3 grid, hipStream_t s, bool persiste
             const void* key = reinterpret_cast<const void*>(kernel);
             auto it = cache.find(key);
             if (it == cache.end()) {
-                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess)
+                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess)
                     per_cu = 0;
                 cache[key] = per_cu;
             } else {
@@ -1242,7 +1246,7 @@ static void launch_tile_kernel(K kernel, dim3 grid, hipStream_t s, bool persiste
             if (grid.x > cap) grid.x = cap;
         }
     }
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, args...);
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, args...);
 }
 
 template <int TW, int TH>
@@ -1258,24 +1262,25 @@ static void launch_render_shape(dim3 grid, hipStream_t s, const RenderArgs& a, c
     ea.seed = a.seed;
     ea.iod = a.iod;
     for (int q = 0; q < 7; ++q) ea.blur_w[q] = a.blur_w[q];
-    // a grid of under four workgroups per CU leaves most of the chip idle and
-    // spreads a tile's particles over all four waves (a shorter walk), a larger
-    // one over as few waves as hold them (less work in all)
-    const int spread = grid.x < 4u * (unsigned)device_cu_count() ? 256 : 64;
+    // a grid of under 1024 threads per CU leaves most of the chip idle and spreads a
+    // tile's particles over all its waves (a shorter walk), a larger one over as
+    // few waves as hold them (less work in all)
+    const int threads = render_threads(TW, TH);
+    const int spread = (int64_t)grid.x * threads < (int64_t)1024 * device_cu_count() ? threads : 64;
 #define SP_B(B_)                                                                                                 \
     case B_:                                                                                                     \
         if (a.aniso)                                                                                             \
-            launch_tile_kernel(render_tile<TW, TH, B_, true, false>, grid, s, false, a.pairs, L, a.n_pairs, \
+            launch_tile_kernel(render_tile<TW, TH, B_, true, false>, grid, threads, s, false, a.pairs, L, a.n_pairs, \
                                r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries,   \
                                tiles,                                                                            \
                                status, status + 8);                                                              \
         else if (cfg.persistent)                                                                                 \
-            launch_tile_kernel(render_tile<TW, TH, B_, false, true>, grid, s, true, a.pairs, L, a.n_pairs,  \
+            launch_tile_kernel(render_tile<TW, TH, B_, false, true>, grid, threads, s, true, a.pairs, L, a.n_pairs,  \
                                r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries,   \
                                tiles,                                                                            \
                                status, status + 8);                                                              \
         else                                                                                                     \
-            launch_tile_kernel(render_tile<TW, TH, B_, false, false>, grid, s, false, a.pairs, L,           \
+            launch_tile_kernel(render_tile<TW, TH, B_, false, false>, grid, threads, s, false, a.pairs, L,           \
                                a.n_pairs, r0, r1, b0, b1, h0, h1, ea, spread, tile_count,              \
                                tile_offset, entries, tiles, status, status + 8);                                 \
         break;
