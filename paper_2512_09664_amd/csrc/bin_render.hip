@@ -882,14 +882,14 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     uint32_t* box = reinterpret_cast<uint32_t*>(work + STAGE * (ANISO ? 24 : 16));   // c0 | w | r0 | h bytes
     float* tmp = reinterpret_cast<float*>(work);                    // blur scratch, reuses the staging
     __shared__ uint32_t s_hist[2][SIZES];       // particles of each patch size, by pass parity
-    // fixed-point range bound: a difference array over the region's rows of the
-    // staged particles' integer peaks (each particle's peak added over the rows
-    // its patch covers).  Every term a particle adds to a pixel is at most its
-    // peak, so a row's prefix sum bounds every pixel sum of that row.  The tile's
-    // whole sum (in units of 256, rounded up) bounds every row: the rows are only
-    // summed where it reaches the range.
-    __shared__ unsigned long long s_rows[RH + 1];
-    __shared__ unsigned long long s_sum;
+    __shared__ uint32_t s_live[2];              // particles with pixels in the region, by pass parity
+    // fixed-point range bound: every term a particle adds to a pixel is at most its
+    // integer peak, so the peaks of the particles that touch a band of rows bound
+    // its pixel sums.  Only where some band's sum (in units of 256, each peak
+    // rounded up) reaches 2^32 are the rows summed one by one.
+    constexpr int BAND = 16, BANDS = (RH + BAND - 1) / BAND;
+    __shared__ unsigned long long s_band[BANDS];
+    __shared__ uint32_t s_over;
 
     // PERSIST: a persistent work list.  Each workgroup pops (frame, tile) items
     // from the queue of its XCD until the queue is empty; the items of one XCD
@@ -946,56 +946,65 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     const float2* __restrict__ shp = (f ? shp1 : shp0) + p_off;
 
     for (int k = t; k < ACC / 4; k += NT) reinterpret_cast<uint4*>(acc)[k] = make_uint4(0u, 0u, 0u, 0u);
-    for (int k = t; k <= RH; k += NT) s_rows[k] = 0ull;
     if (t < 2 * SIZES) (&s_hist[0][0])[t] = 0u;
-    if (t == 0) s_sum = 0ull;
+    if (t < 2) s_live[t] = 0u;
+    if (t < BANDS) s_band[t] = 0ull;
+    if (t == 0) s_over = 0u;
     __syncthreads();
 
+    // particle e's patch box (image pixels) clipped to the region
+    auto clip = [&](int e, int& w, int& h, int& c0, int& r0) {
+        const uint2 pb = bxs[e];
+        const int a0 = max((int)(pb.x & 0xffffu), rx0), a1 = min((int)(pb.x >> 16), rx0 + RW - 1);
+        const int b0 = max((int)(pb.y & 0xffffu), ry0), b1 = min((int)(pb.y >> 16), ry0 + RH - 1);
+        if (!box_empty(pb) && a0 <= a1 && b0 <= b1) {
+            w = a1 - a0 + 1;
+            h = b1 - b0 + 1;
+            c0 = a0 - rx0;
+            r0 = b0 - ry0;
+        }
+    };
+
     for (int base = 0, par = 0; base < cnt; base += STAGE, par ^= 1) {
-        // one particle per thread; its patch box (image pixels) clipped to the region
+        // one particle per thread
         float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         float2 rs = make_float2(0.0f, 0.0f);
-        int w = 0, h = 0, c0 = 0, r0 = 0;
-        if (base + t < cnt) {
-            const int e = list[base + t];
-            r = rec[e];
-            const uint2 pb = bxs[e];
-            if (ANISO) rs = shp[e];
-            if (!box_empty(pb)) {
-                const int a0 = max((int)(pb.x & 0xffffu), rx0), a1 = min((int)(pb.x >> 16), rx0 + RW - 1);
-                const int b0 = max((int)(pb.y & 0xffffu), ry0), b1 = min((int)(pb.y >> 16), ry0 + RH - 1);
-                if (a0 <= a1 && b0 <= b1) {
-                    w = a1 - a0 + 1;
-                    h = b1 - b0 + 1;
-                    c0 = a0 - rx0;
-                    r0 = b0 - ry0;
-                }
+        int w = 0, h = 0, c0 = 0, r0 = 0, size = 0;
+        uint32_t rank = 0;
+        const bool some = base + wave * 64 < cnt;        // the wave has particles (uniform)
+        if (some) {
+            if (base + t < cnt) {
+                const int e = list[base + t];
+                r = rec[e];
+                if (ANISO) rs = shp[e];
+                clip(e, w, h, c0, r0);
+            }
+            size = min(max(w, h), SIZES - 1);
+            const uint32_t in_wave = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(w > 0));
+            if (lane == 0) atomicAdd(&s_live[par], in_wave);
+            if (w > 0) {
+                rank = atomicAdd(&s_hist[par][size], 1u);
+                const unsigned long long peak = (uint32_t)(r.w * 0x1p-8f) + 1u;
+                for (int k = r0 / BAND; k <= (r0 + h - 1) / BAND; ++k)
+                    if (atomicAdd(&s_band[k], peak) + peak >= (1ull << 24)) s_over = 1u;
             }
         }
-        const int size = min(max(w, h), SIZES - 1);
-        uint32_t rank = 0, peak = 0;
-        if (w > 0) {
-            rank = atomicAdd(&s_hist[par][size], 1u);
-            const unsigned long long pk = (unsigned long long)r.w;
-            atomicAdd(&s_rows[r0], pk);
-            atomicAdd(&s_rows[r0 + h], 0ull - pk);
-            peak = (uint32_t)(r.w * 0x1p-8f) + 1u;
-        }
-        peak = wave_scan(peak);
-        if (lane == 63 && peak) atomicAdd(&s_sum, (unsigned long long)peak);
         __syncthreads();
-        // largest patches first: lane l of every wave scans size SIZES - 1 - l
-        const uint32_t inc = wave_scan(s_hist[par][SIZES - 1 - lane]);
-        const int n = __builtin_amdgcn_readlane((int)inc, SIZES - 2);       // patches of size >= 1
-        const uint32_t above = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (SIZES - 2 - size), (int)inc);
-        if (w > 0) {
-            const int slot = (int)((size < SIZES - 1 ? above : 0u) + rank);
-            stg[slot] = r;
-            if (ANISO) stg2[slot] = rs;
-            box[slot] = pack_box(c0, w, r0, h);
+        const int n = __builtin_amdgcn_readfirstlane((int)s_live[par]);
+        if (some) {
+            // largest patches first: lane l of the wave scans size SIZES - 1 - l
+            const uint32_t inc = wave_scan(s_hist[par][SIZES - 1 - lane]);
+            const uint32_t above = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (SIZES - 2 - size), (int)inc);
+            if (w > 0) {
+                const int slot = (int)((size < SIZES - 1 ? above : 0u) + rank);
+                stg[slot] = r;
+                if (ANISO) stg2[slot] = rs;
+                box[slot] = pack_box(c0, w, r0, h);
+            }
         }
         __syncthreads();
         if (t < SIZES) s_hist[par][t] = 0u;      // next used two passes on, past a barrier
+        if (t == 0) s_live[par] = 0u;
         // lanes per particle: 1, or 2 or 4 where the particles then still fit in `spread`
         // lanes; 4 for the full model, whose patches (two diameters, an exponential per
         // pixel) the sort leaves uneven (16 pairs of 1024^2: 1 / 4 / 8 lanes 187 / 146 /
@@ -1052,26 +1061,46 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
         }
     }
     __syncthreads();
-    // prefix sums of the row bounds (wave 0): flag a row whose bound reaches 2^32
-    if (s_sum >= (1ull << 24) && t < 64) {
-        unsigned long long carry = 0ull, top = 0ull;
-        for (int c = 0; c <= RH; c += 64) {
-            unsigned long long v = c + lane <= RH ? s_rows[c + lane] : 0ull;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned long long u = __shfl_up(v, o, 64);
-                if (lane >= o) v += u;
+    if (s_over) {
+        // a difference array over the region's rows (each peak added over the rows
+        // its patch covers), its prefix sums by wave 0: flag a row whose bound
+        // reaches 2^32
+        unsigned long long* rows = reinterpret_cast<unsigned long long*>(work);
+        static_assert((RH + 1) * 8 <= STAGE_BYTES, "the row sums reuse the staging");
+        for (int k = t; k <= RH; k += NT) rows[k] = 0ull;
+        __syncthreads();
+        for (int k = t; k < cnt; k += NT) {
+            const int e = list[k];
+            int w = 0, h = 0, c0 = 0, r0 = 0;
+            clip(e, w, h, c0, r0);
+            if (w > 0) {
+                const unsigned long long pk = (unsigned long long)rec[e].w;
+                atomicAdd(&rows[r0], pk);
+                atomicAdd(&rows[r0 + h], 0ull - pk);
             }
-            v += carry;
-            top = v > top ? v : top;
-            carry = __shfl(v, 63, 64);
         }
+        __syncthreads();
+        if (t < 64) {
+            unsigned long long carry = 0ull, top = 0ull;
+            for (int c = 0; c <= RH; c += 64) {
+                unsigned long long v = c + lane <= RH ? rows[c + lane] : 0ull;
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const unsigned long long u = __shfl_xor(top, o, 64);
-            top = u > top ? u : top;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const unsigned long long u = __shfl_up(v, o, 64);
+                    if (lane >= o) v += u;
+                }
+                v += carry;
+                top = v > top ? v : top;
+                carry = __shfl(v, 63, 64);
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                const unsigned long long u = __shfl_xor(top, o, 64);
+                top = u > top ? u : top;
+            }
+            if (lane == 0 && top >= (1ull << 32)) atomicOr(status, SP_STATUS_FIXED_RANGE);
         }
-        if (lane == 0 && top >= (1ull << 32)) atomicOr(status, SP_STATUS_FIXED_RANGE);
+        __syncthreads();
     }
 
     // fixed point -> float happens as the blur / store passes read the accumulator
@@ -1104,28 +1133,24 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
         __syncthreads();
     }
 
-    // vertical pass, noise, codes, store: four consecutive pixels per work item
-    const int64_t plane = (int64_t)pH * pW;
+    // vertical pass, noise, codes, store: four consecutive pixels per work item,
+    // addressed from the tile's first pixel (offsets fit 32 bits; the stores are
+    // whole vectors at any alignment)
     const int Wq = (pW + 3) >> 2;
     const float Lq = a.bits > 0 ? (float)((1u << a.bits) - 1u) : 0.0f;
-    // the noise words of a thread's next work item are drawn while it finishes
-    // the current one (the Philox rounds are one long dependent chain)
     const bool noisy = a.noise_sigma > 0.0f;
-    u32x4 w_next = {0u, 0u, 0u, 0u};
-    if (noisy && t < TH * Q4)
-        w_next = draw((uint32_t)((ty * TH + t / Q4) * Wq + ((tx * TW) >> 2) + t % Q4), STREAM_NOISE0 + f, pid, a.seed);
-#pragma unroll 1
-    for (int gi = t; gi < TH * Q4; gi += NT) {
-        const int r = gi / Q4;
-        const int c4 = (gi % Q4) * 4;
-        const int R = ty * TH + r;
-        const int C = tx * TW + c4;
-        const u32x4 w = w_next;
-        const int gn = gi + NT;
-        if (noisy && gn < TH * Q4)
-            w_next = draw((uint32_t)((ty * TH + gn / Q4) * Wq + ((tx * TW) >> 2) + gn % Q4), STREAM_NOISE0 + f, pid,
-                          a.seed);
-        if (R >= pH || C >= pW) continue;
+    typedef __attribute__((address_space(1))) unsigned char gbyte;
+    typedef uint32_t codes4 __attribute__((ext_vector_type(2), aligned(2)));
+    typedef float pixels4 __attribute__((ext_vector_type(4), aligned(4)));
+    const int64_t first = p_img + (int64_t)f * ((int64_t)pH * pW) + (int64_t)(ty * TH) * pW + tx * TW;
+    gbyte* img = (gbyte*)a.images + first * (a.bits > 0 ? 2 : 4);
+#pragma unroll
+    for (int k0 = 0; k0 < TH * Q4; k0 += NT) {
+        const int gi = k0 + t;
+        if (k0 + NT > TH * Q4 && gi >= TH * Q4) break;
+        const int r = gi / Q4, q4 = gi % Q4, c4 = 4 * q4;
+        const int left = pW - (tx * TW + c4);                // pixels from here to the image's edge
+        if (ty * TH + r >= pH || left <= 0) continue;
         float o[4];
         if constexpr (B > 0) {
             float4 s4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -1145,6 +1170,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
             o[2] = (float)src[2] * FIX; o[3] = (float)src[3] * FIX;
         }
         if (noisy) {
+            const u32x4 w = draw((uint32_t)((ty * TH + r) * Wq + ((tx * TW) >> 2) + q4), STREAM_NOISE0 + f, pid, a.seed);
             const uint32_t wa[2] = {w.a, w.c};
             const uint32_t wb[2] = {w.b, w.d};
 #pragma unroll
@@ -1157,28 +1183,33 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
                 o[2 * h2 + 1] = __builtin_fmaf(a.noise_sigma, rad * __builtin_amdgcn_sinf(u2), o[2 * h2 + 1]);
             }
         }
-        const int64_t pix = p_img + (int64_t)f * plane + (int64_t)R * pW + C;
-        const int ne = min(4, pW - C);
+        const uint32_t at = (uint32_t)r * (uint32_t)pW + (uint32_t)c4;
         if (a.bits > 0) {
+            // clamp to [0, L] with one median, then round to even by adding 2^23: the code
+            // is the sum's low half (rounding a clamped value clamps the rounded one)
             uint32_t qv[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // clamp to [0, L] with one median (the value is finite)
-                const float t = __builtin_amdgcn_fmed3f(__builtin_rintf(o[e] * Lq), 0.0f, Lq);
-                qv[e] = (uint32_t)t;
-            }
-            uint16_t* dst = reinterpret_cast<uint16_t*>(a.images) + pix;
-            if (ne == 4 && ((uintptr_t)dst & 7) == 0) {
-                *reinterpret_cast<uint2*>(dst) = make_uint2(qv[0] | (qv[1] << 16), qv[2] | (qv[3] << 16));
+            for (int e = 0; e < 4; ++e)
+                qv[e] = __float_as_uint(__builtin_amdgcn_fmed3f(o[e] * Lq, 0.0f, Lq) + 8388608.0f);
+            gbyte* dst = img + 2 * at;
+            if (left >= 4) {
+                const codes4 v = {__builtin_amdgcn_perm(qv[1], qv[0], 0x05040100u),
+                                  __builtin_amdgcn_perm(qv[3], qv[2], 0x05040100u)};
+                *(__attribute__((address_space(1))) codes4*)dst = v;
             } else {
-                for (int e = 0; e < ne; ++e) dst[e] = (uint16_t)qv[e];
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < left) *(__attribute__((address_space(1))) uint16_t*)(dst + 2 * e) = (uint16_t)qv[e];
             }
         } else {
-            float* dst = reinterpret_cast<float*>(a.images) + pix;
-            if (ne == 4 && ((uintptr_t)dst & 15) == 0) {
-                *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
+            gbyte* dst = img + 4 * at;
+            if (left >= 4) {
+                const pixels4 v = {o[0], o[1], o[2], o[3]};
+                *(__attribute__((address_space(1))) pixels4*)dst = v;
             } else {
-                for (int e = 0; e < ne; ++e) dst[e] = o[e];
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < left) *(__attribute__((address_space(1))) float*)(dst + 4 * e) = o[e];
             }
         }
     }
