@@ -793,7 +793,8 @@ scan_pair(const PairLayout* __restrict__ L, uint32_t* __restrict__ hist, uint32_
 // 512 for tiles of 4096 pixels, so that the four of them a CU's LDS holds still
 // fill its 32 wave slots.
 constexpr int render_threads(int tw, int th) { return tw * th >= 4096 ? 512 : 256; }
-constexpr int SLACK = 24;       // accumulator words past the region (a row's zero columns may overrun it)
+constexpr int SLACK = 24;       // accumulator words past the region and one more row (zero columns and rows
+                                // may overrun it)
 constexpr int SIZES = 64;       // patch sizes told apart when a pass is sorted
 
 __device__ __forceinline__ uint32_t pack_box(int c0, int w, int r0, int h)
@@ -828,6 +829,41 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
     }
 }
 
+// The same with two lanes per particle, a the lane's place in its pair: lane a adds
+// the columns a, a + 2, .. and forms the factors of the rows a, a + 2, .., which
+// the pair exchanges.
+template <int N>
+__device__ __forceinline__ float pair_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), N ? 0xF5 : 0xA0, 0xF, 0xF, false));
+}
+
+template <int K, int RW>
+__device__ __forceinline__ void splat_pairs(uint32_t* dst, float fx, float x, int pw, float fy, float y, float kappa,
+                                            float Af, int a, int h)
+{
+    float gx[K / 2];
+#pragma unroll
+    for (int k = 0; k < K / 2; ++k) {
+        const float dx = (fx + (float)(2 * k)) - x;
+        const float g = expneg_lt80(kappa * (dx * dx));
+        gx[k] = 2 * k + a < pw ? g : 0.0f;
+    }
+#pragma unroll 1
+    for (int j = 0; j < h; j += 2) {
+        const float dy = fy - y;
+        float rv = Af * expneg_lt80(kappa * (dy * dy));
+        rv = j + a < h ? rv : 0.0f;
+        const float r0 = pair_lane<0>(rv), r1 = pair_lane<1>(rv);
+#pragma unroll
+        for (int k = 0; k < K / 2; ++k) atomicAdd(dst + 2 * k, (uint32_t)(r0 * gx[k]));
+#pragma unroll
+        for (int k = 0; k < K / 2; ++k) atomicAdd(dst + RW + 2 * k, (uint32_t)(r1 * gx[k]));
+        fy += 2.0f;
+        dst += 2 * RW;
+    }
+}
+
 // Tile renderer, templated on the tile shape and the blur radius (tile-local
 // index arithmetic becomes shifts, blur loops unroll).  ANISO: the full model's
 // particle images (Eq. 1 with sigma_y = d_y / 4 and rho, from the shape
@@ -849,8 +885,9 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
 // with 64 x 32 tiles against one patch row per lane with the column factors in an
 // LDS table: 64 pairs of 1024^2 at 0.05 ppp, 3x3 blur, noise: 505 -> 385 us; 32
 // pairs of 2048^2 at 0.1 ppp, d to 6, 5x5 blur: 2.97 -> 2.31 ms; uneven pairs, ppp
-// to 0.1: 940 -> 664 us; with 64 x 64 tiles 340 us, 2.06 ms and 620 us.  Of the
-// first, the epilogue takes about 150 us.  Sorting by width alone or by an
+// to 0.1: 940 -> 664 us; with 64 x 64 tiles 340 us, 1.96 ms and 612 us, and with
+// wide patches by pairs of lanes 341 us, 1.83 ms and 621 us.  Of the first, the
+// epilogue takes about 150 us.  Sorting by width alone or by an
 // estimate of the work was slower (397 and 408 us with 64 x 32 tiles).
 template <int TW, int TH, int B, bool ANISO, bool PERSIST>
 __global__ void __launch_bounds__(render_threads(TW, TH)) __attribute__((amdgpu_waves_per_eu(PERSIST ? 6 : 8)))
@@ -869,7 +906,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     constexpr int Q4 = TW / 4;
     constexpr int RW = TW + 2 * B;
     constexpr int RH = TH + 2 * B;
-    constexpr int ACC = (RH * RW + SLACK + 3) & ~3;
+    constexpr int ACC = ((RH + 1) * RW + SLACK + 3) & ~3;
     constexpr int STAGE_BYTES = STAGE * (16 + 4 + (ANISO ? 8 : 0));
     constexpr int BLUR_BYTES = B > 0 ? RH * TW * 4 : 0;
     float wb[2 * B + 1];
@@ -1051,12 +1088,39 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
             else if (!__builtin_amdgcn_ballot_w64(pw > 8)) SP_SPLAT(8);
             else if (!__builtin_amdgcn_ballot_w64(pw > 10)) SP_SPLAT(10);
             else if (!__builtin_amdgcn_ballot_w64(pw > 12)) SP_SPLAT(12);
-            else if (!__builtin_amdgcn_ballot_w64(pw > 16)) SP_SPLAT(16);
-            else if (!__builtin_amdgcn_ballot_w64(pw > 20)) SP_SPLAT(20);
-            else
-                for (int cb = 0; __builtin_amdgcn_ballot_w64(pw > cb) != 0; cb += 16)
-                    splat_columns<16, RW>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
+            else if constexpr (ANISO) {
+                for (int cb = 0; __builtin_amdgcn_ballot_w64(pw > cb) != 0; cb += 12)
+                    splat_columns<12, RW>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
                                           pw > cb ? hs : 0, step);
+            } else {
+                // wide patches: two lanes per particle, 32 particles at a time.  The adds of
+                // a pair fall on neighbouring banks, and half the columns need half the
+                // registers.  From 13 columns on, as narrower patches gain less than the
+                // pairs' set-up (32 pairs of 2048^2 with d to 6 / 64 of 1024^2 with d about
+                // 2.5: from 7 columns 1.85 ms / 362 us, from 13 1.83 / 341, from 17 1.91 /
+                // 343, never 1.96 / 342).
+                const int e0 = min(s0 + (64 >> lp), n);
+#pragma unroll 1
+                for (int s2 = s0 + (lane >> 1); __builtin_amdgcn_ballot_w64(s2 < e0) != 0; s2 += 32) {
+                    const bool on2 = s2 < e0;
+                    const int a2 = lane & 1;
+                    const uint32_t b2 = on2 ? box[s2] : 0u;
+                    const float4 f2 = stg[on2 ? s2 : s0];
+                    const int qc0 = (int)(b2 & 255u), qw = (int)((b2 >> 8) & 255u);
+                    const int qr0 = (int)((b2 >> 16) & 255u), qh = (int)(b2 >> 24);
+                    uint32_t* d2 = acc + qr0 * RW + qc0 + a2;
+                    const float gx0 = (float)(rx0 + qc0 + a2) + 0.5f, gy0 = (float)(ry0 + qr0 + a2) + 0.5f;
+#define SP_PAIRS(K_) splat_pairs<K_, RW>(d2, gx0, f2.x, qw, gy0, f2.y, f2.z, f2.w, a2, qh)
+                    if (!__builtin_amdgcn_ballot_w64(qw > 12)) SP_PAIRS(12);
+                    else if (!__builtin_amdgcn_ballot_w64(qw > 16)) SP_PAIRS(16);
+                    else if (!__builtin_amdgcn_ballot_w64(qw > 20)) SP_PAIRS(20);
+                    else
+                        for (int cb = 0; __builtin_amdgcn_ballot_w64(qw > cb) != 0; cb += 20)
+                            splat_pairs<20, RW>(d2 + cb, gx0 + (float)cb, f2.x, qw - cb, gy0, f2.y, f2.z, f2.w, a2,
+                                                qw > cb ? qh : 0);
+#undef SP_PAIRS
+                }
+            }
 #undef SP_SPLAT
         }
     }

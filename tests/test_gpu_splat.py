@@ -47,3 +47,11 @@ def test_patch_widths(d, tile):
     tiles far smaller than them; 8 x 8 tiles make a grid that fills the chip
     (fewest lanes per particle), 64 x 64 tiles one that does not."""
     _check(190, 186, 700, d, tile, 2)
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 65, 129, 513, 600])
+@pytest.mark.parametrize("d", [(3.9, 4.4), (4.2, 5.4), (5.2, 7.0)])
+def test_wide_lists(n, d):
+    """Wide patches in one tile's list: up to two lanes' worth, one wave's worth and
+    more particles, with particles left over at every step of it."""
+    _check(64, 64, n, d, (64, 64, 2048, 128), 3, box=(8.0, 56.0, 8.0, 56.0))
