@@ -222,8 +222,8 @@ int64_t flow_span(const synthpix_pair* ph, int32_t n_pairs)
 
 // Backward workspace: particle-major, no bins.
 struct BwdLayout {
-    size_t status, scale, x2, y2, gx2, gy2, sheet, sheet_part, bound_part, wg_base, head, part, ovf, eblur, parts,
-        loss_part, total;
+    size_t status, scale, x2, y2, gx2, gy2, sheet, sheet_part, bound_part, wg_base, head, part, ovf, eblur, loss_part,
+        total;
 };
 
 // Workgroups of the flow adjoint: 256 particles of one pair each.
@@ -234,7 +234,7 @@ int64_t grid_workgroups(const synthpix_pair* ph, int32_t n_pairs)
     return n;
 }
 
-BwdLayout bwd_layout(int64_t n_span, int64_t n_wg, int32_t n_pairs, int64_t n_eblur, bool tile, int64_t n_loss)
+BwdLayout bwd_layout(int64_t n_span, int64_t n_wg, int32_t n_pairs, int64_t n_eblur, int64_t n_loss)
 {
     BwdLayout w{};
     size_t o = 0;
@@ -253,19 +253,17 @@ BwdLayout bwd_layout(int64_t n_span, int64_t n_wg, int32_t n_pairs, int64_t n_eb
     w.part = o; o = align256(o + sizeof(uint64_t) * 2 * sp::WIN_NODES * (size_t)n_wg);
     w.ovf = o; o = align256(o + sizeof(sp::GridRecord) * sp::GRID_OVF_CAP * (size_t)n_wg);
     w.eblur = o; o = align256(o + sizeof(float) * (size_t)n_eblur);
-    w.parts = o; o = align256(o + (tile ? 2 * 16 * (size_t)n_span : 0));
     w.loss_part = o; o = align256(o + sizeof(double) * (size_t)n_loss);
     w.total = o;
     return w;
 }
 
 // Elements of the blurred-gradient images the backward keeps (B^T dL/dJ, the
-// images' layout): for any blur under the tile-major gather, else when the blur
-// is wide enough (radius >= 2) for the particle-major gather to pay for a
-// per-pixel pass, and always for the loss-fused form (mse); otherwise none.
-int64_t eblur_span(const synthpix_pair* ph, int32_t n_pairs, int blur_radius, bool tile, bool mse)
+// images' layout): when the blur is wide enough (radius >= 2) for a per-pixel
+// pass to pay, and always for the loss-fused form (mse); otherwise none.
+int64_t eblur_span(const synthpix_pair* ph, int32_t n_pairs, int blur_radius, bool mse)
 {
-    if (!mse && blur_radius < (tile ? 1 : 2)) return 0;
+    if (!mse && blur_radius < 2) return 0;
     int64_t span = 0;
     for (int32_t p = 0; p < n_pairs; ++p)
         span = std::max<int64_t>(span, ph[p].image_offset + 2 * (int64_t)ph[p].H * ph[p].W);
@@ -420,12 +418,10 @@ size_t order_bytes(const synthpix_pair* ph, int32_t n_pairs)
     return order_layout(n_pairs, T, 0).total;
 }
 
-// Backward workspace: the gradient layout, then the frame-1 home-block order
-// and, for the tile-major gather, the frame-2 one.
+// Backward workspace: the gradient layout, then the home-block order.
 struct BwdPlan {
     BwdLayout wl;
     size_t ob;
-    bool tile;
     size_t total;
 };
 
@@ -433,7 +429,6 @@ BwdPlan bwd_plan(const synthpix_pair* ph, int32_t n_pairs, int64_t span, const s
 {
     BwdPlan b{};
     b.ob = order_bytes(ph, n_pairs);
-    b.tile = sp::tile_gather_fits(rp.d_max, order_config(ph, n_pairs).log_tw, rp.blur_radius);
     int max_h = 0, max_w = 0;
     for (int32_t p = 0; p < n_pairs; ++p) {
         max_h = std::max(max_h, (int)ph[p].H);
@@ -441,8 +436,8 @@ BwdPlan bwd_plan(const synthpix_pair* ph, int32_t n_pairs, int64_t span, const s
     }
     const int64_t n_loss = mse ? sp::blur_grad_blocks(n_pairs, max_w, max_h, true) : 0;
     b.wl = bwd_layout(span, grid_workgroups(ph, n_pairs), n_pairs,
-                      eblur_span(ph, n_pairs, rp.blur_radius, b.tile, mse), b.tile, n_loss);
-    b.total = b.wl.total + b.ob * (b.tile ? 2 : 1);
+                      eblur_span(ph, n_pairs, rp.blur_radius, mse), n_loss);
+    b.total = b.wl.total + b.ob;
     return b;
 }
 
@@ -851,20 +846,6 @@ synthpix_status backward_common(const synthpix_pair* pairs_host, const synthpix_
     a.x2 = x2 ? x2 : a.x2w;
     a.y2 = y2 ? y2 : a.y2w;
     a.recompute_x2 = x2 == nullptr;
-    if (bp.tile) {
-        // the tile gather groups frame 2 by its own positions: recompute them
-        // first when the caller did not pass them, then order them
-        if (a.recompute_x2) {
-            const hipError_t e = sp::launch_advect(pairs_dev, n_pairs, span, flow, rp->advect, x1, y1, a.x2w, a.y2w,
-                                                   hs, a.order);
-            if (e != hipSuccess) return hip_fail(e, "backward advect launch");
-            a.recompute_x2 = false;
-        }
-        const hipError_t e = enqueue_order(pairs_host, pairs_dev, n_pairs, a.x2, a.y2, ws, wl.total + bp.ob, hs,
-                                           &a.order2);
-        if (e != hipSuccess) return hip_fail(e, "backward order launch");
-        a.parts = reinterpret_cast<float4*>(ws + wl.parts);
-    }
     a.z = z;
     a.d = d;
     a.I0 = I0;
@@ -876,7 +857,7 @@ synthpix_status backward_common(const synthpix_pair* pairs_host, const synthpix_
     a.loss = mse ? loss : nullptr;
     a.loss_part = a.loss ? reinterpret_cast<double*>(ws + wl.loss_part) : nullptr;
     for (int32_t p = 0; p < n_pairs; ++p) a.loss_n += 2 * (int64_t)pairs_host[p].H * pairs_host[p].W;
-    a.eblur = wl.parts > wl.eblur ? reinterpret_cast<float*>(ws + wl.eblur) : nullptr;
+    a.eblur = wl.loss_part > wl.eblur ? reinterpret_cast<float*>(ws + wl.eblur) : nullptr;
     a.g_x1 = g_x1;
     a.g_y1 = g_y1;
     a.g_z = g_z;
@@ -901,6 +882,13 @@ synthpix_status backward_common(const synthpix_pair* pairs_host, const synthpix_
     }
     a.scale = reinterpret_cast<uint32_t*>(ws + wl.scale);
     a.status = reinterpret_cast<uint32_t*>(ws + wl.status);
+    int64_t slots = 0;                       // the ranges are disjoint
+    const int gl = sp::block_group_log(a.order.log_block);
+    for (int32_t p = 0; p < n_pairs; ++p) {
+        slots += pairs_host[p].n_max;
+        a.block_groups += (int64_t)((pairs_host[p].W + (1 << gl) - 1) >> gl) * ((pairs_host[p].H + (1 << gl) - 1) >> gl);
+    }
+    a.gaps = slots != span;
     a.sheet_sigma = rp->sheet_sigma;
     a.d_max = rp->d_max;
     blur_taps(rp->blur_radius, rp->blur_sigma, a.blur_w);

@@ -9,10 +9,11 @@
 //     S0 = sum_q e_q G_q,  Sx = sum e G dx,  Sy = sum e G dy,  Sr = sum e G (dx^2 + dy^2),
 // e = B^T dL/dJ, equal sum_q (dL/dJ)_q Ty_j(r) Tx_k(c) with 1-D tables
 // Tx_k = w * (gx dx^k) (the blur folded into the particle's factor tables).
-// The gather is particle-major (a group of 8 or 16 lanes per particle reads
-// its patch rows of dL/dJ with coalesced loads) or, for wide blurs, tile-major
-// (a home block of the image and its halo staged in LDS, the block's particles
-// gathered from it); nothing is scattered, no partial sums cross tiles.
+// The gather is particle-major: a group of 8 or 16 lanes per particle reads its
+// patch rows of dL/dJ with coalesced loads or, for larger batches once the blur's
+// adjoint has run per pixel, a workgroup stages what the particles of a 64 x 64
+// pixel block cover in LDS and two lanes per particle gather from there; nothing
+// is scattered, no partial sums cross workgroups.
 //
 // Flow adjoint: a reverse sweep through the recomputed Euler / RK4 substeps
 // (checkpointed).  Each bilinear sample passes its upstream gradient to its
@@ -28,23 +29,20 @@
 
 namespace sp {
 
-// Patch rows loaded per batch of the column walk (independent loads in
-// flight): 8 from global memory, 4 from a region staged in LDS (16 measured
-// slower for both, 4 slower from global memory and 2 the same from LDS).  The
-// rows' terms are added in row order whatever the batch.
-constexpr int GROWS_GLOBAL = 8;
-constexpr int GROWS_LDS = 4;
+// Patch rows loaded per batch of the column walk (independent loads in flight; 4
+// and 16 measured slower).  The rows' terms are added in row order whatever the
+// batch.
+constexpr int GROWS = 8;
 
 // A particle's lane group: G = 16 lanes (a DPP row) or 8 (half of one); a
 // workgroup of 256 threads holds 256 / G particles.  BT table slots cover the
 // pixel range (<= 3 d_max + 3 pixels) plus 4 b of zero padding.  The raw
 // factors are stored as the Gaussian values e alone (their dx and dx^2
-// multiples are formed where they are read); the raw row factors are kept
-// only where a blur is folded in (RY).
-template <int G, int BT, bool RY = true>
+// multiples are formed where they are read).
+template <int G, int BT>
 struct GatherLds {
     float rx[256 / G][BT];                      // raw column factors e(c) (slot = c - c0 + 2b)
-    float ry[RY ? 256 / G : 1][RY ? BT : 1];    // raw row factors e(r)
+    float ry[256 / G][BT];                      // raw row factors e(r)
     float4 ty[256 / G][BT];                     // blurred row tables (Ty0, Ty1, Ty2, 0)
 };
 
@@ -110,18 +108,13 @@ __device__ __forceinline__ bool cover_range(float p, float R, int n, int& lo, in
 // the blurred row tables (B > 0) and the gather
 //     S0 = sum e G,  Sx = sum e G dx,  Sy = sum e G dy,  Sr = sum e G (dx^2 + dy^2)
 // over the blurred support inside the image, reading pixel (r, c) of the
-// frame's dL/dJ (B > 0) or B^T dL/dJ (B = 0) at src[(r - sr) * stride + (c - sc)]
-// (global memory, or a region staged in LDS).  Every lane returns the group's
-// sums.  on: the particle is valid and its support [c0, c1] x [r0, r1] is not
-// empty.
-// CS: the source's row stride in elements when known at compile time (rows
-// then load at immediate offsets), 0 for the runtime stride.  GROWS: rows per
-// batch of the column walk.
-template <int B, int BT, bool RY, int G, int CS = 0, int GROWS = GROWS_GLOBAL>
-__device__ __forceinline__ float4 frame_sums(GatherLds<G, BT, RY>& S, int grp, int lane, bool on, float x, float y,
+// frame's dL/dJ (B > 0) or B^T dL/dJ (B = 0) at src[r * W + c].  Every lane returns
+// the group's sums.  on: the particle is valid and its support [c0, c1] x [r0, r1]
+// is not empty.
+template <int B, int BT, int G>
+__device__ __forceinline__ float4 frame_sums(GatherLds<G, BT>& S, int grp, int lane, bool on, float x, float y,
                                              float kap, float R, int c0, int c1, int r0, int r1, int W, int H,
-                                             const float* __restrict__ src, int64_t stride, int sr, int sc,
-                                             const float* blur_w)
+                                             const float* __restrict__ src, const float* blur_w)
 {
     // raw factor tables over the slots the gather reads, 0 .. max(c1 - c0, r1 - r0)
     // + 4b (zeros outside the support); a group stops after its last one
@@ -143,7 +136,6 @@ __device__ __forceinline__ float4 frame_sums(GatherLds<G, BT, RY>& S, int grp, i
             const float u1 = u0 * dy;
             S.ty[grp][slot] = make_float4(u0, u1, u1 * dy, 0.0f);
         } else {
-            static_assert(RY, "a folded blur needs the raw row factors");
             S.ry[grp][slot] = u0;
         }
     }
@@ -203,23 +195,16 @@ __device__ __forceinline__ float4 frame_sums(GatherLds<G, BT, RY>& S, int grp, i
             const int t = tlo + cb + cl;
             // walk down the column slice with a row pointer: whole batches of GROWS
             // rows (their loads issued together), then batches of 4, 2 and 1
-            const int64_t str = CS > 0 ? (int64_t)CS : stride;
-            const float* __restrict__ q = src + (int64_t)(r0 - B + ua - sr) * str + (c0 - B + t - sc);
+            const float* __restrict__ q = src + (int64_t)(r0 - B + ua) * W + (c0 - B + t);
             float P0 = 0.0f, P1 = 0.0f, P2 = 0.0f;
             int u = ua;
 #pragma unroll 1
             for (; u + GROWS <= ub; u += GROWS) {
                 float e[GROWS];
-                if constexpr (CS > 0) {
 #pragma unroll
-                    for (int k = 0; k < GROWS; ++k) e[k] = q[k * CS];
-                    q += GROWS * CS;
-                } else {
-#pragma unroll
-                    for (int k = 0; k < GROWS; ++k) {
-                        e[k] = *q;
-                        q += str;
-                    }
+                for (int k = 0; k < GROWS; ++k) {
+                    e[k] = *q;
+                    q += W;
                 }
 #pragma unroll
                 for (int k = 0; k < GROWS; ++k) {
@@ -233,16 +218,10 @@ __device__ __forceinline__ float4 frame_sums(GatherLds<G, BT, RY>& S, int grp, i
             for (int nb = GROWS / 2; nb >= 1; nb >>= 1) {
                 if (ub - u >= nb) {
                     float e[GROWS / 2];
-                    if constexpr (CS > 0) {
 #pragma unroll
-                        for (int k = 0; k < nb; ++k) e[k] = q[k * CS];
-                        q += nb * CS;
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < nb; ++k) {
-                            e[k] = *q;
-                            q += str;
-                        }
+                    for (int k = 0; k < nb; ++k) {
+                        e[k] = *q;
+                        q += W;
                     }
 #pragma unroll
                     for (int k = 0; k < nb; ++k) {
@@ -355,8 +334,8 @@ bwd_gather(BwdArgs a, int64_t n_span)
         int c0 = 0, c1 = -1, r0 = 0, r1 = -1;
         bool on = valid && cover_range(x, R, W, c0, c1);
         on = on && cover_range(y, R, H, r0, r1);
-        fs[f] = frame_sums<B, BT, true, G>(S, grp, lane, on, x, y, kap, R, c0, c1, r0, r1, W, H,
-                                  a.grad + img + (int64_t)f * H * W, W, 0, 0, a.blur_w);
+        fs[f] = frame_sums<B, BT, G>(S, grp, lane, on, x, y, kap, R, c0, c1, r0, r1, W, H,
+                                     a.grad + img + (int64_t)f * H * W, a.blur_w);
     }
 
     if (lane != 0) return;
@@ -383,125 +362,344 @@ bwd_gather(BwdArgs a, int64_t n_span)
     a.sheet[g] = o.sheet;
 }
 
-// Tile-major gather.  Frame f's particles are grouped by the home block
-// (2^lb x 2^lb pixels) of their frame-f position; a workgroup takes one
-// (frame, block), stages the frame's B^T dL/dJ over the block grown by a halo
-// of hb pixels into LDS (zeros outside the image), then runs the lane-group
-// sums of the block's particles, 16 per pass, from LDS.  With hb >=
-// ceil(1.5 d_max) + 2 every in-image pixel of the support of a particle whose
-// position lies in the block (or beyond the image edge next to it, where the
-// home block is clamped) is inside the staged region.  The sums go to
-// parts[f * n_span + slot]; bwd_particles turns them into gradients.
-// RS: the staged region's row stride (a multiple of 8 at least its width, so
-// the gather's row loads take immediate offsets), 0 for a stride equal to the
-// width.
-template <int RS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
-bwd_tile_gather(BwdArgs a, int64_t n_span, int lb, int hb)
-{
-    extern __shared__ __align__(16) float region[];
-    // sixteen lanes per particle here: eight (more particles per wave, deeper
-    // walks for the wide supports this gather serves) measured slower
-    constexpr int G = 16, NP = 256 / G;
-    __shared__ GatherLds<G, 32, false> S;
-    const int64_t blocks = a.order.blocks;
-    const int64_t item = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int f = item >= blocks ? 1 : 0;
-    const int64_t b = item - (int64_t)f * blocks;
-    const AdvectOrder& O = f ? a.order2 : a.order;
-    const int cnt = (int)O.count[b];
-    if (cnt == 0) return;                      // the whole workgroup, before its barrier
-    const int p = find_pair_by_tile(O.L, a.n_pairs, b);
-    const synthpix_pair P = a.pairs[p];
-    const PairLayout PL = O.L[p];
-    // home blocks are numbered in strips of four block rows, column by column
-    // inside a strip, odd strips right to left (the order's numbering)
-    const int tl = (int)(b - PL.tile_base);
-    const int s0 = (tl / (4 * PL.ntx)) * 4;
-    const int rows = PL.nty - s0 < 4 ? PL.nty - s0 : 4;
-    const int wi = tl - s0 * PL.ntx;
-    const int col = wi / rows, by = s0 + (wi - col * rows);
-    const int bx = (s0 & 4) ? PL.ntx - 1 - col : col;
-    const int side = 1 << lb, rw = side + 2 * hb;
-    const int rs = RS > 0 ? RS : rw;
-    const int ox = (bx << lb) - hb, oy = (by << lb) - hb;
-    const int H = P.H, W = P.W;
-    const float* __restrict__ src = a.grad + P.image_offset + (int64_t)f * H * W;
-    // one region row per wave and step, lanes along the row
-    {
-        const int wave = threadIdx.x >> 6, ln = threadIdx.x & 63;
-        for (int r = wave; r < rw; r += 4) {
-            const int R = oy + r;
-            const bool rin = R >= 0 && R < H;
-            const float* __restrict__ row = src + (int64_t)(rin ? R : 0) * W;
-            for (int c = ln; c < rw; c += 64) {
-                const int C = ox + c;
-                region[r * rs + c] = (rin && C >= 0 && C < W) ? row[C] : 0.0f;
-            }
-        }
-    }
-    __syncthreads();
+// ------------------------------------------------------------------ block gather
 
-    const int grp = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t off = O.offset[b];
-    const float* __restrict__ fx = f ? a.x2 : a.x1;
-    const float* __restrict__ fy = f ? a.y2 : a.y1;
-    for (int base = 0; base < cnt; base += NP) {
-        const int k = base + grp;
-        bool act = k < cnt, on = false;
-        int64_t g = 0;
-        float x = 0.0f, y = 0.0f, d = 1.0f;
-        if (act) {
-            g = P.particle_offset + O.entries[off + k];
-            d = a.d[g];
-            x = fx[g];
-            y = fy[g];
-            on = (a.I0[g] > 0.0f) && (d > 0.0f) && (d <= a.d_max);
+typedef float vec4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(1))) const float glb_float;
+
+__device__ __forceinline__ bool support_box(float x, float y, float d, int W, int H, int& c0, int& c1, int& r0,
+                                            int& r1)
+{
+    const float R = 1.5f * d;
+    return support_range(x, R, W, c0, c1) && support_range(y, R, H, r0, r1);
+}
+
+// Value of lane N of each pair of lanes.
+template <int N>
+__device__ __forceinline__ float pair_lane(float v)
+{
+    return dpp<N ? 0xF5 : 0xA0>(v);
+}
+
+// One lane's part of a particle's sums over rows r0 .. r1 and columns c, c + 2, ..,
+// N of them (a particle has two lanes, c the first column of this one); columns past c1
+// count as zeros.  q points at row r0, column c.  The column factors stay in
+// registers; the two lanes form every other row's factor and exchange them.  Without
+// GUARD, reads run past c1, up to column c + 2 N - 2, and meet zero factors there (a
+// value that is not finite makes the sums NaN: the caller then takes gather_exact).
+template <int N, bool GUARD, typename SRC>
+__device__ __forceinline__ void gather_columns(SRC* q, int stride, float x, float y, float kap, int c, int c1,
+                                               int r0, int r1, int h, float4& s)
+{
+    float g0[N], g1[N], g2[N];
+    const float fx = (float)c + 0.5f;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const float dx = (fx + (float)(2 * k)) - x;
+        const float v = expneg_hw(kap * (dx * dx));
+        g0[k] = c + 2 * k <= c1 ? v : 0.0f;
+        g1[k] = g0[k] * dx;
+        g2[k] = g1[k] * dx;
+    }
+    float fy = (float)(r0 + h) + 0.5f;
+#pragma unroll 1
+    for (int r = r0; r <= r1; r += 2) {
+        const int next = r < r1 ? stride : 0;
+        float ea[N], eb[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) ea[k] = !GUARD || c + 2 * k <= c1 ? q[2 * k] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < N; ++k) eb[k] = !GUARD || c + 2 * k <= c1 ? q[next + 2 * k] : 0.0f;
+        const float dy = fy - y;
+        float u = expneg_hw(kap * (dy * dy));
+        u = r + h <= r1 ? u : 0.0f;
+        const float u1 = u * dy, u2 = u1 * dy;
+        float A0 = 0.0f, A1 = 0.0f, A2 = 0.0f, B0 = 0.0f, B1 = 0.0f, B2 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            A0 = __builtin_fmaf(ea[k], g0[k], A0);
+            A1 = __builtin_fmaf(ea[k], g1[k], A1);
+            A2 = __builtin_fmaf(ea[k], g2[k], A2);
+            B0 = __builtin_fmaf(eb[k], g0[k], B0);
+            B1 = __builtin_fmaf(eb[k], g1[k], B1);
+            B2 = __builtin_fmaf(eb[k], g2[k], B2);
         }
-        const float kap = 8.0f / (d * d);
-        const float R = 1.5f * d;
-        int c0 = 0, c1 = -1, r0 = 0, r1 = -1;
-        on = on && cover_range(x, R, W, c0, c1);
-        on = on && cover_range(y, R, H, r0, r1);
-        // in-image support inside the staged region (always, for d <= d_max)
-        on = on && c0 >= ox && c1 < ox + rw && r0 >= oy && r1 < oy + rw;
-        const float4 sums = frame_sums<0, 32, false, G, RS, GROWS_LDS>(S, grp, lane, on, x, y, kap, R, c0, c1, r0,
-                                                                     r1, W, H, region, rs, oy, ox, a.blur_w);
-        if (act && lane == 0) a.parts[(int64_t)f * n_span + g] = sums;
+        const float a0 = pair_lane<0>(u), b0 = pair_lane<1>(u);
+        s.x = __builtin_fmaf(B0, b0, __builtin_fmaf(A0, a0, s.x));
+        s.y = __builtin_fmaf(B1, b0, __builtin_fmaf(A1, a0, s.y));
+        s.z = __builtin_fmaf(B0, pair_lane<1>(u1), __builtin_fmaf(A0, pair_lane<0>(u1), s.z));
+        s.w = __builtin_fmaf(B2, b0, __builtin_fmaf(A2, a0, s.w));
+        s.w = __builtin_fmaf(B0, pair_lane<1>(u2), __builtin_fmaf(A0, pair_lane<0>(u2), s.w));
+        fy += 2.0f;
+        q += 2 * stride;
     }
 }
 
-// Per-slot gradients from the tile gather's frame sums (zeros for slots in no
-// pair's particle range and for invalid particles).
-__global__ void __launch_bounds__(256) bwd_particles(BwdArgs a, int64_t n_span)
+// The lane's sums in the same order from its own pixels alone, read from the image.
+__device__ __noinline__ float4 gather_exact(const float* src, int W, float x, float y, float kap, int c0, int c1,
+                                            int r0, int r1)
 {
-    const int64_t g0 = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * 256;
-    const int64_t g = g0 + threadIdx.x;
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 1
+    for (int cb = c0; cb <= c1; cb += 16) {
+#pragma unroll 1
+        for (int r = r0; r <= r1; r += 2) {
+            float R[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}}, u[2][3];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float dy = ((float)(r + j) + 0.5f) - y;
+                u[j][0] = r + j <= r1 ? expneg_hw(kap * (dy * dy)) : 0.0f;
+                u[j][1] = u[j][0] * dy;
+                u[j][2] = u[j][1] * dy;
+                if (r + j > r1) continue;
+#pragma unroll 1
+                for (int c = cb; c <= min(c1, cb + 15); c += 2) {
+                    const float dx = ((float)c + 0.5f) - x;
+                    const float v = expneg_hw(kap * (dx * dx)), v1 = v * dx;
+                    const float e = src[(int64_t)(r + j) * W + c];
+                    R[j][0] = __builtin_fmaf(e, v, R[j][0]);
+                    R[j][1] = __builtin_fmaf(e, v1, R[j][1]);
+                    R[j][2] = __builtin_fmaf(e, v1 * dx, R[j][2]);
+                }
+            }
+            s.x = __builtin_fmaf(R[1][0], u[1][0], __builtin_fmaf(R[0][0], u[0][0], s.x));
+            s.y = __builtin_fmaf(R[1][1], u[1][0], __builtin_fmaf(R[0][1], u[0][0], s.y));
+            s.z = __builtin_fmaf(R[1][0], u[1][1], __builtin_fmaf(R[0][0], u[0][1], s.z));
+            s.w = __builtin_fmaf(R[1][2], u[1][0], __builtin_fmaf(R[0][2], u[0][0], s.w));
+            s.w = __builtin_fmaf(R[1][0], u[1][2], __builtin_fmaf(R[0][0], u[0][2], s.w));
+        }
+    }
+    return s;
+}
+
+// Block gather.  A workgroup takes the particles of a 64 x 64 pixel block (gb x gb
+// home blocks of the frame-1 positions) of one pair, NP at a time, sorted by
+// diameter (a counting sort on LDS counters, so that a wave's patches are nearly
+// equal).  For each frame in turn, the rectangle of dL/dJ or B^T dL/dJ that the
+// particles' supports cover is staged in LDS (where it holds at most `cap` pixels,
+// else it is read from global memory) and each particle's two lanes walk down its
+// rows, every other column each.  The order of a particle's sums depends on its own
+// support alone.
+// Two lanes of contiguous work and one LDS word per pixel against eight or sixteen
+// lanes with a row-factor vector of LDS per pixel: 64 pairs of 512^2 at 0.05 ppp, d
+// about 2.5: 207 -> 116 us; 4 pairs of 2048^2 at 0.1 ppp, d to 6: 636 -> 459 us (there
+// from LDS before, one frame and 32-pixel block at a time, which also took an order of
+// the frame-2 positions, 60 us).  Of the first, 20 us are the sums and 28 us the
+// staging; the rest are 7 reads and 8 writes of particle arrays at unrelated addresses
+// and the waits between the phases, which is why small workgroups do better: NP = 256
+// with room for four per CU 116 us, NP = 512 131 us, and on the second batch, whose
+// blocks hold 410 particles (two passes of 256), 507 and 459 us.  Straight from global
+// memory (16-byte loads, one or two lanes per row) it took 167-172 us: each lane's row
+// is a cache line of its own.
+constexpr int REGION_PAD = 32;          // floats past the region that a row's last reads may reach
+
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+__device__ __forceinline__ int64_t uniform(int64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | lo);
+}
+
+template <int NP>
+__global__ void __launch_bounds__(NP)
+bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
+{
+    extern __shared__ __align__(16) float region[];
+    __shared__ float4 s_pos[NP];         // x1, y1, x2, y2
+    __shared__ float4 s_par[NP];         // z, d, I0 (0: invalid), slot in the pair (as bits)
+    __shared__ uint32_t s_hist[64];
+    __shared__ int s_box[2][4];          // per frame: first column, first row, last column, last row
+    const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int p = (int)(bid / ((int64_t)ngx * ngy));
+    const int rem = (int)(bid - (int64_t)p * ngx * ngy);
+    const int gy = rem / ngx, gx = rem - gy * ngx;
+    const int ntx = uniform(a.order.L[p].ntx), nty = uniform(a.order.L[p].nty);
+    if (gb * gx >= ntx || gb * gy >= nty) return;          // the whole workgroup, before its barriers
+    // the blocks' lists; blocks are numbered in strips of four block rows, column by
+    // column inside a strip, odd strips right to left
+    int64_t off[4];
+    int end[4], total = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int bx = gb * gx + (q & 1), by = gb * gy + (q >> 1);
+        off[q] = 0;
+        if (q < gb * gb && bx < ntx && by < nty) {
+            const int s0 = by & ~3, rows = min(4, nty - s0);
+            const int64_t b = a.order.L[p].tile_base + (int64_t)s0 * ntx +
+                              ((s0 & 4) ? ntx - 1 - bx : bx) * rows + (by - s0);
+            off[q] = uniform(a.order.offset[b] - total);
+            total += uniform((int)a.order.count[b]);
+        }
+        end[q] = total;
+    }
+    const int W = uniform(a.pairs[p].W), H = uniform(a.pairs[p].H);
+    const int64_t part0 = uniform(a.pairs[p].particle_offset), img = uniform(a.pairs[p].image_offset);
+    const int t = (int)threadIdx.x, lane = t & 63, h = t & 1;
+    for (int k0 = 0; k0 < total; k0 += NP) {
+        if (t < 64) s_hist[t] = 0u;
+        if (t < 8) s_box[t >> 2][t & 3] = (t & 2) ? -1 : 1 << 30;
+        __syncthreads();
+        const int n = min(NP, total - k0), k = k0 + t;
+        float4 pos = make_float4(0.0f, 0.0f, 0.0f, 0.0f), par = make_float4(0.0f, 1.0f, 0.0f, 0.0f);
+        int size = 0;
+        uint32_t rank = 0;
+        int box[2][4] = {{1 << 30, 1 << 30, -1, -1}, {1 << 30, 1 << 30, -1, -1}};
+        if (t < n) {
+            const int64_t o = k < end[0] ? off[0] : k < end[1] ? off[1] : k < end[2] ? off[2] : off[3];
+            const int i = a.order.entries[o + k];
+            const int64_t g = part0 + i;
+            pos = make_float4(a.x1[g], a.y1[g], a.x2[g], a.y2[g]);
+            const float d = a.d[g], I0 = a.I0[g];
+            bool valid = (I0 > 0.0f) && (d > 0.0f);
+            if (valid && !(d <= a.d_max)) {
+                atomicOr(a.status, SP_STATUS_D_ABOVE_MAX);
+                valid = false;
+            }
+            par = make_float4(a.z[g], d, valid ? I0 : 0.0f, __int_as_float(i));
+            size = valid ? (int)__builtin_fminf(3.0f * d + 1.0f, 63.0f) : 0;
+            rank = atomicAdd(&s_hist[size], 1u);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                int c0, c1, r0, r1;
+                if (valid && support_box(f ? pos.z : pos.x, f ? pos.w : pos.y, d, W, H, c0, c1, r0, r1)) {
+                    box[f][0] = c0;
+                    box[f][1] = r0;
+                    box[f][2] = c1;
+                    box[f][3] = r1;
+                }
+            }
+        }
+        if ((t & ~63) < n) {                             // the wave has particles
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+                for (int f = 0; f < 2; ++f)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const int v = __shfl_xor(box[f][m], o, 64);
+                        box[f][m] = m < 2 ? min(box[f][m], v) : max(box[f][m], v);
+                    }
+            if (lane < 8) {
+                int v = box[0][0];
+#pragma unroll
+                for (int m = 1; m < 8; ++m) v = lane == m ? box[m >> 2][m & 3] : v;
+                if (lane & 2) atomicMax(&s_box[lane >> 2][lane & 3], v);
+                else atomicMin(&s_box[lane >> 2][lane & 3], v);
+            }
+        }
+        __syncthreads();
+        // largest first: lane l scans size 63 - l
+        if ((t & ~63) < n) {
+            const uint32_t inc = wave_scan(s_hist[63 - lane]);
+            const uint32_t above = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (62 - size), (int)inc);
+            if (t < n) {
+                const int slot = (int)((size < 63 ? above : 0u) + rank);
+                s_pos[slot] = pos;
+                s_par[slot] = par;
+            }
+        }
+#pragma unroll 1
+        for (int f = 0; f < 2; ++f) {
+            const float* __restrict__ src = a.grad + img + (int64_t)f * H * W;
+            const int bc = uniform(s_box[f][0]), br = uniform(s_box[f][1]);
+            const int bw = uniform(s_box[f][2]) - bc + 1, bh = uniform(s_box[f][3]) - br + 1;
+            const int rs = (bw + 3) & ~3;                // a row's stride, whole 16-byte groups
+            const bool any = bw > 0 && bh > 0;
+            const bool staged = any && (int64_t)rs * bh <= cap;
+            if (staged) {
+                const int nq = rs >> 2;
+                const float inv = 1.0f / (float)nq;
+                const float* q0 = src + (int64_t)br * W + bc;
+                for (int m = t; m < nq * bh; m += NP) {
+                    const int r = (int)(((float)m + 0.5f) * inv);         // m / nq: both below 2^16
+                    const int c = 4 * (m - r * nq);
+                    glb_float* q = (glb_float*)q0 + ((int64_t)r * W + c);
+                    vec4u v = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if (bc + c + 3 < W) {
+                        v = *(const __attribute__((address_space(1))) vec4u*)q;
+                    } else {                             // the image's last columns
+                        if (bc + c < W) v.x = q[0];
+                        if (bc + c + 1 < W) v.y = q[1];
+                        if (bc + c + 2 < W) v.z = q[2];
+                    }
+                    reinterpret_cast<float4*>(region)[m] = make_float4(v.x, v.y, v.z, v.w);
+                }
+                if (t < REGION_PAD) region[rs * bh + t] = 0.0f;
+            }
+            __syncthreads();
+            for (int sl = t >> 1; sl < n; sl += NP / 2) {
+                pos = s_pos[sl];
+                par = s_par[sl];
+                const bool valid = par.z > 0.0f;
+                const float d = par.y, x = f ? pos.z : pos.x, y = f ? pos.w : pos.y;
+                const float kap = 8.0f / (d * d);
+                int c0 = 0, c1 = -1, r0 = 0, r1 = -1;
+                const bool on = valid && support_box(x, y, d, W, H, c0, c1, r0, r1);
+                const int w = on ? c1 - c0 + 1 : 0;
+                c0 += h;
+                float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (on) {
+                    if (staged) {
+                        lds_float* q = (lds_float*)region + (r0 - br) * rs + (c0 - bc);
+#define SP_COLS(N_) gather_columns<N_, false>(q, rs, x, y, kap, c0, c1, r0, r1, h, s)
+                        if (!__builtin_amdgcn_ballot_w64(w > 4)) SP_COLS(2);
+                        else if (!__builtin_amdgcn_ballot_w64(w > 6)) SP_COLS(3);
+                        else if (!__builtin_amdgcn_ballot_w64(w > 8)) SP_COLS(4);
+                        else if (!__builtin_amdgcn_ballot_w64(w > 10)) SP_COLS(5);
+                        else if (!__builtin_amdgcn_ballot_w64(w > 12)) SP_COLS(6);
+                        else
+#pragma unroll 1
+                            for (int c = 0; c < w; c += 16)
+                                gather_columns<8, false>(q + c, rs, x, y, kap, c0 + c, c1, r0, r1, h, s);
+#undef SP_COLS
+                    } else {
+                        glb_float* q = (glb_float*)src + (int64_t)r0 * W + c0;
+#pragma unroll 1
+                        for (int c = 0; c < w; c += 16)
+                            gather_columns<8, true>(q + c, W, x, y, kap, c0 + c, c1, r0, r1, h, s);
+                    }
+                    if (!__builtin_isfinite((s.x + s.y) + (s.z + s.w)))
+                        s = gather_exact(src, W, x, y, kap, c0, c1, r0, r1);
+                }
+                s = make_float4(s.x + dpp<0xB1>(s.x), s.y + dpp<0xB1>(s.y), s.z + dpp<0xB1>(s.z),
+                                s.w + dpp<0xB1>(s.w));
+                // the two frames' sums meet in frame 2: frame 1 leaves its S0 and Sr in place
+                // of its position, read by the particle's own two lanes alone
+                ParticleGrads o{};
+                if (valid) {
+                    const float4 f0 = f ? make_float4(pos.x, 0.0f, 0.0f, pos.y) : s;
+                    o = particle_grads(par.x, d, par.z, a.sheet_sigma, f0, s);
+                }
+                const int64_t g = part0 + __float_as_int(par.w);
+                if (f == 0) {
+                    (h ? a.g_y1 : a.g_x1)[g] = h ? o.gy1 : o.gx1;
+                    if (h == 0) *reinterpret_cast<float2*>(&s_pos[sl]) = make_float2(s.x, s.w);
+                } else {
+                    (h ? a.gy2 : a.gx2)[g] = h ? o.gy2 : o.gx2;
+                    (h ? a.g_z : a.g_d)[g] = h ? o.gz : o.gd;
+                    (h ? a.sheet : a.g_I0)[g] = h ? o.sheet : o.gI0;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Zero gradients of the slots in no pair's particle range (gaps of the packed arrays).
+__global__ void __launch_bounds__(256) bwd_gaps(BwdArgs a, int64_t n_span)
+{
+    const int64_t g0 = (int64_t)blockIdx.x * 256, g = g0 + threadIdx.x;
     if (g >= n_span) return;
     const int p = find_pair_from(a.pairs, a.n_pairs, g0, g);
-    const synthpix_pair P = a.pairs[p];
-    const int64_t i = g - P.particle_offset;
-    ParticleGrads o{};
-    const bool in_pair = i >= 0 && i < P.n_max;
-    if (in_pair) {
-        const float z = a.z[g], d = a.d[g], I0 = a.I0[g];
-        bool valid = (I0 > 0.0f) && (d > 0.0f);
-        if (valid && !(d <= a.d_max)) {
-            atomicOr(a.status, SP_STATUS_D_ABOVE_MAX);
-            valid = false;
-        }
-        if (valid) o = particle_grads(z, d, I0, a.sheet_sigma, a.parts[g], a.parts[n_span + g]);
-    }
-    a.g_x1[g] = o.gx1;
-    a.g_y1[g] = o.gy1;
-    a.g_z[g] = o.gz;
-    a.g_d[g] = o.gd;
-    a.g_I0[g] = o.gI0;
-    if (in_pair) {
-        a.gx2[g] = o.gx2;
-        a.gy2[g] = o.gy2;
-        a.sheet[g] = o.sheet;
-    }
+    const int64_t i = g - a.pairs[p].particle_offset;
+    if (i >= 0 && i < a.pairs[p].n_max) return;
+    a.g_x1[g] = 0.0f;
+    a.g_y1[g] = 0.0f;
+    a.g_z[g] = 0.0f;
+    a.g_d[g] = 0.0f;
+    a.g_I0[g] = 0.0f;
 }
 
 // One input column x of a strip of the per-pixel pass: its SH + 2b rows from
@@ -1335,6 +1533,19 @@ static unsigned gather_blocks(int64_t n_span, int G)
     return (unsigned)((n_span + 256 / G - 1) / (256 / G));
 }
 
+// Whether the block gather serves a batch: its LDS (the region and up to 17 KB of
+// particles) fits in 64 KB, and there are blocks for most CUs with enough particles
+// each.  Against the particle-major gather: 2 / 4 / 8 pairs of 512^2 at 0.05 ppp (128 /
+// 256 / 512 blocks) 16.7 / 17.3 / 21 us and 14.3 / 22 / 33 us; a block costs about
+// 25 ns however few particles it holds: 64 pairs at 0.005 / 0.02 / 0.03 ppp (20 / 82 /
+// 123 particles a block) 105 / 109 / 114 us and 49 / 99 / 132 us, 4 pairs of 2048^2
+// with d to 6 at 0.01 / 0.02 ppp (41 / 82) 167 / 174 us and 111 / 192 us.
+static bool block_gather_pays(const BwdArgs& a, int64_t n_span)
+{
+    return block_region_side(a.d_max, block_group_log(a.order.log_block)) <= 108 &&
+           4 * a.block_groups >= 3 * (int64_t)device_cu_count() && n_span >= 80 * a.block_groups;
+}
+
 void launch_advect_adjoint(const BwdArgs& a, const synthpix_advect_params& ap, unsigned blocks, hipStream_t s)
 {
     const int S = ap.substeps;
@@ -1360,12 +1571,11 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
                            a.g_sheet, a.n_pairs, a.g_sheet_total, a.pairs, a.grid.wg_base);
     }
     if (a.mse && !a.eblur) return hipErrorInvalidValue;
-    const bool tile = a.order2.entries && a.parts;
     // the blur's adjoint once per pixel (the gather then runs on the unblurred
-    // footprints of B^T dL/dJ): for wide blurs and the tile gather, and always
+    // footprints of B^T dL/dJ): for wide blurs, and always
     // for the loss-fused form, whose pass also forms dL/dJ (and the loss, which
     // the images define even when no pair holds a particle)
-    const bool per_pixel = a.eblur && (a.mse || (blur >= 1 && (tile || blur >= 2)));
+    const bool per_pixel = a.eblur && (a.mse || blur >= 2);
     if (per_pixel && (n_span > 0 || (a.mse && a.loss))) {
         TimedScope ts("bwd_blur", s);
         const int64_t nb = blur_grad_blocks(a.n_pairs, a.max_w, a.max_h, a.mse);
@@ -1393,30 +1603,29 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
         }
         BwdArgs b = a;
         if (per_pixel) b.grad = a.eblur;
-        if (tile) {
+        if ((per_pixel || blur == 0) && block_gather_pays(a, n_span)) {
             TimedScope ts("bwd_gather", s);
-            const int hb = tile_halo(a.d_max);
-            const int rw = (1 << a.order.log_block) + 2 * hb;
-            const int64_t items = 2 * a.order.blocks;
-            if (items > 0xFFFFFFFFll) return hipErrorInvalidValue;
-            // the region's row stride rounded up to one of the compiled ones
-            const int rs = rw <= 40 ? 40 : rw <= 48 ? 48 : rw <= 56 ? 56 : rw <= 64 ? 64 : rw;
-            const size_t lds = sizeof(float) * (size_t)rs * rw;
-#define SP_TILE(RS_) hipLaunchKernelGGL(bwd_tile_gather<RS_>, dim3((unsigned)items), dim3(256), lds, s, b, n_span, \
-                                        a.order.log_block, hb)
-            switch (rs) {
-            case 40: SP_TILE(40); break;
-            case 48: SP_TILE(48); break;
-            case 56: SP_TILE(56); break;
-            case 64: SP_TILE(64); break;
-            default: SP_TILE(0); break;
-            }
-#undef SP_TILE
-            hipLaunchKernelGGL(bwd_particles, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
+            const int gl = block_group_log(a.order.log_block), gb = 1 << (gl - a.order.log_block);
+            const int side = block_region_side(a.d_max, gl), cap = side * side;
+            const int ngx = (a.max_w + (1 << gl) - 1) >> gl, ngy = (a.max_h + (1 << gl) - 1) >> gl;
+            const int64_t nb = (int64_t)a.n_pairs * ngx * ngy;
+            if (nb > 0xFFFFFFFFll) return hipErrorInvalidValue;
+            const size_t lds = sizeof(float) * ((size_t)cap + REGION_PAD);
+            // one pass where a block's particles fit (both sides measured above)
+            if (n_span > 256 * a.block_groups)
+                hipLaunchKernelGGL(bwd_gather_blocks<512>, dim3((unsigned)nb), dim3(512), lds, s, b, gb, ngx, ngy, cap);
+            else
+                hipLaunchKernelGGL(bwd_gather_blocks<256>, dim3((unsigned)nb), dim3(256), lds, s, b, gb, ngx, ngy, cap);
+            if (a.gaps) hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
         } else if (per_pixel) {
             TimedScope ts("bwd_gather", s);
-            if ((int)(3.0f * a.d_max) + 4 <= 32) hipLaunchKernelGGL((bwd_gather<0, 32, 8>), dim3(gather_blocks(n_span, 8)), dim3(256), 0, s, b, n_span);
-            else hipLaunchKernelGGL((bwd_gather<0, 64, 16>), dim3(gather_blocks(n_span, 16)), dim3(256), 0, s, b, n_span);
+            // sixteen lanes per particle for wide blurs, whose patches are wide as a rule
+#define SP_GATHER0(BT_, G_) \
+    hipLaunchKernelGGL((bwd_gather<0, BT_, G_>), dim3(gather_blocks(n_span, G_)), dim3(256), 0, s, b, n_span)
+            if ((int)(3.0f * a.d_max) + 4 > 32) SP_GATHER0(64, 16);
+            else if (blur >= 2) SP_GATHER0(32, 16);
+            else SP_GATHER0(32, 8);
+#undef SP_GATHER0
         } else {
             TimedScope ts("bwd_gather", s);
             // slots needed: floor(3 d_max) + 4 covered pixels + 4 b padding

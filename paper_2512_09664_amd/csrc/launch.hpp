@@ -266,8 +266,6 @@ struct GridAccum {
 
 struct BwdArgs {
     AdvectOrder order;           // home-block order of the frame-1 positions
-    AdvectOrder order2;          // the same for the frame-2 positions (tile gather only)
-    float4* parts;               // per-frame particle sums (S0, Sx, Sy, Sr), 2 x n_span (tile gather only)
     const synthpix_pair* pairs;
     int n_pairs;
     const float* flow;
@@ -293,8 +291,8 @@ struct BwdArgs {
     double* loss_part;
     double* loss;
     int64_t loss_n;
-    float* eblur;                // B^T dL/dJ (workspace, the images' layout): blur radius >= 2, the
-                                 // tile gather, or the mse form
+    float* eblur;                // B^T dL/dJ (workspace, the images' layout): blur radius >= 2 or
+                                 // the mse form
     float* g_x1;
     float* g_y1;
     float* g_z;
@@ -311,6 +309,8 @@ struct BwdArgs {
     GridAccum grid;              // flow-gradient partials (workspace)
     uint32_t* scale;             // fixed-point scale block: max |dL/dx2|, Lipschitz bound, exponent, state
     uint32_t* status;
+    int64_t block_groups;        // blocks of the block gather over all pairs
+    bool gaps;                   // slots of the packed arrays lie in no pair's particle range
     float sheet_sigma;
     float d_max;
     float blur_w[7];
@@ -332,21 +332,16 @@ constexpr int MSE_BLOCKS = 1024;
 hipError_t launch_mse_grad(const float* J, const float* T, int64_t n, float scale, float* grad, double* loss,
                            double* part, hipStream_t s);
 
-// Halo (pixels) of the tile-major adjoint gather's staged region for a diameter
-// bound: every in-image pixel of a footprint whose centre lies in a home block
-// is within this distance of the block.
-inline int tile_halo(float d_max) { return (int)std::ceil(1.5f * d_max) + 2; }
+// Blocks of the block gather: 64 x 64 pixels, one or 2 x 2 home blocks.
+inline int block_group_log(int log_block) { return std::max(log_block, 6); }
 
-// Whether the tile-major gather serves a batch: a blur of radius >= 2 (whose
-// adjoint then runs once per pixel; narrower blurs fold into the particle-major
-// gather's tables, which costs less than staging and the second order), factor
-// tables that hold the support (3 d_max + 4 slots <= 32) and a staged region of
-// a home block of 2^log_block pixels within 64 KB of LDS.
-inline bool tile_gather_fits(float d_max, int log_block, int blur_radius)
+// Side of the square whose pixels the block gather can stage per workgroup: a block
+// and its particles' supports, with 6 pixels for the spread of the frame-2 positions
+// and for whole 16-byte groups (smaller squares leave frame 2 to global memory, larger
+// ones fewer workgroups per CU: four up to d_max = 5).
+inline int block_region_side(float d_max, int group_log)
 {
-    if (blur_radius < 2 || !((int)(3.0f * d_max) + 4 <= 32)) return false;
-    const int rw = (1 << log_block) + 2 * tile_halo(d_max);
-    return (size_t)rw * rw * sizeof(float) <= 64 * 1024;
+    return (1 << group_log) + 2 * ((int)std::ceil(1.5f * d_max) + 1) + 6;
 }
 
 // Peak-rate probes (store, copy, fma, trans, mul64, store_nt = kinds 0..5); *work gets

@@ -839,3 +839,66 @@ def test_backward_mse_with_gaps_matches_packed(blur):
         assert np.array_equal(gf[o:o + fl[p]], rf[ro:ro + fl[p]]), p
         o += fl[p]
         ro += fl[p]
+
+
+@pytest.mark.parametrize("n,d_range,d_max,blur,amp", [
+    (330, (1.0, 4.5), 5.0, 2, 1.2), (330, (0.3, 1.2), 2.0, 3, 1.2), (330, (6.0, 10.0), 10.0, 2, 1.2),
+    (330, (1.0, 6.0), 12.0, 0, 1.2), (700, (1.0, 6.0), 6.0, 2, 1.2), (330, (1.0, 6.0), 6.0, 2, 40.0)])
+def test_block_gather(n, d_range, d_max, blur, amp):
+    """Batches large enough for the block gather (one pass per 64 x 64 block and two;
+    a frame-2 region that fits in LDS and, with displacements of tens of pixels, one
+    that does not) against each pair by itself, which takes the particle-major
+    gather.  The order of the binary32 sums differs: within the tolerance of the
+    oracle comparison.  Copies of a pair agree bit for bit."""
+    sizes, grids = [(70, 97), (33, 130), (9, 3), (128, 64)], [(18, 25), (9, 33), (4, 2), (32, 16)]
+    P, flows, _, _, _ = _batch(sizes, grids, n, 900 + blur, d_range=d_range)
+    flows = [(f * np.float32(amp / 1.2)).astype(np.float32) for f in flows]
+    reps = 20                                   # 10 blocks: 200 in all
+    batch = gu.batch_for(sizes * reps, grids * reps, [n] * 4 * reps)
+    dev = {k: gu.to_dev(np.concatenate(v * reps)) for k, v in P.items()}
+    flow = gu.to_dev(np.concatenate([f.reshape(-1) for f in flows] * reps))
+    rp = sp.render_params(0.5, d_max, blur, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+    rng = np.random.default_rng(n + blur)
+    gJ = [rng.standard_normal(2 * H * W).astype(np.float32) for H, W in sizes]
+    g_all = np.zeros(batch.n_pixels, np.float32)
+    for p in range(4 * reps):
+        o = batch.host[p].image_offset
+        g_all[o:o + gJ[p % 4].size] = gJ[p % 4]
+    args = [dev[k] for k in ("x", "y", "z", "d", "I0")]
+    got = {k: gu.to_np(v) for k, v in sp.render_pair_backward(batch, flow, *args, rp, gu.to_dev(g_all)).items()}
+    for q, (size, grid) in enumerate(zip(sizes, grids)):
+        one = gu.batch_for([size], [grid], [n])
+        a1 = [gu.to_dev(P[k][q]) for k in ("x", "y", "z", "d", "I0")]
+        ref = sp.render_pair_backward(one, gu.to_dev(flows[q].reshape(-1)), *a1, rp, gu.to_dev(gJ[q]))
+        ref = {k: gu.to_np(v) for k, v in ref.items()}
+        for k in ("x1", "y1", "z", "d", "I0"):
+            first = got[k][batch.host[q].particle_offset:][:n]
+            _close(first, ref[k], f"pair {q} {k}", tol=TOL)
+            for r in range(1, reps):
+                assert np.array_equal(got[k][batch.host[4 * r + q].particle_offset:][:n], first), (q, r, k)
+        _close(got["sheet"][q:q + 1], ref["sheet"], f"pair {q} sheet", tol=TOL)
+
+
+def test_block_gather_not_finite():
+    """A pixel that is not a number reaches the particles whose support holds it, and
+    no other; every other gradient keeps its bits."""
+    n, sizes = 330, [(64, 64)] * 200
+    P, flows, batch, dev, flow = _batch(sizes, [(4, 4)] * 200, n, 77, zero_frac=0.0)
+    rp = sp.render_params(0.5, 5.0, 0, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+    g, g_dev = _grad_images(batch, 3)
+    args = [dev[k] for k in ("x", "y", "z", "d", "I0")]
+    x2, y2 = sp.advect(batch, flow, rp.advect, dev["x"], dev["y"])
+    a = sp.render_pair_backward(batch, flow, *args, rp, g_dev, x2=x2, y2=y2)
+    r, c = 30, 41
+    g_dev[batch.host[7].image_offset + r * 64 + c] = float("nan")
+    b = sp.render_pair_backward(batch, flow, *args, rp, g_dev, x2=x2, y2=y2)
+    o = batch.host[7].particle_offset
+    x, y, d = (P[k][7].astype(np.float32) for k in ("x", "y", "d"))
+    R = np.float32(1.5) * d
+    hit = np.zeros(200 * n, bool)
+    hit[o:o + n] = (np.abs(np.float32(c + 0.5) - x) <= R) & (np.abs(np.float32(r + 0.5) - y) <= R)
+    assert hit.any() and not hit[o:o + n].all()
+    for k in ("z", "d", "I0"):
+        av, bv = gu.to_np(a[k]), gu.to_np(b[k])
+        assert np.isnan(bv[hit]).all(), k
+        assert np.array_equal(bv[~hit], av[~hit]), k
