@@ -818,22 +818,16 @@ struct Sample {
 };
 
 // Value bit-identical to sample_flow, plus Jacobian and node weights.
-__device__ __forceinline__ Sample sample_jac(const FlowView& fv, float px, float py)
+__device__ __forceinline__ Sample sample_jac(const FlowView& fv, const FlowWin& fw, lds_vec2* lds, float px, float py)
 {
     Sample o;
     const float gxr = px * fv.sx - 0.5f;
     const float gyr = py * fv.sy - 0.5f;
-    const float gx = __builtin_fminf(__builtin_fmaxf(gxr, 0.0f), (float)(fv.Gw - 1));
-    const float gy = __builtin_fminf(__builtin_fmaxf(gyr, 0.0f), (float)(fv.Gh - 1));
-    int j0 = (int)__builtin_floorf(gx);
-    int i0 = (int)__builtin_floorf(gy);
-    j0 = j0 > fv.Gw - 2 ? fv.Gw - 2 : j0;
-    i0 = i0 > fv.Gh - 2 ? fv.Gh - 2 : i0;
-    const float fx = gx - (float)j0;
-    const float fy = gy - (float)i0;
-    const float2* row0 = fv.F + (size_t)i0 * fv.Gw + j0;
-    const float4 r0 = load_pair(row0);
-    const float4 r1 = load_pair(row0 + fv.Gw);
+    const FlowCell cell = flow_cell(fv, px, py);
+    const int i0 = cell.i0, j0 = cell.j0;
+    const float fx = cell.fx, fy = cell.fy;
+    float4 r0, r1;
+    cell_nodes(fv, cell, in_window(cell, fw), fw, lds, r0, r1);
     const float2 A = make_float2(r0.x, r0.y), Bn = make_float2(r0.z, r0.w);
     const float2 C = make_float2(r1.x, r1.y), E = make_float2(r1.z, r1.w);
     {
@@ -879,6 +873,8 @@ struct NodeRun {
     int wi0, wj0, wh, ww;
     GridRecord* ovf;      // the workgroup's overflow records (global memory)
     unsigned* n_ovf;      // their count (LDS)
+    // grid cells this lane has added to
+    int ti0 = 1 << 30, tj0 = 1 << 30, ti1 = -1, tj1 = -1;
 
     __device__ void add_node(int ni, int nj, int c, unsigned long long q)
     {
@@ -894,6 +890,10 @@ struct NodeRun {
     __device__ void flush(const CellRun& r)
     {
         if (r.i0 < 0) return;
+        ti0 = min(ti0, r.i0);
+        ti1 = max(ti1, r.i0);
+        tj0 = min(tj0, r.j0);
+        tj1 = max(tj1, r.j0);
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
 #pragma unroll
@@ -927,38 +927,40 @@ struct NodeRun {
     }
 };
 
-// Back-propagate one sample with upstream (ku, kv); returns J^T k in (bx, by).
-__device__ __forceinline__ void stage_back(const FlowView& fv, NodeRun& run, float px, float py, float ku, float kv,
-                                           float& bx, float& by)
+// Back-propagate one sample with upstream (ku, kv); J^T k in (bx, by).
+__device__ __forceinline__ void sample_back(NodeRun& run, const Sample& s, float ku, float kv, float& bx, float& by)
 {
-    const Sample s = sample_jac(fv, px, py);
     run.add(s, ku, kv);
     bx = s.jx.x * ku + s.jx.y * kv;
     by = s.jy.x * ku + s.jy.y * kv;
 }
 
-__device__ __forceinline__ void substep_adjoint(const FlowView& fv, NodeRun& run, float px, float py, float h,
-                                                float hh, int integrator, float& gpx, float& gpy)
+// One substep's adjoint from its start (px, py): (gpx, gpy) becomes the gradient with
+// respect to the start.  RK4 keeps the later three stages' samples from the forward
+// walk to the sweep; the first is taken again, as all four leave no registers for
+// four waves per SIMD (4 pairs of 2048^2, 8 substeps: all four 431 us, three 327,
+// two 334, none 346; 64 of 512^2, 4 substeps: 101 / 102 / 105 / 110).
+__device__ __forceinline__ void substep_adjoint(const FlowView& fv, const FlowWin& fw, lds_vec2* lds, NodeRun& run,
+                                                float px, float py, float h, float hh, int integrator, float& gpx,
+                                                float& gpy)
 {
     float bx, by;
     if (integrator == SP_EULER) {
-        stage_back(fv, run, px, py, h * gpx, h * gpy, bx, by);
+        sample_back(run, sample_jac(fv, fw, lds, px, py), h * gpx, h * gpy, bx, by);
         gpx += bx;
         gpy += by;
         return;
     }
-    const float2 k1 = sample_flow(fv, px, py);
-    const float p2x = __builtin_fmaf(hh, k1.x, px), p2y = __builtin_fmaf(hh, k1.y, py);
-    const float2 k2 = sample_flow(fv, p2x, p2y);
-    const float p3x = __builtin_fmaf(hh, k2.x, px), p3y = __builtin_fmaf(hh, k2.y, py);
-    const float2 k3 = sample_flow(fv, p3x, p3y);
-    const float p4x = __builtin_fmaf(h, k3.x, px), p4y = __builtin_fmaf(h, k3.y, py);
+    const float2 k1 = sample_flow(fv, fw, lds, px, py);
+    const Sample s2 = sample_jac(fv, fw, lds, __builtin_fmaf(hh, k1.x, px), __builtin_fmaf(hh, k1.y, py));
+    const Sample s3 = sample_jac(fv, fw, lds, __builtin_fmaf(hh, s2.val.x, px), __builtin_fmaf(hh, s2.val.y, py));
+    const Sample s4 = sample_jac(fv, fw, lds, __builtin_fmaf(h, s3.val.x, px), __builtin_fmaf(h, s3.val.y, py));
     const float c = h / 6.0f;
     float b4x, b4y, b3x, b3y, b2x, b2y, b1x, b1y;
-    stage_back(fv, run, p4x, p4y, c * gpx, c * gpy, b4x, b4y);
-    stage_back(fv, run, p3x, p3y, 2.0f * c * gpx + h * b4x, 2.0f * c * gpy + h * b4y, b3x, b3y);
-    stage_back(fv, run, p2x, p2y, 2.0f * c * gpx + hh * b3x, 2.0f * c * gpy + hh * b3y, b2x, b2y);
-    stage_back(fv, run, px, py, c * gpx + hh * b2x, c * gpy + hh * b2y, b1x, b1y);
+    sample_back(run, s4, c * gpx, c * gpy, b4x, b4y);
+    sample_back(run, s3, 2.0f * c * gpx + h * b4x, 2.0f * c * gpy + h * b4y, b3x, b3y);
+    sample_back(run, s2, 2.0f * c * gpx + hh * b3x, 2.0f * c * gpy + hh * b3y, b2x, b2y);
+    sample_back(run, sample_jac(fv, fw, lds, px, py), c * gpx + hh * b2x, c * gpy + hh * b2y, b1x, b1y);
     gpx += ((b1x + b2x) + b3x) + b4x;
     gpy += ((b1y + b2y) + b3y) + b4y;
 }
@@ -971,12 +973,22 @@ enum { SC_NONE = 0, SC_VALID = 1, SC_NONFINITE = 2 };
 // g_y1) and node sums into the fixed-point grid.  CK checkpoints of the
 // trajectory are kept, one every L = ceil(substeps / CK) substeps; each segment
 // is recomputed into SK >= L slots during the sweep.
+// The grid nodes around the workgroup's particles are copied to LDS, so that the
+// samples of neighbouring lanes do not go through the vector cache line by line, and
+// the box of the nodes to write out follows from the cells added to instead of a
+// search of the window.  4 pairs of 2048^2 at 0.1 ppp, RK4 x 8: 386 -> 327 us (the
+// copy 353, the box 346, the kept samples 327); 64 of 512^2 at 0.05 ppp, RK4 x 4: 112 ->
+// 102 us.  Without the node sums it would take 281 and 89 us: what remains is VALU work
+// and the particle arrays at unrelated addresses.
+constexpr int ADJ_FLOW_NODES = 896;     // LDS copy of grid nodes: 7 KB, with which four workgroups still share a CU
+constexpr int ADJ_FLOW_MARGIN = 4;      // cells around the particles' starting ones
 
 template <int CK, int SK>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CK <= 8 ? 4 : 3)))
 bwd_advect(BwdArgs a, synthpix_advect_params ap)
 {
-    __shared__ unsigned long long win[2 * WIN_NODES];
+    __shared__ __align__(16) unsigned long long win[2 * WIN_NODES];
+    __shared__ vec2f s_flow[ADJ_FLOW_NODES];
     __shared__ int s_box[4][4];
     __shared__ unsigned s_novf;
     // workgroup -> (pair, 256-particle chunk of the pair's ordered particles)
@@ -1059,7 +1071,25 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
     run.ovf = a.grid.ovf + wg * GRID_OVF_CAP;
     run.n_ovf = &s_novf;
     if (use_win) {
-        for (int k = threadIdx.x; k < 2 * wh * ww; k += 256) win[k] = 0ull;
+        for (int k = threadIdx.x; k < wh * ww; k += 256) reinterpret_cast<uint4*>(win)[k] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    // the grid nodes around the starting cells, for the samples
+    FlowWin fw = NO_WIN;
+    lds_vec2* lds = (lds_vec2*)s_flow;
+    if (bi1 >= bi0) {
+        const int i0 = __builtin_amdgcn_readfirstlane(max(bi0 - ADJ_FLOW_MARGIN, 0));
+        const int j0 = __builtin_amdgcn_readfirstlane(max(bj0 - ADJ_FLOW_MARGIN, 0));
+        const int nh = __builtin_amdgcn_readfirstlane(min(bi1 + ADJ_FLOW_MARGIN, P.Gh - 1)) - i0 + 1;
+        const int nw = __builtin_amdgcn_readfirstlane(min(bj1 + ADJ_FLOW_MARGIN, P.Gw - 1)) - j0 + 1;
+        if ((int64_t)nh * nw <= ADJ_FLOW_NODES) {
+            const vec2f* F = reinterpret_cast<const vec2f*>(fv.F) + (int64_t)i0 * P.Gw + j0;
+            const float inv = 1.0f / (float)nw;
+            for (int k = threadIdx.x; k < nh * nw; k += 256) {
+                const int row = (int)(((float)k + 0.5f) * inv);          // k / nw: both below 2^10
+                s_flow[k] = F[(int64_t)row * P.Gw + (k - row * nw)];
+            }
+            fw = FlowWin{i0, j0, nh, nw};
+        }
     }
     __syncthreads();
 
@@ -1076,13 +1106,13 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
                 cpx[s / L] = qx;
                 cpy[s / L] = qy;
             }
-            if (s + 1 < S) substep(fv, qx, qy, h, hh, ap.integrator);
+            if (s + 1 < S) substep(fv, fw, lds, qx, qy, h, hh, ap.integrator);
         }
         if constexpr (SK == 1) {
             // S <= CK: every substep's start is a checkpoint, the sweep walks them
             // (no segment slots, whose runtime indexing would live in scratch)
             for (int seg = nseg - 1; seg >= 0; --seg)
-                substep_adjoint(fv, run, cpx[seg], cpy[seg], h, hh, ap.integrator, gpx, gpy);
+                substep_adjoint(fv, fw, lds, run, cpx[seg], cpy[seg], h, hh, ap.integrator, gpx, gpy);
         } else {
             float spx[SK], spy[SK];
             for (int seg = nseg - 1; seg >= 0; --seg) {
@@ -1092,12 +1122,12 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
                 spy[0] = cpy[seg];
                 for (int k = 1; k < len; ++k) {
                     float tx = spx[k - 1], ty = spy[k - 1];
-                    substep(fv, tx, ty, h, hh, ap.integrator);
+                    substep(fv, fw, lds, tx, ty, h, hh, ap.integrator);
                     spx[k] = tx;
                     spy[k] = ty;
                 }
                 for (int k = len - 1; k >= 0; --k)
-                    substep_adjoint(fv, run, spx[k], spy[k], h, hh, ap.integrator, gpx, gpy);
+                    substep_adjoint(fv, fw, lds, run, spx[k], spy[k], h, hh, ap.integrator, gpx, gpy);
             }
         }
         run.finish();
@@ -1106,20 +1136,9 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
     }
     __syncthreads();
 
-    // the window's nonzero box, then its sums into this workgroup's partial
-    // (rows of the box, (u, v) interleaved) and the header
-    int ti0 = 1 << 30, tj0 = 1 << 30, ti1 = -1, tj1 = -1;
-    if (use_win) {
-        for (int k = threadIdx.x; k < wh * ww; k += 256) {
-            if (win[2 * k] != 0ull || win[2 * k + 1] != 0ull) {
-                const int li = k / ww, lj = k - li * ww;
-                ti0 = min(ti0, li);
-                ti1 = max(ti1, li);
-                tj0 = min(tj0, lj);
-                tj1 = max(tj1, lj);
-            }
-        }
-    }
+    // the window nodes of the cells added to, then their sums into this workgroup's
+    // partial (rows of the box, (u, v) interleaved) and the header
+    int ti0 = run.ti0, tj0 = run.tj0, ti1 = run.ti1, tj1 = run.tj1;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         ti0 = min(ti0, __shfl_xor(ti0, o, 64));
@@ -1135,14 +1154,16 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
         s_box[threadIdx.x >> 6][3] = tj1;
     }
     __syncthreads();
-    ti0 = min(min(s_box[0][0], s_box[1][0]), min(s_box[2][0], s_box[3][0]));
-    tj0 = min(min(s_box[0][1], s_box[1][1]), min(s_box[2][1], s_box[3][1]));
-    ti1 = max(max(s_box[0][2], s_box[1][2]), max(s_box[2][2], s_box[3][2]));
-    tj1 = max(max(s_box[0][3], s_box[1][3]), max(s_box[2][3], s_box[3][3]));
-    const int th = ti1 >= ti0 ? ti1 - ti0 + 1 : 0, tw = ti1 >= ti0 ? tj1 - tj0 + 1 : 0;
+    ti0 = max(min(min(s_box[0][0], s_box[1][0]), min(s_box[2][0], s_box[3][0])) - run.wi0, 0);
+    tj0 = max(min(min(s_box[0][1], s_box[1][1]), min(s_box[2][1], s_box[3][1])) - run.wj0, 0);
+    ti1 = min(max(max(s_box[0][2], s_box[1][2]), max(s_box[2][2], s_box[3][2])) + 1 - run.wi0, run.wh - 1);
+    tj1 = min(max(max(s_box[0][3], s_box[1][3]), max(s_box[2][3], s_box[3][3])) + 1 - run.wj0, ww - 1);
+    const bool some = ti1 >= ti0 && tj1 >= tj0;
+    const int th = some ? ti1 - ti0 + 1 : 0, tw = some ? tj1 - tj0 + 1 : 0;
     unsigned long long* part = a.grid.part + wg * (2 * WIN_NODES);
+    const float inv_tw = 1.0f / (float)tw;
     for (int k = threadIdx.x; k < th * tw; k += 256) {
-        const int r = k / tw, c = k - r * tw;
+        const int r = (int)(((float)k + 0.5f) * inv_tw), c = k - r * tw;     // k / tw: both below 2^12
         const int src = (ti0 + r) * ww + (tj0 + c);
         part[2 * k] = win[2 * src];
         part[2 * k + 1] = win[2 * src + 1];

@@ -78,12 +78,12 @@ __device__ __forceinline__ unsigned window_node(const FlowCell& c, const FlowWin
     return __umul24((unsigned)(c.i0 - win.wi0), (unsigned)win.ww) + (unsigned)(c.j0 - win.wj0);
 }
 
-// (u, v) of a cell: its two nodes of one grid row are adjacent, one 16-byte load
-// per row, from the LDS window when the cell lies inside it.
-__device__ __forceinline__ float2 sample_cell(const FlowView& fv, const FlowCell& c, bool inside, const FlowWin& win,
-                                              lds_vec2* lds)
+// The (u, v) nodes of a cell, (left, right) of its upper and of its lower grid row:
+// adjacent, one 16-byte load per row, or from the LDS window when the cell lies
+// inside it.
+__device__ __forceinline__ void cell_nodes(const FlowView& fv, const FlowCell& c, bool inside, const FlowWin& win,
+                                           lds_vec2* lds, float4& r0, float4& r1)
 {
-    float4 r0, r1;
     if (inside) {
         lds_vec2* w0 = lds + window_node(c, win);
         lds_vec2* w1 = w0 + win.ww;
@@ -96,12 +96,27 @@ __device__ __forceinline__ float2 sample_cell(const FlowView& fv, const FlowCell
         r0 = load_pair(fv.F + k);
         r1 = load_pair(fv.F + k + fv.Gw);
     }
+}
+
+// (u, v) in a cell.
+__device__ __forceinline__ float2 sample_cell(const FlowView& fv, const FlowCell& c, bool inside, const FlowWin& win,
+                                              lds_vec2* lds)
+{
+    float4 r0, r1;
+    cell_nodes(fv, c, inside, win, lds, r0, r1);
     return make_float2(bilinear(r0.x, r0.z, r1.x, r1.z, c.fx, c.fy), bilinear(r0.y, r0.w, r1.y, r1.w, c.fx, c.fy));
 }
 
 __device__ __forceinline__ float2 sample_flow(const FlowView& fv, float px, float py)
 {
     return sample_cell(fv, flow_cell(fv, px, py), false, NO_WIN, nullptr);
+}
+
+__device__ __forceinline__ float2 sample_flow(const FlowView& fv, const FlowWin& win, lds_vec2* lds, float px,
+                                              float py)
+{
+    const FlowCell c = flow_cell(fv, px, py);
+    return sample_cell(fv, c, in_window(c, win), win, lds);
 }
 
 __device__ __forceinline__ FlowView flow_view(const synthpix_pair& P, const float* flow)
@@ -125,18 +140,19 @@ __device__ __forceinline__ float rk4_mean(float k1, float k2, float k3, float k4
 // One substep of the frozen-field integrator, the same operations in the same
 // order as the advection kernel: Euler p = fma(h, u, p); RK4 stages at
 // fma(h/2, k, p) and fma(h, k3, p), update fma(h, (((k1 + 2 k2) + 2 k3) + k4) / 6, p).
-__device__ __forceinline__ void substep(const FlowView& fv, float& px, float& py, float h, float hh, int integrator)
+__device__ __forceinline__ void substep(const FlowView& fv, const FlowWin& win, lds_vec2* lds, float& px, float& py,
+                                        float h, float hh, int integrator)
 {
     if (integrator == SP_EULER) {
-        const float2 u = sample_flow(fv, px, py);
+        const float2 u = sample_flow(fv, win, lds, px, py);
         px = __builtin_fmaf(h, u.x, px);
         py = __builtin_fmaf(h, u.y, py);
         return;
     }
-    const float2 k1 = sample_flow(fv, px, py);
-    const float2 k2 = sample_flow(fv, __builtin_fmaf(hh, k1.x, px), __builtin_fmaf(hh, k1.y, py));
-    const float2 k3 = sample_flow(fv, __builtin_fmaf(hh, k2.x, px), __builtin_fmaf(hh, k2.y, py));
-    const float2 k4 = sample_flow(fv, __builtin_fmaf(h, k3.x, px), __builtin_fmaf(h, k3.y, py));
+    const float2 k1 = sample_flow(fv, win, lds, px, py);
+    const float2 k2 = sample_flow(fv, win, lds, __builtin_fmaf(hh, k1.x, px), __builtin_fmaf(hh, k1.y, py));
+    const float2 k3 = sample_flow(fv, win, lds, __builtin_fmaf(hh, k2.x, px), __builtin_fmaf(hh, k2.y, py));
+    const float2 k4 = sample_flow(fv, win, lds, __builtin_fmaf(h, k3.x, px), __builtin_fmaf(h, k3.y, py));
     px = __builtin_fmaf(h, rk4_mean(k1.x, k2.x, k3.x, k4.x), px);
     py = __builtin_fmaf(h, rk4_mean(k1.y, k2.y, k3.y, k4.y), py);
 }

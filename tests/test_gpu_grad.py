@@ -902,3 +902,35 @@ def test_block_gather_not_finite():
         av, bv = gu.to_np(a[k]), gu.to_np(b[k])
         assert np.isnan(bv[hit]).all(), k
         assert np.array_equal(bv[~hit], av[~hit]), k
+
+
+@pytest.mark.parametrize("shift", [0.0, 24.0])
+def test_flow_adjoint_node_copy(shift):
+    """The flow adjoint samples grid nodes around its particles from a copy: particles
+    whose nodes fit in it, without and with trajectories that leave it, against the
+    same particles joined by faint ones (1e-20 of the intensity) spread so widely that
+    no copy is taken.  Position gradients do not depend on the copy, bit for bit; the
+    flow's differ by the faint particles and the fixed-point scale alone."""
+    rng = np.random.default_rng(5)
+    H = W = 128
+    n, m = 100, 60
+    q = {"x": rng.uniform(40, 58, n), "y": rng.uniform(40, 58, n)}
+    f = {"x": rng.uniform(14, 86, m), "y": rng.uniform(14, 86, m)}
+    f["x"][:2], f["y"][:2] = (14, 86), (14, 86)
+    for s, k, i0 in ((q, n, 1.0), (f, m, 1e-20)):
+        s.update(z=rng.uniform(-0.5, 0.5, k), d=rng.uniform(1.0, 4.0, k), I0=np.full(k, i0))
+    flow = gu.to_dev((rng.normal(0.0, 0.5, (64, 64, 2)) + (shift, 0.5 * shift)).astype(np.float32).reshape(-1))
+    rp = sp.render_params(0.5, 5.0, 1, 0.8, 0.0, 0, 0, 1.0, 3, "rk4")
+    gJ = gu.to_dev(rng.standard_normal(2 * H * W).astype(np.float32))
+    out = []
+    for parts in ([q], [q, f]):
+        k = sum(len(s["x"]) for s in parts)
+        batch = gu.batch_for([(H, W)], [(64, 64)], [k])
+        args = [gu.to_dev(np.concatenate([s[c] for s in parts]).astype(np.float32)) for c in ("x", "y", "z", "d", "I0")]
+        ws = sp.alloc_workspace(batch, rp, backward=True)
+        g = sp.render_pair_backward(batch, flow, *args, rp, gJ, workspace=ws)
+        assert sp.read_status(ws) == 0
+        out.append({c: gu.to_np(v) for c, v in g.items()})
+    for c in ("x1", "y1", "z", "d", "I0"):
+        assert np.array_equal(out[0][c], out[1][c][:n]), c
+    _close(out[1]["flow"], out[0]["flow"], "flow", tol=1e-6)
