@@ -1513,16 +1513,28 @@ mse_grad_kernel(const float* __restrict__ J, const float* __restrict__ T, int64_
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// loss = (sum of the MSE_BLOCKS partials, as a fixed tree) / n
-__global__ void __launch_bounds__(256)
+// loss = (sum of the partials: each thread's in index order, then a fixed tree) / n.
+// One workgroup, bound by the latency of its loads: 1024 threads with eight in
+// flight each (256 threads, one at a time: 11 us for the 8192 partials of 64 pairs of
+// 512^2, 3.5 us so; 101 us for the 65536 of 32 pairs of 2048^2).
+constexpr int FINISH_NT = 1024;
+
+__global__ void __launch_bounds__(FINISH_NT)
 mse_finish(const double* __restrict__ part, int64_t n_part, int64_t n, double* __restrict__ loss)
 {
-    __shared__ double red[256];
+    constexpr int BATCH = 8;
+    __shared__ double red[FINISH_NT];
     double v = 0.0;
-    for (int64_t k = threadIdx.x; k < n_part; k += 256) v += part[k];
+    for (int64_t k = threadIdx.x; k < n_part; k += BATCH * FINISH_NT) {
+        double e[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) e[j] = k + j * FINISH_NT < n_part ? part[k + j * FINISH_NT] : 0.0;
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) v += e[j];
+    }
     red[threadIdx.x] = v;
     __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
+    for (int w = FINISH_NT / 2; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
@@ -1536,7 +1548,7 @@ hipError_t launch_mse_grad(const float* J, const float* T, int64_t n, float scal
     const int64_t want = (n / 4 + 255) / 256;
     const unsigned grid = loss ? (unsigned)MSE_BLOCKS : (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, MSE_BLOCKS));
     hipLaunchKernelGGL(mse_grad_kernel, dim3(grid), dim3(256), 0, s, J, T, n, scale, grad, loss ? part : nullptr);
-    if (loss) hipLaunchKernelGGL(mse_finish, dim3(1), dim3(256), 0, s, part, (int64_t)MSE_BLOCKS, n, loss);
+    if (loss) hipLaunchKernelGGL(mse_finish, dim3(1), dim3(FINISH_NT), 0, s, part, (int64_t)MSE_BLOCKS, n, loss);
     return hipGetLastError();
 }
 
@@ -1614,7 +1626,7 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
         }
 #undef SP_BLUR
         if (a.mse && a.loss)
-            hipLaunchKernelGGL(mse_finish, dim3(1), dim3(256), 0, s, a.loss_part, nb, a.loss_n, a.loss);
+            hipLaunchKernelGGL(mse_finish, dim3(1), dim3(FINISH_NT), 0, s, a.loss_part, nb, a.loss_n, a.loss);
     }
     if (n_span > 0) {
         if (a.recompute_x2) {
