@@ -293,6 +293,7 @@ bwd_gather(BwdArgs a, int64_t n_span)
     const int grp = threadIdx.x / G, lane = threadIdx.x % G;
     const int64_t g0 = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * (256 / G);
     int64_t g = g0 + grp;
+    const int64_t slot = g;              // of the home-block order
 
     bool in_pair = false, valid = false;
     int H = 1, W = 1;
@@ -357,8 +358,8 @@ bwd_gather(BwdArgs a, int64_t n_span)
     a.g_z[g] = o.gz;
     a.g_d[g] = o.gd;
     a.g_I0[g] = o.gI0;
-    a.gx2[g] = o.gx2;
-    a.gy2[g] = o.gy2;
+    a.gx2[slot] = o.gx2;
+    a.gy2[slot] = o.gy2;
     a.sheet[g] = o.sheet;
 }
 
@@ -508,7 +509,8 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
 {
     extern __shared__ __align__(16) float region[];
     __shared__ float4 s_pos[NP];         // x1, y1, x2, y2
-    __shared__ float4 s_par[NP];         // z, d, I0 (0: invalid), slot in the pair (as bits)
+    __shared__ float4 s_par[NP];         // z, d, I0 (0: invalid), particle of the pair (as bits)
+    __shared__ int s_slot[NP];           // its place in the pair's home-block order
     __shared__ uint32_t s_hist[64];
     __shared__ int s_box[2][4];          // per frame: first column, first row, last column, last row
     const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -535,7 +537,8 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
         end[q] = total;
     }
     const int W = uniform(a.pairs[p].W), H = uniform(a.pairs[p].H);
-    const int64_t part0 = uniform(a.pairs[p].particle_offset), img = uniform(a.pairs[p].image_offset);
+    const int64_t part0 = uniform(a.pairs[p].particle_offset), entry0 = uniform((int64_t)a.order.L[p].entry_base);
+    const int64_t img = uniform(a.pairs[p].image_offset);
     const int t = (int)threadIdx.x, lane = t & 63, h = t & 1;
     for (int k0 = 0; k0 < total; k0 += NP) {
         if (t < 64) s_hist[t] = 0u;
@@ -543,12 +546,13 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
         __syncthreads();
         const int n = min(NP, total - k0), k = k0 + t;
         float4 pos = make_float4(0.0f, 0.0f, 0.0f, 0.0f), par = make_float4(0.0f, 1.0f, 0.0f, 0.0f);
-        int size = 0;
+        int size = 0, place = 0;
         uint32_t rank = 0;
         int box[2][4] = {{1 << 30, 1 << 30, -1, -1}, {1 << 30, 1 << 30, -1, -1}};
         if (t < n) {
             const int64_t o = k < end[0] ? off[0] : k < end[1] ? off[1] : k < end[2] ? off[2] : off[3];
             const int i = a.order.entries[o + k];
+            place = (int)(o + k - entry0);
             const int64_t g = part0 + i;
             pos = make_float4(a.x1[g], a.y1[g], a.x2[g], a.y2[g]);
             const float d = a.d[g], I0 = a.I0[g];
@@ -598,6 +602,7 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
                 const int slot = (int)((size < 63 ? above : 0u) + rank);
                 s_pos[slot] = pos;
                 s_par[slot] = par;
+                s_slot[slot] = place;
             }
         }
 #pragma unroll 1
@@ -677,7 +682,7 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
                     (h ? a.g_y1 : a.g_x1)[g] = h ? o.gy1 : o.gx1;
                     if (h == 0) *reinterpret_cast<float2*>(&s_pos[sl]) = make_float2(s.x, s.w);
                 } else {
-                    (h ? a.gy2 : a.gx2)[g] = h ? o.gy2 : o.gx2;
+                    (h ? a.gy2 : a.gx2)[part0 + s_slot[sl]] = h ? o.gy2 : o.gx2;
                     (h ? a.g_z : a.g_d)[g] = h ? o.gz : o.gd;
                     (h ? a.sheet : a.g_I0)[g] = h ? o.sheet : o.gI0;
                 }
@@ -1012,10 +1017,10 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
     if (i < P.n_max) {
         // slots follow the home-block order: neighbouring lanes sample, and add
         // into, neighbouring grid cells
+        gpx = a.gx2[P.particle_offset + i];      // stored in that order
+        gpy = a.gy2[P.particle_offset + i];
         if (a.order.entries) i = a.order.entries[a.order.L[p].entry_base + i];
         g = P.particle_offset + i;
-        gpx = a.gx2[g];
-        gpy = a.gy2[g];
         px = a.x1[g];
         py = a.y1[g];
         live = (gpx != 0.0f || gpy != 0.0f) && __builtin_isfinite(px) && __builtin_isfinite(py);

@@ -301,7 +301,7 @@ struct BwdArgs {
     float* g_sheet;
     float* g_sheet_total;        // optional (null): the sum over pairs
     float* g_flow;
-    float* gx2;                  // dL/dx2, dL/dy2 (workspace)
+    float* gx2;                  // dL/dx2, dL/dy2, each pair's in its home-block order (workspace)
     float* gy2;
     float* sheet;                // per-particle sheet-width terms (workspace)
     double* sheet_part;          // per (pair, slice) float64 sums of those terms (workspace)
