@@ -283,6 +283,15 @@ __device__ __forceinline__ ParticleGrads particle_grads(float z, float d, float 
     return o;
 }
 
+// Where the gather leaves dL/dx1, dL/dy1 of frame 1's render for the flow adjoint, which
+// adds its own part and stores the sums: the first 2 KB of the partial of the adjoint
+// workgroup that takes the particle (256 consecutive places of the pair's home-block
+// order), which writes its partial after it has read them.
+__device__ __forceinline__ float2* start_grads(const BwdArgs& a, int p, int64_t place)
+{
+    return reinterpret_cast<float2*>(a.grid.part + (a.grid.wg_base[p] + (place >> 8)) * (2 * WIN_NODES)) + (place & 255);
+}
+
 // Particle-major gather: G lanes per particle read their patch rows of the
 // frame's gradient image from global memory (any diameter bound and blur).
 template <int B, int BT, int G>
@@ -298,12 +307,14 @@ bwd_gather(BwdArgs a, int64_t n_span)
     bool in_pair = false, valid = false;
     int H = 1, W = 1;
     int64_t img = 0;
+    float2* start = nullptr;
     float z = 0.0f, d = 1.0f, I0 = 0.0f;
     if (g < n_span) {
         const int p = find_pair_from(a.pairs, a.n_pairs, g0, g);
         const synthpix_pair P = a.pairs[p];
         int64_t i = g - P.particle_offset;
         if (i >= 0 && i < P.n_max) {
+            start = start_grads(a, p, i);
             // slots follow the home-block order: neighbouring groups read
             // overlapping rows of dL/dJ
             if (a.order.entries) i = a.order.entries[a.order.L[p].entry_base + i];
@@ -353,8 +364,7 @@ bwd_gather(BwdArgs a, int64_t n_span)
     }
     ParticleGrads o{};
     if (valid) o = particle_grads(z, d, I0, a.sheet_sigma, fs[0], fs[1]);
-    a.g_x1[g] = o.gx1;
-    a.g_y1[g] = o.gy1;
+    *start = make_float2(o.gx1, o.gy1);
     a.g_z[g] = o.gz;
     a.g_d[g] = o.gd;
     a.g_I0[g] = o.gI0;
@@ -483,15 +493,17 @@ __device__ __noinline__ float4 gather_exact(const float* src, int W, float x, fl
 // support alone.
 // Two lanes of contiguous work and one LDS word per pixel against eight or sixteen
 // lanes with a row-factor vector of LDS per pixel: 64 pairs of 512^2 at 0.05 ppp, d
-// about 2.5: 207 -> 116 us; 4 pairs of 2048^2 at 0.1 ppp, d to 6: 636 -> 459 us (there
-// from LDS before, one frame and 32-pixel block at a time, which also took an order of
-// the frame-2 positions, 60 us).  Of the first, 20 us are the sums and 28 us the
-// staging; the rest are 7 reads and 8 writes of particle arrays at unrelated addresses
-// and the waits between the phases, which is why small workgroups do better: NP = 256
-// with room for four per CU 116 us, NP = 512 131 us, and on the second batch, whose
-// blocks hold 410 particles (two passes of 256), 507 and 459 us.  Straight from global
-// memory (16-byte loads, one or two lanes per row) it took 167-172 us: each lane's row
-// is a cache line of its own.
+// about 2.5: 207 -> 117 us; 4 pairs of 2048^2 at 0.1 ppp, d to 6: 636 -> 377 us (from
+// LDS before as well, one frame and 32-pixel block at a time, which also took an order
+// of the frame-2 positions, 60 us), of which 85 came from leaving dL/dx1 and dL/dx2 in
+// the home-block order instead of at the particles' own addresses.  Of the first, 20
+// us are the sums and 28 us the staging; the rest are the particle arrays (seven
+// reads and four writes at unrelated addresses) and the waits between the phases,
+// which is why small workgroups do better: NP = 256 with room for four per CU 116 us,
+// NP = 512 131 us; on the second batch, whose blocks hold 410 particles (two passes of
+// 256), 507 and 459 us (before the home-block order of the results).  Straight from
+// global memory (16-byte loads, one or two lanes per row) the first took 167-172 us:
+// each lane's row is a cache line of its own.
 constexpr int REGION_PAD = 32;          // floats past the region that a row's last reads may reach
 
 // A value that is the same in every lane, moved to scalar registers.
@@ -679,7 +691,7 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
                 }
                 const int64_t g = part0 + __float_as_int(par.w);
                 if (f == 0) {
-                    (h ? a.g_y1 : a.g_x1)[g] = h ? o.gy1 : o.gx1;
+                    reinterpret_cast<float*>(start_grads(a, p, s_slot[sl]))[h] = h ? o.gy1 : o.gx1;
                     if (h == 0) *reinterpret_cast<float2*>(&s_pos[sl]) = make_float2(s.x, s.w);
                 } else {
                     (h ? a.gy2 : a.gx2)[part0 + s_slot[sl]] = h ? o.gy2 : o.gx2;
@@ -974,16 +986,16 @@ __device__ __forceinline__ void substep_adjoint(const FlowView& fv, const FlowWi
 enum { SC_G2MAX = 0, SC_LIP = 1, SC_EXP = 2, SC_STATE = 3 };
 enum { SC_NONE = 0, SC_VALID = 1, SC_NONFINITE = 2 };
 
-// Reverse sweep of every particle: final position gradient (added to g_x1,
-// g_y1) and node sums into the fixed-point grid.  CK checkpoints of the
+// Reverse sweep of every particle: final position gradient (frame 1's
+// plus the sweep's, to g_x1, g_y1) and node sums into the fixed-point grid.  CK checkpoints of the
 // trajectory are kept, one every L = ceil(substeps / CK) substeps; each segment
 // is recomputed into SK >= L slots during the sweep.
 // The grid nodes around the workgroup's particles are copied to LDS, so that the
 // samples of neighbouring lanes do not go through the vector cache line by line, and
 // the box of the nodes to write out follows from the cells added to instead of a
 // search of the window.  4 pairs of 2048^2 at 0.1 ppp, RK4 x 8: 386 -> 327 us (the
-// copy 353, the box 346, the kept samples 327); 64 of 512^2 at 0.05 ppp, RK4 x 4: 112 ->
-// 102 us.  Without the node sums it would take 281 and 89 us: what remains is VALU work
+// copy 353, the box 346, the kept samples 327) and, with dL/dx1 and dL/dx2 read in the
+// home-block order, 308; 64 of 512^2 at 0.05 ppp, RK4 x 4: 112 -> 98 us.  Without the node sums it would take 281 and 89 us: what remains is VALU work
 // and the particle arrays at unrelated addresses.
 constexpr int ADJ_FLOW_NODES = 896;     // LDS copy of grid nodes: 7 KB, with which four workgroups still share a CU
 constexpr int ADJ_FLOW_MARGIN = 4;      // cells around the particles' starting ones
@@ -1011,7 +1023,8 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
     const synthpix_pair P = a.pairs[p];
     const int64_t chunk = wg - a.grid.wg_base[p];
     int64_t i = chunk * 256 + threadIdx.x;
-    int64_t g = 0;
+    int64_t g = -1;
+    const int64_t place = i;
     bool live = false;
     float gpx = 0.0f, gpy = 0.0f, px = 0.0f, py = 0.0f;
     if (i < P.n_max) {
@@ -1136,8 +1149,11 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
             }
         }
         run.finish();
-        a.g_x1[g] += gpx;
-        a.g_y1[g] += gpy;
+    }
+    if (g >= 0) {
+        const float2 b = *start_grads(a, p, place);
+        a.g_x1[g] = live ? b.x + gpx : b.x;
+        a.g_y1[g] = live ? b.y + gpy : b.y;
     }
     __syncthreads();
 
