@@ -221,7 +221,7 @@ struct EpilogueArgs {
 };
 
 // Particle records and tile lists of both frames (layout, prep, count, scan,
-// scatter): what the tile renderer and the tile-major backward read.
+// scatter): what the tile renderer reads.
 hipError_t launch_bins(const RenderArgs& a, const RenderConfig& cfg, const BatchTotals& tot, char* ws,
                        const WorkspaceLayout& wl, hipStream_t s);
 
@@ -236,7 +236,7 @@ constexpr int BWD_SLICES = 128;
 // Everything the backward kernels read and write.
 // Flow-grid gradient without global atomics: the flow adjoint runs one
 // workgroup per 256 particles of one pair; each accumulates its node sums (64-bit
-// fixed point) in an LDS window and writes the window's nonzero box to its own
+// fixed point) in an LDS window and writes the box of the cells added to to its own
 // partial (and any contribution outside the window as a record); a reduction
 // then adds, per node, the partials and records of the pair's workgroups.
 constexpr int WIN_NODES = 2048;      // LDS window capacity (nodes; 32 KB of (u, v) sums)
