@@ -934,3 +934,53 @@ def test_flow_adjoint_node_copy(shift):
     for c in ("x1", "y1", "z", "d", "I0"):
         assert np.array_equal(out[0][c], out[1][c][:n]), c
     _close(out[1]["flow"], out[0]["flow"], "flow", tol=1e-6)
+
+
+def test_block_gather_gaps():
+    """The block gather on packed arrays with gaps before every pair (not numbers in the
+    images' gaps): the pairs' gradients equal those without gaps bit for bit, and the
+    particle gaps come back 0."""
+    n, k, gaps = 330, 200, (7, 12, 4)
+    sizes, grids = [(64, 64)] * k, [(4, 4)] * k
+    P, flows, batch, dev, flow = _batch(sizes, grids, n, 78)
+    gb = sp.PairBatch.build(sizes, grids, [n] * k, device=gu.DEV, gaps=gaps)
+    rp = sp.render_params(0.5, 5.0, 0, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+    _, g_dev = _grad_images(batch, 4)
+
+    def spread(t, gap, fill):
+        rows = t.reshape(k, -1)
+        pad = torch.full((k, gap), fill, dtype=t.dtype, device=t.device)
+        return torch.cat([pad, rows], 1).reshape(-1)
+
+    names = ("x", "y", "z", "d", "I0")
+    a = sp.render_pair_backward(batch, flow, *[dev[c] for c in names], rp, g_dev)
+    b = sp.render_pair_backward(gb, spread(flow, gaps[2], 0.0), *[spread(dev[c], gaps[0], 1.0) for c in names], rp,
+                                spread(g_dev, gaps[1], float("nan")))
+    for c in ("x1", "y1", "z", "d", "I0"):
+        rows = b[c][:k * (n + gaps[0])].reshape(k, n + gaps[0])
+        assert torch.equal(rows[:, gaps[0]:].reshape(-1), a[c][:k * n]), c
+        assert torch.all(rows[:, :gaps[0]] == 0.0), c
+
+
+def test_block_gather_large_pair():
+    """A pair of more than 16384 home blocks of 32 pixels (64-pixel blocks then, one to
+    a workgroup): against the particle-major gather, which a diameter bound above 12
+    takes."""
+    H = W = 4160
+    n = 400_000
+    gen = torch.Generator(device=gu.DEV).manual_seed(9)
+
+    def u(lo, hi, m=n):
+        return lo + (hi - lo) * torch.rand(m, generator=gen, device=gu.DEV)
+
+    args = [u(0.0, W), u(0.0, H), u(-0.5, 0.5), u(1.0, 4.0), u(0.5, 1.0)]
+    batch = gu.batch_for([(H, W)], [(8, 8)], [n])
+    flow = u(-3.0, 3.0, 128)
+    gJ = torch.randn(2 * H * W, generator=gen, device=gu.DEV)
+    out = []
+    for d_max in (4.0, 13.0):
+        rp = sp.render_params(0.5, d_max, 0, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+        out.append({c: gu.to_np(v) for c, v in sp.render_pair_backward(batch, flow, *args, rp, gJ).items()})
+    for c in ("x1", "y1", "z", "d", "I0"):
+        _close(out[0][c], out[1][c], c, tol=TOL)
+        assert not np.array_equal(out[0][c], out[1][c]), "the same gather twice"
