@@ -883,10 +883,9 @@ synthpix_status backward_common(const synthpix_pair* pairs_host, const synthpix_
     a.scale = reinterpret_cast<uint32_t*>(ws + wl.scale);
     a.status = reinterpret_cast<uint32_t*>(ws + wl.status);
     int64_t slots = 0;                       // the ranges are disjoint
-    const int gl = sp::block_group_log(a.order.log_block);
     for (int32_t p = 0; p < n_pairs; ++p) {
         slots += pairs_host[p].n_max;
-        a.block_groups += (int64_t)((pairs_host[p].W + (1 << gl) - 1) >> gl) * ((pairs_host[p].H + (1 << gl) - 1) >> gl);
+        a.block_groups += (int64_t)((pairs_host[p].W + 63) / 64) * ((pairs_host[p].H + 63) / 64);
     }
     a.gaps = slots != span;
     a.sheet_sigma = rp->sheet_sigma;

@@ -10,10 +10,12 @@
 // e = B^T dL/dJ, equal sum_q (dL/dJ)_q Ty_j(r) Tx_k(c) with 1-D tables
 // Tx_k = w * (gx dx^k) (the blur folded into the particle's factor tables).
 // The gather is particle-major: a group of 8 or 16 lanes per particle reads its
-// patch rows of dL/dJ with coalesced loads or, for larger batches once the blur's
-// adjoint has run per pixel, a workgroup stages what the particles of a 64 x 64
-// pixel block cover in LDS and two lanes per particle gather from there; nothing
-// is scattered, no partial sums cross workgroups.
+// patch rows of dL/dJ with coalesced loads.  Once no blur is left to fold (none, or
+// its adjoint has run per pixel), the sums are added in one order by two forms: a
+// workgroup stages what the particles of a 64 x 64 pixel block cover in LDS and two
+// lanes per particle gather from there, or, for small and sparse batches, eight
+// lanes per particle gather row by row from global memory.  Nothing is scattered,
+// no partial sums cross workgroups, and which form runs leaves no trace in the bits.
 //
 // Flow adjoint: a reverse sweep through the recomputed Euler / RK4 substeps
 // (checkpointed).  Each bilinear sample passes its upstream gradient to its
@@ -293,9 +295,10 @@ __device__ __forceinline__ float2* start_grads(const BwdArgs& a, int p, int64_t 
 }
 
 // Particle-major gather: G lanes per particle read their patch rows of the
-// frame's gradient image from global memory (any diameter bound and blur).
+// frame's gradient image from global memory (a blur of radius 1 folded into the
+// tables, or diameters beyond the block and row gathers).
 template <int B, int BT, int G>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 8 ? 6 : BT == 32 ? 7 : 4)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 8 ? 6 : 4)))
 bwd_gather(BwdArgs a, int64_t n_span)
 {
     __shared__ GatherLds<G, BT> S;
@@ -702,6 +705,143 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
             __syncthreads();
         }
     }
+}
+
+// ------------------------------------------------------------------ row gather
+
+// One frame's sums of a particle by eight lanes, added in the block gather's order: lane
+// 2 j + h forms the row sums of every fourth row from row j on over the columns c, c + 2,
+// .. (c the first column of parity h), and the particle's sums pass between the lanes of
+// rows 0 and 2 of each four, which add their own and the next row as gather_columns does.
+// Only the support's own pixels are read.
+template <int N>
+__device__ __forceinline__ void row_block(const float* __restrict__ src, int W, float x, float y, float kap, int c,
+                                          int c1, int r0, int r1, int j, float4& s)
+{
+    float g0[N], g1[N], g2[N];
+    const float fx = (float)c + 0.5f;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const float dx = (fx + (float)(2 * k)) - x;
+        const float v = expneg_hw(kap * (dx * dx));
+        g0[k] = c + 2 * k <= c1 ? v : 0.0f;
+        g1[k] = g0[k] * dx;
+        g2[k] = g1[k] * dx;
+    }
+#pragma unroll 1
+    for (int rb = r0; rb <= r1; rb += 4) {
+        const int r = rb + j;
+        const float* q = src + ((int64_t)r * W + c);
+        float e[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) e[k] = r <= r1 && c + 2 * k <= c1 ? q[2 * k] : 0.0f;
+        const float dy = ((float)r + 0.5f) - y;
+        float u = expneg_hw(kap * (dy * dy));
+        u = r <= r1 ? u : 0.0f;
+        const float u1 = u * dy, u2 = u1 * dy;
+        float A0 = 0.0f, A1 = 0.0f, A2 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            A0 = __builtin_fmaf(e[k], g0[k], A0);
+            A1 = __builtin_fmaf(e[k], g1[k], A1);
+            A2 = __builtin_fmaf(e[k], g2[k], A2);
+        }
+        // the next row's, from two lanes on (row_shl:2)
+        const float B0 = dpp<0x102>(A0), B1 = dpp<0x102>(A1), B2 = dpp<0x102>(A2);
+        const float v = dpp<0x102>(u), v1 = dpp<0x102>(u1), v2 = dpp<0x102>(u2);
+#pragma unroll
+        for (int step = 0; step < 2; ++step) {
+            s.x = __builtin_fmaf(B0, v, __builtin_fmaf(A0, u, s.x));
+            s.y = __builtin_fmaf(B1, v, __builtin_fmaf(A1, u, s.y));
+            s.z = __builtin_fmaf(B0, v1, __builtin_fmaf(A0, u1, s.z));
+            s.w = __builtin_fmaf(B2, v, __builtin_fmaf(A2, u, s.w));
+            s.w = __builtin_fmaf(B0, v2, __builtin_fmaf(A0, u2, s.w));
+            // on to the lanes of rows 2 and 3 (row_shr:4) and back (row_shl:4)
+            if (step == 0) s = make_float4(dpp<0x114>(s.x), dpp<0x114>(s.y), dpp<0x114>(s.z), dpp<0x114>(s.w));
+            else s = make_float4(dpp<0x104>(s.x), dpp<0x104>(s.y), dpp<0x104>(s.z), dpp<0x104>(s.w));
+        }
+    }
+}
+
+// The sums, in lane 0 of the eight.
+__device__ __forceinline__ float4 row_sums(const float* __restrict__ src, int W, float x, float y, float kap, int c0,
+                                           int c1, int r0, int r1, int lane)
+{
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int h = lane & 1, w = c1 - c0 + 1;
+#define SP_ROWS(N_) row_block<N_>(src, W, x, y, kap, c0 + h + c, c1, r0, r1, lane >> 1, s)
+#pragma unroll 1
+    for (int c = 0; c < w; c += 16) {
+        if (!__builtin_amdgcn_ballot_w64(w - c > 4)) SP_ROWS(2);
+        else if (!__builtin_amdgcn_ballot_w64(w - c > 8)) SP_ROWS(4);
+        else if (!__builtin_amdgcn_ballot_w64(w - c > 12)) SP_ROWS(6);
+        else SP_ROWS(8);
+    }
+#undef SP_ROWS
+    return make_float4(s.x + dpp<0xB1>(s.x), s.y + dpp<0xB1>(s.y), s.z + dpp<0xB1>(s.z), s.w + dpp<0xB1>(s.w));
+}
+
+// Row gather, for batches with too few blocks or particles for the block gather: the same
+// sums in the same order, so a particle's gradients have the same bits whatever batch it
+// comes in.  Eight lanes per particle read its support from global memory; BOTH: sixteen,
+// one half for each frame.
+// Bound by the latency of its loads for few particles, by the rows' cache lines (one per
+// row and load) and VALU for many.  Against bwd_gather<0, 32, 8 or 16>, which added in an
+// order of its own: one pair of 256^2 at 0.05 ppp, d about 2.5, 11.6 -> 8.3 us, of 512^2
+// with d 2 to 6 14.6 -> 18.2 us; 64 of 512^2 at 0.005 / 0.01 ppp 43.6 / 64.6 -> 42.0 /
+// 62.9 us; 4 of 2048^2, d 2 to 6, 65 / 112 -> 76 / 122 us.  The next rows' pixels loaded
+// ahead: 67 us for 62.9 (registers); eight rows at a time by sixteen lanes: 90 us.
+template <bool BOTH>
+__global__ void __launch_bounds__(256)
+bwd_gather_rows(BwdArgs a, int64_t n_span)
+{
+    constexpr int G = BOTH ? 16 : 8;
+    const int lane = threadIdx.x % G;
+    const int64_t g0 = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * (256 / G);
+    const int64_t slot = g0 + threadIdx.x / G;          // of the home-block order
+    if (slot >= n_span) return;
+    const int p = find_pair_from(a.pairs, a.n_pairs, g0, slot);
+    const synthpix_pair P = a.pairs[p];
+    const int64_t i = slot - P.particle_offset;
+    if (i < 0 || i >= P.n_max) {
+        // a slot in no pair's particle range (a gap of the packed arrays): zero gradients
+        if (lane == 0) {
+            a.g_x1[slot] = 0.0f;
+            a.g_y1[slot] = 0.0f;
+            a.g_z[slot] = 0.0f;
+            a.g_d[slot] = 0.0f;
+            a.g_I0[slot] = 0.0f;
+        }
+        return;
+    }
+    const int64_t g = P.particle_offset + a.order.entries[a.order.L[p].entry_base + i];
+    const float z = a.z[g], d = a.d[g], I0 = a.I0[g];
+    bool valid = (I0 > 0.0f) && (d > 0.0f);
+    if (valid && !(d <= a.d_max)) {
+        if (lane == 0) atomicOr(a.status, SP_STATUS_D_ABOVE_MAX);
+        valid = false;
+    }
+    const float kap = 8.0f / (d * d);
+    auto frame = [&](int f) {
+        const float x = f ? a.x2[g] : a.x1[g], y = f ? a.y2[g] : a.y1[g];
+        int c0, c1, r0, r1;
+        if (!valid || !support_box(x, y, d, P.W, P.H, c0, c1, r0, r1)) return make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        return row_sums(a.grad + P.image_offset + (int64_t)f * P.H * P.W, P.W, x, y, kap, c0, c1, r0, r1, lane & 7);
+    };
+    const float4 s1 = frame(BOTH ? lane >> 3 : 0);
+    float4 s2;
+    if constexpr (BOTH) s2 = make_float4(dpp<0x108>(s1.x), dpp<0x108>(s1.y), dpp<0x108>(s1.z), dpp<0x108>(s1.w));
+    else s2 = frame(1);
+    if (lane != 0) return;
+    ParticleGrads o{};
+    if (valid) o = particle_grads(z, d, I0, a.sheet_sigma, s1, s2);
+    *start_grads(a, p, i) = make_float2(o.gx1, o.gy1);
+    a.g_z[g] = o.gz;
+    a.g_d[g] = o.gd;
+    a.g_I0[g] = o.gI0;
+    a.gx2[slot] = o.gx2;
+    a.gy2[slot] = o.gy2;
+    a.sheet[g] = o.sheet;
 }
 
 // Zero gradients of the slots in no pair's particle range (gaps of the packed arrays).
@@ -1587,18 +1727,29 @@ static unsigned gather_blocks(int64_t n_span, int G)
     return (unsigned)((n_span + 256 / G - 1) / (256 / G));
 }
 
-// Whether the block gather serves a batch: its LDS (the region and up to 17 KB of
-// particles) fits in 64 KB, and there are blocks for most CUs with enough particles
-// each.  Against the particle-major gather: 2 / 4 / 8 pairs of 512^2 at 0.05 ppp (128 /
-// 256 / 512 blocks) 16.7 / 17.3 / 21 us and 14.3 / 22 / 33 us; a block costs about
-// 25 ns however few particles it holds: 64 pairs at 0.005 / 0.02 / 0.03 ppp (20 / 82 /
-// 123 particles a block) 105 / 109 / 114 us and 49 / 99 / 132 us, 4 pairs of 2048^2
-// with d to 6 at 0.01 / 0.02 ppp (41 / 82) 167 / 174 us and 111 / 192 us.
+// Diameter bound of the block and row gathers (wider particles take bwd_gather): the block
+// gather's region then fits in LDS.
+static bool narrow_particles(const BwdArgs& a)
+{
+    return block_region_side(a.d_max, BLOCK_LOG) <= 108;
+}
+
+// Whether the block gather is the faster one: enough particles to repay its phases (about
+// 16 us however few) and its blocks (about 16 ns each), as the row gather costs 0.26 ns per
+// particle of d about 2.5 and 0.55 of d to 6.  Row / block gather in us: one pair of 1024^2
+// (256 blocks) at 123 / 205 / 410 particles a block 16 / 22 / 35 and 21 / 23 / 25; 64 pairs
+// of 256^2 (1024 blocks) at 41 / 82 / 205 22 / 32 / 60 and 20 / 21 / 30; 64 of 512^2 (4096)
+// at 20 / 41 / 61 / 82 42 / 63 / 82 / 103 and 67 / 72 / 76 / 78; 4 of 2048^2 with d to 6
+// (4096) at 20 / 41 / 61 / 82 76 / 122 / 171 / 214 and 130 / 138 / 143 / 150.
 static bool block_gather_pays(const BwdArgs& a, int64_t n_span)
 {
-    return block_region_side(a.d_max, block_group_log(a.order.log_block)) <= 108 &&
-           4 * a.block_groups >= 3 * (int64_t)device_cu_count() && n_span >= 80 * a.block_groups;
+    return n_span >= 40 * a.block_groups + 24000 && a.order.log_block <= BLOCK_LOG;
 }
+
+// Whether the row gather gives each frame lanes of its own: while that leaves the chip
+// unfilled (one pair of 512^2 at 0.05 ppp 11.5 us either way, 20 / 82 a block 11.1 / 11.0
+// -> 8.4 / 8.7; 2 of them at 0.1 ppp, 52 k particles, 21.5 -> 23.7).
+static bool rows_both(int64_t n_span) { return n_span <= 64 * (int64_t)device_cu_count(); }
 
 void launch_advect_adjoint(const BwdArgs& a, const synthpix_advect_params& ap, unsigned blocks, hipStream_t s)
 {
@@ -1657,11 +1808,12 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
         }
         BwdArgs b = a;
         if (per_pixel) b.grad = a.eblur;
-        if ((per_pixel || blur == 0) && block_gather_pays(a, n_span)) {
+        const bool unfolded = per_pixel || blur == 0;        // no blur left for the gather's tables
+        if (unfolded && narrow_particles(a) && block_gather_pays(a, n_span)) {
             TimedScope ts("bwd_gather", s);
-            const int gl = block_group_log(a.order.log_block), gb = 1 << (gl - a.order.log_block);
-            const int side = block_region_side(a.d_max, gl), cap = side * side;
-            const int ngx = (a.max_w + (1 << gl) - 1) >> gl, ngy = (a.max_h + (1 << gl) - 1) >> gl;
+            const int gb = 1 << (BLOCK_LOG - a.order.log_block);
+            const int side = block_region_side(a.d_max, BLOCK_LOG), cap = side * side;
+            const int ngx = (a.max_w + 63) / 64, ngy = (a.max_h + 63) / 64;
             const int64_t nb = (int64_t)a.n_pairs * ngx * ngy;
             if (nb > 0xFFFFFFFFll) return hipErrorInvalidValue;
             const size_t lds = sizeof(float) * ((size_t)cap + REGION_PAD);
@@ -1671,30 +1823,23 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
             else
                 hipLaunchKernelGGL(bwd_gather_blocks<256>, dim3((unsigned)nb), dim3(256), lds, s, b, gb, ngx, ngy, cap);
             if (a.gaps) hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
-        } else if (per_pixel) {
+        } else if (unfolded && narrow_particles(a)) {
             TimedScope ts("bwd_gather", s);
-            // sixteen lanes per particle for wide blurs, whose patches are wide as a rule
-#define SP_GATHER0(BT_, G_) \
-    hipLaunchKernelGGL((bwd_gather<0, BT_, G_>), dim3(gather_blocks(n_span, G_)), dim3(256), 0, s, b, n_span)
-            if ((int)(3.0f * a.d_max) + 4 > 32) SP_GATHER0(64, 16);
-            else if (blur >= 2) SP_GATHER0(32, 16);
-            else SP_GATHER0(32, 8);
-#undef SP_GATHER0
+            if (rows_both(n_span))
+                hipLaunchKernelGGL(bwd_gather_rows<true>, dim3(gather_blocks(n_span, 16)), dim3(256), 0, s, b, n_span);
+            else
+                hipLaunchKernelGGL(bwd_gather_rows<false>, dim3(gather_blocks(n_span, 8)), dim3(256), 0, s, b, n_span);
+        } else if (unfolded) {
+            TimedScope ts("bwd_gather", s);
+            hipLaunchKernelGGL((bwd_gather<0, 64, 16>), dim3(gather_blocks(n_span, 16)), dim3(256), 0, s, b, n_span);
         } else {
             TimedScope ts("bwd_gather", s);
-            // slots needed: floor(3 d_max) + 4 covered pixels + 4 b padding
-            const bool small = (int)(3.0f * a.d_max) + 4 + 4 * blur <= 32;
-#define SP_GATHER(BB)                                                                  \
-    do {                                                                               \
-        if (small) hipLaunchKernelGGL((bwd_gather<BB, 32, 8>), dim3(gather_blocks(n_span, 8)), dim3(256), 0, s, a, n_span); \
-        else hipLaunchKernelGGL((bwd_gather<BB, 64, 16>), dim3(gather_blocks(n_span, 16)), dim3(256), 0, s, a, n_span);       \
-    } while (0)
-            switch (blur) {
-            case 0: SP_GATHER(0); break;
-            case 1: SP_GATHER(1); break;
-            default: return hipErrorInvalidValue;
-            }
-#undef SP_GATHER
+            if (blur != 1) return hipErrorInvalidValue;
+            // slots needed: floor(3 d_max) + 4 covered pixels + 4 of padding
+            if ((int)(3.0f * a.d_max) + 8 <= 32)
+                hipLaunchKernelGGL((bwd_gather<1, 32, 8>), dim3(gather_blocks(n_span, 8)), dim3(256), 0, s, a, n_span);
+            else
+                hipLaunchKernelGGL((bwd_gather<1, 64, 16>), dim3(gather_blocks(n_span, 16)), dim3(256), 0, s, a, n_span);
         }
         {
             TimedScope ts("bwd_bounds", s);

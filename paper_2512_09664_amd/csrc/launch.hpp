@@ -333,7 +333,7 @@ hipError_t launch_mse_grad(const float* J, const float* T, int64_t n, float scal
                            double* part, hipStream_t s);
 
 // Blocks of the block gather: 64 x 64 pixels, one or 2 x 2 home blocks.
-inline int block_group_log(int log_block) { return std::max(log_block, 6); }
+constexpr int BLOCK_LOG = 6;
 
 // Side of the square whose pixels the block gather can stage per workgroup: a block
 // and its particles' supports, with 6 pixels for the spread of the frame-2 positions

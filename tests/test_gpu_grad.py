@@ -984,3 +984,70 @@ def test_block_gather_large_pair():
     for c in ("x1", "y1", "z", "d", "I0"):
         _close(out[0][c], out[1][c], c, tol=TOL)
         assert not np.array_equal(out[0][c], out[1][c]), "the same gather twice"
+
+
+@pytest.mark.parametrize("blur,mse", [(0, False), (2, False), (1, True)])
+@pytest.mark.parametrize("d_range,d_max", [((0.3, 1.2), 2.0), ((1.0, 4.5), 5.0), ((3.0, 9.0), 9.0), ((6.0, 12.0), 12.0)])
+def test_gradients_do_not_depend_on_the_batch(d_range, d_max, blur, mse):
+    """A pair's particle gradients have the same bits alone and in any batch that
+    holds it: a small one, a sparse one of many particles, and dense ones with up to
+    256 and with more particles per 64-pixel block (each of which another form of the
+    gather serves)."""
+    size, grid, n = (70, 97), (18, 25), 330
+    P, flows, one, dev, flow = _batch([size], [grid], n, 1100 + blur, d_range=d_range)
+    rng = np.random.default_rng(blur)
+    gJ, gT = (rng.standard_normal(2 * size[0] * size[1]).astype(np.float32) for _ in range(2))
+    rp = sp.render_params(0.5, d_max, blur, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+
+    def run(extra, m, seed):
+        """The pair between two halves of `extra` pairs of m particles each."""
+        half = len(extra) // 2
+        sizes = extra[:half] + [size] + extra[half:]
+        grids = [(4, 4)] * half + [grid] + [(4, 4)] * (len(extra) - half)
+        batch = gu.batch_for(sizes, grids, [m] * half + [n] + [m] * (len(extra) - half))
+        gen = torch.Generator(device=gu.DEV).manual_seed(seed)
+
+        def around(t, count, lo, hi):
+            a, b = (lo + (hi - lo) * torch.rand(k, generator=gen, device=gu.DEV) for k in count)
+            return torch.cat([a, t, b])
+
+        k = (half * m, (len(extra) - half) * m)
+        px = tuple(sum(2 * h * w for h, w in e) for e in (extra[:half], extra[half:]))
+        args = [around(dev[c][:n], k, *r) for c, r in (("x", (0.0, 64.0)), ("y", (0.0, 64.0)), ("z", (-0.5, 0.5)),
+                                                     ("d", d_range), ("I0", (0.5, 1.0)))]
+        fl = around(flow, (32 * half, 32 * (len(extra) - half)), -1.0, 1.0)
+        J, T = (around(gu.to_dev(v), px, -1.0, 1.0) for v in (gJ, gT))
+        ws = sp.alloc_workspace(batch, rp, backward="mse" if mse else True)
+        if mse:
+            g = sp.render_pair_backward_mse(batch, fl, *args, rp, J, T, 0.25, workspace=ws)
+        else:
+            g = sp.render_pair_backward(batch, fl, *args, rp, J, workspace=ws)
+        assert sp.read_status(ws) == 0
+        o = batch.host[half].particle_offset
+        return {c: gu.to_np(g[c])[o:o + n] for c in ("x1", "y1", "z", "d", "I0")}
+
+    alone = run([], 0, 0)
+    for extra, m in (([(40, 40)] * 2, 50), ([(2048, 1024)] * 2, 10_000), ([(64, 64)] * 200, 250), ([(64, 64)] * 200, 400)):
+        got = run(extra, m, len(extra) + m)
+        for c in alone:
+            assert np.array_equal(got[c], alone[c]), (len(extra), m, c)
+
+
+@pytest.mark.parametrize("n", [330, 700])
+@pytest.mark.parametrize("d_range,d_max,blur", [((0.3, 1.2), 2.0, 0), ((1.0, 6.0), 6.0, 2), ((6.0, 12.0), 12.0, 2)])
+def test_block_gather_matches_particle_gather(n, d_range, d_max, blur):
+    """The block gather, in one pass per block and in two, up to the widest particles it
+    takes, against the particle-major gather (which a diameter bound above 12 takes)."""
+    sizes, grids = [(70, 97), (33, 130), (9, 3), (128, 64)], [(18, 25), (9, 33), (4, 2), (32, 16)]
+    reps = 60
+    P, flows, _, _, _ = _batch(sizes, grids, n, 1200 + blur, d_range=d_range)
+    batch = gu.batch_for(sizes * reps, grids * reps, [n] * 4 * reps)
+    args = [gu.to_dev(np.concatenate(P[k] * reps)) for k in ("x", "y", "z", "d", "I0")]
+    flow = gu.to_dev(np.concatenate([f.reshape(-1) for f in flows] * reps))
+    g, g_dev = _grad_images(batch, n)
+    out = []
+    for bound in (d_max, 13.0):
+        rp = sp.render_params(0.5, bound, blur, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+        out.append({c: gu.to_np(v) for c, v in sp.render_pair_backward(batch, flow, *args, rp, g_dev).items()})
+    for c in ("x1", "y1", "z", "d", "I0", "sheet"):
+        _close(out[0][c], out[1][c], c, tol=TOL)
