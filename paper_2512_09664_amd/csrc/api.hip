@@ -882,12 +882,10 @@ synthpix_status backward_common(const synthpix_pair* pairs_host, const synthpix_
     }
     a.scale = reinterpret_cast<uint32_t*>(ws + wl.scale);
     a.status = reinterpret_cast<uint32_t*>(ws + wl.status);
-    int64_t slots = 0;                       // the ranges are disjoint
     for (int32_t p = 0; p < n_pairs; ++p) {
-        slots += pairs_host[p].n_max;
+        a.slots += pairs_host[p].n_max;
         a.block_groups += (int64_t)((pairs_host[p].W + 63) / 64) * ((pairs_host[p].H + 63) / 64);
     }
-    a.gaps = slots != span;
     a.sheet_sigma = rp->sheet_sigma;
     a.d_max = rp->d_max;
     blur_taps(rp->blur_radius, rp->blur_sigma, a.blur_w);

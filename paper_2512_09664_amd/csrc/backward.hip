@@ -1741,15 +1741,15 @@ static bool narrow_particles(const BwdArgs& a)
 // of 256^2 (1024 blocks) at 41 / 82 / 205 22 / 32 / 60 and 20 / 21 / 30; 64 of 512^2 (4096)
 // at 20 / 41 / 61 / 82 42 / 63 / 82 / 103 and 67 / 72 / 76 / 78; 4 of 2048^2 with d to 6
 // (4096) at 20 / 41 / 61 / 82 76 / 122 / 171 / 214 and 130 / 138 / 143 / 150.
-static bool block_gather_pays(const BwdArgs& a, int64_t n_span)
+static bool block_gather_pays(const BwdArgs& a)
 {
-    return n_span >= 40 * a.block_groups + 24000 && a.order.log_block <= BLOCK_LOG;
+    return a.slots >= 40 * a.block_groups + 24000 && a.order.log_block <= BLOCK_LOG;
 }
 
 // Whether the row gather gives each frame lanes of its own: while that leaves the chip
 // unfilled (one pair of 512^2 at 0.05 ppp 11.5 us either way, 20 / 82 a block 11.1 / 11.0
 // -> 8.4 / 8.7; 2 of them at 0.1 ppp, 52 k particles, 21.5 -> 23.7).
-static bool rows_both(int64_t n_span) { return n_span <= 64 * (int64_t)device_cu_count(); }
+static bool rows_both(const BwdArgs& a) { return a.slots <= 64 * (int64_t)device_cu_count(); }
 
 void launch_advect_adjoint(const BwdArgs& a, const synthpix_advect_params& ap, unsigned blocks, hipStream_t s)
 {
@@ -1809,7 +1809,7 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
         BwdArgs b = a;
         if (per_pixel) b.grad = a.eblur;
         const bool unfolded = per_pixel || blur == 0;        // no blur left for the gather's tables
-        if (unfolded && narrow_particles(a) && block_gather_pays(a, n_span)) {
+        if (unfolded && narrow_particles(a) && block_gather_pays(a)) {
             TimedScope ts("bwd_gather", s);
             const int gb = 1 << (BLOCK_LOG - a.order.log_block);
             const int side = block_region_side(a.d_max, BLOCK_LOG), cap = side * side;
@@ -1818,14 +1818,14 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
             if (nb > 0xFFFFFFFFll) return hipErrorInvalidValue;
             const size_t lds = sizeof(float) * ((size_t)cap + REGION_PAD);
             // one pass where a block's particles fit (both sides measured above)
-            if (n_span > 256 * a.block_groups)
+            if (a.slots > 256 * a.block_groups)
                 hipLaunchKernelGGL(bwd_gather_blocks<512>, dim3((unsigned)nb), dim3(512), lds, s, b, gb, ngx, ngy, cap);
             else
                 hipLaunchKernelGGL(bwd_gather_blocks<256>, dim3((unsigned)nb), dim3(256), lds, s, b, gb, ngx, ngy, cap);
-            if (a.gaps) hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
+            if (a.slots != n_span) hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
         } else if (unfolded && narrow_particles(a)) {
             TimedScope ts("bwd_gather", s);
-            if (rows_both(n_span))
+            if (rows_both(a))
                 hipLaunchKernelGGL(bwd_gather_rows<true>, dim3(gather_blocks(n_span, 16)), dim3(256), 0, s, b, n_span);
             else
                 hipLaunchKernelGGL(bwd_gather_rows<false>, dim3(gather_blocks(n_span, 8)), dim3(256), 0, s, b, n_span);

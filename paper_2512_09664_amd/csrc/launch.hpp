@@ -310,7 +310,8 @@ struct BwdArgs {
     uint32_t* scale;             // fixed-point scale block: max |dL/dx2|, Lipschitz bound, exponent, state
     uint32_t* status;
     int64_t block_groups;        // blocks of the block gather over all pairs
-    bool gaps;                   // slots of the packed arrays lie in no pair's particle range
+    int64_t slots;               // candidate particles of all pairs (n_span also counts the gaps of
+                                 // the packed arrays)
     float sheet_sigma;
     float d_max;
     float blur_w[7];

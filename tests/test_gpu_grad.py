@@ -1051,3 +1051,19 @@ def test_block_gather_matches_particle_gather(n, d_range, d_max, blur):
         out.append({c: gu.to_np(v) for c, v in sp.render_pair_backward(batch, flow, *args, rp, g_dev).items()})
     for c in ("x1", "y1", "z", "d", "I0", "sheet"):
         _close(out[0][c], out[1][c], c, tol=TOL)
+
+
+def test_gap_slots_are_not_particles():
+    """A pair without candidate particles whose packed arrays hold a gap of many slots
+    (its home-block lists are then never written): every gradient comes back 0."""
+    size, gap = (3008, 3008), 200_000
+    batch = sp.PairBatch.build([size], [(2, 2)], [0], device=gu.DEV, gaps=(gap, 0, 0))
+    args = [torch.full((gap,), v, device=gu.DEV) for v in (9.0, 9.0, 0.0, 2.0, 1.0)]
+    gJ = torch.ones(batch.n_pixels, device=gu.DEV)
+    rp = sp.render_params(0.5, 5.0, 0, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+    ws = sp.alloc_workspace(batch, rp, backward=True)
+    ws.fill_(255)
+    g = sp.render_pair_backward(batch, torch.zeros(8, device=gu.DEV), *args, rp, gJ, workspace=ws)
+    assert sp.read_status(ws) == 0
+    for c in g:
+        assert not g[c].any(), c
