@@ -87,6 +87,9 @@ class PairBatch:
         if gaps[2] % 2:
             raise ValueError("flow gaps must be even (one (u, v) node is two floats)")
         n = len(sizes)
+        for name, v in (("grids", grids), ("n_max", n_max), ("pair_ids", pair_ids), ("flow_index", flow_index)):
+            if v is not None and len(v) < n:
+                raise IndexError(f"{name} holds {len(v)} entries for {n} pairs")
         tab = np.zeros(n, dtype=_PAIR)
         hw = np.array([(int(H), int(W)) for H, W in sizes], dtype=np.int64).reshape(n, 2)
         g = np.array([(int(Gh), int(Gw)) for Gh, Gw in grids[:n]], dtype=np.int64).reshape(n, 2)
@@ -112,7 +115,9 @@ class PairBatch:
         return b
 
     def with_pair_ids(self, pair_ids: Sequence[int], non_blocking: bool = False) -> "PairBatch":
-        """The same batch under other pair ids (its own table on host and device)."""
+        """The same batch under other pair ids, one per pair (its own table on host and device)."""
+        if len(pair_ids) != self.n_pairs:
+            raise ValueError(f"{len(pair_ids)} pair ids for {self.n_pairs} pairs")
         tab = np.frombuffer(self.host, dtype=_PAIR).copy()
         tab["pair_id"] = _pair_ids(pair_ids)
         b = copy.copy(self)
