@@ -1097,12 +1097,12 @@ __device__ __forceinline__ void sample_back(NodeRun& run, const Sample& s, float
 // walk to the sweep; the first is taken again, as all four leave no registers for
 // four waves per SIMD (4 pairs of 2048^2, 8 substeps: all four 431 us, three 327,
 // two 334, none 346; 64 of 512^2, 4 substeps: 101 / 102 / 105 / 110).
+template <bool RK4>
 __device__ __forceinline__ void substep_adjoint(const FlowView& fv, const FlowWin& fw, lds_vec2* lds, NodeRun& run,
-                                                float px, float py, float h, float hh, int integrator, float& gpx,
-                                                float& gpy)
+                                                float px, float py, float h, float hh, float& gpx, float& gpy)
 {
-    float bx, by;
-    if (integrator == SP_EULER) {
+    if constexpr (!RK4) {
+        float bx, by;
         sample_back(run, sample_jac(fv, fw, lds, px, py), h * gpx, h * gpy, bx, by);
         gpx += bx;
         gpy += by;
@@ -1135,12 +1135,17 @@ enum { SC_NONE = 0, SC_VALID = 1, SC_NONFINITE = 2 };
 // the box of the nodes to write out follows from the cells added to instead of a
 // search of the window.  4 pairs of 2048^2 at 0.1 ppp, RK4 x 8: 386 -> 327 us (the
 // copy 353, the box 346, the kept samples 327) and, with dL/dx1 and dL/dx2 read in the
-// home-block order, 308; 64 of 512^2 at 0.05 ppp, RK4 x 4: 112 -> 98 us.  Without the node sums it would take 281 and 89 us: what remains is VALU work
-// and the particle arrays at unrelated addresses.
+// home-block order, 308; 64 of 512^2 at 0.05 ppp, RK4 x 4: 112 -> 98 us.  Without the
+// node sums it would take 281 and 89 us: what remains is VALU work and the particle
+// arrays at unrelated addresses.
+// The integrators are apart, as RK4's kept samples cost Euler its registers (spills at 1,
+// 8 and more than 16 substeps): 64 of 512^2, Euler x 12 / 24 / 48 105 / 188 / 483 -> 86 /
+// 159 / 291 us (before the kept samples 117 / 169 / 367), RK4 x 8 / 16 / 33 160 / 293 /
+// 844 -> 156 / 289 / 693.
 constexpr int ADJ_FLOW_NODES = 896;     // LDS copy of grid nodes: 7 KB, with which four workgroups still share a CU
 constexpr int ADJ_FLOW_MARGIN = 4;      // cells around the particles' starting ones
 
-template <int CK, int SK>
+template <int CK, int SK, bool RK4>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CK <= 8 ? 4 : 3)))
 bwd_advect(BwdArgs a, synthpix_advect_params ap)
 {
@@ -1264,13 +1269,13 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
                 cpx[s / L] = qx;
                 cpy[s / L] = qy;
             }
-            if (s + 1 < S) substep(fv, fw, lds, qx, qy, h, hh, ap.integrator);
+            if (s + 1 < S) substep(fv, fw, lds, qx, qy, h, hh, RK4 ? SP_RK4 : SP_EULER);
         }
         if constexpr (SK == 1) {
             // S <= CK: every substep's start is a checkpoint, the sweep walks them
             // (no segment slots, whose runtime indexing would live in scratch)
             for (int seg = nseg - 1; seg >= 0; --seg)
-                substep_adjoint(fv, fw, lds, run, cpx[seg], cpy[seg], h, hh, ap.integrator, gpx, gpy);
+                substep_adjoint<RK4>(fv, fw, lds, run, cpx[seg], cpy[seg], h, hh, gpx, gpy);
         } else {
             float spx[SK], spy[SK];
             for (int seg = nseg - 1; seg >= 0; --seg) {
@@ -1280,12 +1285,12 @@ bwd_advect(BwdArgs a, synthpix_advect_params ap)
                 spy[0] = cpy[seg];
                 for (int k = 1; k < len; ++k) {
                     float tx = spx[k - 1], ty = spy[k - 1];
-                    substep(fv, fw, lds, tx, ty, h, hh, ap.integrator);
+                    substep(fv, fw, lds, tx, ty, h, hh, RK4 ? SP_RK4 : SP_EULER);
                     spx[k] = tx;
                     spy[k] = ty;
                 }
                 for (int k = len - 1; k >= 0; --k)
-                    substep_adjoint(fv, fw, lds, run, spx[k], spy[k], h, hh, ap.integrator, gpx, gpy);
+                    substep_adjoint<RK4>(fv, fw, lds, run, spx[k], spy[k], h, hh, gpx, gpy);
             }
         }
         run.finish();
@@ -1754,7 +1759,11 @@ static bool rows_both(const BwdArgs& a) { return a.slots <= 64 * (int64_t)device
 void launch_advect_adjoint(const BwdArgs& a, const synthpix_advect_params& ap, unsigned blocks, hipStream_t s)
 {
     const int S = ap.substeps;
-#define SP_ADJ(CK, SK) hipLaunchKernelGGL((bwd_advect<CK, SK>), dim3(blocks), dim3(256), 0, s, a, ap)
+#define SP_ADJ(CK, SK)                                                                                              \
+    do {                                                                                                            \
+        if (ap.integrator == SP_RK4) hipLaunchKernelGGL((bwd_advect<CK, SK, true>), dim3(blocks), dim3(256), 0, s, a, ap); \
+        else hipLaunchKernelGGL((bwd_advect<CK, SK, false>), dim3(blocks), dim3(256), 0, s, a, ap);                 \
+    } while (0)
     if (S <= 1) SP_ADJ(1, 1);
     else if (S <= 2) SP_ADJ(2, 1);
     else if (S <= 4) SP_ADJ(4, 1);

@@ -1067,3 +1067,57 @@ def test_gap_slots_are_not_particles():
     assert sp.read_status(ws) == 0
     for c in g:
         assert not g[c].any(), c
+
+
+@pytest.mark.parametrize("integ", ["euler", "rk4"])
+@pytest.mark.parametrize("n_sub", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 65])
+def test_flow_adjoint_substeps(integ, n_sub):
+    """Both integrators where the adjoint's checkpoints change form, against the oracle;
+    the flow is affine (its derivative has no kinks) and carries no particle out of the
+    grid's hull."""
+    H, W, Gh, Gw, n = 40, 48, 10, 12, 60
+    rng = np.random.default_rng(n_sub)
+    P = {"x": rng.uniform(12, 36, n), "y": rng.uniform(12, 28, n), "z": rng.uniform(-0.5, 0.5, n),
+         "d": rng.uniform(1.0, 4.0, n), "I0": rng.uniform(0.5, 1.0, n)}
+    P = {k: [v.astype(np.float32)] for k, v in P.items()}
+    gx, gy = np.meshgrid((np.arange(Gw) + 0.5) * (W / Gw), (np.arange(Gh) + 0.5) * (H / Gh))
+    flow = np.stack([1.0 + 0.03 * gx - 0.05 * gy, -0.5 + 0.04 * gx + 0.02 * gy], -1).astype(np.float32)
+    batch = gu.batch_for([(H, W)], [(Gh, Gw)], [n])
+    rp = sp.render_params(0.5, 5.0, 0, 0.8, 0.0, 0, 0, 1.0, n_sub, integ)
+    gJ, gJ_dev = _grad_images(batch, 40 + n_sub)
+    ws = sp.alloc_workspace(batch, rp, backward=True)
+    g = sp.render_pair_backward(batch, gu.to_dev(flow.reshape(-1)), *[gu.to_dev(P[k][0]) for k in ("x", "y", "z", "d", "I0")],
+                                rp, gJ_dev, workspace=ws)
+    assert sp.read_status(ws) == 0
+    ref = _oracle_pair(P, 0, [flow], H, W, gJ, 0, rp, 0)
+    for k in ("x1", "y1", "z", "d", "I0"):
+        _close(gu.to_np(g[k])[:n], ref[k], k)
+    _close(gu.to_np(g["flow"]).reshape(flow.shape), ref["flow"], "flow")
+
+
+def test_flow_adjoint_cost_per_substep():
+    """Twice the substeps take at most 2.3 times as long beyond the checkpoints' reach:
+    a substep's adjoint and, for every other one, its start once more, which costs at
+    most a third of that (one sample against one with its Jacobian and node sums)."""
+    b = gu.batch_for([(512, 512)] * 64, [(128, 128)] * 64, [13107] * 64)
+    gen = torch.Generator(device=gu.DEV).manual_seed(3)
+    u = lambda lo, hi, m: lo + (hi - lo) * torch.rand(m, generator=gen, device=gu.DEV)  # noqa: E731
+    args = [u(0, 512, b.n_particles), u(0, 512, b.n_particles), u(-0.5, 0.5, b.n_particles), u(1.5, 3.5, b.n_particles),
+            u(0.5, 1.0, b.n_particles)]
+    coarse = torch.randn(64, 2, 8, 8, generator=gen, device=gu.DEV)
+    flow = torch.nn.functional.interpolate(coarse, size=(128, 128), mode="bicubic", align_corners=False)
+    flow = flow.permute(0, 2, 3, 1).contiguous().reshape(-1)
+    gJ = u(-1.0, 1.0, b.n_pixels)
+    best = {}
+    for n_sub in (24, 48):
+        rp = sp.render_params(0.5, 5.0, 0, 0.8, 0.0, 0, 0, 1.0, n_sub, "euler")
+        ws = sp.alloc_workspace(b, rp, backward=True)
+        for _ in range(6):
+            sp.timing_read(None)
+            sp.timing_enable(True)
+            sp.render_pair_backward(b, flow, *args, rp, gJ, workspace=ws)
+            torch.cuda.synchronize()
+            sp.timing_enable(False)
+            best[n_sub] = min(best.get(n_sub, 1e9), sp.timing_read("bwd_advect")[0])
+    sp.timing_read(None)
+    assert best[48] <= 2.3 * best[24], best
