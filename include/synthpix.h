@@ -312,6 +312,13 @@ synthpix_status synthpix_seed_shape(const synthpix_pair* pairs_host, const synth
 synthpix_status synthpix_advect_workspace_size(const synthpix_pair* pairs_host, int32_t n_pairs,
                                                size_t* bytes_out);
 
+/* Bytes of workspace that synthpix_advect makes use of for this batch and these
+ * parameters (out_of_plane: with wflow): the size above where the home-block order
+ * repays itself, 0 where particles run in index order whatever workspace is passed. */
+synthpix_status synthpix_advect_workspace_needed(const synthpix_pair* pairs_host, int32_t n_pairs,
+                                                 const synthpix_advect_params* ap, int32_t out_of_plane,
+                                                 size_t* bytes_out);
+
 /* Render both exposures of every pair and apply blur, noise and storage
  * (Eq. 1; Section 2, "Considerations on the aggregation", "Efficient
  * rasterization").  Frame 1 uses (x1, y1), frame 2 (x2, y2); z, d, I0 are

@@ -119,6 +119,8 @@ SIGNATURES = {
     "synthpix_seed_shape": [_PP, _P, ctypes.c_int32, ctypes.POINTER(SeedParams), ctypes.c_float, ctypes.c_float,
                             ctypes.c_uint64, _P, _P, _P],
     "synthpix_advect_workspace_size": [_PP, ctypes.c_int32, ctypes.POINTER(ctypes.c_size_t)],
+    "synthpix_advect_workspace_needed": [_PP, ctypes.c_int32, ctypes.POINTER(AdvectParams), ctypes.c_int32,
+                                         ctypes.POINTER(ctypes.c_size_t)],
     "synthpix_render_pair": [_PP, _P, ctypes.c_int32, ctypes.POINTER(Tiling), _P, _P, _P, _P, _P, _P, _P,
                              ctypes.POINTER(ParticleExtras), ctypes.POINTER(RenderParams), _P, _P, ctypes.c_size_t,
                              _P],

@@ -251,11 +251,19 @@ def advect_workspace_size(batch: PairBatch) -> int:
     return n.value
 
 
+def advect_workspace_needed(batch: PairBatch, ap, out_of_plane: bool = False) -> int:
+    """Bytes of workspace that ``advect`` makes use of (0: it runs in index order)."""
+    n = ctypes.c_size_t(0)
+    L.check(L.load().synthpix_advect_workspace_needed(batch.host, batch.n_pairs, ctypes.byref(ap),
+                                                      1 if out_of_plane else 0, ctypes.byref(n)))
+    return n.value
+
+
 def advect(batch: PairBatch, flow: torch.Tensor, ap, x1: torch.Tensor, y1: torch.Tensor, x2=None, y2=None,
            workspace: Optional[torch.Tensor] = None, ordered: bool = True, wflow=None, z1=None, z2=None):
     """Run ``synthpix_advect``.  ``ordered`` processes particles in home-block
-    order (same results, faster); its scratch is ``workspace`` if given (e.g. a
-    render workspace), else a temporary.  With ``wflow`` (each pair's w grid)
+    order where that repays itself (same results); its scratch is ``workspace``
+    if given (e.g. a render workspace), else a temporary.  With ``wflow`` (each pair's w grid)
     and ``z1``, z is moved too and (x2, y2, z2) is returned."""
     _need_cuda(flow, x1, y1, wflow, z1, z2)
     x2 = torch.empty_like(x1) if x2 is None else x2
@@ -263,7 +271,13 @@ def advect(batch: PairBatch, flow: torch.Tensor, ap, x1: torch.Tensor, y1: torch
     if wflow is not None and z2 is None:
         z2 = torch.empty_like(z1)
     if ordered and workspace is None:
-        workspace = torch.empty(max(advect_workspace_size(batch), 256), dtype=torch.uint8, device=x1.device)
+        need = advect_workspace_needed(batch, ap, wflow is not None)
+        try:
+            workspace = torch.empty(need, dtype=torch.uint8, device=x1.device) if need else None
+        except torch.OutOfMemoryError:
+            if wflow is None:        # motion out of the plane needs no order
+                raise
+    ordered = ordered and workspace is not None
     ws, nb = (_ptr(workspace), workspace.numel()) if ordered else (None, 0)
     w, zi, zo = (_ptr(wflow), _ptr(z1), _ptr(z2)) if wflow is not None else (None, None, None)
     L.check(L.load().synthpix_advect(batch.host, batch.dev.data_ptr(), batch.n_pairs, _ptr(flow), ctypes.byref(ap),

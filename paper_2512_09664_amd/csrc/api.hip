@@ -680,6 +680,21 @@ synthpix_status synthpix_advect_workspace_size(const synthpix_pair* pairs_host, 
     return SP_OK;
 }
 
+synthpix_status synthpix_advect_workspace_needed(const synthpix_pair* pairs_host, int32_t n_pairs,
+                                                 const synthpix_advect_params* ap, int32_t out_of_plane,
+                                                 size_t* bytes_out)
+{
+    if (!bytes_out) return fail(SP_ERR_INVALID_ARG, "bytes_out must be non-NULL");
+    int64_t span;
+    synthpix_status st = check_pairs(pairs_host, pairs_host, n_pairs, &span);
+    if (st) return st;
+    if ((st = check_advect_params(ap))) return st;
+    const size_t b = order_bytes(pairs_host, n_pairs);
+    if (!b && !out_of_plane) return fail(SP_ERR_UNSUPPORTED, "batch too large for the advection order");
+    *bytes_out = order_pays(span, *ap) ? b : 0;
+    return SP_OK;
+}
+
 synthpix_status synthpix_advect(const synthpix_pair* pairs_host, const synthpix_pair* pairs_dev, int32_t n_pairs,
                                 const float* flow, const synthpix_advect_params* ap, const float* x1,
                                 const float* y1, float* x2, float* y2, const float* wflow, const float* z1,

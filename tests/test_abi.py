@@ -368,3 +368,30 @@ def test_model_validation(L):
     assert lib.synthpix_render_pair_backward(pairs, fake, 1, None, fake, fake, fake, None, None, fake, fake, fake,
                                              ctypes.byref(rp), fake, fake, fake, fake, fake, fake, fake, None, fake,
                                              ws, 1 << 30, None) == L.SP_ERR_UNSUPPORTED
+
+
+def test_advect_workspace_needed(L):
+    """0 where the order is not built, the workspace's size where it is; a batch too
+    large for the order is refused for planar motion alone."""
+    lib = L.load()
+    n, size = ctypes.c_size_t(7), ctypes.c_size_t()
+    rk4 = L.AdvectParams(1.0, 4, 1)
+
+    def needed(pairs, count, ap, out_of_plane):
+        return lib.synthpix_advect_workspace_needed(pairs, count, ctypes.byref(ap), out_of_plane, ctypes.byref(n))
+
+    small = _pairs(L, [(64, 64, 16, 16, 100)])
+    for w in (0, 1):
+        assert needed(small, 1, rk4, w) == 0 and n.value == 0
+    large = _pairs(L, [(1024, 1024, 256, 256, 52429)] * 64)
+    assert lib.synthpix_advect_workspace_size(large, 64, ctypes.byref(size)) == 0
+    for w in (0, 1):
+        assert needed(large, 64, rk4, w) == 0 and n.value == size.value
+        assert needed(large, 64, L.AdvectParams(1.0, 1, 0), w) == 0 and n.value == 0
+    assert needed(large, 64, L.AdvectParams(1.0, 0, 1), 0) == L.SP_ERR_INVALID_ARG
+    assert lib.synthpix_advect_workspace_needed(large, 64, ctypes.byref(rk4), 0, None) == L.SP_ERR_INVALID_ARG
+    huge = (L.Pair * 65536)()
+    for p in huge:
+        p.H, p.W, p.Gh, p.Gw = 16384, 16384, 2, 2
+    assert needed(huge, 65536, rk4, 0) == L.SP_ERR_UNSUPPORTED
+    assert needed(huge, 65536, rk4, 1) == 0 and n.value == 0

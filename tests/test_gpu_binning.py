@@ -121,3 +121,39 @@ def test_order_does_not_change_positions_out_of_plane(batch, integrator):
     for u, v, s in zip(ordered, plain, small):
         assert torch.equal(u, v) and torch.equal(u, s)
     assert torch.equal(planar[0], ordered[0]) and torch.equal(planar[1], ordered[1])
+
+
+@pytest.mark.parametrize("out_of_plane", [False, True])
+def test_index_order_allocates_nothing(out_of_plane):
+    """Without a workspace, a call that runs in index order takes no memory."""
+    b = gu.batch_for([(96, 128)], [(12, 10)], [8192])
+    flow = torch.zeros(b.n_flow, device=gu.DEV)
+    x, y, z, x2, y2, z2 = (torch.ones(8192, device=gu.DEV) for _ in range(6))
+    ap = sp.advect_params(1.0, 4, "rk4")
+    kw = dict(wflow=torch.zeros(b.n_flow // 2, device=gu.DEV), z1=z, z2=z2) if out_of_plane else {}
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    sp.advect(b, flow, ap, x, y, x2, y2, **kw)
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    assert torch.equal(x2, x) and torch.equal(y2, y)
+
+
+def test_out_of_plane_runs_without_memory_for_the_order(monkeypatch):
+    """Motion out of the plane falls back to index order where the order's temporary
+    cannot be had, as it never needed one."""
+    n = 200_000
+    b = gu.batch_for([(512, 512)] * 16, [(128, 128)] * 16, [n // 16] * 16)
+    rng = np.random.default_rng(4)
+    flow, w = (gu.to_dev(rng.normal(0, 2, k).astype(np.float32)) for k in (b.n_flow, b.n_flow // 2))
+    x, y, z = (gu.to_dev(rng.uniform(0, 512, n).astype(np.float32)) for _ in range(3))
+    ap = sp.advect_params(1.0, 16, "rk4")
+    want = sp.advect(b, flow, ap, x, y, wflow=w, z1=z)
+    assert sp.advect_workspace_needed(b, ap, True) > 0
+
+    def refuse(*a, **k):
+        raise torch.OutOfMemoryError("no memory")
+
+    monkeypatch.setattr(torch, "empty", refuse)
+    got = sp.advect(b, flow, ap, x, y, wflow=w, z1=z)
+    monkeypatch.undo()
+    for u, v in zip(got, want):
+        assert torch.equal(u, v)
