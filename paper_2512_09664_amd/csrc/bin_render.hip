@@ -1383,15 +1383,10 @@ static void launch_render_shape(dim3 grid, hipStream_t s, const RenderArgs& a, c
 #undef SP_B
 }
 
-// Whether one workgroup per pair (and frame) bins a batch: the pairs' particles
-// take one CU about 2.3 us per 1024 (order 0.7 us), the chunked launches 25 (16)
-// us however few there are (one pair of 3277 particles 14 / 25 us, of 13107 37 /
-// 26; order 9 / 16 and 18 / 15).
-constexpr int SMALL_BINS = 8192, SMALL_ORDER = 8192;
-
+// Whether one workgroup per pair (and frame) bins a batch.
 static bool small_pairs(const BatchTotals& tot, int most)
 {
-    return tot.max_n <= most && tot.max_tiles <= 8192;
+    return tot.max_n <= most && tot.max_tiles <= SMALL_TILES;
 }
 
 hipError_t launch_bins(const RenderArgs& a, const RenderConfig& cfg, const BatchTotals& tot, char* ws,

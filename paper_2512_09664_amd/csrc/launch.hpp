@@ -107,6 +107,12 @@ struct BatchTotals {
     int64_t max_n;          // max n_max over pairs
 };
 
+// One workgroup per pair (and frame) bins or orders a batch whose pairs have at most so
+// many particles and tiles (blocks): the particles take one CU about 2.3 us per 1024 (order
+// 0.7 us), the chunked launches 25 (16) us however few there are (one pair of 3277
+// particles 14 / 25 us, of 13107 37 / 26; order 9 / 16 and 18 / 15).
+constexpr int SMALL_BINS = 8192, SMALL_ORDER = 8192, SMALL_TILES = 8192;
+
 // Workspace layout (byte offsets, 256-aligned).
 struct WorkspaceLayout {
     size_t status;          // uint32 [4]

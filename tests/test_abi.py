@@ -395,3 +395,37 @@ def test_advect_workspace_needed(L):
         p.H, p.W, p.Gh, p.Gw = 16384, 16384, 2, 2
     assert needed(huge, 65536, rk4, 0) == L.SP_ERR_UNSUPPORTED
     assert needed(huge, 65536, rk4, 1) == 0 and n.value == 0
+
+
+@pytest.mark.parametrize("pairs,substeps,rk4,planar,out_of_plane", [
+    # (count, side, particles) of equal pairs; whether the order is the faster side by more
+    # than a few us (None: the sides are that close), as measured
+    ((1, 256, 3277), 8, True, False, False), ((16, 256, 3277), 4, True, False, False),
+    ((64, 256, 6554), 4, True, True, True), ((1, 512, 13107), 8, True, False, False),
+    ((64, 512, 5243), 1, True, False, None), ((64, 512, 5243), 4, True, True, True),
+    ((16, 512, 13107), 4, True, None, True), ((16, 1024, 20972), 2, True, None, True),
+    ((64, 1024, 52429), 1, False, False, False), ((64, 1024, 52429), 1, True, None, True),
+    ((64, 1024, 52429), 4, True, True, True), ((1, 2048, 83886), 4, True, False, False),
+    ((1, 2048, 209715), 4, True, False, True), ((1, 2048, 220200), 4, True, False, True),
+    ((1, 2048, 419430), 8, True, True, True), ((4, 2048, 419430), 2, True, None, True),
+    ((1, 4096, 335544), 4, True, False, True), ((1, 4096, 838861), 2, True, False, True),
+    ((1, 4096, 838861), 4, True, True, True), ((32, 2048, 209715), 1, True, False, False),
+    ((32, 2048, 209715), 2, True, True, True)])
+def test_advection_order_rule(L, pairs, substeps, rk4, planar, out_of_plane):
+    count, side, n = pairs
+    tab = _pairs(L, [(side, side, side // 4, side // 4, n)] * count)
+    ap, b = L.AdvectParams(1.0, substeps, 1 if rk4 else 0), ctypes.c_size_t()
+    for w, want in ((0, planar), (1, out_of_plane)):
+        if want is None:
+            continue
+        assert L.load().synthpix_advect_workspace_needed(tab, count, ctypes.byref(ap), w, ctypes.byref(b)) == 0
+        assert (b.value > 0) == want, w
+
+
+def test_advection_order_rule_counts_particles(L):
+    """Slots in a gap of the packed arrays are no particles."""
+    tab = _pairs(L, [(512, 512, 128, 128, 13107)])
+    tab[0].particle_offset = 10_000_000
+    ap, b = L.AdvectParams(1.0, 4, 1), ctypes.c_size_t()
+    assert L.load().synthpix_advect_workspace_needed(tab, 1, ctypes.byref(ap), 0, ctypes.byref(b)) == 0
+    assert b.value == 0
