@@ -1259,48 +1259,57 @@ synthpix_status synthpix_plan_create(const synthpix_pair* pairs_host, int32_t n_
     P->live = reinterpret_cast<int32_t*>(static_cast<char*>(P->workspace) + live_off);
     P->tiling = ok[0];
     if (autotune) {
-        // time each candidate's render of this batch (seed/advect once, render warm-up + 3 runs):
-        // first every shape x capacity, then the binning block sizes for the fastest
+        // Time each candidate's binning and render of this batch as the plan will run them
+        // (seed and advect once): first the tile shapes, then the binning block sizes of the
+        // fastest, then its persistent form.  The candidates of a stage run in turn, several
+        // rounds after one that only warms up, and each one's best counts: clocks rise over
+        // the first launches after an idle spell (by a tenth), which told against whichever
+        // came first.  Another takes the place of the one so far if it is faster by more
+        // than the rounds of one candidate differ (2%).
+        constexpr int ROUNDS = 3;
+        constexpr float MARGIN = 0.98f;
         e = enqueue_batch(P, ok[0], s, false);
         hipEvent_t a = nullptr, b = nullptr;
         if (e == hipSuccess) e = hipEventCreate(&a);
         if (e == hipSuccess) e = hipEventCreate(&b);
-        float best = 1e30f;
         auto time_one = [&](const synthpix_tiling& t) {
             const sp::RenderConfig cfg = make_config(*rp, t);
             sp::BatchTotals T;
-            if (batch_totals(pairs_host, n_pairs, cfg, &T) != SP_OK) return;
+            if (batch_totals(pairs_host, n_pairs, cfg, &T) != SP_OK) return 1e30f;
             const sp::WorkspaceLayout wl = workspace_layout(n_pairs, T, 0, pairs_host);
-            auto run = [&]() {
-                return enqueue_render(P->pairs_dev, n_pairs, cfg, T, wl, io->x1, io->y1, io->x2, io->y2, io->z,
-                                      io->d, io->I0, *rp, io->images, P->workspace, s, P->io_dev);
-            };
-            e = run();
+            float ms = 1e30f;
             if (e == hipSuccess) e = hipEventRecord(a, s);
-            for (int r = 0; r < 3 && e == hipSuccess; ++r) e = run();
+            if (e == hipSuccess)
+                e = enqueue_render(P->pairs_dev, n_pairs, cfg, T, wl, io->x1, io->y1, io->x2, io->y2, io->z, io->d,
+                                   io->I0, *rp, io->images, P->workspace, s, P->io_dev, nullptr, P->live);
             if (e == hipSuccess) e = hipEventRecord(b, s);
             if (e == hipSuccess) e = hipEventSynchronize(b);
-            float ms = 0.0f;
             if (e == hipSuccess) e = hipEventElapsedTime(&ms, a, b);
-            if (e == hipSuccess && ms < best) {
-                best = ms;
-                P->tiling = t;
-            }
+            return ms;
         };
-        for (size_t i = 0; i < ok.size() && e == hipSuccess; ++i) time_one(ok[i]);
-        const synthpix_tiling shape_best = P->tiling;
+        // candidate 0 is the one so far
+        auto stage = [&](const std::vector<synthpix_tiling>& c) {
+            std::vector<float> best(c.size(), 1e30f);
+            for (int r = 0; r <= ROUNDS; ++r)
+                for (size_t i = 0; i < c.size() && e == hipSuccess; ++i) {
+                    const float ms = time_one(c[i]);
+                    if (r > 0) best[i] = std::min(best[i], ms);
+                }
+            size_t k = 0;
+            for (size_t i = 1; i < c.size(); ++i)
+                if (best[i] < (k ? best[k] : MARGIN * best[0])) k = i;
+            P->tiling = c[k];
+        };
+        stage(ok);
+        std::vector<synthpix_tiling> next{P->tiling};
         for (int ch : CHUNK_CANDIDATES) {
-            if (e != hipSuccess) break;
-            synthpix_tiling tc = shape_best;
-            tc.chunk = ch;
-            time_one(tc);
+            next.push_back(P->tiling);
+            next.back().chunk = ch;
         }
-        // then the persistent form of the fastest
-        if (e == hipSuccess) {
-            synthpix_tiling tp = P->tiling;
-            tp.persistent = 1;
-            time_one(tp);
-        }
+        stage(next);
+        next = {P->tiling, P->tiling};
+        next[1].persistent = 1;
+        stage(next);
         if (a) hipEventDestroy(a);
         if (b) hipEventDestroy(b);
         if (e != hipSuccess) {

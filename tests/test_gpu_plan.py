@@ -2,6 +2,8 @@
 eager calls give, the autotuner only changes speed, and pair-id advance draws
 the next batch of pairs."""
 
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -151,3 +153,38 @@ def test_plan_launch_into_new_buffers():
     _, _, _, img1 = _eager(batch, flow_dev, sprm, aprm, rprm, wl.seed)
     assert _same(io1["images"], img1)
     plan.close()
+
+
+def test_autotuned_plan_after_an_idle_spell():
+    """Clocks that rise while the candidates are timed decide nothing: a plan tuned right
+    after an idle spell is no slower than the default one (the best of many replays of
+    both in turn; 1.5% allowed)."""
+    n, side, ppp = 64, 1024, 0.05
+    m = sp.particle_count(side, side, ppp)
+    batch = sp.PairBatch.build([(side, side)] * n, [(256, 256)] * n, [m] * n, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    flow = torch.nn.functional.interpolate(torch.randn(n, 2, 16, 16, generator=gen, device="cuda"), size=(256, 256),
+                                           mode="bicubic").permute(0, 2, 3, 1).contiguous().reshape(-1)
+    io = {k: torch.empty(batch.n_particles, device="cuda") for k in ("x1", "y1", "x2", "y2", "z", "d", "I0")}
+    io.update(flow=flow, images=torch.empty(batch.n_pixels, dtype=sp.api.U16, device="cuda"))
+    args = (batch, sp.seed_params((ppp, ppp), "normal", (2.5, 0.5, 1.0, 5.0)), 1, sp.advect_params(1.0, 4, "rk4"),
+            sp.render_params(0.5, 5.0, 1, 0.7, 0.01, 12), io)
+    plans = [sp.Plan(*args)]
+    torch.cuda.synchronize()
+    time.sleep(2.0)
+    plans.append(sp.Plan(*args, autotune=True))
+    best = [1e9, 1e9]
+    for _ in range(20):
+        for k, plan in enumerate(plans):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            plan.launch()
+            a.record()
+            for _ in range(5):
+                plan.launch()
+            b.record()
+            b.synchronize()
+            best[k] = min(best[k], a.elapsed_time(b))
+    t = plans[1].tiling
+    for plan in plans:
+        plan.close()
+    assert best[1] <= 1.015 * best[0], (best, t.tile_w, t.tile_h, t.chunk, t.persistent)
