@@ -155,8 +155,10 @@ __device__ __forceinline__ Velocity velocity(const FlowView& fv, const float* __
 // its own moves the random accesses out of this kernel: 64 pairs of 1024^2, order
 // and advection 154 -> 177 us, 32 dense pairs of 2048^2 960 -> 952.)
 //
-// A wave whose slots belong to several pairs takes them one after another, so a
-// pair's grid, scales and window are wave-uniform (scalar) values.
+// A wave whose slots belong to one or two pairs takes them one after another, so a
+// pair's grid, scales and window are wave-uniform (scalar) values; of more pairs, each
+// lane has its own pair's (64 pairs of 8 particles, RK4 x 4: one after another 41 us, all
+// at once 8.5).
 // Bound together by VALU issue (0.87 of the nominal rate), the LDS window's reads
 // (active 0.74 of the time, half of it bank conflicts) and, for large pairs, the
 // random reads and writes of the positions: 64 pairs of 1024^2, RK4 x 4, 110 us, 80
@@ -260,14 +262,7 @@ advect_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_sp
     const float hh = h * 0.5f;
     lds_vec2* lds = (lds_vec2*)s_win;
     lds_float* ldsw = (lds_float*)s_winw;
-    // the wave's pairs, in turn (lanes without a particle belong to none)
-    for (unsigned long long left = __builtin_amdgcn_ballot_w64(p >= 0); left != 0;) {
-        const int q = __builtin_amdgcn_readlane(p, __builtin_ctzll(left));
-        left &= ~__builtin_amdgcn_ballot_w64(p == q);
-        if (p != q) continue;
-        const FlowView fv = flow_view(pairs[q], flow);
-        const float* G = W3 ? wflow + pairs[q].flow_offset / 2 : nullptr;
-        const FlowWin win = SORTED && q == pw ? win0 : NO_WIN;
+    auto move = [&](const FlowView& fv, const float* G, const FlowWin& win) {
         if (ap.integrator == SP_EULER) {
             for (int s = 0; s < ap.substeps; ++s) {
                 const Velocity k = velocity<W3>(fv, G, px, py, win, lds, ldsw);
@@ -288,6 +283,22 @@ advect_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_sp
                 py = __builtin_fmaf(h, rk4_mean(k1.v, k2.v, k3.v, k4.v), py);
                 if (W3) pz = __builtin_fmaf(h, rk4_mean(k1.w, k2.w, k3.w, k4.w), pz);
             }
+        }
+    };
+    const unsigned long long some = __builtin_amdgcn_ballot_w64(p >= 0);
+    if (some != 0) {
+        const int first = __builtin_amdgcn_readlane(p, __builtin_ctzll(some));
+        const int last = __builtin_amdgcn_readlane(p, 63 - __builtin_clzll(some));
+        if (last - first <= 1) {
+            // one or two pairs, in turn
+            for (int q = first; q <= last; ++q)
+                if (p == q)
+                    move(flow_view(pairs[q], flow), W3 ? wflow + pairs[q].flow_offset / 2 : nullptr,
+                         SORTED && q == pw ? win0 : NO_WIN);
+        } else if (p >= 0) {
+            // more (pairs of a few particles): all at once, each lane with its own pair's values
+            move(flow_view(pairs[p], flow), W3 ? wflow + pairs[p].flow_offset / 2 : nullptr,
+                 SORTED && p == pw ? win0 : NO_WIN);
         }
     }
     if (p >= 0) {

@@ -157,3 +157,53 @@ def test_out_of_plane_runs_without_memory_for_the_order(monkeypatch):
     monkeypatch.undo()
     for u, v in zip(got, want):
         assert torch.equal(u, v)
+
+
+def _tiny(counts, grid=(4, 4), side=32, seed=6):
+    rng = np.random.default_rng(seed)
+    b = gu.batch_for([(side, side)] * len(counts), [grid] * len(counts), counts)
+    x, y, z = (gu.to_dev(rng.uniform(-2, side + 2, b.n_particles).astype(np.float32)) for _ in range(3))
+    flow, w = (gu.to_dev(rng.normal(0, 2, k).astype(np.float32)) for k in (b.n_flow, b.n_flow // 2))
+    return b, x, y, z, flow, w
+
+
+@pytest.mark.parametrize("integrator", ["euler", "rk4"])
+@pytest.mark.parametrize("out_of_plane", [False, True])
+def test_waves_of_many_pairs(integrator, out_of_plane):
+    """Pairs of a few particles each, so that a wave holds one, two or many of them,
+    against each pair by itself."""
+    counts = [1, 70, 0, 3, 64, 2, 2, 0, 0, 5, 130, 1, 1, 1, 40, 17, 9, 60, 4]
+    b, x, y, z, flow, w = _tiny(counts)
+    ap = sp.advect_params(1.0, 3, integrator)
+    got = sp.advect(b, flow, ap, x, y, **(dict(wflow=w, z1=z) if out_of_plane else {}))
+    one_flow = flow.reshape(len(counts), -1)
+    one_w = w.reshape(len(counts), -1)
+    for p, n in enumerate(counts):
+        if not n:
+            continue
+        o = b.host[p].particle_offset
+        one = gu.batch_for([(32, 32)], [(4, 4)], [n])
+        xs, ys, zs = (t[o:o + n].clone() for t in (x, y, z))
+        kw = dict(wflow=one_w[p].clone(), z1=zs) if out_of_plane else {}
+        for u, v in zip(sp.advect(one, one_flow[p].clone(), ap, xs, ys, **kw), got):
+            assert torch.equal(u, v[o:o + n]), p
+
+
+def test_waves_of_many_pairs_cost():
+    """The same particles in eight times as many pairs take at most twice as long (a
+    wave's pairs are moved together)."""
+    ap = sp.advect_params(1.0, 256, "rk4")
+    best = []
+    for pairs in (8, 64):
+        b, x, y, _, flow, _ = _tiny([512 // pairs] * pairs)
+        t = 1e9
+        for _ in range(6):
+            sp.timing_read(None)
+            sp.timing_enable(True)
+            sp.advect(b, flow, ap, x, y, ordered=False)
+            torch.cuda.synchronize()
+            sp.timing_enable(False)
+            t = min(t, sp.timing_read("advect")[0])
+        best.append(t)
+    sp.timing_read(None)
+    assert best[1] <= 2.0 * best[0], best
