@@ -444,48 +444,57 @@ BwdPlan bwd_plan(const synthpix_pair* ph, int32_t n_pairs, int64_t span, const s
 // Whether the home-block order pays for an advection: the smaller of two estimates in
 // us, each within a fifth of its measured side at most sizes, which is closer than the
 // sides lie to one another but near the crossing.
-//   Index order: 3 + a chain of samples (0.25 each) or, if longer, per particle and sample
-//   5.6 ps where the grids are small enough for a CU's cache, 8.4 where they fit an XCD's,
-//   14 beyond; with w 9.8, 16.5, 40.
-//   Order: one launch for pairs of at most 8192 particles; else counting, scanning and
-//   scattering, whose time goes with the blocks and chunks of a pair (clearing, and a
-//   serial walk) and with their product over the batch (counters in memory).
-//   Advection in that order: 3.5 + the chain (0.2 each, from LDS), and per particle 18 ps (32 in pairs of
-//   many particles, whose own reads and writes then miss the caches; with w 1.6 times
-//   that) + 0.85 ps a sample.
+//   Index order: 3 + a chain of samples (0.19 each, 0.15 on the smallest grids) or, if
+//   longer, per particle and sample 3.8 or 5.6 ps where the grids are well or just small
+//   enough for a CU's cache, 8.4 where they fit an XCD's, 14 beyond; with w 6.0, 9.8, 16.5,
+//   40.
+//   Order: one launch for pairs of at most 8192 particles, a workgroup each; else counting,
+//   scanning and scattering, whose time goes with the blocks and chunks of a pair
+//   (clearing, and a serial walk) and with their product over the batch (counters in
+//   memory).
+//   Advection in that order: 3.5 + the chain (0.155 each, from LDS), and per particle 18 ps
+//   (32 in pairs of many particles, whose own reads and writes then miss the caches; with w
+//   1.6 times that) + 0.85 ps a sample (with w 1.2).
 // Measured index / order + advection, RK4 x 4 (16 samples): 64 pairs of 1024^2 of 52 k
 // particles 422 / 136 us, x 1 113 / 112; one pair of 2048^2 of 84 / 210 / 419 k 17 / 37, 34
 // / 45, 59 / 62; of 4096^2 of 336 / 839 k 79 / 86, 188 / 137; of 512^2 of 13 k 7 / 21; 64 of
 // 512^2 of 5 k 47 / 28; 64 of 256^2 of 1.3 k 11 / 18; with w 64 of 1024^2 x 1 213 / 142, 16
-// of 512^2 of 13 k 54 / 34, one of 2048^2 of 210 k 61 / 52.  Over 23 batches and five sample
+// of 512^2 of 13 k 54 / 34, one of 2048^2 of 210 k 61 / 52, 512 of 128^2 of 0.3 k 19 / 30.  Over 23 batches and five sample
 // counts of both forms the choice is at most 4 us slower than the other side (a threshold on
 // particles x samples alone: 40 us planar, 71 us with w).
-bool order_pays(const synthpix_pair* ph, int32_t n_pairs, const synthpix_advect_params& ap, bool out_of_plane)
+bool order_pays(const synthpix_pair* ph, int32_t n_pairs, int64_t n_span, const synthpix_advect_params& ap, bool w)
 {
-    const sp::RenderConfig cfg = order_config(ph, n_pairs);
     const double samples = (double)ap.substeps * (ap.integrator == SP_RK4 ? 4 : 1);
-    double n = 0, index = 0, move = 3.5 + 0.2 * samples, counters = 0;
+    const double chain = (w ? 1.35 : 1.0) * samples, launch = 11.0 + 0.01 * n_pairs;
+    // most that index order can take against least that the order can: no walk over the
+    // pairs of the many small calls
+    if (3.0 + std::max(0.19 * chain, 1e-6 * (double)n_span * samples * (w ? 40.0 : 14.0)) <= launch + 0.155 * chain)
+        return false;
+    const sp::RenderConfig cfg = order_config(ph, n_pairs);
+    double n = 0, index = 0, move = 0, counters = 0, grid = 0;
     int64_t max_n = 0, max_blocks = 0, max_chunks = 0;
     for (int32_t p = 0; p < n_pairs; ++p) {
         const synthpix_pair& P = ph[p];
-        const double grid = (out_of_plane ? 12.0 : 8.0) * P.Gh * P.Gw;      // bytes
-        const double i = grid <= 48 << 10 ? (out_of_plane ? 9.8 : 5.6) : grid <= 4 << 20 ? (out_of_plane ? 16.5 : 8.4)
-                                                                                         : (out_of_plane ? 40.0 : 14.0);
+        const double bytes = (w ? 12.0 : 8.0) * P.Gh * P.Gw;
+        const double i = bytes <= 16 << 10   ? (w ? 6.0 : 3.8)
+                         : bytes <= 48 << 10 ? (w ? 9.8 : 5.6)
+                         : bytes <= 4 << 20  ? (w ? 16.5 : 8.4)
+                                             : (w ? 40.0 : 14.0);
         const int64_t blocks = (int64_t)((P.W + cfg.tile_w - 1) >> cfg.log_tw) * ((P.H + cfg.tile_h - 1) >> cfg.log_th);
         const int64_t chunks = ((int64_t)P.n_max + cfg.chunk - 1) / cfg.chunk;
         index += 1e-6 * P.n_max * samples * i;
-        move += 1e-6 * P.n_max * ((P.n_max > 150000 ? 32.0 : 18.0) * (out_of_plane ? 1.6 : 1.0) +
-                                  samples * (out_of_plane ? 1.2 : 0.85));
+        move += 1e-6 * P.n_max * ((P.n_max > 150000 ? 32.0 : 18.0) * (w ? 1.6 : 1.0) + samples * (w ? 1.2 : 0.85));
         n += P.n_max;
         counters += (double)chunks * (double)blocks;
+        grid = std::max(grid, bytes);
         max_n = std::max<int64_t>(max_n, P.n_max);
         max_blocks = std::max(max_blocks, blocks);
         max_chunks = std::max(max_chunks, chunks);
     }
     const bool one = max_n <= sp::SMALL_ORDER && max_blocks <= sp::SMALL_TILES;
-    const double order = one ? 7.5 + 0.6e-3 * (double)max_n
-                             : 15.0 + 2e-3 * (double)max_blocks + 0.08 * (double)max_chunks + 3e-6 * counters + 4e-6 * n;
-    return n > 0 && order + move < 3.0 + std::max(index, 0.25 * samples);
+    const double order = one ? launch + 0.6e-3 * (double)max_n
+                             : 18.5 + 2e-3 * (double)max_blocks + 0.08 * (double)max_chunks + 3e-6 * counters + 4e-6 * n;
+    return n > 0 && order + move + 0.155 * chain < 3.0 + std::max(index, (grid <= 8 << 10 ? 0.15 : 0.19) * chain);
 }
 
 // Builds the home-block order of (x, y) in `ws` at byte offset `base` and
@@ -725,9 +734,10 @@ synthpix_status synthpix_advect_workspace_needed(const synthpix_pair* pairs_host
     synthpix_status st = check_pairs(pairs_host, pairs_host, n_pairs, &span);
     if (st) return st;
     if ((st = check_advect_params(ap))) return st;
-    const size_t b = order_bytes(pairs_host, n_pairs);
+    const bool pays = order_pays(pairs_host, n_pairs, span, *ap, out_of_plane != 0);
+    const size_t b = pays || !out_of_plane ? order_bytes(pairs_host, n_pairs) : 0;
     if (!b && !out_of_plane) return fail(SP_ERR_UNSUPPORTED, "batch too large for the advection order");
-    *bytes_out = b && order_pays(pairs_host, n_pairs, *ap, out_of_plane != 0) ? b : 0;
+    *bytes_out = pays ? b : 0;
     return SP_OK;
 }
 
@@ -752,19 +762,19 @@ synthpix_status synthpix_advect(const synthpix_pair* pairs_host, const synthpix_
         if (z1 == z2) return fail(SP_ERR_INVALID_ARG, "z2 must not alias z1");
     }
     sp::AdvectOrder order{};
-    bool usable = workspace != nullptr;
-    if (workspace) {
+    bool use = workspace && order_pays(pairs_host, n_pairs, span, *ap, wflow != nullptr);
+    if (workspace && (use || !wflow)) {
+        // motion out of the plane takes any workspace and uses one that fits
         const size_t need = order_bytes(pairs_host, n_pairs);
         if (wflow) {
-            // motion out of the plane takes any workspace and uses one that fits
-            usable = aligned(workspace, 256) && need && ws_bytes >= need;
+            use = aligned(workspace, 256) && need && ws_bytes >= need;
         } else {
             if (!aligned(workspace, 256)) return fail(SP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
             if (!need) return fail(SP_ERR_UNSUPPORTED, "batch too large for the advection order");
             if (ws_bytes < need) return fail(SP_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
         }
     }
-    if (usable && order_pays(pairs_host, n_pairs, *ap, wflow != nullptr)) {
+    if (use) {
         const hipError_t e = enqueue_order(pairs_host, pairs_dev, n_pairs, x1, y1, static_cast<char*>(workspace), 0,
                                            as_stream(stream), &order);
         if (e != hipSuccess) return hip_fail(e, "advect order launch");
@@ -1122,7 +1132,7 @@ hipError_t enqueue_batch(synthpix_plan* P, const synthpix_tiling& t, hipStream_t
     if (e != hipSuccess) return e;
     sp::AdvectOrder order{};
     order.live = P->live;
-    if (order_pays(P->pairs_host.data(), P->n_pairs, P->ap, false)) {
+    if (order_pays(P->pairs_host.data(), P->n_pairs, P->span, P->ap, false)) {
         e = enqueue_order(P->pairs_host.data(), P->pairs_dev, P->n_pairs, io.x1, io.y1,
                           static_cast<char*>(P->workspace), 0, s, &order, iod, P->live);
         if (e != hipSuccess) return e;

@@ -410,7 +410,10 @@ def test_advect_workspace_needed(L):
     ((1, 2048, 419430), 8, True, True, True), ((4, 2048, 419430), 2, True, None, True),
     ((1, 4096, 335544), 4, True, False, True), ((1, 4096, 838861), 2, True, False, True),
     ((1, 4096, 838861), 4, True, True, True), ((32, 2048, 209715), 1, True, False, False),
-    ((32, 2048, 209715), 2, True, True, True)])
+    ((32, 2048, 209715), 2, True, True, True),
+    ((4096, 32, 40), 4, True, False, False), ((512, 128, 327), 4, True, None, False),
+    ((1, 64, 100), 1024, True, False, None), ((64, 256, 1311), 128, True, True, True),
+    ((1, 512, 13107), 1024, True, True, True)])
 def test_advection_order_rule(L, pairs, substeps, rk4, planar, out_of_plane):
     count, side, n = pairs
     tab = _pairs(L, [(side, side, side // 4, side // 4, n)] * count)
