@@ -155,10 +155,10 @@ __device__ __forceinline__ Velocity velocity(const FlowView& fv, const float* __
 // its own moves the random accesses out of this kernel: 64 pairs of 1024^2, order
 // and advection 154 -> 177 us, 32 dense pairs of 2048^2 960 -> 952.)
 //
-// A wave whose slots belong to one or two pairs takes them one after another, so a
-// pair's grid, scales and window are wave-uniform (scalar) values; of more pairs, each
-// lane has its own pair's (64 pairs of 8 particles, RK4 x 4: one after another 41 us, all
-// at once 8.5).
+// Where all of a wave's slots belong to one pair, the pair's grid, scales and window are
+// wave-uniform (scalar) values; else each lane has its own pair's.  (A wave's pairs one
+// after another, for scalar values throughout: 64 pairs of 8 particles, RK4 x 4, 41 us for
+// 8.5; 1024 of 82 in pairs of two 10.6 for 8.9.)
 // Bound together by VALU issue (0.87 of the nominal rate), the LDS window's reads
 // (active 0.74 of the time, half of it bank conflicts) and, for large pairs, the
 // random reads and writes of the positions: 64 pairs of 1024^2, RK4 x 4, 110 us, 80
@@ -287,16 +287,12 @@ advect_kernel(const synthpix_pair* __restrict__ pairs, int n_pairs, int64_t n_sp
     };
     const unsigned long long some = __builtin_amdgcn_ballot_w64(p >= 0);
     if (some != 0) {
-        const int first = __builtin_amdgcn_readlane(p, __builtin_ctzll(some));
-        const int last = __builtin_amdgcn_readlane(p, 63 - __builtin_clzll(some));
-        if (last - first <= 1) {
-            // one or two pairs, in turn
-            for (int q = first; q <= last; ++q)
-                if (p == q)
-                    move(flow_view(pairs[q], flow), W3 ? wflow + pairs[q].flow_offset / 2 : nullptr,
-                         SORTED && q == pw ? win0 : NO_WIN);
+        const int q = __builtin_amdgcn_readlane(p, __builtin_ctzll(some));
+        if (__builtin_amdgcn_ballot_w64(p == q) == some) {
+            if (p == q)
+                move(flow_view(pairs[q], flow), W3 ? wflow + pairs[q].flow_offset / 2 : nullptr,
+                     SORTED && q == pw ? win0 : NO_WIN);
         } else if (p >= 0) {
-            // more (pairs of a few particles): all at once, each lane with its own pair's values
             move(flow_view(pairs[p], flow), W3 ? wflow + pairs[p].flow_offset / 2 : nullptr,
                  SORTED && p == pw ? win0 : NO_WIN);
         }
