@@ -465,14 +465,12 @@ BwdPlan bwd_plan(const synthpix_pair* ph, int32_t n_pairs, int64_t span, const s
 bool order_pays(const synthpix_pair* ph, int32_t n_pairs, int64_t n_span, const synthpix_advect_params& ap, bool w)
 {
     const double samples = (double)ap.substeps * (ap.integrator == SP_RK4 ? 4 : 1);
-    const double chain = (w ? 1.35 : 1.0) * samples, launch = 11.0 + 0.01 * n_pairs;
+    const double chain = (w ? 1.35 : 1.0) * samples, launch = 11.0 + 0.004 * n_pairs;
     // most that index order can take against least that the order can: no walk over the
     // pairs of the many small calls
     if (3.0 + std::max(0.19 * chain, 1e-6 * (double)n_span * samples * (w ? 40.0 : 14.0)) <= launch + 0.155 * chain)
         return false;
-    const sp::RenderConfig cfg = order_config(ph, n_pairs);
-    double n = 0, index = 0, move = 0, counters = 0, grid = 0;
-    int64_t max_n = 0, max_blocks = 0, max_chunks = 0;
+    double n = 0, index = 0, grid = 0;
     for (int32_t p = 0; p < n_pairs; ++p) {
         const synthpix_pair& P = ph[p];
         const double bytes = (w ? 12.0 : 8.0) * P.Gh * P.Gw;
@@ -480,13 +478,21 @@ bool order_pays(const synthpix_pair* ph, int32_t n_pairs, int64_t n_span, const 
                          : bytes <= 48 << 10 ? (w ? 9.8 : 5.6)
                          : bytes <= 4 << 20  ? (w ? 16.5 : 8.4)
                                              : (w ? 40.0 : 14.0);
+        index += 1e-6 * P.n_max * samples * i;
+        n += P.n_max;
+        grid = std::max(grid, bytes);
+    }
+    index = 3.0 + std::max(index, (grid <= 8 << 10 ? 0.15 : 0.19) * chain);
+    if (index <= launch + 0.155 * chain + 18e-6 * n) return false;
+    const sp::RenderConfig cfg = order_config(ph, n_pairs);
+    double move = 0.155 * chain, counters = 0;
+    int64_t max_n = 0, max_blocks = 0, max_chunks = 0;
+    for (int32_t p = 0; p < n_pairs; ++p) {
+        const synthpix_pair& P = ph[p];
         const int64_t blocks = (int64_t)((P.W + cfg.tile_w - 1) >> cfg.log_tw) * ((P.H + cfg.tile_h - 1) >> cfg.log_th);
         const int64_t chunks = ((int64_t)P.n_max + cfg.chunk - 1) / cfg.chunk;
-        index += 1e-6 * P.n_max * samples * i;
         move += 1e-6 * P.n_max * ((P.n_max > 150000 ? 32.0 : 18.0) * (w ? 1.6 : 1.0) + samples * (w ? 1.2 : 0.85));
-        n += P.n_max;
         counters += (double)chunks * (double)blocks;
-        grid = std::max(grid, bytes);
         max_n = std::max<int64_t>(max_n, P.n_max);
         max_blocks = std::max(max_blocks, blocks);
         max_chunks = std::max(max_chunks, chunks);
@@ -494,7 +500,7 @@ bool order_pays(const synthpix_pair* ph, int32_t n_pairs, int64_t n_span, const 
     const bool one = max_n <= sp::SMALL_ORDER && max_blocks <= sp::SMALL_TILES;
     const double order = one ? launch + 0.6e-3 * (double)max_n
                              : 18.5 + 2e-3 * (double)max_blocks + 0.08 * (double)max_chunks + 3e-6 * counters + 4e-6 * n;
-    return n > 0 && order + move + 0.155 * chain < 3.0 + std::max(index, (grid <= 8 << 10 ? 0.15 : 0.19) * chain);
+    return n > 0 && order + move < index;
 }
 
 // Builds the home-block order of (x, y) in `ws` at byte offset `base` and
