@@ -484,16 +484,19 @@ order_pass(const synthpix_pair* __restrict__ pairs, PairLayout* __restrict__ L, 
 // One workgroup does a whole pair's (and frame's) binning where the pairs are
 // small: layout, records, tile counts, their scan and the scatter in one launch
 // instead of six, the counts never leaving LDS.  It walks the particles twice
-// with 1024 threads.
-constexpr int SMALL_THREADS = 1024;
+// with 1024 threads, or with 256 where there are more workgroups of 1024 than the chip
+// holds at once (two to a CU): 4096 pairs of 20 particles 157 us / 43, 1000 of
+// 205 45 / 19, 300 of 6554 63 / 68 (order of 4096 66 / 24).
+static int small_threads(int64_t workgroups) { return workgroups <= 2 * (int64_t)device_cu_count() ? 1024 : 256; }
 
 // Pair p's layout: the tiles and entry slots of the pairs before it, summed over
 // the workgroup (the chunk tables of the chunked passes stay empty).
+template <int NT>
 __device__ __forceinline__ PairLayout small_layout(const synthpix_pair* __restrict__ pairs, int p,
-                                                   const RenderConfig& cfg, int64_t (*s_part)[SMALL_THREADS / 64])
+                                                   const RenderConfig& cfg, int64_t (*s_part)[NT / 64])
 {
     int64_t tiles = 0, slots = 0;
-    for (int q = (int)threadIdx.x; q < p; q += SMALL_THREADS) {
+    for (int q = (int)threadIdx.x; q < p; q += NT) {
         const int tx = (pairs[q].W + cfg.tile_w - 1) >> cfg.log_tw, ty = (pairs[q].H + cfg.tile_h - 1) >> cfg.log_th;
         tiles += (int64_t)tx * ty;
         slots += 2 * (int64_t)pairs[q].n_max * cfg.kx * cfg.ky;
@@ -510,7 +513,7 @@ __device__ __forceinline__ PairLayout small_layout(const synthpix_pair* __restri
     __syncthreads();
     tiles = slots = 0;
 #pragma unroll
-    for (int w = 0; w < SMALL_THREADS / 64; ++w) {
+    for (int w = 0; w < NT / 64; ++w) {
         tiles += s_part[0][w];
         slots += s_part[1][w];
     }
@@ -529,12 +532,13 @@ __device__ __forceinline__ PairLayout small_layout(const synthpix_pair* __restri
 
 // Exclusive scan of the nt tile counts in lh, in place; counts and list offsets
 // (seg0 plus the prefix) go to count and offset.
+template <int NT>
 __device__ __forceinline__ void small_scan(uint32_t* lh, int nt, int64_t seg0, uint32_t* __restrict__ count,
                                            int64_t* __restrict__ offset, uint32_t* s_wave)
 {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     uint32_t carry = 0;
-    for (int b = 0; b < nt; b += SMALL_THREADS) {
+    for (int b = 0; b < nt; b += NT) {
         const int t = b + (int)threadIdx.x;
         const uint32_t v = t < nt ? lh[t] : 0u;
         const uint32_t inc = wave_scan(v);
@@ -542,7 +546,7 @@ __device__ __forceinline__ void small_scan(uint32_t* lh, int nt, int64_t seg0, u
         __syncthreads();
         uint32_t before = 0, total = 0;
 #pragma unroll
-        for (int w = 0; w < SMALL_THREADS / 64; ++w) {
+        for (int w = 0; w < NT / 64; ++w) {
             const uint32_t sw = s_wave[w];
             if (w < wid) before += sw;
             total += sw;
@@ -561,8 +565,8 @@ __device__ __forceinline__ void small_scan(uint32_t* lh, int nt, int64_t seg0, u
 // Grid (pair, frame).  A status bit of pair p and frame f is left in the pair's
 // layout: the renderer raises it (the status words are cleared here, by one of
 // the workgroups).
-template <bool MODEL>
-__global__ void __launch_bounds__(SMALL_THREADS)
+template <bool MODEL, int NT>
+__global__ void __launch_bounds__(NT)
 bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig cfg, PairLayout* __restrict__ L,
            float4* __restrict__ rec0, float4* __restrict__ rec1, uint2* __restrict__ box0, uint2* __restrict__ box1,
            float2* __restrict__ shp0, float2* __restrict__ shp1, uint32_t* __restrict__ tile_count,
@@ -570,17 +574,17 @@ bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig c
            const int32_t* __restrict__ live, uint32_t* __restrict__ status)
 {
     extern __shared__ uint32_t lh[];
-    __shared__ int64_t s_part[2][SMALL_THREADS / 64];
-    __shared__ uint32_t s_wave[SMALL_THREADS / 64];
+    __shared__ int64_t s_part[2][NT / 64];
+    __shared__ uint32_t s_wave[NT / 64];
     __shared__ uint32_t s_flags;
     const int p = blockIdx.x, f = blockIdx.y, t = (int)threadIdx.x;
     if (!MODEL && a.iod) a.use(*a.iod);
     const synthpix_pair P = pairs[p];
     if (t == 0) s_flags = 0u;
     if (p == 0 && f == 0 && t < 16) status[t] = 0u;
-    const PairLayout o = small_layout(pairs, p, cfg, s_part);
+    const PairLayout o = small_layout<NT>(pairs, p, cfg, s_part);
     const int nt = o.ntx * o.nty;
-    for (int k = t; k < nt; k += SMALL_THREADS) lh[k] = 0u;
+    for (int k = t; k < nt; k += NT) lh[k] = 0u;
     __syncthreads();
     float4* __restrict__ rec = (f ? rec1 : rec0) + P.particle_offset;
     uint2* __restrict__ box = (f ? box1 : box0) + P.particle_offset;
@@ -588,11 +592,11 @@ bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig c
     const int n = live ? min(live[p], P.n_max) : P.n_max;
     uint32_t flags = 0u;
     // two particles per thread and step, so that their loads overlap
-    for (int i0 = t; i0 < n; i0 += 2 * SMALL_THREADS) {
+    for (int i0 = t; i0 < n; i0 += 2 * NT) {
         Record r[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int i = i0 + q * SMALL_THREADS;
+            const int i = i0 + q * NT;
             const int64_t g = P.particle_offset + min(i, n - 1);
             if (MODEL) {
                 u32x4 hide = {0u, 0u, 0u, 0u};
@@ -604,7 +608,7 @@ bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig c
         }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int i = i0 + q * SMALL_THREADS;
+            const int i = i0 + q * NT;
             if (i >= n) break;
             rec[i] = r[q].rec;
             box[i] = r[q].box;
@@ -619,7 +623,7 @@ bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig c
     if (flags) atomicOr(&s_flags, flags);
     __syncthreads();
     const int64_t seg0 = o.entry_base + (int64_t)f * o.entry_cap;
-    small_scan(lh, nt, seg0, tile_count + f * tiles_total + o.tile_base, tile_offset + f * tiles_total + o.tile_base,
+    small_scan<NT>(lh, nt, seg0, tile_count + f * tiles_total + o.tile_base, tile_offset + f * tiles_total + o.tile_base,
                s_wave);
     if (t == 0) {
         if (f == 0) {
@@ -632,7 +636,7 @@ bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig c
         reinterpret_cast<uint8_t*>(&L[p].flags)[f] = (uint8_t)s_flags;
     }
     int32_t* seg = entries + seg0;
-    for (int i = t; i < n; i += SMALL_THREADS) {
+    for (int i = t; i < n; i += NT) {
         int tx0, tx1, ty0, ty1;
         if (!tile_rect(box[i], cfg, o.ntx, o.nty, tx0, tx1, ty0, ty1)) continue;
         for (int ty = ty0; ty <= ty1; ++ty)
@@ -641,34 +645,35 @@ bins_small(const synthpix_pair* __restrict__ pairs, RenderArgs a, RenderConfig c
 }
 
 // The home-block order of small pairs in one launch: one workgroup per pair.
-__global__ void __launch_bounds__(SMALL_THREADS)
+template <int NT>
+__global__ void __launch_bounds__(NT)
 order_small(const synthpix_pair* __restrict__ pairs, const float* __restrict__ x, const float* __restrict__ y,
             RenderConfig cfg, PairLayout* __restrict__ L, uint32_t* __restrict__ tile_count,
             int64_t* __restrict__ tile_offset, int32_t* __restrict__ entries,
             const synthpix_batch_io* __restrict__ iod, const int32_t* __restrict__ live)
 {
     extern __shared__ uint32_t lh[];
-    __shared__ int64_t s_part[2][SMALL_THREADS / 64];
-    __shared__ uint32_t s_wave[SMALL_THREADS / 64];
+    __shared__ int64_t s_part[2][NT / 64];
+    __shared__ uint32_t s_wave[NT / 64];
     const int p = blockIdx.x, t = (int)threadIdx.x;
     if (iod) {
         x = iod->x1;
         y = iod->y1;
     }
     const synthpix_pair P = pairs[p];
-    const PairLayout o = small_layout(pairs, p, cfg, s_part);
+    const PairLayout o = small_layout<NT>(pairs, p, cfg, s_part);
     const int nt = o.ntx * o.nty;
-    for (int k = t; k < nt; k += SMALL_THREADS) lh[k] = 0u;
+    for (int k = t; k < nt; k += NT) lh[k] = 0u;
     __syncthreads();
     x += P.particle_offset;
     y += P.particle_offset;
     const int n = live ? min(live[p], P.n_max) : P.n_max;
-    for (int i = t; i < n; i += SMALL_THREADS) atomicAdd(&lh[home_block(x[i], y[i], P.W, P.H, o, cfg)], 1u);
+    for (int i = t; i < n; i += NT) atomicAdd(&lh[home_block(x[i], y[i], P.W, P.H, o, cfg)], 1u);
     __syncthreads();
-    small_scan(lh, nt, o.entry_base, tile_count + o.tile_base, tile_offset + o.tile_base, s_wave);
+    small_scan<NT>(lh, nt, o.entry_base, tile_count + o.tile_base, tile_offset + o.tile_base, s_wave);
     if (t == 0) L[p] = o;
     int32_t* seg = entries + o.entry_base;
-    for (int i = t; i < n; i += SMALL_THREADS)
+    for (int i = t; i < n; i += NT)
         seg[atomicAdd(&lh[home_block(x[i], y[i], P.W, P.H, o, cfg)], 1u)] = i;
 }
 
@@ -1410,13 +1415,16 @@ hipError_t launch_bins(const RenderArgs& a, const RenderConfig& cfg, const Batch
     const int32_t* live = a.model ? nullptr : a.live;
     if (small_pairs(tot, SMALL_BINS)) {
         TimedScope ts("bins", s);
-        const dim3 grid((unsigned)a.n_pairs, 2), block(SMALL_THREADS);
-        if (a.model)
-            hipLaunchKernelGGL(bins_small<true>, grid, block, hist_lds, s, a.pairs, a, cfg, L, rec0, rec1, box0, box1,
-                               shp0, shp1, tile_count, tile_offset, tot.tiles, entries, live, status);
-        else
-            hipLaunchKernelGGL(bins_small<false>, grid, block, hist_lds, s, a.pairs, a, cfg, L, rec0, rec1, box0,
-                               box1, shp0, shp1, tile_count, tile_offset, tot.tiles, entries, live, status);
+        const int nt = small_threads(2 * (int64_t)a.n_pairs);
+#define SP_BINS(MODEL_, NT_)                                                                                        \
+    hipLaunchKernelGGL((bins_small<MODEL_, NT_>), dim3((unsigned)a.n_pairs, 2), dim3(NT_), hist_lds, s, a.pairs, a,  \
+                       cfg, L, rec0, rec1, box0, box1, shp0, shp1, tile_count, tile_offset, tot.tiles, entries, live, \
+                       status)
+        if (a.model && nt == 1024) SP_BINS(true, 1024);
+        else if (a.model) SP_BINS(true, 256);
+        else if (nt == 1024) SP_BINS(false, 1024);
+        else SP_BINS(false, 256);
+#undef SP_BINS
         return hipGetLastError();
     }
     const bool inl = a.n_pairs <= INLINE_PAIRS && tot.chunks > 0;
@@ -1497,8 +1505,12 @@ hipError_t launch_order(const synthpix_pair* pairs_dev, int n_pairs, const float
     TimedScope ts("order", s);
     const size_t hist_lds = (size_t)tot.max_tiles * sizeof(uint32_t);
     if (small_pairs(tot, SMALL_ORDER)) {
-        hipLaunchKernelGGL(order_small, dim3((unsigned)n_pairs), dim3(SMALL_THREADS), hist_lds, s, pairs_dev, x, y,
-                           cfg, L, tile_count, tile_offset, entries, iod, live);
+        if (small_threads(n_pairs) == 1024)
+            hipLaunchKernelGGL(order_small<1024>, dim3((unsigned)n_pairs), dim3(1024), hist_lds, s, pairs_dev, x, y,
+                               cfg, L, tile_count, tile_offset, entries, iod, live);
+        else
+            hipLaunchKernelGGL(order_small<256>, dim3((unsigned)n_pairs), dim3(256), hist_lds, s, pairs_dev, x, y, cfg,
+                               L, tile_count, tile_offset, entries, iod, live);
         return hipGetLastError();
     }
     const bool inl = n_pairs <= INLINE_PAIRS && tot.chunks > 0;

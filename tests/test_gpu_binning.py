@@ -207,3 +207,101 @@ def test_waves_of_many_pairs_cost():
         best.append(t)
     sp.timing_read(None)
     assert best[1] <= 2.0 * best[0], best
+
+
+MANY = [3, 0, 300, 1, 1100] * 120       # more pairs than the chip holds workgroups of 1024
+
+
+@pytest.mark.parametrize("tile", [(64, 32, 2048, 64), (8, 8, 256, 64)])
+def test_many_small_pairs_lists_and_flags(tile):
+    """Pairs enough for the smaller workgroups: tile lists against the oracle for every
+    seventh pair, counts of all pairs, and status bits of the last one."""
+    sizes = [(40, 24)] * len(MANY)
+    q = _particles(sizes, MANY, 17)
+    b = gu.batch_for(sizes, [(4, 4)] * len(sizes), MANY)
+    rp = sp.render_params(0.5, 5.0, 1, 0.7, 0.0, 12)
+    t = {k: gu.to_dev(v) for k, v in q.items()}
+    tl = sp.tiling(*tile)
+    ws = sp.alloc_workspace(b, rp, tl)
+    args = [t[k] for k in ("x", "y", "x2", "y2", "z", "d", "I0")]
+    sp.render_pair(b, *args, rp, tl, workspace=ws)
+    assert sp.read_status(ws) == 0
+    count, offset, entries = (gu.to_np(v) for v in sp.bin_views(b, rp, tl, ws))
+    nt = int(np.prod(obins.tile_grid(40, 24, tile[1], tile[0])))
+    for p, n in enumerate(MANY):
+        o = b.host[p].particle_offset
+        sl = slice(o, o + n)
+        for f, (xk, yk) in enumerate((("x", "y"), ("x2", "y2"))):
+            got = count[f, p * nt:(p + 1) * nt]
+            if not (q["I0"][sl] > 0).any():
+                assert not got.any()
+                continue
+            if p % 7 and n > 3:
+                continue
+            c, off, ent = obins.bin_frame(q[xk][sl], q[yk][sl], q["d"][sl], q["I0"][sl], 40, 24, tile[1], tile[0], 1)
+            assert np.array_equal(got, c), (p, f)
+            go = offset[f, p * nt:(p + 1) * nt]
+            for k in range(nt):
+                assert np.array_equal(np.sort(entries[go[k]:go[k] + c[k]]), ent[off[k]:off[k + 1]]), (p, f, k)
+    t["d"][-1], t["I0"][-1] = 6.0, 0.01
+    sp.render_pair(b, *args, rp, tl, workspace=ws)
+    assert sp.read_status(ws) == sp._lib.SP_STATUS_D_ABOVE_MAX
+
+
+ORDERED = {     # sizes, particles, grid, substeps: batches whose order is built in both forms
+    "one launch, 600 pairs": ([(40, 24)] * 600, MANY, (12, 10), 1024),
+    "one launch, 70 pairs": ([(96, 128)] * 70, [4000, 0, 700, 1, 8192] * 14, (24, 32), 64),
+    "chunks, a wave of pairs": ([(256, 256)] * 64, [9000] * 64, (64, 64), 16),
+    "chunks, more pairs": ([(256, 256)] * 66, [9000, 0, 3] * 22, (64, 64), 64),
+    "64-pixel blocks": ([(4160, 4160), (300, 200)], [300_000, 5000], (64, 64), 32),
+    "64-pixel blocks, the most": ([(8192, 8192)], [400_000], (64, 64), 32),
+    "128-pixel blocks": ([(16384, 16384), (64, 64)], [400_000, 100], (64, 64), 32),
+    "separate scans": ([(2048, 2048)], [300_000], (512, 512), 16)}
+
+
+@pytest.mark.parametrize("integrator", ["euler", "rk4"])
+@pytest.mark.parametrize("name", list(ORDERED))
+def test_ordered_advection(name, integrator):
+    """The home-block order in every form that it is built in (asserted), planar and out
+    of the plane, with particles outside the image and outside the windows: the same bits
+    as in index order."""
+    sizes, counts, grid, substeps = ORDERED[name]
+    substeps = min(substeps * (4 if integrator == "euler" else 1), 1024)
+    b = gu.batch_for(sizes, [grid] * len(sizes), counts)
+    gen = torch.Generator(device=gu.DEV).manual_seed(len(name))
+    side = torch.tensor([[w, h] for h, w in sizes], dtype=torch.float32, device=gu.DEV)
+    side = side.repeat_interleave(torch.tensor(counts, device=gu.DEV), 0)
+    xy = torch.rand(b.n_particles, 2, generator=gen, device=gu.DEV) * (side + 8.0) - 4.0
+    x, y = xy[:, 0].contiguous(), xy[:, 1].contiguous()
+    x[::501], y[::777] = float("nan"), 3.0e7
+    z = torch.rand(b.n_particles, generator=gen, device=gu.DEV)
+    flow, w = (3.0 * torch.randn(k, generator=gen, device=gu.DEV) for k in (b.n_flow, b.n_flow // 2))
+    ap = sp.advect_params(1.0, substeps, integrator)
+    for kw in ({}, dict(wflow=w, z1=z)):
+        assert sp.advect_workspace_needed(b, ap, bool(kw)) > 0
+        got = sp.advect(b, flow, ap, x, y, **kw)
+        want = sp.advect(b, flow, ap, x, y, ordered=False, **kw)
+        for u, v in zip(got, want):
+            assert torch.equal(u.view(torch.int32), v.view(torch.int32))
+
+
+@pytest.mark.parametrize("tile", [(64, 32, 256, 64), (32, 32, 256, 64)])
+@pytest.mark.parametrize("n", [16384, 16385, 17000])
+def test_separate_scans(n, tile):
+    """A pair on either side of the chunk count from which its scans are launches of
+    their own: tile lists against the oracle."""
+    size = (96, 128)
+    q = _particles([size], [n], n)
+    b = gu.batch_for([size], [(4, 4)], [n])
+    rp = sp.render_params(0.5, 5.0, 1, 0.7, 0.0, 12)
+    tl = sp.tiling(*tile)
+    ws = sp.alloc_workspace(b, rp, tl)
+    sp.render_pair(b, *[gu.to_dev(q[k]) for k in ("x", "y", "x2", "y2", "z", "d", "I0")], rp, tl, workspace=ws)
+    count, offset, entries = (gu.to_np(v) for v in sp.bin_views(b, rp, tl, ws))
+    for f, (xk, yk) in enumerate((("x", "y"), ("x2", "y2"))):
+        c, off, ent = obins.bin_frame(q[xk], q[yk], q["d"], q["I0"], *size, tile[1], tile[0], 1)
+        assert np.array_equal(count[f], c)
+        assert np.array_equal(offset[f] - offset[f][0], off[:-1])
+        for k in range(len(c)):
+            o = offset[f][k]
+            assert np.array_equal(np.sort(entries[o:o + c[k]]), ent[off[k]:off[k + 1]]), (f, k)

@@ -188,3 +188,30 @@ def test_autotuned_plan_after_an_idle_spell():
     for plan in plans:
         plan.close()
     assert best[1] <= 1.015 * best[0], (best, t.tile_w, t.tile_h, t.chunk, t.persistent)
+
+
+@pytest.mark.parametrize("sizes,substeps", [([(256, 256)] * 64, 8), ([(40, 48)] * 600, 64), ([(512, 512)] * 16, 8),
+                                            ([(256, 256)] * 70 + [(512, 384)], 8)])
+def test_plan_order_with_live_counts(sizes, substeps):
+    """Plans whose home-block order is built (asserted) from the active particles alone, in
+    one launch and in chunks: images and positions as the eager calls give them in index
+    order."""
+    wl = get_workload("uneven_256").with_(sizes=tuple(sizes), ppp=(0.01, 0.1), bits=12, noise_sigma=0.01, blur_radius=1,
+                                          integrator="rk4", substeps=substeps, flow="lamb_oseen")
+    flows, batch, flow_dev = workload_inputs(wl)
+    sprm, aprm, rprm = params_of(wl)
+    assert sp.advect_workspace_needed(batch, aprm) > 0
+    rprm.seed = wl.seed
+    P = sp.seed(batch, sprm, wl.seed)
+    x2, y2 = sp.advect(batch, flow_dev, aprm, P["x"], P["y"], ordered=False)
+    img = sp.render_pair(batch, P["x"], P["y"], x2, y2, P["z"], P["d"], P["I0"], rprm)
+    io = _io(batch, flow_dev, 12)
+    plan = sp.Plan(batch, sprm, wl.seed, aprm, rprm, io)
+    for _ in range(2):
+        io["x2"].fill_(-7.0)
+        plan.launch()
+        torch.cuda.synchronize()
+        assert _same(io["images"], img)
+        assert np.array_equal(to_np(io["x2"]), _plan_x2(batch, P, P["x"], x2))
+        assert np.array_equal(to_np(io["y2"]), _plan_x2(batch, P, P["y"], y2))
+    plan.close()
