@@ -796,8 +796,18 @@ scan_pair(const PairLayout* __restrict__ L, uint32_t* __restrict__ hist, uint32_
 
 // Threads of a renderer workgroup, and particles staged per pass (one per thread):
 // 512 for tiles of 4096 pixels, so that the four of them a CU's LDS holds still
-// fill its 32 wave slots.
-constexpr int render_threads(int tw, int th) { return tw * th >= 4096 ? 512 : 256; }
+// fill its 32 wave slots; one wave for tiles of at most 256, whose lists would leave
+// the others idle (16 pairs of 512^2, d about 2.5: 16 x 16 tiles 88 -> 47 us, 8 x 8 265 ->
+// 108).
+constexpr int render_threads(int tw, int th) { return tw * th >= 4096 ? 512 : tw * th <= 256 ? 64 : 256; }
+
+// Whether a tile's patches may fill most of its rows (`WIDE`, tiles below the default's
+// size): they then lie over one another, so lanes that walk them in step add to the same
+// words.  Each lane starts at a row of its own, four lanes take a patch's rows in turn,
+// and the columns go in blocks.  16 pairs of 512^2 with d 4 to 16, in step / so, in
+// us: 64 x 32 tiles 330 / 202, 32 x 32 464 / 220, 16 x 16 784 / 320, 8 x 8 1933 / 613; with
+// d about 2.5 the walk of its own costs 7 %, with registers for both forms in one kernel 6 %.
+constexpr bool wide_patches(int tw, int th, float d_max) { return tw * th < 4096 && 4.5f * d_max > (float)th; }
 constexpr int SLACK = 24;       // accumulator words past the region and one more row (zero columns and rows
                                 // may overrun it)
 constexpr int SIZES = 64;       // patch sizes told apart when a pass is sorted
@@ -807,14 +817,15 @@ __device__ __forceinline__ uint32_t pack_box(int c0, int w, int r0, int h)
     return (uint32_t)c0 | ((uint32_t)w << 8) | ((uint32_t)r0 << 16) | ((uint32_t)h << 24);
 }
 
-// K columns of one particle's patch, from column fx on, over its rows j, j + step,
+// K columns of one particle's patch, from column fx on, over its rows j, j + 2^lp,
 // ..: the column factors stay in registers (zero past the patch's pw columns),
 // each row's factor is formed as the row is added.  fx, fy: the first column's
 // and row j's pixel centres (exact in binary32, so adding small integers to
-// them gives every other centre exactly).
-template <int K, int RW>
+// them gives every other centre exactly).  TURN: from a row of the lane's own on, back to
+// the first behind the last.
+template <int K, int RW, bool TURN>
 __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, float kx, int pw, float fy, float y,
-                                              float ky, float Af, int j, int h, int step)
+                                              float ky, float Af, int j, int h, int lp, int lane)
 {
     float gx[K];
 #pragma unroll
@@ -823,14 +834,30 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
         const float g = expneg_lt80(kx * (dx * dx));
         gx[k] = k < pw ? g : 0.0f;
     }
+    const int step = 1 << lp;
+    const int n = TURN ? (h - j + step - 1) >> lp : 0;      // the lane's rows
+    int r = TURN ? (lane * n) >> 6 : 0, left = n;
+    if (TURN) {
+        dst += r * step * RW;
+        fy += (float)(r * step);
+    }
 #pragma unroll 1
-    for (; j < h; j += step) {
+    while (TURN ? left > 0 : j < h) {
         const float dy = fy - y;
         const float rv = Af * expneg_lt80(ky * (dy * dy));
 #pragma unroll
         for (int k = 0; k < K; ++k) atomicAdd(dst + k, (uint32_t)(rv * gx[k]));
-        fy += (float)step;
-        dst += step * RW;
+        int to = step;
+        if (TURN) {
+            const bool last = ++r == n;
+            to = last ? (1 - n) * step : step;
+            r = last ? 0 : r;
+            --left;
+        } else {
+            j += step;
+        }
+        fy += (float)to;
+        dst += to * RW;
     }
 }
 
@@ -894,7 +921,7 @@ __device__ __forceinline__ void splat_pairs(uint32_t* dst, float fx, float x, in
 // wide patches by pairs of lanes 341 us, 1.83 ms and 621 us.  Of the first, the
 // epilogue takes about 150 us.  Sorting by width alone or by an
 // estimate of the work was slower (397 and 408 us with 64 x 32 tiles).
-template <int TW, int TH, int B, bool ANISO, bool PERSIST>
+template <int TW, int TH, int B, bool ANISO, bool PERSIST, bool WIDE>
 __global__ void __launch_bounds__(render_threads(TW, TH)) __attribute__((amdgpu_waves_per_eu(PERSIST ? 6 : 8)))
 render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restrict__ L, int n_pairs,
             const float4* __restrict__ rec0, const float4* __restrict__ rec1, const uint2* __restrict__ box0,
@@ -988,7 +1015,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     const float2* __restrict__ shp = (f ? shp1 : shp0) + p_off;
 
     for (int k = t; k < ACC / 4; k += NT) reinterpret_cast<uint4*>(acc)[k] = make_uint4(0u, 0u, 0u, 0u);
-    if (t < 2 * SIZES) (&s_hist[0][0])[t] = 0u;
+    for (int k = t; k < 2 * SIZES; k += NT) (&s_hist[0][0])[k] = 0u;
     if (t < 2) s_live[t] = 0u;
     if (t < BANDS) s_band[t] = 0ull;
     if (t == 0) s_over = 0u;
@@ -1051,7 +1078,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
         // lanes; 4 for the full model, whose patches (two diameters, an exponential per
         // pixel) the sort leaves uneven (16 pairs of 1024^2: 1 / 4 / 8 lanes 187 / 146 /
         // 155 us, one patch row per lane 177)
-        const int lp = ANISO || 4 * n <= spread ? 2 : 2 * n <= spread ? 1 : 0;
+        const int lp = ANISO || WIDE || 4 * n <= spread ? 2 : 2 * n <= spread ? 1 : 0;
         for (int s0 = wave * (64 >> lp); s0 < n; s0 += (NT / 64) * (64 >> lp)) {
             const int slot = s0 + (lane >> lp);
             const int step = 1 << lp, j = lane & (step - 1);
@@ -1087,16 +1114,18 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
                 }
                 if (__builtin_amdgcn_ballot_w64(hs > 0) == 0) continue;
             }
-#define SP_SPLAT(K_) splat_columns<K_, RW>(dst, fx, sf.x, sf.z, pw, fy, sf.y, ky, sf.w, j, hs, step)
+#define SP_SPLAT(K_) splat_columns<K_, RW, WIDE>(dst, fx, sf.x, sf.z, pw, fy, sf.y, ky, sf.w, j, hs, lp, lane)
             if (!__builtin_amdgcn_ballot_w64(pw > 4)) SP_SPLAT(4);
             else if (!__builtin_amdgcn_ballot_w64(pw > 6)) SP_SPLAT(6);
             else if (!__builtin_amdgcn_ballot_w64(pw > 8)) SP_SPLAT(8);
             else if (!__builtin_amdgcn_ballot_w64(pw > 10)) SP_SPLAT(10);
             else if (!__builtin_amdgcn_ballot_w64(pw > 12)) SP_SPLAT(12);
-            else if constexpr (ANISO) {
-                for (int cb = 0; __builtin_amdgcn_ballot_w64(pw > cb) != 0; cb += 12)
-                    splat_columns<12, RW>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
-                                          pw > cb ? hs : 0, step);
+            else if constexpr (ANISO || WIDE) {
+                // blocks of at most 12 columns that a patch as wide as the region fills
+                constexpr int NB = (RW + 11) / 12, K = ANISO ? 12 : (RW + NB - 1) / NB;
+                for (int cb = 0; __builtin_amdgcn_ballot_w64(pw > cb) != 0; cb += K)
+                    splat_columns<K, RW, WIDE>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
+                                               pw > cb ? hs : 0, lp, lane);
             } else {
                 // wide patches: two lanes per particle, 32 particles at a time.  The adds of
                 // a pair fall on neighbouring banks, and half the columns need half the
@@ -1367,25 +1396,23 @@ static void launch_render_shape(dim3 grid, hipStream_t s, const RenderArgs& a, c
     // few waves as hold them (less work in all)
     const int threads = render_threads(TW, TH);
     const int spread = (int64_t)grid.x * threads < (int64_t)1024 * device_cu_count() ? threads : 64;
-#define SP_B(B_)                                                                                                 \
-    case B_:                                                                                                     \
-        if (a.aniso)                                                                                             \
-            launch_tile_kernel(render_tile<TW, TH, B_, true, false>, grid, threads, s, false, a.pairs, L, a.n_pairs, \
-                               r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries,   \
-                               tiles,                                                                            \
-                               status, status + 8);                                                              \
-        else if (cfg.persistent)                                                                                 \
-            launch_tile_kernel(render_tile<TW, TH, B_, false, true>, grid, threads, s, true, a.pairs, L, a.n_pairs,  \
-                               r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries,   \
-                               tiles,                                                                            \
-                               status, status + 8);                                                              \
-        else                                                                                                     \
-            launch_tile_kernel(render_tile<TW, TH, B_, false, false>, grid, threads, s, false, a.pairs, L,           \
-                               a.n_pairs, r0, r1, b0, b1, h0, h1, ea, spread, tile_count,              \
-                               tile_offset, entries, tiles, status, status + 8);                                 \
+#define SP_TILE(B_, ANISO_, PERSIST_, WIDE_)                                                                         \
+    launch_tile_kernel(render_tile<TW, TH, B_, ANISO_, PERSIST_, WIDE_>, grid, threads, s, PERSIST_, a.pairs, L,     \
+                       a.n_pairs, r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries, tiles,      \
+                       status, status + 8)
+    constexpr bool CAN = TW * TH < 4096;
+    const bool wide = wide_patches(TW, TH, cfg.d_max);
+#define SP_B(B_)                                                                                                    \
+    case B_:                                                                                                        \
+        if (a.aniso) SP_TILE(B_, true, false, false);                                                               \
+        else if (cfg.persistent && wide) SP_TILE(B_, false, true, CAN);                                             \
+        else if (cfg.persistent) SP_TILE(B_, false, true, false);                                                   \
+        else if (wide) SP_TILE(B_, false, false, CAN);                                                              \
+        else SP_TILE(B_, false, false, false);                                                                      \
         break;
     switch (cfg.apron) { SP_B(0) SP_B(1) SP_B(2) SP_B(3) default: break; }
 #undef SP_B
+#undef SP_TILE
 }
 
 // Whether one workgroup per pair (and frame) bins a batch.
