@@ -354,17 +354,20 @@ hipError_t enqueue_render(const synthpix_pair* pairs_dev, int32_t n_pairs, const
 
 // Tiles of 64 x 64 pixels: fewer particles straddle tiles than with 64 x 32 (1.32
 // against 1.49 lists per particle of 7.5-pixel patches), and a workgroup of 512
-// threads keeps the same number of waves in flight (binning and rendering 64 pairs
-// of 1024^2: 540 -> 484 us, 32 dense pairs of 2048^2: 3.00 -> 2.63 ms, one pair of
-// 256^2 the same).  A batch with a pair of more than 16384 tiles of 64 x 32 keeps
-// those, and is refused for them.
+// threads keeps the same number of waves in flight (rendering 64 pairs of 1024^2: 385
+// -> 361 us, 32 dense pairs of 2048^2: 2.31 -> 2.07 ms, one pair of 256^2 the same).
+// Of 64 x 32 where every image fits in their rows (4096 pairs of 32^2: 45 us, with 64 x
+// 64 tiles 70), and for a batch with a pair of more than 16384 of them, which is refused.
 synthpix_tiling default_tiling(const synthpix_pair* ph, int32_t n_pairs)
 {
     synthpix_tiling t;
     t.tile_w = 64;
-    t.tile_h = 64;
-    for (int32_t p = 0; ph && p < n_pairs; ++p)
-        if ((int64_t)((ph[p].W + 63) / 64) * ((ph[p].H + 31) / 32) > 16384) t.tile_h = 32;
+    bool low = ph && n_pairs > 0, many = false;
+    for (int32_t p = 0; ph && p < n_pairs; ++p) {
+        low = low && ph[p].H <= 32;
+        many = many || (int64_t)((ph[p].W + 63) / 64) * ((ph[p].H + 31) / 32) > 16384;
+    }
+    t.tile_h = low || many ? 32 : 64;
     t.chunk = 2048;    // smaller binning blocks keep more of each tile list's writes in L2
     t.cap = 64;
     t.persistent = 0;

@@ -432,3 +432,18 @@ def test_advection_order_rule_counts_particles(L):
     ap, b = L.AdvectParams(1.0, 4, 1), ctypes.c_size_t()
     assert L.load().synthpix_advect_workspace_needed(tab, 1, ctypes.byref(ap), 0, ctypes.byref(b)) == 0
     assert b.value == 0
+
+
+@pytest.mark.parametrize("sizes,tile_h", [([(32, 32)] * 3, 32), ([(1, 500), (32, 9)], 32), ([(32, 32), (33, 8)], 64),
+                                          ([(64, 64)], 64), ([(16384, 16384)], 32)])
+def test_default_tiling_follows_the_images(L, sizes, tile_h):
+    """Images that fit in the rows of 64 x 32 tiles take those; a batch with too many of
+    them for one image keeps them and is refused."""
+    tab = _pairs(L, [(h, w, 8, 8, 4) for h, w in sizes])
+    t, n = L.Tiling(), ctypes.c_size_t()
+    assert L.load().synthpix_default_tiling(tab, len(sizes), ctypes.byref(_rp(L)), ctypes.byref(t)) == 0
+    assert (t.tile_w, t.tile_h) == (64, tile_h)
+    assert L.load().synthpix_default_tiling(None, 0, ctypes.byref(_rp(L)), ctypes.byref(t)) == 0
+    assert (t.tile_w, t.tile_h) == (64, 64)
+    st = L.load().synthpix_workspace_size(tab, len(sizes), ctypes.byref(_rp(L)), None, 0, ctypes.byref(n))
+    assert st == (L.SP_ERR_UNSUPPORTED if sizes[0][0] == 16384 else 0)
