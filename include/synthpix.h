@@ -163,7 +163,9 @@ typedef struct {
     int32_t tile_w, tile_h;
     int32_t chunk;              /* particles per binning block (256 .. 16384, multiple of 256) */
     int32_t cap;                /* 32 .. 256; accepted and reported, no longer a tuning choice: a
-                                   render pass stages up to 256 particles whatever it holds   */
+                                   render pass stages a particle per thread whatever it holds
+                                   (512 for 64 x 64 tiles, 64 for tiles of at most 256 pixels,
+                                   else 256)                                                  */
     int32_t persistent;         /* 1: one persistent render launch whose workgroups (as many as
                                    the device holds) pop (frame, tile) items from per-XCD work
                                    queues; 0: one workgroup per item.  Same images either way. */
@@ -488,8 +490,9 @@ typedef struct synthpix_plan synthpix_plan;
  * copies the pair table to plan-owned device memory, sizes and allocates the
  * render workspace and the device-side io descriptor, and, if `autotune` != 0,
  * times the tiling candidates (synthpix_tiling_candidates: tile shape, then
- * the binning block size of the fastest) on this
- * batch and keeps the fastest (all candidates give bit-identical images).  The
+ * the binning block size of the fastest, then its persistent form) on this
+ * batch and keeps the first unless another is faster by more than 2% (all
+ * candidates give bit-identical images).  The
  * whole path -- seed, advect, bin, render, epilogue -- is then captured once
  * into a hipGraph whose kernels take their buffers, draw key and pair-id
  * offset from the descriptor.  io: the first launch's buffers (also used while

@@ -509,6 +509,22 @@ __device__ __noinline__ float4 gather_exact(const float* src, int W, float x, fl
 // each lane's row is a cache line of its own.
 constexpr int REGION_PAD = 32;          // floats past the region that a row's last reads may reach
 
+// The particles of a pass.
+template <int NP>
+struct BlockLds {
+    float4 pos[NP];          // x1, y1, x2, y2
+    float4 par[NP];          // z, d, I0 (0: invalid), particle of the pair (as bits)
+    int slot[NP];            // its place in the pair's home-block order
+    uint32_t hist[64];
+    int box[2][4];           // per frame: first column, first row, last column, last row
+};
+
+// The largest region: up to diameters of 12, with the particles of the larger pass within
+// the 64 KB that a workgroup may have.
+constexpr int REGION_SIDE_MAX = 108;
+static_assert(sizeof(BlockLds<512>) + sizeof(float) * (REGION_SIDE_MAX * REGION_SIDE_MAX + REGION_PAD) <= 64 * 1024,
+              "a workgroup's LDS");
+
 // A value that is the same in every lane, moved to scalar registers.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -523,11 +539,12 @@ __global__ void __launch_bounds__(NP)
 bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
 {
     extern __shared__ __align__(16) float region[];
-    __shared__ float4 s_pos[NP];         // x1, y1, x2, y2
-    __shared__ float4 s_par[NP];         // z, d, I0 (0: invalid), particle of the pair (as bits)
-    __shared__ int s_slot[NP];           // its place in the pair's home-block order
-    __shared__ uint32_t s_hist[64];
-    __shared__ int s_box[2][4];          // per frame: first column, first row, last column, last row
+    __shared__ BlockLds<NP> lds;
+    auto& s_pos = lds.pos;
+    auto& s_par = lds.par;
+    auto& s_slot = lds.slot;
+    auto& s_hist = lds.hist;
+    auto& s_box = lds.box;
     const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
     const int p = (int)(bid / ((int64_t)ngx * ngy));
     const int rem = (int)(bid - (int64_t)p * ngx * ngy);
@@ -1736,7 +1753,7 @@ static unsigned gather_blocks(int64_t n_span, int G)
 // gather's region then fits in LDS.
 static bool narrow_particles(const BwdArgs& a)
 {
-    return block_region_side(a.d_max, BLOCK_LOG) <= 108;
+    return block_region_side(a.d_max, BLOCK_LOG) <= REGION_SIDE_MAX;
 }
 
 // Whether the block gather is the faster one: enough particles to repay its phases (about

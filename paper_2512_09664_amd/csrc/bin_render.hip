@@ -904,7 +904,7 @@ __device__ __forceinline__ void splat_pairs(uint32_t* dst, float fx, float x, in
 // evaluates exp(-q) per pixel, q = dx (kappa_x dx + kappa_xy dy) + kappa_y dy^2,
 // kappa_xy = -16 rho / (om d d_y); the patch is |dx| <= 1.5 d, |dy| <= 1.5 d_y.
 //
-// The tile's particles are staged in LDS up to 256 (512) at a time, one per thread,
+// The tile's particles are staged in LDS up to 64, 256 or 512 at a time, one per thread,
 // sorted by patch size (a counting sort on LDS counters), and splatted one
 // particle per lane: a lane keeps its patch's column factors in registers and
 // walks down the rows, so an exponential is computed once per patch column and
