@@ -462,9 +462,10 @@ BwdPlan bwd_plan(const synthpix_pair* ph, int32_t n_pairs, int64_t span, const s
 // particles 422 / 136 us, x 1 113 / 112; one pair of 2048^2 of 84 / 210 / 419 k 17 / 37, 34
 // / 45, 59 / 62; of 4096^2 of 336 / 839 k 79 / 86, 188 / 137; of 512^2 of 13 k 7 / 21; 64 of
 // 512^2 of 5 k 47 / 28; 64 of 256^2 of 1.3 k 11 / 18; with w 64 of 1024^2 x 1 213 / 142, 16
-// of 512^2 of 13 k 54 / 34, one of 2048^2 of 210 k 61 / 52, 512 of 128^2 of 0.3 k 19 / 30.  Over 23 batches and five sample
-// counts of both forms the choice is at most 4 us slower than the other side (a threshold on
-// particles x samples alone: 40 us planar, 71 us with w).
+// of 512^2 of 13 k 54 / 34, one of 2048^2 of 210 k 61 / 52, 512 of 128^2 of 0.3 k 19 / 30.
+// Over 23 batches and five sample counts of both forms the choice is at most 4 us slower
+// than the other side (a threshold on particles x samples alone: 40 us planar, 71 us with
+// w).
 bool order_pays(const synthpix_pair* ph, int32_t n_pairs, int64_t n_span, const synthpix_advect_params& ap, bool w)
 {
     const double samples = (double)ap.substeps * (ap.integrator == SP_RK4 ? 4 : 1);
