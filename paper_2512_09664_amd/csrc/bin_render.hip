@@ -801,13 +801,14 @@ scan_pair(const PairLayout* __restrict__ L, uint32_t* __restrict__ hist, uint32_
 // 108).
 constexpr int render_threads(int tw, int th) { return tw * th >= 4096 ? 512 : tw * th <= 256 ? 64 : 256; }
 
-// Whether a tile's patches may fill most of its rows (`WIDE`, tiles below the default's
-// size): they then lie over one another, so lanes that walk them in step add to the same
-// words.  Each lane starts at a row of its own, four lanes take a patch's rows in turn,
-// and the columns go in blocks.  16 pairs of 512^2 with d 4 to 16, in step / so, in
-// us: 64 x 32 tiles 330 / 202, 32 x 32 464 / 220, 16 x 16 784 / 320, 8 x 8 1933 / 613; with
-// d about 2.5 the walk of its own costs 7 %, with registers for both forms in one kernel 6 %.
-constexpr bool wide_patches(int tw, int th, float d_max) { return tw * th < 4096 && 4.5f * d_max > (float)th; }
+// Whether a tile's patches may fill most of its rows (`WIDE`): they then lie over one
+// another, so lanes that walk them in step add to the same words.  Each lane starts at a
+// row of its own, four lanes take a patch's rows in turn, and the columns go in blocks.  16
+// pairs of 512^2 with d 4 to 16, 3x3 blur, in step / so, in us: 64 x 64 tiles 234 / 162, 64
+// x 32 330 / 200, 32 x 32 464 / 220, 16 x 16 784 / 320, 8 x 8 1933 / 613; one pair with 64 x
+// 64, 3x3 / 7x7 blur 54 / 76 -> 39 / 52; d to 9 with 128 x 32 96 / 85.  Where d is about 2.5
+// all the same the walk of its own costs 7 %, with registers for both forms in one kernel 6 %.
+constexpr bool wide_patches(int th, float d_max) { return 4.5f * d_max > (float)th; }
 constexpr int SLACK = 24;       // accumulator words past the region and one more row (zero columns and rows
                                 // may overrun it)
 constexpr int SIZES = 64;       // patch sizes told apart when a pass is sorted
@@ -823,7 +824,7 @@ __device__ __forceinline__ uint32_t pack_box(int c0, int w, int r0, int h)
 // and row j's pixel centres (exact in binary32, so adding small integers to
 // them gives every other centre exactly).  TURN: from a row of the lane's own on, back to
 // the first behind the last.
-template <int K, int RW, bool TURN>
+template <int K, int RS, bool TURN>
 __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, float kx, int pw, float fy, float y,
                                               float ky, float Af, int j, int h, int lp, int lane)
 {
@@ -838,7 +839,7 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
     const int n = TURN ? (h - j + step - 1) >> lp : 0;      // the lane's rows
     int r = TURN ? (lane * n) >> 6 : 0, left = n;
     if (TURN) {
-        dst += r * step * RW;
+        dst += r * step * RS;
         fy += (float)(r * step);
     }
 #pragma unroll 1
@@ -857,7 +858,7 @@ __device__ __forceinline__ void splat_columns(uint32_t* dst, float fx, float x, 
             j += step;
         }
         fy += (float)to;
-        dst += to * RW;
+        dst += to * RS;
     }
 }
 
@@ -870,7 +871,7 @@ __device__ __forceinline__ float pair_lane(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), N ? 0xF5 : 0xA0, 0xF, 0xF, false));
 }
 
-template <int K, int RW>
+template <int K, int RS>
 __device__ __forceinline__ void splat_pairs(uint32_t* dst, float fx, float x, int pw, float fy, float y, float kappa,
                                             float Af, int a, int h)
 {
@@ -890,9 +891,9 @@ __device__ __forceinline__ void splat_pairs(uint32_t* dst, float fx, float x, in
 #pragma unroll
         for (int k = 0; k < K / 2; ++k) atomicAdd(dst + 2 * k, (uint32_t)(r0 * gx[k]));
 #pragma unroll
-        for (int k = 0; k < K / 2; ++k) atomicAdd(dst + RW + 2 * k, (uint32_t)(r1 * gx[k]));
+        for (int k = 0; k < K / 2; ++k) atomicAdd(dst + RS + 2 * k, (uint32_t)(r1 * gx[k]));
         fy += 2.0f;
-        dst += 2 * RW;
+        dst += 2 * RS;
     }
 }
 
@@ -938,7 +939,10 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
     constexpr int Q4 = TW / 4;
     constexpr int RW = TW + 2 * B;
     constexpr int RH = TH + 2 * B;
-    constexpr int ACC = ((RH + 1) * RW + SLACK + 3) & ~3;
+    // words from row to row: those of rows that are a whole number of bank cycles long fall
+    // on one bank (d 4 to 16, no blur, 16 pairs of 512^2: 369 us, so 152, lanes in step 276)
+    constexpr int RS = WIDE && B == 0 ? RW + 2 : RW;
+    constexpr int ACC = ((RH + 1) * RS + SLACK + 3) & ~3;
     constexpr int STAGE_BYTES = STAGE * (16 + 4 + (ANISO ? 8 : 0));
     constexpr int BLUR_BYTES = B > 0 ? RH * TW * 4 : 0;
     float wb[2 * B + 1];
@@ -1087,7 +1091,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
             const float4 sf = stg[on ? slot : s0];
             const int pc0 = (int)(bx & 255u), pw = (int)((bx >> 8) & 255u);
             const int pr0 = (int)((bx >> 16) & 255u), ph = (int)(bx >> 24);
-            uint32_t* dst = acc + (pr0 + j) * RW + pc0;
+            uint32_t* dst = acc + (pr0 + j) * RS + pc0;
             const float fx = (float)(rx0 + pc0) + 0.5f, fy = (float)(ry0 + pr0 + j) + 0.5f;
             float ky = sf.z;
             int hs = ph;
@@ -1100,7 +1104,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
                     for (int jr = j; jr < ph; jr += step) {
                         const float dy = fr - sf.y;
                         const float ra = s2.y * dy, rb = s2.x * (dy * dy);
-                        uint32_t* dr = dst + (jr - j) * RW;
+                        uint32_t* dr = dst + (jr - j) * RS;
                         float fc = fx;
                         for (int c = 0; c < pw; ++c) {
                             const float dx = fc - sf.x;
@@ -1114,7 +1118,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
                 }
                 if (__builtin_amdgcn_ballot_w64(hs > 0) == 0) continue;
             }
-#define SP_SPLAT(K_) splat_columns<K_, RW, WIDE>(dst, fx, sf.x, sf.z, pw, fy, sf.y, ky, sf.w, j, hs, lp, lane)
+#define SP_SPLAT(K_) splat_columns<K_, RS, WIDE>(dst, fx, sf.x, sf.z, pw, fy, sf.y, ky, sf.w, j, hs, lp, lane)
             if (!__builtin_amdgcn_ballot_w64(pw > 4)) SP_SPLAT(4);
             else if (!__builtin_amdgcn_ballot_w64(pw > 6)) SP_SPLAT(6);
             else if (!__builtin_amdgcn_ballot_w64(pw > 8)) SP_SPLAT(8);
@@ -1124,7 +1128,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
                 // blocks of at most 12 columns that a patch as wide as the region fills
                 constexpr int NB = (RW + 11) / 12, K = ANISO ? 12 : (RW + NB - 1) / NB;
                 for (int cb = 0; __builtin_amdgcn_ballot_w64(pw > cb) != 0; cb += K)
-                    splat_columns<K, RW, WIDE>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
+                    splat_columns<K, RS, WIDE>(dst + cb, fx + (float)cb, sf.x, sf.z, pw - cb, fy, sf.y, ky, sf.w, j,
                                                pw > cb ? hs : 0, lp, lane);
             } else {
                 // wide patches: two lanes per particle, 32 particles at a time.  The adds of
@@ -1142,15 +1146,15 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
                     const float4 f2 = stg[on2 ? s2 : s0];
                     const int qc0 = (int)(b2 & 255u), qw = (int)((b2 >> 8) & 255u);
                     const int qr0 = (int)((b2 >> 16) & 255u), qh = (int)(b2 >> 24);
-                    uint32_t* d2 = acc + qr0 * RW + qc0 + a2;
+                    uint32_t* d2 = acc + qr0 * RS + qc0 + a2;
                     const float gx0 = (float)(rx0 + qc0 + a2) + 0.5f, gy0 = (float)(ry0 + qr0 + a2) + 0.5f;
-#define SP_PAIRS(K_) splat_pairs<K_, RW>(d2, gx0, f2.x, qw, gy0, f2.y, f2.z, f2.w, a2, qh)
+#define SP_PAIRS(K_) splat_pairs<K_, RS>(d2, gx0, f2.x, qw, gy0, f2.y, f2.z, f2.w, a2, qh)
                     if (!__builtin_amdgcn_ballot_w64(qw > 12)) SP_PAIRS(12);
                     else if (!__builtin_amdgcn_ballot_w64(qw > 16)) SP_PAIRS(16);
                     else if (!__builtin_amdgcn_ballot_w64(qw > 20)) SP_PAIRS(20);
                     else
                         for (int cb = 0; __builtin_amdgcn_ballot_w64(qw > cb) != 0; cb += 20)
-                            splat_pairs<20, RW>(d2 + cb, gx0 + (float)cb, f2.x, qw - cb, gy0, f2.y, f2.z, f2.w, a2,
+                            splat_pairs<20, RS>(d2 + cb, gx0 + (float)cb, f2.x, qw - cb, gy0, f2.y, f2.z, f2.w, a2,
                                                 qw > cb ? qh : 0);
 #undef SP_PAIRS
                 }
@@ -1213,7 +1217,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
             const int c = (k % Q4) * 4;
             // the fixed-point scale rides on the weights: w (v 2^-24) and (w 2^-24) v
             // are the same binary32 products (exact power-of-two scaling, no underflow)
-            const uint32_t* src = acc + r * RW + c;
+            const uint32_t* src = acc + r * RS + c;
             float vv[4 + 2 * B];
 #pragma unroll
             for (int q = 0; q < 4 + 2 * B; ++q) vv[q] = (float)src[q];
@@ -1263,7 +1267,7 @@ render_tile(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
             }
             o[0] = s4.x; o[1] = s4.y; o[2] = s4.z; o[3] = s4.w;
         } else {
-            const uint32_t* src = acc + r * RW + c4;
+            const uint32_t* src = acc + r * RS + c4;
             o[0] = (float)src[0] * FIX; o[1] = (float)src[1] * FIX;
             o[2] = (float)src[2] * FIX; o[3] = (float)src[3] * FIX;
         }
@@ -1400,14 +1404,13 @@ static void launch_render_shape(dim3 grid, hipStream_t s, const RenderArgs& a, c
     launch_tile_kernel(render_tile<TW, TH, B_, ANISO_, PERSIST_, WIDE_>, grid, threads, s, PERSIST_, a.pairs, L,     \
                        a.n_pairs, r0, r1, b0, b1, h0, h1, ea, spread, tile_count, tile_offset, entries, tiles,      \
                        status, status + 8)
-    constexpr bool CAN = TW * TH < 4096;
-    const bool wide = wide_patches(TW, TH, cfg.d_max);
+    const bool wide = wide_patches(TH, cfg.d_max);
 #define SP_B(B_)                                                                                                    \
     case B_:                                                                                                        \
         if (a.aniso) SP_TILE(B_, true, false, false);                                                               \
-        else if (cfg.persistent && wide) SP_TILE(B_, false, true, CAN);                                             \
+        else if (cfg.persistent && wide) SP_TILE(B_, false, true, true);                                            \
         else if (cfg.persistent) SP_TILE(B_, false, true, false);                                                   \
-        else if (wide) SP_TILE(B_, false, false, CAN);                                                              \
+        else if (wide) SP_TILE(B_, false, false, true);                                                             \
         else SP_TILE(B_, false, false, false);                                                                      \
         break;
     switch (cfg.apron) { SP_B(0) SP_B(1) SP_B(2) SP_B(3) default: break; }

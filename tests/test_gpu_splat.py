@@ -102,3 +102,29 @@ def test_wide_patches_on_small_tiles_cost():
             best[tile] = min(best.get(tile, 1e9), sp.timing_read("render_tile")[0])
     sp.timing_read(None)
     assert best[(32, 32)] <= 1.5 * best[(64, 64)], best
+
+
+@pytest.mark.parametrize("blur", [0, 1, 2, 3])
+def test_wide_patches_on_default_tiles(blur):
+    """A few wide patches on the default tiles: the image of smaller tiles bit for bit, in
+    at most a quarter more time (tiles of twice the area, half as many workgroups)."""
+    side, n = 512, 2621
+    rng = np.random.default_rng(blur)
+    b = gu.batch_for([(side, side)], [(4, 4)], [n])
+    x, y, z, d, I0 = (gu.to_dev(rng.uniform(*r, n).astype(np.float32))
+                      for r in ((-5, side + 5), (-5, side + 5), (-1, 1), (4.0, 16.0), (0.01, 0.02)))
+    rp = sp.render_params(0.5, 16.0, blur, 0.7, 0.0, 0)
+    best, img = {}, {}
+    for tile in ((64, 64), (64, 32)):
+        tl = sp.tiling(*tile, 2048, 64)
+        ws = sp.alloc_workspace(b, rp, tl)
+        for _ in range(8):
+            sp.timing_read(None)
+            sp.timing_enable(True)
+            img[tile] = sp.render_pair(b, x, y, y, x, z, d, I0, rp, tl, workspace=ws)
+            torch.cuda.synchronize()
+            sp.timing_enable(False)
+            best[tile] = min(best.get(tile, 1e9), sp.timing_read("render_tile")[0])
+    sp.timing_read(None)
+    assert torch.equal(img[(64, 64)], img[(64, 32)])
+    assert best[(64, 64)] <= 1.25 * best[(64, 32)], best
