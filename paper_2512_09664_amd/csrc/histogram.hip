@@ -28,11 +28,24 @@
 namespace sp {
 namespace {
 
-// Pixels per counting / applying workgroup.  The counting workgroup clears and
-// flushes a histogram of its own, so it takes more pixels with more threads.
-constexpr int COUNT_THREADS = 1024, COUNT_CHUNK = COUNT_THREADS * 64;
+// Pixels per applying workgroup.
 constexpr int APPLY_CHUNK = 256 * 128;
-constexpr int LUT_THREADS = 1024;
+constexpr int COUNT_THREADS = 1024, LUT_THREADS = 1024;
+
+// Pixels per counting workgroup.  It clears and flushes a histogram of its own, so it takes
+// many, but no more than leave every CU one: codes that repeat add to one LDS word, one
+// after another, for as long as its workgroup has them.  Images of one code / of all codes
+// alike, 12 bits, the whole call in us with 8 / 16 / 32 / 64 k: one pair of 256^2 31 / 37 /
+// 49 / 74 and 26 / 27 / 29 / 33, of 1024^2 34 / 39 / 50 / 75 and 32 / 30 / 30 / 35, 16 of
+// 512^2 53 / 55 / 54 / 79 and 42 / 37 / 35 / 39, one of 4096^2 137 / 114 / 102 / 95 and 123
+// / 84 / 65 / 61.
+constexpr int COUNT_CHUNK_MIN = 8192, COUNT_CHUNK_MAX = 65536;
+int count_chunk(int64_t max_pixels, int64_t nimg)
+{
+    int chunk = COUNT_CHUNK_MAX;
+    while (chunk > COUNT_CHUNK_MIN && nimg * ((max_pixels + chunk - 1) / chunk) < device_cu_count()) chunk /= 2;
+    return chunk;
+}
 
 __device__ __forceinline__ void image_of(const synthpix_pair* __restrict__ pairs, int img, int64_t& off, int64_t& n)
 {
@@ -82,19 +95,19 @@ __device__ __forceinline__ void each_code(uint16_t* __restrict__ im, int64_t c0,
 // addition for all of them instead of as many on one LDS word.
 __global__ void __launch_bounds__(COUNT_THREADS)
 hist_count(const synthpix_pair* __restrict__ pairs, uint16_t* __restrict__ images, int B,
-           uint32_t* __restrict__ hist, uint32_t* __restrict__ status)
+           int chunk, uint32_t* __restrict__ hist, uint32_t* __restrict__ status)
 {
     extern __shared__ uint32_t lh[];
     const int img = blockIdx.y;
     int64_t off, n;
     image_of(pairs, img, off, n);
-    const int64_t c0 = (int64_t)blockIdx.x * COUNT_CHUNK;
+    const int64_t c0 = (int64_t)blockIdx.x * chunk;
     if (c0 >= n) return;
     for (int b = threadIdx.x; b < B; b += COUNT_THREADS) lh[b] = 0u;
     __syncthreads();
     bool wide = false;
     uint32_t zeros = 0u;                                     // the wave's, in every lane
-    each_code<COUNT_THREADS, false>(images + off, c0, min(c0 + COUNT_CHUNK, n), [&](uint32_t c, bool on) {
+    each_code<COUNT_THREADS, false>(images + off, c0, min(c0 + chunk, n), [&](uint32_t c, bool on) {
         zeros += (uint32_t)__popcll(__ballot(on && c == 0u));
         if (on && c != 0u) {
             wide = wide || c >= (uint32_t)B;
@@ -216,11 +229,13 @@ hipError_t launch_histogram_match(const synthpix_pair* pairs_dev, int n_pairs, i
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + 256);
     uint16_t* lut = reinterpret_cast<uint16_t*>(ws + 256 + (((size_t)nimg * B * 4 + 255) & ~(size_t)255));
     const int64_t nh = (int64_t)nimg * B;
-    const dim3 count_grid((unsigned)((max_pixels + COUNT_CHUNK - 1) / COUNT_CHUNK), (unsigned)nimg);
+    const int chunk = count_chunk(max_pixels, nimg);
+    const dim3 count_grid((unsigned)((max_pixels + chunk - 1) / chunk), (unsigned)nimg);
     const dim3 apply_grid((unsigned)((max_pixels + APPLY_CHUNK - 1) / APPLY_CHUNK), (unsigned)nimg);
     TimedScope ts("histogram_match", s);
     hipLaunchKernelGGL(hist_clear, dim3((unsigned)((nh + 255) / 256)), dim3(256), 0, s, hist, nh, status);
-    hipLaunchKernelGGL(hist_count, count_grid, dim3(COUNT_THREADS), (size_t)B * 4, s, pairs_dev, images, B, hist, status);
+    hipLaunchKernelGGL(hist_count, count_grid, dim3(COUNT_THREADS), (size_t)B * 4, s, pairs_dev, images, B, chunk, hist,
+                       status);
     hipLaunchKernelGGL(hist_lut, dim3((unsigned)nimg), dim3(LUT_THREADS), (size_t)B * 8, s, pairs_dev, target, B, hist,
                        lut, status);
     hipLaunchKernelGGL(hist_apply, apply_grid, dim3(256), (size_t)B * 2, s, pairs_dev, images, B, lut);

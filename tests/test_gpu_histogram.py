@@ -103,3 +103,42 @@ def test_unaligned_and_ragged_images(size, gap):
             src = np.minimum(im[o:o + H * W], (1 << bits) - 1).reshape(H, W)
             want[o:o + H * W] = oh.match(src, target, bits).reshape(-1)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("pairs,size", [(1, (64, 128)), (1, (1, 8193)), (1, (129, 64)), (9, (257, 257)), (20, (257, 257)),
+                                        (33, (257, 257)), (140, (257, 257)), (16, (512, 512))])
+def test_chunks_of_every_length(pairs, size):
+    """Batches whose counting workgroups take the shortest to the longest chunks, with a
+    pixel or more past the last whole one, and images of mostly one code."""
+    rng = np.random.default_rng(pairs)
+    b = sp.PairBatch.build([size] * pairs, [(2, 2)] * pairs, [1] * pairs, device=DEV)
+    two = np.where(rng.random((2, *size)) < 0.9, 7, rng.integers(0, 256, (2, *size))).astype(np.uint16)
+    img = to_dev(np.tile(two.reshape(-1), pairs))
+    target = rng.integers(1, 1000, 256).astype(np.uint32)
+    ws = sp.histogram_match(b, img, to_dev(target), 8)
+    torch.cuda.synchronize()
+    assert sp.read_status(ws) == 0
+    want = np.concatenate([oh.match(f, target, 8).reshape(-1) for f in two])
+    assert np.array_equal(to_np(img).reshape(pairs, -1), np.tile(want, (pairs, 1)))
+
+
+def test_one_code_costs_little_more():
+    """One pair of 256^2 whose pixels share one code (each an addition to one counter) takes
+    at most 2.25 times as long as one of 32^2, whose count is next to nothing."""
+    best = []
+    for side in (32, 256):
+        b = sp.PairBatch.build([(side, side)], [(2, 2)], [1], device=DEV)
+        img = to_dev(np.full(b.n_pixels, 9, np.uint16))
+        target = to_dev(np.ones(4096, np.uint32))
+        ws = sp.histogram_match(b, img, target, 12)
+        t = 1e9
+        for _ in range(10):
+            sp.timing_read(None)
+            sp.timing_enable(True)
+            sp.histogram_match(b, img, target, 12, ws)
+            torch.cuda.synchronize()
+            sp.timing_enable(False)
+            t = min(t, sp.timing_read("histogram_match")[0])
+        best.append(t)
+    sp.timing_read(None)
+    assert best[1] <= 2.25 * best[0], best
