@@ -507,6 +507,13 @@ __device__ __noinline__ float4 gather_exact(const float* src, int W, float x, fl
 // 256), 507 and 459 us (before the home-block order of the results).  Straight from
 // global memory (16-byte loads, one or two lanes per row) the first took 167-172 us:
 // each lane's row is a cache line of its own.
+// Particles may crowd, and one workgroup would take a full block's passes one after
+// another: those of a home block past the first `most` are for the first n_rest
+// workgroups, a segment of the home-block order at a time.  100 k particles of one pair in
+// one place / in 32 x 32 pixels 4050 / 3270 -> 29 / 31 us, 64 pairs of 13 k 630 / 540 -> 156 /
+// 168, in one row of pixels 134 -> 165; spread evenly 101 -> 105 (two copies of the passes in
+// one kernel; one copy with both kinds of list in one loop 114, a launch of their own 111).
+// Register allocation for four waves per SIMD, as for more it spills.
 constexpr int REGION_PAD = 32;          // floats past the region that a row's last reads may reach
 
 // The particles of a pass.
@@ -525,6 +532,29 @@ constexpr int REGION_SIDE_MAX = 108;
 static_assert(sizeof(BlockLds<512>) + sizeof(float) * (REGION_SIDE_MAX * REGION_SIDE_MAX + REGION_PAD) <= 64 * 1024,
               "a workgroup's LDS");
 
+// The particles of a home block past the first `most` in a segment of `most` places of the
+// home-block order: where it holds any of them, its first particle is of the same block (at
+// most `most` places before them), so that block alone is looked up.
+struct Segment {
+    int pair, first, end;       // places of the pair's order; none: first >= end
+};
+
+__device__ __forceinline__ Segment crowded_segment(const BwdArgs& a, int64_t n_span, int most, int64_t seg)
+{
+    Segment none{0, 0, 0};
+    if (seg * most >= n_span) return none;
+    const int p = find_pair_by_particle(a.pairs, a.n_pairs, seg * most);
+    const synthpix_pair P = a.pairs[p];
+    const int64_t i = seg * most - P.particle_offset;
+    if (i < 0 || i >= P.n_max) return none;
+    const PairLayout L = a.order.L[p];
+    const int64_t g = P.particle_offset + a.order.entries[L.entry_base + i];
+    const int64_t b = L.tile_base + home_block(a.x1[g], a.y1[g], P.W, P.H, L.ntx, L.nty, a.order.log_block,
+                                               a.order.log_block);
+    const int64_t at = a.order.offset[b] - L.entry_base;        // its first place
+    return {p, (int)max(i, at + most), (int)min(i + most, at + (int64_t)a.order.count[b])};
+}
+
 // A value that is the same in every lane, moved to scalar registers.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -534,44 +564,21 @@ __device__ __forceinline__ int64_t uniform(int64_t v)
     return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | lo);
 }
 
+// The passes over the particles of a list: places off[q] + k of the order's entries for
+// the k below end[q], `total` in all, of pair p.
 template <int NP>
-__global__ void __launch_bounds__(NP)
-bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
+__device__ __forceinline__ void gather_list(const BwdArgs& a, BlockLds<NP>& lds, float* region, int cap, int p,
+                                            const int64_t (&off)[4], const int (&end)[4], int total)
 {
-    extern __shared__ __align__(16) float region[];
-    __shared__ BlockLds<NP> lds;
     auto& s_pos = lds.pos;
     auto& s_par = lds.par;
     auto& s_slot = lds.slot;
     auto& s_hist = lds.hist;
     auto& s_box = lds.box;
-    const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int p = (int)(bid / ((int64_t)ngx * ngy));
-    const int rem = (int)(bid - (int64_t)p * ngx * ngy);
-    const int gy = rem / ngx, gx = rem - gy * ngx;
-    const int ntx = uniform(a.order.L[p].ntx), nty = uniform(a.order.L[p].nty);
-    if (gb * gx >= ntx || gb * gy >= nty) return;          // the whole workgroup, before its barriers
-    // the blocks' lists; blocks are numbered in strips of four block rows, column by
-    // column inside a strip, odd strips right to left
-    int64_t off[4];
-    int end[4], total = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int bx = gb * gx + (q & 1), by = gb * gy + (q >> 1);
-        off[q] = 0;
-        if (q < gb * gb && bx < ntx && by < nty) {
-            const int s0 = by & ~3, rows = min(4, nty - s0);
-            const int64_t b = a.order.L[p].tile_base + (int64_t)s0 * ntx +
-                              ((s0 & 4) ? ntx - 1 - bx : bx) * rows + (by - s0);
-            off[q] = uniform(a.order.offset[b] - total);
-            total += uniform((int)a.order.count[b]);
-        }
-        end[q] = total;
-    }
+    const int t = (int)threadIdx.x, lane = t & 63, h = t & 1;
     const int W = uniform(a.pairs[p].W), H = uniform(a.pairs[p].H);
     const int64_t part0 = uniform(a.pairs[p].particle_offset), entry0 = uniform((int64_t)a.order.L[p].entry_base);
     const int64_t img = uniform(a.pairs[p].image_offset);
-    const int t = (int)threadIdx.x, lane = t & 63, h = t & 1;
     for (int k0 = 0; k0 < total; k0 += NP) {
         if (t < 64) s_hist[t] = 0u;
         if (t < 8) s_box[t >> 2][t & 3] = (t & 2) ? -1 : 1 << 30;
@@ -722,6 +729,58 @@ bwd_gather_blocks(BwdArgs a, int gb, int ngx, int ngy, int cap)
             __syncthreads();
         }
     }
+}
+
+template <int NP>
+__global__ void __launch_bounds__(NP) __attribute__((amdgpu_waves_per_eu(4, 4)))
+bwd_gather_blocks(BwdArgs a, int64_t n_span, int most, unsigned n_rest, int gb, int ngx, int ngy, int cap)
+{
+    extern __shared__ __align__(16) float region[];
+    __shared__ BlockLds<NP> lds;
+    int64_t off[4];
+    int end[4], total = 0;
+    if (blockIdx.x < n_rest) {
+        // each wave finds them for itself, the same in every one: the passes' barriers meet
+        const int64_t segs = (n_span + most - 1) / most;
+        for (int64_t s0 = blockIdx.x; s0 < segs; s0 += 64 * (int64_t)n_rest) {
+            const Segment mine = crowded_segment(a, n_span, most, s0 + (int64_t)n_rest * (threadIdx.x & 63));
+            for (unsigned long long left = __builtin_amdgcn_ballot_w64(mine.first < mine.end); left != 0;
+                 left &= left - 1) {
+                const int l = __builtin_ctzll(left), p = __builtin_amdgcn_readlane(mine.pair, l);
+                const int first = __builtin_amdgcn_readlane(mine.first, l);
+                total = __builtin_amdgcn_readlane(mine.end, l) - first;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    off[q] = uniform((int64_t)a.order.L[p].entry_base) + first;
+                    end[q] = total;
+                }
+                gather_list<NP>(a, lds, region, cap, p, off, end, total);
+            }
+        }
+        return;
+    }
+    const int64_t bid = xcd_contiguous(blockIdx.x - n_rest, gridDim.x - n_rest);
+    const int p = (int)(bid / ((int64_t)ngx * ngy));
+    const int rem = (int)(bid - (int64_t)p * ngx * ngy);
+    const int gy = rem / ngx, gx = rem - gy * ngx;
+    const int ntx = uniform(a.order.L[p].ntx), nty = uniform(a.order.L[p].nty);
+    if (gb * gx >= ntx || gb * gy >= nty) return;          // the whole workgroup, before its barriers
+    // the blocks' lists; blocks are numbered in strips of four block rows, column by
+    // column inside a strip, odd strips right to left
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int bx = gb * gx + (q & 1), by = gb * gy + (q >> 1);
+        off[q] = 0;
+        if (q < gb * gb && bx < ntx && by < nty) {
+            const int s0 = by & ~3, rows = min(4, nty - s0);
+            const int64_t b = a.order.L[p].tile_base + (int64_t)s0 * ntx +
+                              ((s0 & 4) ? ntx - 1 - bx : bx) * rows + (by - s0);
+            off[q] = uniform(a.order.offset[b] - total);
+            total += min(uniform((int)a.order.count[b]), most);
+        }
+        end[q] = total;
+    }
+    gather_list<NP>(a, lds, region, cap, p, off, end, total);
 }
 
 // ------------------------------------------------------------------ row gather
@@ -1749,6 +1808,14 @@ static unsigned gather_blocks(int64_t n_span, int G)
     return (unsigned)((n_span + 256 / G - 1) / (256 / G));
 }
 
+// Workgroups for the crowded blocks' rest: a multiple of the 8 XCDs, so that the blocks
+// after them keep their places.
+static unsigned rest_workgroups(int64_t n_span, int most, int64_t blocks)
+{
+    const int64_t segs = (n_span + most - 1) / most, cus = device_cu_count();
+    return (unsigned)((std::min(segs, std::max(cus, std::min(4 * cus, blocks / 16))) + 7) / 8 * 8);
+}
+
 // Diameter bound of the block and row gathers (wider particles take bwd_gather): the block
 // gather's region then fits in LDS.
 static bool narrow_particles(const BwdArgs& a)
@@ -1841,13 +1908,19 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
             const int side = block_region_side(a.d_max, BLOCK_LOG), cap = side * side;
             const int ngx = (a.max_w + 63) / 64, ngy = (a.max_h + 63) / 64;
             const int64_t nb = (int64_t)a.n_pairs * ngx * ngy;
-            if (nb > 0xFFFFFFFFll) return hipErrorInvalidValue;
             const size_t lds = sizeof(float) * ((size_t)cap + REGION_PAD);
             // one pass where a block's particles fit (both sides measured above)
-            if (a.slots > 256 * a.block_groups)
-                hipLaunchKernelGGL(bwd_gather_blocks<512>, dim3((unsigned)nb), dim3(512), lds, s, b, gb, ngx, ngy, cap);
+            const int np = a.slots > 256 * a.block_groups ? 512 : 256;
+            // twice the mean of a home block: evenly spread particles stay below
+            const int64_t mean = (a.slots + a.order.blocks - 1) / a.order.blocks;
+            const int most = (int)std::min<int64_t>(std::max<int64_t>(np, 2 * mean), 1 << 28);
+            const unsigned rest = rest_workgroups(n_span, most, nb);
+            if (nb + rest > 0xFFFFFFFFll) return hipErrorInvalidValue;
+            const dim3 grid((unsigned)nb + rest);
+            if (np == 512)
+                hipLaunchKernelGGL(bwd_gather_blocks<512>, grid, dim3(512), lds, s, b, n_span, most, rest, gb, ngx, ngy, cap);
             else
-                hipLaunchKernelGGL(bwd_gather_blocks<256>, dim3((unsigned)nb), dim3(256), lds, s, b, gb, ngx, ngy, cap);
+                hipLaunchKernelGGL(bwd_gather_blocks<256>, grid, dim3(256), lds, s, b, n_span, most, rest, gb, ngx, ngy, cap);
             if (a.slots != n_span) hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
         } else if (unfolded && narrow_particles(a)) {
             TimedScope ts("bwd_gather", s);

@@ -425,13 +425,7 @@ bin_scatter(const synthpix_pair* __restrict__ pairs, const PairLayout* __restric
 __device__ __forceinline__ int home_block(float x, float y, int W, int H, const PairLayout& PL,
                                           const RenderConfig& cfg)
 {
-    const int cx = !(x >= 0.0f) ? 0 : (x >= (float)W ? W - 1 : (int)x);
-    const int cy = !(y >= 0.0f) ? 0 : (y >= (float)H ? H - 1 : (int)y);
-    const int bx = cx >> cfg.log_tw, by = cy >> cfg.log_th;
-    const int s0 = by & ~3;                                   // first block row of the strip
-    const int rows = PL.nty - s0 < 4 ? PL.nty - s0 : 4;       // rows in this strip
-    const int col = (by & 4) ? PL.ntx - 1 - bx : bx;          // odd strips run right to left
-    return s0 * PL.ntx + col * rows + (by - s0);
+    return home_block(x, y, W, H, PL.ntx, PL.nty, cfg.log_tw, cfg.log_th);
 }
 
 template <bool SCATTER, bool INLINE>

@@ -238,6 +238,20 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v)
     return v;
 }
 
+// Home block of a position, clamped into the image: blocks of 2^log_w x 2^log_h pixels,
+// ntx x nty of them, numbered in strips of four block rows, column by column inside a
+// strip, odd strips from right to left.
+__device__ __forceinline__ int home_block(float x, float y, int W, int H, int ntx, int nty, int log_w, int log_h)
+{
+    const int cx = !(x >= 0.0f) ? 0 : (x >= (float)W ? W - 1 : (int)x);
+    const int cy = !(y >= 0.0f) ? 0 : (y >= (float)H ? H - 1 : (int)y);
+    const int bx = cx >> log_w, by = cy >> log_h;
+    const int s0 = by & ~3;                                   // first block row of the strip
+    const int rows = nty - s0 < 4 ? nty - s0 : 4;             // rows in this strip
+    const int col = (by & 4) ? ntx - 1 - bx : bx;             // odd strips run right to left
+    return s0 * ntx + col * rows + (by - s0);
+}
+
 // Pair lookup: the pair whose particle range [offset, offset + n_max) holds g.
 // Pairs are sorted by particle_offset (validated on the host).
 __device__ __forceinline__ int find_pair_by_particle(const synthpix_pair* pairs, int n_pairs, int64_t g)

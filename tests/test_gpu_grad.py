@@ -1121,3 +1121,79 @@ def test_flow_adjoint_cost_per_substep():
             best[n_sub] = min(best.get(n_sub, 1e9), sp.timing_read("bwd_advect")[0])
     sp.timing_read(None)
     assert best[48] <= 2.3 * best[24], best
+
+
+@pytest.mark.parametrize("blur,mse", [(0, False), (1, True)])
+@pytest.mark.parametrize("crowd,m", [(255, 1200), (256, 1200), (257, 1200), (513, 1200), (769, 1200), (20_000, 1200),
+                                     (512, 3500), (513, 3500), (1025, 3500), (5000, 3500)])
+def test_crowded_blocks(crowd, m, blur, mse):
+    """A pair whose particles crowd into one home block (and one whose lie beside the image)
+    among others, in packed arrays with gaps: the bits of the same pair alone, which is too
+    small for the block gather, around the number of particles past which a home block's own
+    workgroup leaves them to others."""
+    size, n_sparse = (130, 170), 40
+    rng = np.random.default_rng(crowd)
+    rp = sp.render_params(0.5, 5.0, blur, 0.8, 0.0, 0, 0, 1.0, 1, "euler")
+
+    def particles(n, x, y):
+        return [rng.uniform(*r, n).astype(np.float32) for r in (x, y, (-0.5, 0.5), (1.0, 5.0), (0.5, 1.0))]
+
+    here, there = particles(crowd, (64, 96), (32, 64)), particles(crowd, (-9, -1), (300, 310))
+    sets = [particles(m, (0, 170), (0, 130)) for _ in range(n_sparse)]
+    sets[7], sets[30] = here, there
+    J, T = (rng.standard_normal((2, *size)).astype(np.float32) for _ in range(2))
+    node = rng.uniform(-2, 2, (5, 6, 2)).astype(np.float32)
+
+    def run(sets, gaps):
+        batch = sp.PairBatch.build([size] * len(sets), [(5, 6)] * len(sets), [len(s[0]) for s in sets], device=gu.DEV,
+                                   gaps=gaps)
+        args = [np.full(batch.n_particles, 9.0, np.float32) for _ in range(5)]
+        imgs = [np.full(batch.n_pixels, np.nan, np.float32) for _ in range(2)]
+        fl = np.zeros(batch.n_flow, np.float32)
+        for P, s in zip(batch.host, sets):
+            for a, v in zip(args, s):
+                a[P.particle_offset:P.particle_offset + P.n_max] = v
+            for a, v in zip(imgs, (J, T)):
+                a[P.image_offset:P.image_offset + v.size] = v.reshape(-1)
+            fl[P.flow_offset:P.flow_offset + node.size] = node.reshape(-1)
+        args, imgs, fl = [gu.to_dev(a) for a in args], [gu.to_dev(a) for a in imgs], gu.to_dev(fl)
+        ws = sp.alloc_workspace(batch, rp, backward="mse" if mse else True)
+        if mse:
+            g = sp.render_pair_backward_mse(batch, fl, *args, rp, *imgs, 0.25, workspace=ws)
+        else:
+            g = sp.render_pair_backward(batch, fl, *args, rp, imgs[0], workspace=ws)
+        assert sp.read_status(ws) == 0
+        return batch, {c: gu.to_np(g[c]) for c in ("x1", "y1", "z", "d", "I0")}
+
+    for gaps in ((0, 0, 0), (37, 3, 2)):
+        batch, got = run(sets, gaps)
+        for k in (7, 30, 3):
+            _, alone = run([sets[k]], (0, 0, 0))
+            o, n = batch.host[k].particle_offset, batch.host[k].n_max
+            for c in alone:
+                assert np.array_equal(got[c][o:o + n], alone[c]), (gaps, k, c)
+
+
+def test_crowded_blocks_cost():
+    """Particles crowded into one block of each pair take at most three times as long to
+    gather as the same number spread out."""
+    n, side, m = 16, 512, 13107
+    batch = gu.batch_for([(side, side)] * n, [(8, 8)] * n, [m] * n)
+    gen = torch.Generator(device=gu.DEV).manual_seed(1)
+    u = lambda lo, hi: lo + (hi - lo) * torch.rand(batch.n_particles, generator=gen, device=gu.DEV)  # noqa: E731
+    x, y, z, d, I0 = u(0, 1), u(0, 1), u(-1, 1), u(1.5, 3.5), u(0.1, 0.2)
+    rp = sp.render_params(0.5, 3.5, 0, 0.7, 0.0, 0, 0, 1.0, 1, "euler")
+    fl, J = torch.zeros(batch.n_flow, device=gu.DEV), torch.ones(batch.n_pixels, device=gu.DEV)
+    ws = sp.alloc_workspace(batch, rp, backward=True)
+    best = {}
+    for part in (512.0, 32.0):
+        for _ in range(6):
+            sp.timing_read(None)
+            sp.timing_enable(True)
+            sp.render_pair_backward(batch, fl, 64.0 + (x * part) % 448.0, 64.0 + (y * part) % 448.0, z, d, I0, rp, J,
+                                    workspace=ws)
+            torch.cuda.synchronize()
+            sp.timing_enable(False)
+            best[part] = min(best.get(part, 1e9), sp.timing_read("bwd_gather")[0])
+    sp.timing_read(None)
+    assert best[32.0] <= 3.0 * best[512.0], best
