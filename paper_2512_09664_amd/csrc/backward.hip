@@ -510,10 +510,10 @@ __device__ __noinline__ float4 gather_exact(const float* src, int W, float x, fl
 // Particles may crowd, and one workgroup would take a full block's passes one after
 // another: those of a home block past the first `most` are for the first n_rest
 // workgroups, a segment of the home-block order at a time.  100 k particles of one pair in
-// one place / in 32 x 32 pixels 4050 / 3270 -> 29 / 31 us, 64 pairs of 13 k 630 / 540 -> 156 /
-// 168, in one row of pixels 134 -> 165; spread evenly 101 -> 105 (two copies of the passes in
-// one kernel; one copy with both kinds of list in one loop 114, a launch of their own 111).
-// Register allocation for four waves per SIMD, as for more it spills.
+// one place / in 32 x 32 pixels 4050 / 3270 -> 29 / 31 us, 64 pairs of 13 k 630 / 540 -> 153 /
+// 165, in one row of pixels 135 -> 157; spread evenly 99 -> 100, 64 pairs of 3 k 29 -> 31
+// (two copies of the passes in one kernel; one copy with both kinds of list in one loop
+// 114 for 99, the further workgroups in a launch of their own 111, last in the grid 108).
 constexpr int REGION_PAD = 32;          // floats past the region that a row's last reads may reach
 
 // The particles of a pass.
@@ -543,9 +543,13 @@ __device__ __forceinline__ Segment crowded_segment(const BwdArgs& a, int64_t n_s
 {
     Segment none{0, 0, 0};
     if (seg * most >= n_span) return none;
-    const int p = find_pair_by_particle(a.pairs, a.n_pairs, seg * most);
+    const int64_t slot = seg * most;
+    // the pair where even ones would have it, else searched for (64 pairs: 0.7 us)
+    int p = min((int)((float)slot * ((float)a.n_pairs / (float)n_span)), a.n_pairs - 1);
+    if (a.pairs[p].particle_offset > slot || a.pairs[min(p + 1, a.n_pairs - 1)].particle_offset <= slot)
+        p = find_pair_by_particle(a.pairs, a.n_pairs, slot);
     const synthpix_pair P = a.pairs[p];
-    const int64_t i = seg * most - P.particle_offset;
+    const int64_t i = slot - P.particle_offset;
     if (i < 0 || i >= P.n_max) return none;
     const PairLayout L = a.order.L[p];
     const int64_t g = P.particle_offset + a.order.entries[L.entry_base + i];
@@ -564,11 +568,12 @@ __device__ __forceinline__ int64_t uniform(int64_t v)
     return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | lo);
 }
 
-// The passes over the particles of a list: places off[q] + k of the order's entries for
-// the k below end[q], `total` in all, of pair p.
+// The passes over the `total` particles of pair p at the places o0 + k of the order's
+// entries for the k below e0, o1 + k for the next below e1, and so on.
 template <int NP>
 __device__ __forceinline__ void gather_list(const BwdArgs& a, BlockLds<NP>& lds, float* region, int cap, int p,
-                                            const int64_t (&off)[4], const int (&end)[4], int total)
+                                            int64_t o0, int64_t o1, int64_t o2, int64_t o3, int e0, int e1, int e2,
+                                            int total)
 {
     auto& s_pos = lds.pos;
     auto& s_par = lds.par;
@@ -589,7 +594,7 @@ __device__ __forceinline__ void gather_list(const BwdArgs& a, BlockLds<NP>& lds,
         uint32_t rank = 0;
         int box[2][4] = {{1 << 30, 1 << 30, -1, -1}, {1 << 30, 1 << 30, -1, -1}};
         if (t < n) {
-            const int64_t o = k < end[0] ? off[0] : k < end[1] ? off[1] : k < end[2] ? off[2] : off[3];
+            const int64_t o = k < e0 ? o0 : k < e1 ? o1 : k < e2 ? o2 : o3;
             const int i = a.order.entries[o + k];
             place = (int)(o + k - entry0);
             const int64_t g = part0 + i;
@@ -732,13 +737,11 @@ __device__ __forceinline__ void gather_list(const BwdArgs& a, BlockLds<NP>& lds,
 }
 
 template <int NP>
-__global__ void __launch_bounds__(NP) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ void __launch_bounds__(NP)
 bwd_gather_blocks(BwdArgs a, int64_t n_span, int most, unsigned n_rest, int gb, int ngx, int ngy, int cap)
 {
     extern __shared__ __align__(16) float region[];
     __shared__ BlockLds<NP> lds;
-    int64_t off[4];
-    int end[4], total = 0;
     if (blockIdx.x < n_rest) {
         // each wave finds them for itself, the same in every one: the passes' barriers meet
         const int64_t segs = (n_span + most - 1) / most;
@@ -748,13 +751,9 @@ bwd_gather_blocks(BwdArgs a, int64_t n_span, int most, unsigned n_rest, int gb, 
                  left &= left - 1) {
                 const int l = __builtin_ctzll(left), p = __builtin_amdgcn_readlane(mine.pair, l);
                 const int first = __builtin_amdgcn_readlane(mine.first, l);
-                total = __builtin_amdgcn_readlane(mine.end, l) - first;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    off[q] = uniform((int64_t)a.order.L[p].entry_base) + first;
-                    end[q] = total;
-                }
-                gather_list<NP>(a, lds, region, cap, p, off, end, total);
+                const int total = __builtin_amdgcn_readlane(mine.end, l) - first;
+                const int64_t o = uniform((int64_t)a.order.L[p].entry_base) + first;
+                gather_list<NP>(a, lds, region, cap, p, o, o, o, o, total, total, total, total);
             }
         }
         return;
@@ -767,6 +766,8 @@ bwd_gather_blocks(BwdArgs a, int64_t n_span, int most, unsigned n_rest, int gb, 
     if (gb * gx >= ntx || gb * gy >= nty) return;          // the whole workgroup, before its barriers
     // the blocks' lists; blocks are numbered in strips of four block rows, column by
     // column inside a strip, odd strips right to left
+    int64_t off[4];
+    int end[4], total = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int bx = gb * gx + (q & 1), by = gb * gy + (q >> 1);
@@ -780,7 +781,7 @@ bwd_gather_blocks(BwdArgs a, int64_t n_span, int most, unsigned n_rest, int gb, 
         }
         end[q] = total;
     }
-    gather_list<NP>(a, lds, region, cap, p, off, end, total);
+    gather_list<NP>(a, lds, region, cap, p, off[0], off[1], off[2], off[3], end[0], end[1], end[2], total);
 }
 
 // ------------------------------------------------------------------ row gather
@@ -1918,10 +1919,13 @@ hipError_t launch_backward(const BwdArgs& a, int64_t n_span, int64_t n_flow, con
             if (nb + rest > 0xFFFFFFFFll) return hipErrorInvalidValue;
             const dim3 grid((unsigned)nb + rest);
             if (np == 512)
-                hipLaunchKernelGGL(bwd_gather_blocks<512>, grid, dim3(512), lds, s, b, n_span, most, rest, gb, ngx, ngy, cap);
+                hipLaunchKernelGGL(bwd_gather_blocks<512>, grid, dim3(512), lds, s, b, n_span, most, rest, gb, ngx, ngy,
+                                   cap);
             else
-                hipLaunchKernelGGL(bwd_gather_blocks<256>, grid, dim3(256), lds, s, b, n_span, most, rest, gb, ngx, ngy, cap);
-            if (a.slots != n_span) hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
+                hipLaunchKernelGGL(bwd_gather_blocks<256>, grid, dim3(256), lds, s, b, n_span, most, rest, gb, ngx, ngy,
+                                   cap);
+            if (a.slots != n_span)
+                hipLaunchKernelGGL(bwd_gaps, dim3((unsigned)((n_span + 255) / 256)), dim3(256), 0, s, b, n_span);
         } else if (unfolded && narrow_particles(a)) {
             TimedScope ts("bwd_gather", s);
             if (rows_both(a))
