@@ -101,7 +101,8 @@ __global__ void __launch_bounds__(256) probe_mul64(uint32_t* __restrict__ sink, 
     if (s == 0x9e3779b9u) sink[threadIdx.x] = s;
 }
 
-// Mixed chains in the proportions of the renderer's inner loops: per
+// Mixed chains, five float to four integer instructions (the renderer: about five to
+// five, moves and selects among the latter): per
 // iteration and chain nine VALU instructions as compiled for gfx950 (one
 // float32 FMA, two multiplies, a float -> u32 and a u32 -> float conversion,
 // an integer add, a shift, a xor and a three-input bit operation).
